@@ -1,0 +1,70 @@
+"""GPU parity at the edges of dispatch rules and of kernels' tiles: the HIP path
+against the oracle, bit for bit (whole numbers) at the sizes where a path
+begins, ends or leaves a remainder."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+@pytest.fixture(scope="module")
+def sbs():
+    import paper_2001_07809_amd as m
+    m.lib()
+    return m
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def pair(rng, W, H, C, levels=256):
+    shape = (H, W) if C == 1 else (H, W, C)
+    L = (rng.integers(0, levels, shape) * (256 // levels)).astype(np.uint8)
+    R = np.roll(L, -5, axis=1)
+    R[::3] = rng.integers(0, 256, R[::3].shape, dtype=np.uint8)
+    return L, R
+
+
+def check_search(torch, sbs, L, R, idx, block, dmax, what):
+    d, c = sbs.sad_disparity(dev(torch, L), dev(torch, R), dev(torch, idx.astype(np.uint32).view(np.int32)), block, dmax)
+    torch.cuda.synchronize()
+    ed, ec, _ = oracle.sad(L, R, idx.astype(np.uint32), block, dmax)
+    gd, gc = d.cpu().numpy(), c.cpu().numpy().view(np.uint32)
+    bad = np.flatnonzero((gd != ed) | (gc != ec))
+    assert bad.size == 0, f"{what}: {bad.size} of {idx.size} differ, first at entry {bad[:3]}"
+
+
+@pytest.mark.parametrize("run", [1, 3, 255, 256, 257, 1024, 5000])
+def test_lists_ordered_in_runs(torch, sbs, run):
+    """Lists made of ascending runs in a shuffled order, with some entries
+    repeated far apart: wavefronts of the order check that see a descent lie
+    beside ones that see none, down to a single descent in the whole list."""
+    rng = np.random.default_rng(100 + run)
+    W, H = 331, 97
+    L, R = pair(rng, W, H, 3)
+    idx = np.sort(rng.choice(W * H, 7013, replace=False))
+    cuts = [idx[i:i + run] for i in range(0, idx.size, run)]
+    order = np.roll(np.arange(len(cuts)), 1) if len(cuts) < 3 else rng.permutation(len(cuts))
+    lst = np.concatenate([cuts[i] for i in order] + [idx[:40]])
+    check_search(torch, sbs, L, R, lst, 9, 33, f"runs of {run}")
+
+
+@pytest.mark.parametrize("H", [1, 4096, 4097])
+def test_unordered_lists_tall_images(torch, sbs, H):
+    """The row bits of an unordered list gathered in LDS (up to 4096 words:
+    one per row here) and, one row more, set in memory."""
+    rng = np.random.default_rng(H)
+    W = 40
+    L, R = pair(rng, W, H, 1)
+    lst = rng.choice(W * H, max(W * H // 9, 20))
+    check_search(torch, sbs, L, R, lst, 5, 11, f"{W}x{H}")
