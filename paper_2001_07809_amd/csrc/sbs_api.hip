@@ -123,6 +123,10 @@ std::string plan_key(const sbs_frame& f, int nframes) {
 
 bool packs(const sbs_frame& f) { return 2 * (int64_t)f.block * 255 * f.C <= 65535; }
 
+// Whole windows that fit 16 bits (their packed pairs need no widening in the
+// tile kernel's horizontal stage). A window of one column (block 1) packs too.
+bool narrow(const sbs_frame& f) { return (int64_t)f.block * f.block * 255 * f.C <= 65535; }
+
 // The tile kernel packs a row's list range as (first - tile's first slot) <<
 // shift | count, with shift 8 (4 columns per lane) or 9 (8 columns per
 // lane); the offset is at most min(n, (tile rows - 1) x W).
@@ -394,7 +398,7 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     d.n = f.n;
     d.W = f.W; d.H = f.H; d.C = f.C;
     d.r = (f.block - 1) / 2;
-    d.pack = packs(f) ? 1 : 0;
+    d.pack = !packs(f) ? 0 : (narrow(f) ? 2 : 1);
     d.cpl = cpl[(size_t)i];
     d.linpl = (f.C == 3 && ((uintptr_t)f.left & 3) == 0 && (f.pitch_bytes & 3) == 0) ? 1 : 0;
     d.dmax = f.dmax;

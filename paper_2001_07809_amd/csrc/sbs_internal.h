@@ -43,7 +43,8 @@ struct FrameDev {
   int32_t ntx, nty;      // tiles per row / column
   int32_t nch, chunk;    // disparity chunks and their size
   int32_t tpw;           // entries per row of tptr (ntx + 1)
-  int32_t pack;          // 1: the sum of two window columns (<= 2 * block * 255 * C) fits in 16 bits
+  int32_t pack;          // 1: the sum of two window columns (<= 2 * block * 255 * C) fits in 16 bits;
+                         // 2: so does a whole window's sum (<= block^2 * 255 * C)
   int32_t cpl;           // window columns per lane: 4, or 8 (ordered lists, 8-disparity chunks, pack == 1)
   int32_t linpl;         // 1: tiles whose window lies inside the image read the left image in place
                          // (C == 3, 4-byte-aligned rows); the left copy then holds only the edge bands

@@ -596,17 +596,29 @@ __device__ __forceinline__ void slide_row(RowRegs<DC, COLS>& en, RowRegs<DC, COL
     }
 }
 
+// Narrow windows (kNarrow: a whole window's sum, at most block^2 * 255 * C,
+// fits 16 bits; 9x9 RGB, 15x15 grey and below): the packed pair of column
+// sums goes through the horizontal stage as it is. Prefix sums, differences
+// and window sums of such words are plain 32-bit arithmetic, exact modulo
+// 2^32, and a window's two sums come out of the difference of two prefix
+// words with no carry between them, since each fits its half. That is 12
+// instead of 22 instructions per pair of disparities for the prefix sums and
+// half the LDS words written and read (384x288 grey, block 15, dmax 15: 50.4 ->
+// 47.0 us per call; 4096x2304 grey, block 9, dmax 63 in 16 x 32 items: 180 ->
+// 160 us).
+//
 // One pass over output columns [xs, xe) of tile `tile` (row-major over the
 // frame's ntx x nty tiles) for disparity chunk `chunk` (disparities
 // chunk*DC .. +DC-1), COLS window columns per lane. Ordered lists take the
 // whole tile in one pass; unordered lists may take a tile in several
 // narrower passes. The window columns of the pass start lpad > r columns
 // left of xs.
-template <int DC, bool kSorted, bool kPack, int COLS>
+template <int DC, bool kSorted, bool kPack, int COLS, bool kNarrow = false>
 __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int chunk, int xs, int xe, TileLds& smu) {
   static_assert(COLS == 4 || (kSorted && kPack), "8 columns per lane: ordered lists, packed accumulators");
   constexpr int kSpanC = Geom<COLS>::kSpanC;
-  constexpr int G = Geom<COLS>::G;
+  static_assert(!kNarrow || (kPack && COLS == 4), "narrow windows: packed accumulators, 4 columns per lane");
+  constexpr int G = kNarrow ? DC : Geom<COLS>::G;   // disparities whose prefix sums share the LDS
   constexpr int kTpShift = Geom<COLS>::kTpShift;
   constexpr int NB = kSorted ? COLS / 4 : 1;   // list entries of a row held in registers: 64 * NB
   auto& sm = LdsOf<COLS>::get(smu);
@@ -730,7 +742,15 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   // only two prefix pairs in flight per wait when a window sum is read.
   uint32_t dkey[DC];
 #pragma unroll
-  for (int k = 0; k < DC; ++k) dkey[k] = __builtin_amdgcn_readfirstlane(k < dcount ? (uint32_t)(d0 + k) : 0xFFFFFFFFu);
+  for (int k = 0; k < DC; ++k)
+    dkey[k] = __builtin_amdgcn_readfirstlane(k < dcount ? (uint32_t)(d0 + k) : (kNarrow ? 0xFFFFu : 0xFFFFFFFFu));
+  // narrow windows: key bytes (disparity, sum low, sum high, 0 or 0xFF past
+  // dmax) picked from the pair's word (low or high half) and dkey
+  uint32_t sel_lo = 0x01050400u, sel_hi = 0x01070600u;
+  if constexpr (kNarrow) {
+    asm volatile("" : "+v"(sel_lo));   // in vector registers: dkey takes the instruction's one scalar
+    asm volatile("" : "+v"(sel_hi));
+  }
 
   // acc: per window column COLS * lane + c and disparity d0 + k, the sum over
   // the window's rows of the absolute differences (summed over channels).
@@ -806,6 +826,26 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   // 64 * NB listed pixels in the tile).
   // prefix sums of disparities d0 + g .. d0 + g + G - 1 to LDS
   auto prefix_group = [&](int g) {
+    if constexpr (kNarrow) {
+#pragma unroll
+      for (int j0 = 0; j0 < DC / 2; j0 += 4) {
+        uint32_t t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = (acc.v[0][j0 + i] + acc.v[1][j0 + i]) + (acc.v[2][j0 + i] + acc.v[3][j0 + i]);
+        wave_incl_scan4(t[0], t[1], t[2], t[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          u32x4 w;
+          w.w = t[i];
+          w.z = w.w - acc.v[3][j0 + i];
+          w.y = w.z - acc.v[2][j0 + i];
+          w.x = w.y - acc.v[1][j0 + i];
+          *(lds_u32x4*)&sm.pre[j0 + i][4 * lane] = w;
+        }
+      }
+      wave_lds_order();
+      return;
+    }
 #pragma unroll
     for (int k0 = 0; k0 < G; k0 += 4) {
       // t: the lane's column total, then (after the wave scan) the prefix at
@@ -870,12 +910,19 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   // 5.42 ms; one such frame 293 -> 289 us; 384x288 grey 52.9 -> 51.3 us).
   auto group_best = [&](int g, int o, uint32_t best) -> uint32_t {
     const int ih = o + lpad + r, il = o + lpad - r - 1;   // il >= 0: lpad > r
-    uint32_t hi[G], lo[G];
+    constexpr int kRows = kNarrow ? G / 2 : G;   // LDS rows of a group
+    uint32_t hi[kRows], lo[kRows];
 #pragma unroll
-    for (int k = 0; k < G; ++k) { hi[k] = sm.pre[k][ih]; lo[k] = sm.pre[k][il]; }
+    for (int k = 0; k < kRows; ++k) { hi[k] = sm.pre[k][ih]; lo[k] = sm.pre[k][il]; }
     __builtin_amdgcn_sched_barrier(0);   // all reads in flight before the first is used
 #pragma unroll
-    for (int k = 0; k < G; ++k) best = min(best, ((hi[k] - lo[k]) << 8) | dkey[g + k]);
+    for (int k = 0; k < kRows; ++k) {
+      const uint32_t s = hi[k] - lo[k];
+      if constexpr (kNarrow)
+        best = min(best, min(__builtin_amdgcn_perm(s, dkey[2 * k], sel_lo), __builtin_amdgcn_perm(s, dkey[2 * k + 1], sel_hi)));
+      else
+        best = min(best, (s << 8) | dkey[g + k]);
+    }
     return best;
   };
   // a global (not flat) atomic: it counts only against the vector-memory counter
@@ -1030,6 +1077,10 @@ __device__ __forceinline__ void tile_item(const FrameDev& f, int tile, int chunk
     static_assert(DC == 8, "wide launches use 8-disparity chunks");
     if (f.cpl == 8 && !unsorted) tile_item_impl<8, true, true, 8>(f, tile, chunk, x0, x1, sm);
     else tile_item_wide_rest(f, tile, chunk, unsorted, x0, x1, sm);
+    return;
+  }
+  if (f.pack == 2 && !unsorted) {
+    tile_item_impl<DC, true, true, 4, true>(f, tile, chunk, x0, x1, sm);
     return;
   }
   if (DC == 16 && f.pack && !unsorted) {

@@ -68,3 +68,25 @@ def test_unordered_lists_tall_images(torch, sbs, H):
     L, R = pair(rng, W, H, 1)
     lst = rng.choice(W * H, max(W * H // 9, 20))
     check_search(torch, sbs, L, R, lst, 5, 11, f"{W}x{H}")
+
+
+@pytest.mark.parametrize("C,block", [(1, 15), (1, 17), (3, 9), (3, 11), (1, 1), (3, 1)])
+@pytest.mark.parametrize("chunk", [8, 16])
+def test_narrow_windows(torch, sbs, C, block, chunk):
+    """Windows whose sums just fit 16 bits (15x15 grey, 9x9 RGB) and the next
+    larger blocks, with sums up to the largest (black against white), largest
+    disparities around the chunks' ends, and widths around a tile's."""
+    rng = np.random.default_rng(7 * block + C)
+    sbs.set_plan(cols_per_lane=4, chunk=chunk, tile_rows=16)
+    try:
+        for W, H, dmax, white in [(241, 37, 15, True), (240, 20, 16, False), (530, 33, 33, True), (60, 9, 0, True)]:
+            L, R = pair(rng, W, H, C)
+            if white:
+                L[: H // 2] = 0
+                R[: H // 2] = 255
+                L[:, : W // 3] = 255
+                R[:, : W // 3] = 0
+            idx = np.sort(rng.choice(W * H, W * H // 3, replace=False))
+            check_search(torch, sbs, L, R, idx, block, dmax, f"{W}x{H}x{C} block {block} dmax {dmax}")
+    finally:
+        sbs.set_plan()
