@@ -64,13 +64,14 @@ struct QueueTotals {
 struct WsHeader {
   uint32_t error;        // bit 0: an index >= W*H was seen
   uint32_t pad0[15];
-  struct {
-    unsigned long long head;  // next item of this queue (own 64-byte line)
-    uint64_t pad[7];
-  } q[kQueues];
+  // The next item of queue q, each on a 128-byte L2 line of its own: adds to
+  // one line queue up one after another at the memory side, and so do reads
+  // of anything beside it.
+  unsigned long long heads[16 * kQueues - 8];
+  __device__ __forceinline__ unsigned long long* head(int q) { return &heads[16 * q]; }
 };
 constexpr size_t kHeaderBytes = 1024;
-static_assert(sizeof(WsHeader) <= kHeaderBytes, "header");
+static_assert(sizeof(WsHeader) <= kHeaderBytes && 16 * (kQueues - 1) < 16 * kQueues - 8, "header");
 
 // Records `msg` as the calling thread's last error (sbs_last_error) and returns status.
 int report_error(int status, const char* msg);

@@ -90,3 +90,28 @@ def test_narrow_windows(torch, sbs, C, block, chunk):
             check_search(torch, sbs, L, R, idx, block, dmax, f"{W}x{H}x{C} block {block} dmax {dmax}")
     finally:
         sbs.set_plan()
+
+
+@pytest.mark.parametrize("nframes,W,H,wpc", [(1, 40, 20, 16), (3, 90, 33, 16), (9, 250, 130, 16), (2, 700, 300, 1)])
+def test_queue_starts(torch, sbs, nframes, W, H, wpc):
+    """Batched launches with fewer work items than queues, about as many as
+    workgroups, and several items for each workgroup."""
+    rng = np.random.default_rng(nframes)
+    sbs.set_plan(waves_per_cu=wpc, tile_rows=8 if wpc == 1 else 0)
+    try:
+        host, frames = [], []
+        for t in range(nframes):
+            L, R = pair(rng, W, H, 3)
+            idx = np.sort(rng.choice(W * H, W * H // 5, replace=False)).astype(np.uint32)
+            host.append((L, R, idx))
+            frames.append((dev(torch, L), dev(torch, R), dev(torch, idx.view(np.int32)), 7, 40))
+        runner = sbs.BatchRunner(frames)
+        for rep in range(2):
+            runner.run()
+        torch.cuda.synchronize()
+        for t, (L, R, idx) in enumerate(host):
+            ed, ec, _ = oracle.sad(L, R, idx, 7, 40)
+            assert np.array_equal(runner.disp[t].cpu().numpy(), ed), t
+            assert np.array_equal(runner.cost[t].cpu().numpy().view(np.uint32), ec), t
+    finally:
+        sbs.set_plan()
