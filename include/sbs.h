@@ -199,7 +199,8 @@ int sbs_sad_disparity_per_frame(const sbs_frame* frames, int32_t nframes, void* 
  * (2 * block * 255 * C <= 65535) and min(n, (tile_rows - 1) * W) < 2^23;
  * other frames of the same call run with 4. A frame whose
  * min(n, (tile_rows - 1) * W) reaches 2^24 (2^23 at 8 columns per lane) runs
- * with tile_rows halved until it does not.
+ * with tile_rows halved until it does not. A launch of one frame runs its
+ * last work items with half of tile_rows.
  */
 typedef struct {
   int32_t cols_per_lane;

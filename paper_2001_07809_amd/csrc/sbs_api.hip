@@ -148,38 +148,63 @@ int ty_of(const sbs_frame& f, int ty, int cpl) {
   return ty;
 }
 
-// Work items of frame f with a given disparity chunk, tile height and lane width.
-int64_t items_of(const sbs_frame& f, int chunk, int ty, int cpl = 4) {
-  if (f.n <= 0) return 0;
+// Tiles of frame f under a plan: columns of tiles, rows of main tiles (`ty`
+// rows each, from the top) and, from row `ysplit` on, rows of tail tiles
+// (`ty2` rows each). Launches of one frame run their last kTailItems work
+// items' worth of main tiles (half a wavefront slot's worth each) as tail
+// tiles of half the height: an item is a serial chain of row steps, so while
+// the last items run the chip empties, and lower ones last half as long
+// (4096x2304, block 31, dmax 127, 16-disparity items of 32 rows: 354 -> 326
+// us; 2560x1440 in 16 x 16: 152 -> 137 us), and a small frame, which is all
+// tail, gets more items (384x288 in 8 x 8: 29 -> 26 us). Batches showed no
+// gain (24 frames of 4096x2304: 5.57 -> 5.60 ms) and run without.
+constexpr int kTailItems = 256 * 16 / 2;
+struct Tiles {
+  int ntx, nty, ysplit, ty, ty2, nch;
+  int64_t nrows;                                     // rows of tiles, main and tail
+  int64_t items() const { return (int64_t)ntx * nrows * nch; }
+};
+Tiles tiles_of(const sbs_frame& f, int chunk, int ty, int cpl, bool tail) {
+  Tiles t{};
   const int r = (f.block - 1) / 2;
   const int lpad = (r + 4) & ~3;
   const int c = cpl_of(f, cpl, chunk, ty);
   const int txo = (kWave * c - lpad - r) & ~3;
-  const int t = ty_of(f, ty, c);
-  return (int64_t)((f.W + txo - 1) / txo) * ((f.H + t - 1) / t) * ((f.dmax + chunk) / chunk);
+  t.ty = ty_of(f, ty, c);
+  t.ty2 = std::max(1, t.ty / 2);
+  t.ntx = (f.W + txo - 1) / txo;
+  t.nch = (f.dmax + chunk) / chunk;
+  const int64_t all = (f.H + t.ty - 1) / t.ty;
+  const int64_t per = (int64_t)t.ntx * t.nch;
+  t.nty = (int)(tail ? std::max<int64_t>(0, all - (kTailItems + per - 1) / per) : all);
+  t.ysplit = (int)std::min<int64_t>(f.H, (int64_t)t.nty * t.ty);
+  t.nrows = t.nty + (f.H - t.ysplit + t.ty2 - 1) / t.ty2;
+  return t;
 }
 
-// Default plan for the frames one launch covers: the largest items that
-// still give the chip at least four work items per wavefront slot (256 CUs x
-// 16), tried in the order (16 disparities, 128 rows), then 8 disparities with
-// 128, 64 and 32 rows; 8 x 32 below that. Larger items amortise the window
-// warm-up and the per-item work; more items balance the load (measured: one
-// 4096x2304 frame runs 8% faster with 8 x 32 items than with 8 x 128, a
-// 1390x1110 frame 44% faster; 250 such frames run best with 16 x 128).
+// Default plan for the frames one launch covers, by the launch's size as
+// its number of 16-disparity, 16-row items against the chip's 4096 wavefront
+// slots. Larger items amortise the window's first sum (2r + 1 rows) and the
+// item's start; lower ones end sooner, and an item is a serial chain of about
+// 1 us (8 disparities) or 1.9 us (16) per row, so a launch that cannot fill
+// the slots is as long as its longest item. Below an eighth of the slots the
+// smallest items win (384x288 grey 50 -> 27 us against 8 x 32 items, 640x480
+// 54 -> 28 us); then 16 disparities at rows that double as the launch grows
+// fourfold: 16 rows (1390x1110, block 21, dmax 63: 76 -> 63 us against 8 x
+// 32; 2560x1440: 167 -> 137 us; 8 frames of 640x480: 96 -> 86 us), 32 rows
+// (4096x2304: 357 -> 325 us; a serving mix of ten frames: 690 -> 629 us
+// against 8 x 64), 64 rows (8192x4608: 16 rows 1094, 64 rows 941 us; 6 frames
+// of 4096x2304 1.55 -> 1.42 ms against 128 rows), 96 rows (24 such frames:
+// 64 rows 5.39, 96 rows 5.36, 128 rows 5.44 ms), 128 rows beyond.
 Plan default_plan(const sbs_frame* frames, int nframes) {
-  auto items = [&](int chunk, int ty) {
-    int64_t t = 0;
-    for (int i = 0; i < nframes; ++i) t += items_of(frames[i], chunk, ty, 4);
-    return t;
-  };
-  const int64_t want = 4LL * 256 * 16;
+  int64_t n16 = 0;
+  for (int i = 0; i < nframes; ++i)
+    if (frames[i].n > 0) n16 += tiles_of(frames[i], 16, 16, 4, false).items();
+  constexpr int64_t kSlots = 256 * 16;
   Plan p;
   p.wpc = 16;
-  if (items(16, 128) >= want) { p.chunk = 16; p.ty = 128; return p; }
-  p.chunk = 8;
-  for (int ty : {128, 64, 32})
-    if (items(8, ty) >= want) { p.ty = ty; return p; }
-  p.ty = 32;
+  p.chunk = n16 < kSlots / 8 ? 8 : 16;
+  p.ty = n16 < kSlots / 8 ? 8 : n16 < 4 * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
   return p;
 }
 
@@ -404,15 +429,18 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     d.dmax = f.dmax;
     d.lpw = L.lpw; d.rpw = L.rpw; d.ph = L.ph; d.lpad = L.lpad; d.rpad = L.rpad; d.rbw = L.rbw;
     d.txo = L.txo;
-    d.ty = ty_of(f, plan.ty, cpl[(size_t)i]);
-    d.ntx = L.ntx;
-    d.nty = (f.H + d.ty - 1) / d.ty;
+    const Tiles t = tiles_of(f, plan.chunk, plan.ty, plan.cpl, mode != kBatched);
+    d.ty = t.ty;
+    d.ty2 = t.ty2;
+    d.ysplit = t.ysplit;
+    d.ntx = t.ntx;
+    d.nty = t.nty;
     d.chunk = plan.chunk;
-    d.nch = (f.dmax + 1 + plan.chunk - 1) / plan.chunk;
+    d.nch = t.nch;
     d.item_base = items;
-    d.nitems = f.n > 0 ? (int64_t)d.ntx * d.nty * d.nch : 0;
+    d.nitems = f.n > 0 ? t.items() : 0;
     items += d.nitems;
-    const int64_t ntiles = f.n > 0 ? (int64_t)d.ntx * d.nty : 0;
+    const int64_t ntiles = f.n > 0 ? (int64_t)t.ntx * t.nrows : 0;
     for (int q = 0; q < kQueues; ++q) {
       d.xbase[q] = qt.t[q];
       const int64_t tq = ntiles > q ? (ntiles - q + kQueues - 1) / kQueues : 0;

@@ -40,7 +40,8 @@ struct FrameDev {
   int32_t lpad, rpad;    // copy column of image column c: c + lpad (left), c + rpad (right); multiples of 4
   int32_t rbw;           // u64 words per row in rowbits
   int32_t txo, ty;       // tile: output columns and rows
-  int32_t ntx, nty;      // tiles per row / column
+  int32_t ntx, nty;      // tiles per row / column (the main tiles: ty rows each, from the top)
+  int32_t ysplit, ty2;   // rows from ysplit on lie in tiles of ty2 rows (the tail tiles, after the main ones)
   int32_t nch, chunk;    // disparity chunks and their size
   int32_t tpw;           // entries per row of tptr (ntx + 1)
   int32_t pack;          // 1: the sum of two window columns (<= 2 * block * 255 * C) fits in 16 bits;

@@ -643,11 +643,13 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   const int32_t* const f_map = f.map;
   const int32_t* const f_tptr = f.tptr;
   const uint64_t* const f_rowbits = f.rowbits;
-  const int f_tpw = f.tpw, f_rbw = f.rbw, f_ty = f.ty;
+  const int f_tpw = f.tpw, f_rbw = f.rbw;
   const int tx = tile % f.ntx, tyi = tile / f.ntx;
+  const bool tail = tyi >= f.nty;   // main tiles first, then the lower tail tiles
+  const int f_ty = tail ? f.ty2 : f.ty;
   const int W = f.W, H = f.H, r = f.r;
-  const int x0 = xs, y0 = tyi * f_ty;
-  const int x1 = xe, y1 = min(y0 + f_ty, H);
+  const int x0 = xs, y0 = tail ? f.ysplit + (tyi - f.nty) * f_ty : tyi * f_ty;
+  const int x1 = xe, y1 = min(y0 + f_ty, tail ? H : f.ysplit);
   const int d0 = chunk * DC;
   const int dcount = min(DC, f.dmax + 1 - d0);
   const int lpad = f.lpad;

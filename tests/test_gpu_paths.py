@@ -115,3 +115,35 @@ def test_queue_starts(torch, sbs, nframes, W, H, wpc):
             assert np.array_equal(runner.cost[t].cpu().numpy().view(np.uint32), ec), t
     finally:
         sbs.set_plan()
+
+
+@pytest.mark.parametrize("H", [1, 3, 4, 5, 7, 8, 9, 130])
+def test_tail_tiles(torch, sbs, H):
+    """Images that are all tail tiles (half of the plan's rows each), of fewer
+    rows than a tile, one row more, and several tiles."""
+    rng = np.random.default_rng(H)
+    W = 30
+    L, R = pair(rng, W, H, 1)
+    idx = np.unique(np.concatenate([rng.choice(W * H, W * H // 4, replace=False), np.arange(min(W, W * H)),
+                                    np.arange(max(0, W * H - 2 * W), W * H)]))
+    for tile_rows, chunk in ((8, 8), (9, 16), (0, 0)):
+        sbs.set_plan(chunk=chunk, tile_rows=tile_rows)
+        try:
+            check_search(torch, sbs, L, R, idx, 3, 15, f"H {H} tile rows {tile_rows}")
+        finally:
+            sbs.set_plan()
+
+
+@pytest.mark.parametrize("H", [9000, 9009])
+def test_main_and_tail_tiles(torch, sbs, H):
+    """Enough items for main tiles above the tail ones (8 rows, two chunks of
+    one tile column: 1,125 and 1,127 tile rows, the last 1,024 of them tail)."""
+    rng = np.random.default_rng(H)
+    W = 24
+    L, R = pair(rng, W, H, 1)
+    idx = np.sort(rng.choice(W * H, W * H // 6, replace=False))
+    sbs.set_plan(chunk=8, tile_rows=8)
+    try:
+        check_search(torch, sbs, L, R, idx, 5, 15, f"H {H}")
+    finally:
+        sbs.set_plan()
