@@ -277,312 +277,229 @@ __global__ __launch_bounds__(kBlock) void k_label(const uint8_t* __restrict__ L8
 }
 
 // ---------------------------------------------------------------------------
-// 3x3 refinement stencils (one fused kernel per mode below):
+// The 3x3 refinement on bit planes: 32 pixels of a row are one 32-bit word,
+// so a step on them is a handful of ands or ors.
 //   erosion (min) and dilation (max) with replicate borders;
 //   Moore boundary: 1 iff an in-image 8-neighbour differs;
 //   'fill': a 0 whose eight neighbours are all 1 becomes 1 (outside = 0);
 //   'remove': a 1 whose four 4-neighbours are all 1 becomes 0 (outside = 0).
+// MODE 0 (open, close, boundary of the labels): the planes are the
+// thresholds label >= t, t = 1 .. K - 1. Minimum and maximum of labels are
+// the ands and ors of their threshold planes, a neighbour that the replicate
+// border repeats is one the window holds anyway (so cells outside the image
+// are left out: ones to an and, zeros to an or), and two labels differ where
+// some plane does. MODE 1 (boundary, fill, remove): the planes are the bits
+// of the label.
+// A wavefront takes kRfCols columns x (64 - 2 halo) rows: lane = row, four
+// words per plane in registers, a word of halo columns on either side (six
+// words waste fewer columns but leave the chip with half the wavefronts:
+// 26 us at 4096x2304 against 20 us); the
+// rows above and below are the neighbouring lanes (DPP). No LDS and no
+// barriers but for the table that spreads a lightness value's label over
+// four planes: a byte each, so that eight pixels gather in one register and
+// four of those transpose to a word of each plane. Planes go four at a time
+// (one group up to K = 5, or K = 16 in MODE 1). Bound by the latency of one
+// wavefront's chain (row loads, table lookups, the steps), so all row loads
+// go out first (20 -> 17 us). Against label bytes with a byte-packed minimum
+// per word in LDS tiles and a pass of its own for the labels: MODE 0, K = 4:
+// 71 -> 17 us at 4096x2304, 28 -> 6 us at 640x480; MODE 1, K = 10: 24 -> 11
+// us at 1390x1110.
+constexpr int kRfWords = 4;
+constexpr int kRfCols = 32 * (kRfWords - 2);
+template <int MODE> constexpr int kRfHalo = MODE == 0 ? 5 : 3;
+template <int MODE> constexpr int kRfRows = 64 - 2 * kRfHalo<MODE>;
 
-// The configured refinement in one pass over the image: erode, dilate
-// (open), dilate, erode (close) with replicate borders, then the Moore
-// boundary, per tile of kMorphT x kMorphT pixels with a 5-pixel halo held in
-// LDS (one HBM read of the labels and one write of the boundary map, instead
-// of five of each). Each step runs on a box one pixel narrower on every side
-// than the one before, so its neighbours are always in the box. Clamping a
-// neighbour into the image is the same as reading a frame whose cells
-// outside the image repeat the nearest cell inside: the labels are loaded
-// that way, and on tiles at an image edge every step's result is repeated
-// into its outside cells before the next step reads them. The boundary step
-// ignores neighbours outside the image. `closed`
-// (optional) receives the labels after the close.
-constexpr int kMorphT = 64, kMorphHalo = 5, kMorphF = kMorphT + 2 * kMorphHalo;   // frame: 74 x 74
-constexpr int kMorphP = 84;   // LDS row pitch: a multiple of 4 with room for the word-wide reads past the frame
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const u32x4 g_u32x4;
 
-// Per-byte minimum / maximum of four labels packed in a word (labels < 128:
-// (a | 0x80) - b keeps each byte apart, and its bit 7 says a >= b).
-__device__ __forceinline__ uint32_t ge_mask4(uint32_t a, uint32_t b) {
-  return ((((a | 0x80808080u) - b) >> 7) & 0x01010101u) * 0xFFu;
-}
-__device__ __forceinline__ uint32_t min4(uint32_t a, uint32_t b) { const uint32_t m = ge_mask4(a, b); return (b & m) | (a & ~m); }
-__device__ __forceinline__ uint32_t max4(uint32_t a, uint32_t b) { const uint32_t m = ge_mask4(a, b); return (a & m) | (b & ~m); }
-
-// Four cells per thread and step, from two aligned LDS words per row and
-// byte shifts. A step on the box inset by k reads its source from column
-// fx - 1; the buffer it writes keeps frame column c at byte c + (-k mod 4),
-// so that the next step's reads start on a word again (the loaded frame has
-// offset 0, and so has the closed frame the boundary step reads). Groups at
-// a box's right end spill up to three cells past it; no later step reads
-// those. Frames inside the image with rows of whole words load and store
-// words; the others load bytes with clamped coordinates and store bytes,
-// and at an image edge every step's cells outside the image are then set to
-// the nearest cell inside, and the boundary of cells on the image's border
-// rows and columns is taken again without the neighbours outside.
-__global__ __launch_bounds__(kBlock) void k_morph_refine(const uint8_t* __restrict__ lab, int32_t W, int32_t H,
-                                                         uint8_t* __restrict__ B, uint8_t* __restrict__ closed,
-                                                         int32_t words) {
-  __shared__ __attribute__((aligned(16))) uint8_t buf[2][kMorphF * kMorphP];
-  const int x0 = blockIdx.x * kMorphT - kMorphHalo, y0 = blockIdx.y * kMorphT - kMorphHalo;   // frame origin
-  const bool edge = x0 < 0 || y0 < 0 || x0 + kMorphF > W || y0 + kMorphF > H;
-  const bool wide = !edge && words;   // word loads and stores
-  if (wide) {
-    constexpr int kWords = (kMorphF + 3 + 3) / 4;   // global words covering a frame row from column x0 - 3
-    for (int c = threadIdx.x; c < kMorphF * kWords; c += kBlock) {
-      const int fy = c / kWords, w = c - fy * kWords;
-      const uint8_t* row = lab + (int64_t)(y0 + fy) * W;
-      const int g0 = x0 - 3 + 4 * w;   // a multiple of 4 (x0 = 64 bx - 5)
-      uint32_t v = 0u;
-      if (g0 + 3 < W) v = *(const uint32_t*)(row + g0);
-      else
-        for (int j = 0; j < 4; ++j)
-          if (g0 + j < W) v |= (uint32_t)row[g0 + j] << (8 * j);
+// Pixels x .. x + 15 of a row (those outside the row come out as anything).
+// words: rows start on 4-byte boundaries and hold whole words; else the words
+// from the boundary below are shifted into place, and a group within 4 pixels
+// of the row's ends is read byte by byte.
+__device__ __forceinline__ void load16(const uint8_t* row, int x, int W, bool words, uint32_t (&v)[4]) {
+  if (words) {
+    if (x >= 0 && x + 16 <= W) {
+      const u32x4 q = *(g_u32x4*)(row + x);
+      v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int fx = 4 * w + j - 3;
-        if (fx >= 0 && fx < kMorphF) buf[0][fy * kMorphP + fx] = (uint8_t)(v >> (8 * j));
-      }
+      for (int j = 0; j < 4; ++j) v[j] = x + 4 * j >= 0 && x + 4 * j + 4 <= W ? *(const uint32_t*)(row + x + 4 * j) : 0u;
     }
+  } else if (x >= 4 && x + 20 <= W) {
+    const uint32_t sh = (uint32_t)(uintptr_t)(row + x) & 3u;
+    const uint8_t* p = row + x - sh;
+    const u32x4 q = *(g_u32x4*)p;
+    const uint32_t e = *(const uint32_t*)(p + 16);
+    v[0] = __builtin_amdgcn_alignbyte(q.y, q.x, sh);
+    v[1] = __builtin_amdgcn_alignbyte(q.z, q.y, sh);
+    v[2] = __builtin_amdgcn_alignbyte(q.w, q.z, sh);
+    v[3] = __builtin_amdgcn_alignbyte(e, q.w, sh);
   } else {
-    constexpr int kPer = (kMorphF * kMorphF + kBlock - 1) / kBlock;
-    uint8_t v[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = threadIdx.x + i * kBlock;
-      v[i] = 0;
-      if (c < kMorphF * kMorphF) {
-        const int fy = c / kMorphF, fx = c - fy * kMorphF;
-        const int gy = min(max(y0 + fy, 0), H - 1), gx = min(max(x0 + fx, 0), W - 1);
-        v[i] = lab[(int64_t)gy * W + gx];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = threadIdx.x + i * kBlock;
-      if (c < kMorphF * kMorphF) buf[0][(c / kMorphF) * kMorphP + c % kMorphF] = v[i];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 1; k <= 4; ++k) {
-    const uint8_t* src = buf[(k - 1) & 1];
-    uint8_t* dst = buf[k & 1];
-    const int os = (1 - k) & 3, od = (-k) & 3;   // byte offsets of frame column 0
-    const bool mx = k == 2 || k == 3;
-    constexpr int kMaxGroups = (kMorphF - 2 + 3) / 4;
-    const int n = kMorphF - 2 * k, ng = (n + 3) / 4;
-    for (int c = threadIdx.x; c < n * kMaxGroups; c += kBlock) {
-      const int fy = k + c / kMaxGroups, g = c % kMaxGroups;
-      if (g >= ng) continue;
-      const int fx = k + 4 * g;
-      uint32_t h[3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const uint32_t* q = (const uint32_t*)(src + (fy - 1 + j) * kMorphP + fx - 1 + os);
-        const uint32_t a = q[0], b = q[1];
-        const uint32_t l = a, m = __builtin_amdgcn_alignbyte(b, a, 1), r = __builtin_amdgcn_alignbyte(b, a, 2);
-        h[j] = mx ? max4(max4(l, m), r) : min4(min4(l, m), r);
-      }
-      const uint32_t o = mx ? max4(max4(h[0], h[1]), h[2]) : min4(min4(h[0], h[1]), h[2]);
-      *(uint32_t*)(dst + fy * kMorphP + fx + od) = o;
-    }
-    __syncthreads();
-    if (edge) {
-      // the box's cells outside the image take the nearest cell inside
-      for (int c = threadIdx.x; c < n * n; c += kBlock) {
-        const int fy = k + c / n, fx = k + c % n;
-        const int gy = y0 + fy, gx = x0 + fx;
-        if (gy >= 0 && gy < H && gx >= 0 && gx < W) continue;
-        const int cy = min(max(gy, 0), H - 1) - y0, cx = min(max(gx, 0), W - 1) - x0;
-        dst[fy * kMorphP + fx + od] = dst[cy * kMorphP + cx + od];
-      }
-      __syncthreads();
-    }
-  }
-  // boundary of the tile from the closed labels (buf[0], offset 0)
-  const uint8_t* lb = buf[0];
-  constexpr int kTileGroups = kMorphT / 4;
-  for (int c = threadIdx.x; c < kMorphT * kTileGroups; c += kBlock) {
-    const int ty = c / kTileGroups, g = c % kTileGroups;
-    const int fy = kMorphHalo + ty, fx = kMorphHalo + 4 * g;
-    uint32_t nb[3][3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const uint32_t* q = (const uint32_t*)(lb + (fy - 1 + j) * kMorphP + fx - 1);
-      const uint32_t a = q[0], b = q[1];
-      nb[j][0] = a; nb[j][1] = __builtin_amdgcn_alignbyte(b, a, 1); nb[j][2] = __builtin_amdgcn_alignbyte(b, a, 2);
-    }
-    const uint32_t v = nb[1][1];
-    uint32_t acc = 0u;   // bit 7 of a byte: some neighbour differs
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-        if (j != 1 || i != 1) acc |= ((nb[j][i] ^ v) + 0x7F7F7F7Fu) & 0x80808080u;
-    const uint32_t r = (acc >> 7) & 0x01010101u;
-    const int gy = y0 + fy, gx = x0 + fx;   // gx a multiple of 4
-    if (wide) {
-      *(uint32_t*)(B + (int64_t)gy * W + gx) = r;
-      if (closed) *(uint32_t*)(closed + (int64_t)gy * W + gx) = v;
-      continue;
-    }
-    if (gy >= H) continue;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int x = gx + j;
-      if (x >= W) break;
-      uint8_t bj = (uint8_t)(r >> (8 * j));
-      if (gy == 0 || gy == H - 1 || x == 0 || x == W - 1) {
-        // on the image's border: neighbours outside the image do not count
-        const uint8_t* q = lb + fy * kMorphP + fx + j;
-        const int cv = q[0];
-        bool d = false;
-        for (int dy = -1; dy <= 1; ++dy)
-          for (int dx = -1; dx <= 1; ++dx)
-            if ((dy || dx) && gy + dy >= 0 && gy + dy < H && x + dx >= 0 && x + dx < W)
-              d |= q[dy * kMorphP + dx] != cv;
-        bj = d ? 1 : 0;
+      v[j] = 0u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int xx = x + 4 * j + b;
+        if (xx >= 0 && xx < W) v[j] |= (uint32_t)row[xx] << (8 * b);
       }
-      B[(int64_t)gy * W + x] = bj;
-      if (closed) closed[(int64_t)gy * W + x] = (uint8_t)(v >> (8 * j));
     }
   }
 }
 
-// The paper's refinement in one pass over the image: the Moore boundary of
-// the labels, then 'fill', then 'remove', per tile of kMorphT x kMorphT
-// pixels with a 3-pixel halo in LDS, four cells per thread and step as in
-// k_morph_refine (the maps after the first step hold 0 and 1, so 'fill' and
-// 'remove' are plain bitwise ands and ors of neighbour words). The boundary
-// step ignores neighbours outside the image (cells on the image's border
-// rows and columns are taken again without them); 'fill' and 'remove' take
-// them as 0, so at an image edge every step's cells outside the image are
-// set to 0 before the next step reads them.
-constexpr int kPaperHalo = 3, kPaperF = kMorphT + 2 * kPaperHalo;   // frame: 70 x 70
-__global__ __launch_bounds__(kBlock) void k_paper_refine(const uint8_t* __restrict__ lab, int32_t W, int32_t H,
-                                                         uint8_t* __restrict__ B, int32_t words) {
-  __shared__ __attribute__((aligned(16))) uint8_t buf[2][kPaperF * kMorphP];
-  const int x0 = blockIdx.x * kMorphT - kPaperHalo, y0 = blockIdx.y * kMorphT - kPaperHalo;   // frame origin
-  const bool edge = x0 < 0 || y0 < 0 || x0 + kPaperF > W || y0 + kPaperF > H;
-  const bool wide = !edge && words;
-  auto inside = [&](int gy, int gx) { return gy >= 0 && gy < H && gx >= 0 && gx < W; };
-  if (wide) {
-    constexpr int kWords = (kPaperF + 1 + 3) / 4;   // global words covering a frame row from column x0 - 1
-    for (int c = threadIdx.x; c < kPaperF * kWords; c += kBlock) {
-      const int fy = c / kWords, w = c - fy * kWords;
-      const uint8_t* row = lab + (int64_t)(y0 + fy) * W;
-      const int g0 = x0 - 1 + 4 * w;   // a multiple of 4 (x0 = 64 bx - 3)
-      uint32_t v = 0u;
-      if (g0 + 3 < W) v = *(const uint32_t*)(row + g0);
-      else
-        for (int j = 0; j < 4; ++j)
-          if (g0 + j < W) v |= (uint32_t)row[g0 + j] << (8 * j);
+// The row above (the lane below) and the row below; the wavefront's first and
+// last rows get their own value.
+__device__ __forceinline__ uint32_t row_up(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xf, 0xf, false);   // wave_shr:1
+}
+__device__ __forceinline__ uint32_t row_down(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130, 0xf, 0xf, false);   // wave_shl:1
+}
+// the pixels to the left and right of a word's (the outermost words take their own edge pixel)
+__device__ __forceinline__ uint32_t px_left(const uint32_t (&w)[kRfWords], int i) {
+  return __builtin_amdgcn_alignbit(w[i], w[i > 0 ? i - 1 : 0], 31);
+}
+__device__ __forceinline__ uint32_t px_right(const uint32_t (&w)[kRfWords], int i) {
+  return __builtin_amdgcn_alignbit(w[i < kRfWords - 1 ? i + 1 : i], w[i], 1);
+}
+
+// One erosion (kMin) or dilation of a plane, in place.
+template <bool kMin>
+__device__ __forceinline__ void plane_step(uint32_t (&w)[kRfWords], const uint32_t (&valid)[kRfWords]) {
+  uint32_t a[kRfWords];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int fx = 4 * w + j - 1;
-        if (fx >= 0 && fx < kPaperF) buf[0][fy * kMorphP + fx] = (uint8_t)(v >> (8 * j));
-      }
-    }
-  } else {
-    constexpr int kPer = (kPaperF * kPaperF + kBlock - 1) / kBlock;
-    uint8_t v[kPer];
+  for (int i = 0; i < kRfWords; ++i) a[i] = kMin ? w[i] | ~valid[i] : w[i] & valid[i];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = threadIdx.x + i * kBlock;
-      v[i] = 0;
-      if (c < kPaperF * kPaperF) {
-        const int fy = c / kPaperF, fx = c - fy * kPaperF;
-        const int gy = min(max(y0 + fy, 0), H - 1), gx = min(max(x0 + fx, 0), W - 1);
-        v[i] = lab[(int64_t)gy * W + gx];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int c = threadIdx.x + i * kBlock;
-      if (c < kPaperF * kPaperF) buf[0][(c / kPaperF) * kMorphP + c % kPaperF] = v[i];
-    }
+  for (int i = 0; i < kRfWords; ++i) {
+    const uint32_t l = px_left(a, i), r = px_right(a, i);
+    const uint32_t h = kMin ? a[i] & l & r : a[i] | l | r;
+    w[i] = kMin ? h & row_up(h) & row_down(h) : h | row_up(h) | row_down(h);
   }
-  __syncthreads();
-  // the three neighbour words (left, centre, right) of a row of four cells
-  auto row3 = [&](const uint8_t* p, uint32_t& l, uint32_t& m, uint32_t& r) {
-    const uint32_t a = ((const uint32_t*)p)[0], b = ((const uint32_t*)p)[1];
-    l = a; m = __builtin_amdgcn_alignbyte(b, a, 1); r = __builtin_amdgcn_alignbyte(b, a, 2);
-  };
-  // steps 1 and 2 on the frame inset by k (k = 1: boundary, k = 2: fill); offsets as in k_morph_refine
+}
+
+// out |= pixels of the plane with an in-image neighbour that differs
+__device__ __forceinline__ void plane_boundary(const uint32_t (&w)[kRfWords], const uint32_t (&valid)[kRfWords],
+                                               uint32_t (&out)[kRfWords]) {
+  uint32_t lo[kRfWords], hi[kRfWords];
 #pragma unroll
-  for (int k = 1; k <= 2; ++k) {
-    const uint8_t* src = buf[(k - 1) & 1];
-    uint8_t* dst = buf[k & 1];
-    const int os = (1 - k) & 3, od = (-k) & 3;
-    constexpr int kMaxGroups = (kPaperF - 2 + 3) / 4;
-    const int n = kPaperF - 2 * k, ng = (n + 3) / 4;
-    for (int c = threadIdx.x; c < n * kMaxGroups; c += kBlock) {
-      const int fy = k + c / kMaxGroups, g = c % kMaxGroups;
-      if (g >= ng) continue;
-      const int fx = k + 4 * g;
-      uint32_t nb[3][3];
+  for (int i = 0; i < kRfWords; ++i) { lo[i] = w[i]; hi[i] = w[i]; }
+  plane_step<true>(lo, valid);
+  plane_step<false>(hi, valid);
 #pragma unroll
-      for (int j = 0; j < 3; ++j) row3(src + (fy - 1 + j) * kMorphP + fx - 1 + os, nb[j][0], nb[j][1], nb[j][2]);
-      const uint32_t v = nb[1][1];
-      uint32_t o;
-      if (k == 1) {
-        uint32_t acc = 0u;   // bit 7 of a byte: some neighbour differs (labels < 128)
+  for (int i = 0; i < kRfWords; ++i) out[i] |= hi[i] & ~lo[i] & valid[i];
+}
+
+// Boundary map as bits: word wpr * y + (x >> 6), bit x & 63. `closed`
+// (optional, MODE 0) receives the labels after the close.
+template <int MODE>
+__global__ __launch_bounds__(64) void k_refine(const uint8_t* __restrict__ lum, int32_t W, int32_t H, int32_t K,
+                                               const uint8_t* __restrict__ lut, unsigned long long* __restrict__ B,
+                                               int32_t wpr, uint8_t* __restrict__ closed, int32_t words) {
+  __shared__ uint32_t code[256];
+  const int lane = threadIdx.x;
+  const int x0 = blockIdx.x * kRfCols, gx = x0 - 32;        // first output column, first column held
+  const int gy = (int)blockIdx.y * kRfRows<MODE> - kRfHalo<MODE> + lane;
+  const bool row_in = gy >= 0 && gy < H;
+  const uint8_t* row = lum + (int64_t)min(max(gy, 0), H - 1) * W;
+  uint32_t valid[kRfWords];
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
+  for (int i = 0; i < kRfWords; ++i) {
+    const int lo = max(0, -(gx + 32 * i)), hi = min(32, W - (gx + 32 * i));   // columns of the word inside the image
+    const uint32_t m = hi <= lo ? 0u : (hi == 32 ? ~0u : (1u << hi) - 1u) & ~((1u << lo) - 1u);
+    valid[i] = row_in ? m : 0u;
+  }
+  // planes: MODE 0 label >= 1 .. K - 1, MODE 1 the label's bits
+  const int np = MODE == 0 ? K - 1 : 32 - __builtin_clz(max(K - 1, 1));
+  uint32_t acc[kRfWords];
 #pragma unroll
-          for (int i = 0; i < 3; ++i)
-            if (j != 1 || i != 1) acc |= ((nb[j][i] ^ v) + 0x7F7F7F7Fu) & 0x80808080u;
-        o = (acc >> 7) & 0x01010101u;
-      } else {
-        uint32_t all = 0x01010101u;   // every neighbour 1
+  for (int i = 0; i < kRfWords; ++i) acc[i] = 0u;
+  // the lane's pixels, all loads in flight together (and under the table's making)
+  uint32_t px[kRfWords][8];
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
+  for (int i = 0; i < kRfWords; ++i) {
+    uint32_t q[4];
+    load16(row, gx + 32 * i, W, words, q);
+    px[i][0] = q[0]; px[i][1] = q[1]; px[i][2] = q[2]; px[i][3] = q[3];
+    load16(row, gx + 32 * i + 16, W, words, q);
+    px[i][4] = q[0]; px[i][5] = q[1]; px[i][6] = q[2]; px[i][7] = q[3];
+  }
+  for (int g = 0; g == 0 || 4 * g < np; ++g) {
+    __syncthreads();
+    for (int b = lane; b < 256; b += 64) {
+      const int lab = lut[b];
+      uint32_t c = 0u;
 #pragma unroll
-          for (int i = 0; i < 3; ++i)
-            if (j != 1 || i != 1) all &= nb[j][i];
-        o = v | all;
+      for (int p = 0; p < 4; ++p) {
+        const int t = 4 * g + p;
+        if (t < np && (MODE == 0 ? lab > t : (lab >> t) & 1)) c |= 1u << (8 * p);
       }
-      *(uint32_t*)(dst + fy * kMorphP + fx + od) = o;
+      code[b] = c;
     }
     __syncthreads();
-    if (edge) {
-      for (int c = threadIdx.x; c < n * n; c += kBlock) {
-        const int fy = k + c / n, fx = k + c % n;
-        const int gy = y0 + fy, gx = x0 + fx;
-        uint8_t* d = dst + fy * kMorphP + fx + od;
-        if (!inside(gy, gx)) { *d = 0; continue; }   // outside: 0 for the steps that follow
-        if (k == 1 && (gy == 0 || gy == H - 1 || gx == 0 || gx == W - 1)) {
-          // on the image's border: the boundary without the neighbours outside
-          const uint8_t* q = src + fy * kMorphP + fx + os;
-          const int cv = q[0];
-          bool diff = false;
-          for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx)
-              if ((dy || dx) && inside(gy + dy, gx + dx)) diff |= q[dy * kMorphP + dx] != cv;
-          *d = diff ? 1 : 0;
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // step 3: 'remove' on the tile, from buf[0] (offset 2)
-  constexpr int kTileGroups = kMorphT / 4;
-  for (int c = threadIdx.x; c < kMorphT * kTileGroups; c += kBlock) {
-    const int ty = c / kTileGroups, g = c % kTileGroups;
-    const int fy = kPaperHalo + ty, fx = kPaperHalo + 4 * g;
-    uint32_t u, l, v, r, dn, t0, t1;
-    row3(buf[0] + (fy - 1) * kMorphP + fx - 1 + 2, t0, u, t1);
-    row3(buf[0] + fy * kMorphP + fx - 1 + 2, l, v, r);
-    row3(buf[0] + (fy + 1) * kMorphP + fx - 1 + 2, t0, dn, t1);
-    const uint32_t o = v & ~(u & dn & l & r);
-    const int gy = y0 + fy, gx = x0 + fx;   // gx a multiple of 4
-    if (wide) {
-      *(uint32_t*)(B + (int64_t)gy * W + gx) = o;
-      continue;
-    }
-    if (gy >= H) continue;
+    uint32_t P[4][kRfWords];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (gx + j < W) B[(int64_t)gy * W + gx + j] = (uint8_t)(o >> (8 * j));
+    for (int i = 0; i < kRfWords; ++i) {
+      const uint32_t (&v)[8] = px[i];
+      uint32_t a[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[q] = 0u;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) a[q] |= code[(v[2 * q + (b >> 2)] >> (8 * (b & 3))) & 0xFFu] << b;
+      }
+      const uint32_t t0 = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u), t1 = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u);
+      const uint32_t t2 = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u), t3 = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+      P[0][i] = __builtin_amdgcn_perm(t2, t0, 0x05040100u);
+      P[1][i] = __builtin_amdgcn_perm(t2, t0, 0x07060302u);
+      P[2][i] = __builtin_amdgcn_perm(t3, t1, 0x05040100u);
+      P[3][i] = __builtin_amdgcn_perm(t3, t1, 0x07060302u);
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      if (4 * g + p >= np) continue;
+      if constexpr (MODE == 0) {
+        plane_step<true>(P[p], valid);    // open
+        plane_step<false>(P[p], valid);
+        plane_step<false>(P[p], valid);   // close
+        plane_step<true>(P[p], valid);
+      }
+      plane_boundary(P[p], valid, acc);
+    }
+    if constexpr (MODE == 0) {
+      // the closed label of a pixel is the number of planes it is set in
+      if (closed && row_in && lane >= kRfHalo<MODE> && lane < 64 - kRfHalo<MODE>) {
+        uint8_t* crow = closed + (int64_t)gy * W;
+#pragma unroll
+        for (int i = 1; i < kRfWords - 1; ++i)
+          for (int j = 0; j < 32; ++j) {
+            const int x = gx + 32 * i + j;
+            if (x >= W) break;
+            int lab = g > 0 ? crow[x] : 0;
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+              if (4 * g + p < np) lab += (P[p][i] >> j) & 1u;
+            crow[x] = (uint8_t)lab;
+          }
+      }
+    }
   }
+  if constexpr (MODE == 1) {
+    // 'fill', then 'remove'; acc is 0 outside the image
+    uint32_t f[kRfWords];
+#pragma unroll
+    for (int i = 0; i < kRfWords; ++i) {
+      const uint32_t l = px_left(acc, i), r = px_right(acc, i), h = acc[i] & l & r;
+      f[i] = (acc[i] | (l & r & row_up(h) & row_down(h))) & valid[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kRfWords; ++i)
+      acc[i] = f[i] & ~(px_left(f, i) & px_right(f, i) & row_up(f[i]) & row_down(f[i]));
+  }
+  if (!row_in || lane < kRfHalo<MODE> || lane >= 64 - kRfHalo<MODE>) return;
+  unsigned long long* out = B + (int64_t)gy * wpr + (x0 >> 6);
+#pragma unroll
+  for (int i = 1; i < kRfWords - 1; i += 2)
+    if ((x0 >> 6) + i / 2 < wpr) out[i / 2] = (unsigned long long)acc[i] | (unsigned long long)acc[i + 1] << 32;
 }
 
 // ---------------------------------------------------------------------------
@@ -650,8 +567,8 @@ __device__ __forceinline__ void lds_union(int32_t* lp, int32_t a, int32_t b) {
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_cc_tile(const uint8_t* __restrict__ B, int32_t W, int32_t H,
-                                                    int32_t* parent, int32_t* size) {
+__global__ __launch_bounds__(kBlock) void k_cc_tile(const unsigned long long* __restrict__ B, int32_t wpr, int32_t W,
+                                                    int32_t H, int32_t* parent, int32_t* size) {
   __shared__ int32_t lp[kTileW * kTileH];
   __shared__ int32_t lsz[kTileW * kTileH];
   const int x0 = blockIdx.x * kTileW, y0 = blockIdx.y * kTileH;
@@ -665,12 +582,11 @@ __global__ __launch_bounds__(kBlock) void k_cc_tile(const uint8_t* __restrict__ 
 #pragma unroll
   for (int j = 0; j < kTileH / kRowsPerPass; ++j) {
     const int ly = (int)(threadIdx.x / kTileW) * kBand + j;
-    const int x = x0 + lx, y = y0 + ly;
-    on[j] = x < W && y < H && B[(int64_t)y * W + x] != 0;
-    // a wavefront holds one tile row (kTileW == 64): each pixel links
-    // straight to the first pixel of its horizontal run, so left neighbours
-    // need no union below
-    const uint64_t row = __builtin_amdgcn_ballot_w64(on[j]);
+    // a wavefront holds one tile row, one word of the map (kTileW == 64):
+    // each pixel links straight to the first pixel of its horizontal run, so
+    // left neighbours need no union below
+    const uint64_t row = y0 + ly < H ? B[(int64_t)(y0 + ly) * wpr + blockIdx.x] : 0ull;
+    on[j] = (row >> lx) & 1ull;
     const uint64_t upto = lx == 63 ? ~0ull : ((2ull << lx) - 1ull);   // bits 0 .. lx
     const uint64_t gaps = ~row & upto;
     const int start = gaps ? 64 - __builtin_clzll(gaps) : 0;   // just past the last gap at or before lx
@@ -732,8 +648,12 @@ __global__ __launch_bounds__(kBlock) void k_cc_tile(const uint8_t* __restrict__ 
 // tiles, or by the left-column unions of the tile holding their right part),
 // so a run's first pixel takes up-left, and up when up-left is off, and every
 // pixel takes up-right only when up is off.
-__global__ __launch_bounds__(128) void k_cc_edges(const uint8_t* __restrict__ B, int32_t W, int32_t H,
-                                                  int32_t* parent) {
+__device__ __forceinline__ bool map_bit(const unsigned long long* B, int32_t wpr, int x, int y) {
+  return (B[(int64_t)y * wpr + (x >> 6)] >> (x & 63)) & 1ull;
+}
+
+__global__ __launch_bounds__(128) void k_cc_edges(const unsigned long long* __restrict__ B, int32_t wpr, int32_t W,
+                                                  int32_t H, int32_t* parent) {
   const int x0 = blockIdx.x * kTileW, y0 = blockIdx.y * kTileH;
   const int t = threadIdx.x;
   int lx = 0, ly = 0;
@@ -743,7 +663,7 @@ __global__ __launch_bounds__(128) void k_cc_edges(const uint8_t* __restrict__ B,
   const int x = x0 + lx, y = y0 + ly;
   const bool in = t < kTileW + 2 * (kTileH - 1) && x < W && y < H;
   const int32_t i = y * W + x;
-  const bool on = in && B[i] != 0;
+  const bool on = in && map_bit(B, wpr, x, y);
   bool first = true;
   if (t < kTileW) {   // wavefront 0 holds the top row (kTileW == 64)
     const uint64_t row = __builtin_amdgcn_ballot_w64(on);
@@ -751,19 +671,20 @@ __global__ __launch_bounds__(128) void k_cc_edges(const uint8_t* __restrict__ B,
   }
   if (!on) return;
   // raster-earlier neighbours that lie in another tile
-  if (x > 0 && lx == 0 && B[i - 1]) uf_union(parent, i, i - 1);
+  if (x > 0 && lx == 0 && map_bit(B, wpr, x - 1, y)) uf_union(parent, i, i - 1);
   if (y > 0) {
     const int32_t u = i - W;
     if (ly == 0) {
-      const bool ul = x > 0 && B[u - 1], uc = B[u] != 0, ur = x + 1 < W && B[u + 1];
+      const bool ul = x > 0 && map_bit(B, wpr, x - 1, y - 1), uc = map_bit(B, wpr, x, y - 1),
+                 ur = x + 1 < W && map_bit(B, wpr, x + 1, y - 1);
       if (first) {
         if (ul) uf_union(parent, i, u - 1);
         if (uc && !ul) uf_union(parent, i, u);
       }
       if (ur && !uc) uf_union(parent, i, u + 1);
     } else {
-      if (lx == 0 && x > 0 && B[u - 1]) uf_union(parent, i, u - 1);
-      if (lx == kTileW - 1 && x + 1 < W && B[u + 1]) uf_union(parent, i, u + 1);
+      if (lx == 0 && x > 0 && map_bit(B, wpr, x - 1, y - 1)) uf_union(parent, i, u - 1);
+      if (lx == kTileW - 1 && x + 1 < W && map_bit(B, wpr, x + 1, y - 1)) uf_union(parent, i, u + 1);
     }
   }
 }
@@ -923,7 +844,6 @@ struct FracState {
 };
 
 struct ScanCtx {
-  const uint8_t* B;       // boundary map after refinement
   const int32_t* parent;  // flattened: root of each boundary pixel, -1 elsewhere
   const int32_t* size;    // size at roots
   const DropRule* rule;   // paper filter (nullptr: configured filter)
@@ -1690,7 +1610,7 @@ int fail(int st, const char* fmt, ...) {
 size_t a256(size_t v) { return (v + 255) / 256 * 256; }
 
 struct Layout {
-  size_t L8, lab, lab2, B, parent, size, cnt, bsum, bits, hist, g, dist, frank, rhist, dhist, lut, misc, end;
+  size_t L8, cls, B, parent, size, cnt, bsum, bits, hist, g, dist, frank, rhist, dhist, lut, misc, end;
 };
 
 Layout layout(int32_t W, int32_t H) {
@@ -1701,9 +1621,8 @@ Layout layout(int32_t W, int32_t H) {
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off += a256(bytes); return at; };
   o.L8 = take(N);
-  o.lab = take(N);
-  o.lab2 = take(N);
-  o.B = take(N);
+  o.cls = take(N);
+  o.B = take((size_t)H * ((W + 63) / 64) * 8);
   o.parent = take((size_t)N * 4);
   o.size = take((size_t)N * 4);
   o.cnt = take(((size_t)N + 1) * 4);
@@ -1811,7 +1730,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   if (K < 1 || K > kMaxK) return fail(SBS_ERR_INVALID_ARG, "K must be in [1, %d]", kMaxK);
   if (mode != 0 && mode != 1) return fail(SBS_ERR_INVALID_ARG, "mode must be 0 (configured) or 1 (paper)");
   if (mode == 0 && min_cc < 0) return fail(SBS_ERR_INVALID_ARG, "min_cc < 0");
-  if (H > 4 * 65535) return fail(SBS_ERR_UNSUPPORTED, "H > %d", 4 * 65535);   // 2-D stencil grid: 4 rows per block
+  if (H > 4 * 65535) return fail(SBS_ERR_UNSUPPORTED, "H > %d", 4 * 65535);
   if (!(frac < 0.0) && !(frac <= 1.0)) return fail(SBS_ERR_INVALID_ARG, "frac must be < 0 (off) or in [0, 1]");
   const int64_t N = (int64_t)W * H;
   const Layout Lo = layout(W, H);
@@ -1820,9 +1739,8 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)workspace;
   uint8_t* L8 = (uint8_t*)(base + Lo.L8);
-  uint8_t* lab = (uint8_t*)(base + Lo.lab);
-  uint8_t* lab2 = (uint8_t*)(base + Lo.lab2);
-  uint8_t* B = (uint8_t*)(base + Lo.B);
+  unsigned long long* B = (unsigned long long*)(base + Lo.B);
+  const int32_t wpr = (W + 63) / 64;   // words per row of the maps held as bits
   int32_t* parent = (int32_t*)(base + Lo.parent);
   int32_t* size = (int32_t*)(base + Lo.size);
   int32_t* cnt = (int32_t*)(base + Lo.cnt);
@@ -1854,33 +1772,22 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   // at most 512 blocks: each ends with up to 256 global adds
   hipLaunchKernelGGL(k_hist, dim3(std::min(grid_for((N + 15) / 16), 512)), dim3(kBlock), 0, s, lum, N, hist);
   hipLaunchKernelGGL(k_kmeans, dim3(1), dim3(256), 0, s, hist, K, lut, passes);
-  hipLaunchKernelGGL(k_label, dim3(g), dim3(kBlock), 0, s, lum, N, lut, lab);
-  const uint8_t* labels = lab;
+  const int32_t words = (W & 3) == 0 && ((uintptr_t)lum & 3) == 0 ? 1 : 0;
+  auto rf_grid = [&](int rows) { return dim3((W + kRfCols - 1) / kRfCols, (H + rows - 1) / rows); };
   if (mode == 0) {
-    // open, close and boundary in one pass; the closed labels go straight to
-    // out_labels when asked for
-    const dim3 gm((W + kMorphT - 1) / kMorphT, (H + kMorphT - 1) / kMorphT);
-    // word-wide interior path: rows of whole words, the outputs word-aligned too
-    const int32_t words = (W & 3) == 0 && ((uintptr_t)out_labels & 3) == 0 ? 1 : 0;
-    hipLaunchKernelGGL(k_morph_refine, gm, dim3(kBlock), 0, s, lab, W, H, B, out_labels, words);
-    labels = nullptr;
+    hipLaunchKernelGGL(k_refine<0>, rf_grid(kRfRows<0>), dim3(64), 0, s, lum, W, H, K, lut, B, wpr, out_labels, words);
   } else {
-    // boundary, fill and remove in one pass
-    const dim3 gm((W + kMorphT - 1) / kMorphT, (H + kMorphT - 1) / kMorphT);
-    hipLaunchKernelGGL(k_paper_refine, gm, dim3(kBlock), 0, s, lab, W, H, B, (W & 3) == 0 ? 1 : 0);
-  }
-  if (out_labels && labels) {
-    const hipError_t ce = hipMemcpyAsync(out_labels, labels, (size_t)N, hipMemcpyDeviceToDevice, s);
-    if (ce != hipSuccess) return fail(SBS_ERR_HIP, "boundaries: %s", hipGetErrorString(ce));
+    hipLaunchKernelGGL(k_refine<1>, rf_grid(kRfRows<1>), dim3(64), 0, s, lum, W, H, K, lut, B, wpr, (uint8_t*)nullptr, words);
+    if (out_labels) hipLaunchKernelGGL(k_label, dim3(g), dim3(kBlock), 0, s, lum, N, lut, out_labels);
   }
   const dim3 gt((W + kTileW - 1) / kTileW, (H + kTileH - 1) / kTileH);
-  hipLaunchKernelGGL(k_cc_tile, gt, dim3(kBlock), 0, s, B, W, H, parent, size);
-  hipLaunchKernelGGL(k_cc_edges, gt, dim3(128), 0, s, B, W, H, parent);
+  hipLaunchKernelGGL(k_cc_tile, gt, dim3(kBlock), 0, s, B, wpr, W, H, parent, size);
+  hipLaunchKernelGGL(k_cc_edges, gt, dim3(128), 0, s, B, wpr, W, H, parent);
   hipLaunchKernelGGL(k_cc_flatten, dim3(g), dim3(kBlock), 0, s, N, parent, size);
 
   const int64_t nb = (N + kScanPer - 1) / kScanPer;
   ScanCtx c{};
-  c.B = B; c.parent = parent; c.size = size; c.rule = nullptr; c.min_cc = min_cc; c.W = W; c.N = N;
+  c.parent = parent; c.size = size; c.rule = nullptr; c.min_cc = min_cc; c.W = W; c.N = N;
   c.rank = cnt;   // the rank array reuses cnt: ranks are written after k_drop_find has read the counts
   c.out = out_idx; c.refined = out_refined; c.count = (long long*)out_count;
   c.bits = (unsigned long long*)(base + Lo.bits);
@@ -1899,7 +1806,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   if (frac >= 0.0) {
     const long long want = std::min<long long>((long long)N, std::llround(frac * (double)N));
     const long long n0 = W == 1 ? H : 2LL * H;
-    uint8_t* cls = lab2;   // free once the refinement is done
+    uint8_t* cls = (uint8_t*)(base + Lo.cls);
     hipLaunchKernelGGL(k_fc_class, dim3(g), dim3(kBlock), 0, s, c, cls, n1);
     // Component sizes are at most N: with N below 2^24 the top digit of ~size is
     // 0xFF for every kept pixel, so it is set here and its pass skipped.

@@ -147,3 +147,39 @@ def test_main_and_tail_tiles(torch, sbs, H):
         check_search(torch, sbs, L, R, idx, 5, 15, f"H {H}")
     finally:
         sbs.set_plan()
+
+
+def check_front(torch, sbs, dimg, img, K, mode, min_cc, what):
+    lst, refined, labels = sbs.boundaries(dimg, K=K, mode=mode, min_cc=min_cc, with_maps=True)
+    exp_list, exp_map = oracle.boundaries(img, K=K, mode=mode, min_cc=min_cc, frac=-1.0, return_map=True)
+    L8 = oracle.lightness(img)
+    lab = oracle.label_pixels(L8, oracle.kmeans_bins(oracle.histogram(L8), K)[0])
+    if mode == 0:
+        lab = oracle.label_open_close(lab)
+    assert np.array_equal(labels.cpu().numpy(), lab), f"{what}: labels"
+    assert np.array_equal(refined.cpu().numpy(), exp_map), f"{what}: kept map"
+    assert np.array_equal(lst.cpu().numpy().view(np.uint32), exp_list), f"{what}: list"
+    assert np.array_equal(sbs.boundaries(dimg, K=K, mode=mode, min_cc=min_cc).cpu().numpy().view(np.uint32), exp_list), what
+
+
+def blotches(rng, W, H, levels=9):
+    """A grey image of flat patches a few pixels wide, with specks."""
+    img = np.kron(rng.integers(0, levels, (H // 5 + 1, W // 7 + 1)), np.ones((5, 7)))[:H, :W] * (255 // levels)
+    img[rng.random((H, W)) < 0.02] = 255
+    return img.astype(np.uint8)
+
+
+@pytest.mark.parametrize("W,H", [(63, 54), (64, 55), (65, 58), (68, 59), (127, 64), (130, 109), (200, 117), (20, 3), (35, 240)])
+def test_refinement_tiles(torch, sbs, W, H):
+    """Images around the refinement's tiles (64 columns; 54 rows configured,
+    58 in paper mode), rows of whole words and not, images at odd addresses,
+    and numbers of clusters at the edges of a group of planes."""
+    rng = np.random.default_rng(W * H)
+    img = blotches(rng, W, H)
+    for off in (0, 1):
+        buf = torch.zeros(W * H + 8, dtype=torch.uint8, device="cuda")
+        view = buf[off:off + W * H].view(H, W)
+        view.copy_(dev(torch, img))
+        for mode, Ks in ((0, (2, 5, 6, 9)), (1, (2, 4, 16, 17))):
+            for K in Ks:
+                check_front(torch, sbs, view, img, K, mode, 5, f"{W}x{H} offset {off} mode {mode} K {K}")
