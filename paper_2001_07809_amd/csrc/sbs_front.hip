@@ -35,8 +35,6 @@
 namespace sbs_front {
 
 constexpr int kBlock = 256;
-constexpr int kScanPer = 1024;     // elements per block in the device-wide scans
-constexpr int kRsPasses = 8;       // most counting passes of one radix select (a 64-bit key)
 constexpr int kMaxK = 64;
 constexpr int kMaxPasses = 1000;
 constexpr int kN1Parts = 64;        // partial counts of kept pixels (fraction control)
@@ -149,8 +147,11 @@ __global__ __launch_bounds__(kBlock) void k_light4(const uint8_t* __restrict__ i
 void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t pitch, uint8_t* L8, int grid,
                   hipStream_t s);
 
-__global__ __launch_bounds__(kBlock) void k_fill(uint8_t* p, int64_t n, uint8_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
+// n bytes of zeros (16-byte aligned, a multiple of 16), by a kernel: no
+// memset nodes if the caller captures the stream.
+__global__ __launch_bounds__(kBlock) void k_clear(uint4* p, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n / 16; i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = uint4{0u, 0u, 0u, 0u};
 }
 
 // Histogram: 16-byte loads (16 pixels per thread and step where the buffer
@@ -718,19 +719,98 @@ __global__ __launch_bounds__(kBlock) void k_cc_flatten(int64_t N, int32_t* paren
 }
 
 // ---------------------------------------------------------------------------
+// Maps held as bits: word y * wpr + (x >> 6), bit x & 63, the words of a row
+// ending with it. Words in order are pixels in raster order.
+struct Bits {
+  int32_t W, H, wpr;
+  int64_t words;   // H * wpr
+  int64_t per;     // words per block of the passes that number the list (a multiple of kSelWords)
+};
+constexpr int kSelWords = 64;       // words a block takes at a time: 16 per wavefront
+constexpr int kSelBlocks = 1024;    // most blocks of those passes, so that each can add up the counts before its own
+
+struct WordPos {
+  int c, y, i;                // word column, row, and raster index of its first pixel (W * H < 2^31)
+  unsigned long long border;  // its pixels in the image's first and last column
+};
+__device__ __forceinline__ void word_border(const Bits& b, WordPos& p) {
+  p.border = (p.c == 0 ? 1ull : 0ull) | (p.c == b.wpr - 1 ? 1ull << ((b.W - 1) & 63) : 0ull);
+}
+__device__ __forceinline__ WordPos word_pos(const Bits& b, int64_t wi) {
+  WordPos p;
+  p.y = (int)((uint32_t)wi / (uint32_t)b.wpr);   // words < 2^31
+  p.c = (int)((uint32_t)wi - (uint32_t)p.y * (uint32_t)b.wpr);
+  p.i = p.y * b.W + 64 * p.c;
+  word_border(b, p);
+  return p;
+}
+// kWaveWords words of a map from w0 on (zeros from w_end on): lane j holds
+// word j, its first pixel and its border pixels; word(j) and first(j) give
+// them to every lane as scalars. One load and one division for all of them
+// (a division per word, and words a few at a time with a round trip to memory
+// for each step, made k_kept 29 us at 4096x2304, 20 us so).
+constexpr int kWaveWords = kSelWords / (kBlock / 64);   // 16
+struct WaveWords {
+  unsigned long long v, border;
+  int i;
+  __device__ __forceinline__ unsigned long long word(int j) const {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, j) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), j) << 32;
+  }
+  __device__ __forceinline__ unsigned long long border_of(int j) const {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)border, j) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(border >> 32), j) << 32;
+  }
+  __device__ __forceinline__ int first(int j) const { return __builtin_amdgcn_readlane(i, j); }
+};
+__device__ __forceinline__ WaveWords wave_words(const Bits& b, const unsigned long long* map, int64_t w0, int64_t w_end) {
+  const int lane = threadIdx.x & 63;
+  WaveWords r{0ull, 0ull, 0};
+  if (lane < kWaveWords && w0 + lane < w_end) {
+    r.v = map[w0 + lane];
+    const WordPos p = word_pos(b, w0 + lane);
+    r.i = p.i;
+    r.border = p.border;
+  }
+  return r;
+}
+// a[i] at the lanes that start a horizontal run of word j, `none` elsewhere.
+__device__ __forceinline__ void at_run_starts(const WaveWords& w, const int32_t* a, int32_t none, int32_t (&v)[kWaveWords]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < kWaveWords; ++j) {
+    v[j] = none;
+    const unsigned long long m = w.word(j);
+    if (!m) continue;
+    if (__builtin_amdgcn_inverse_ballot_w64(m & ~(m << 1))) v[j] = a[w.first(j) + lane];
+  }
+}
+// The bits of the horizontal run of w that starts at bit a.
+__device__ __forceinline__ unsigned long long run_from(unsigned long long w, int a) {
+  const unsigned long long m = 1ull << a;
+  return w & ~(w + m) & ~(m - 1ull);   // adding the start bit clears exactly its run
+}
+
+// ---------------------------------------------------------------------------
 // Paper filter: components in ascending (size, root) order are dropped while
 // the dropped total stays <= floor(0.04 * total). With cnt[s] the number of
 // components of size s (s <= budget), everything below the first size s* that
 // no longer fits whole is dropped, and of size s* the first m by root.
+constexpr double kDropFrac = 0.04;
 struct DropRule {
   long long total;    // boundary pixels
-  long long budget;   // floor(drop_frac * total)
-  int32_t s_star;     // sizes < s_star dropped; 0: none
+  long long budget;   // floor(kDropFrac * total)
+  int32_t s_star;     // sizes < s_star dropped
   int32_t m;          // components of size s_star dropped (smallest roots first)
+  int32_t first;      // the first root of size s_star that is kept
 };
 
-// cnt[s] += 1 for every component of size s; total = all boundary pixels.
-__global__ __launch_bounds__(kBlock) void k_drop_count(const int32_t* __restrict__ size, int64_t N,
+// cnt[s] += 1 for every component of size s that the budget could hold
+// (s <= kDropFrac N, the array's length); total = all boundary pixels. Sizes
+// are read at the starts of the map's runs only: every root is one, and after
+// k_cc_flatten a run start's size is non-zero exactly at roots.
+__global__ __launch_bounds__(kBlock) void k_drop_count(Bits b, const unsigned long long* __restrict__ B,
+                                                       const int32_t* __restrict__ size, int64_t ncnt,
                                                        unsigned long long* total, int32_t* cnt) {
   constexpr int kSmall = 1024;   // sizes below this are counted per block in LDS first
   __shared__ unsigned long long part;
@@ -738,49 +818,38 @@ __global__ __launch_bounds__(kBlock) void k_drop_count(const int32_t* __restrict
   for (int j = threadIdx.x; j < kSmall; j += blockDim.x) small[j] = 0;
   if (threadIdx.x == 0) part = 0;
   __syncthreads();
+  const int lane = threadIdx.x & 63;
   unsigned long long mine = 0;
-  // After k_cc_flatten a pixel's size is non-zero exactly at the roots
-  // (tile roots that are not roots handed their counts on and hold 0).
-  auto count_root = [&](int32_t s) {
-    if (s <= 0) return;
-    mine += (unsigned long long)s;
-    if (s < kSmall) atomicAdd(&small[s], 1);
-    else atomicAdd(&cnt[s], 1);
-  };
-  // four pixels per thread and step (one 16-byte load of sizes: the grid is
-  // small, so each thread needs several loads in flight), then the tail
-  const int64_t nq = N >> 2;
-  const int4* sq = (const int4*)size;   // 16-byte aligned: in the 256-byte aligned workspace
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += (int64_t)gridDim.x * blockDim.x) {
-    const int4 v = sq[q];
-    count_root(v.x);
-    count_root(v.y);
-    count_root(v.z);
-    count_root(v.w);
-  }
-  if (blockIdx.x == 0)
-    for (int64_t i = (nq << 2) + threadIdx.x; i < N; i += blockDim.x) count_root(size[i]);
-  // one LDS add per wavefront (adds to one word from every lane serialise)
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t w0 = kWaveWords * ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)); w0 < b.words; w0 += kWaveWords * nw) {
+    const WaveWords w = wave_words(b, B, w0, b.words);
+    int32_t s[kWaveWords];
+    at_run_starts(w, size, 0, s);
+    mine += (unsigned long long)__builtin_popcountll(w.v);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&part, mine);
+    for (int j = 0; j < kWaveWords; ++j) {
+      if (s[j] <= 0) continue;
+      if (s[j] < kSmall) atomicAdd(&small[s[j]], 1);
+      else if (s[j] < ncnt) atomicAdd(&cnt[s[j]], 1);
+    }
+  }
+  if (lane < kWaveWords && mine) atomicAdd(&part, mine);
   __syncthreads();
-  for (int j = threadIdx.x; j < kSmall && j <= N; j += blockDim.x)
+  for (int j = threadIdx.x; j < kSmall && j < ncnt; j += blockDim.x)
     if (small[j]) atomicAdd(&cnt[j], small[j]);
-  if (threadIdx.x == 0) atomicAdd(total, part);
+  if (threadIdx.x == 0 && part) atomicAdd(total, part);
 }
 
-// One block: the budget floor(drop_frac * total) (the rule's comparison in
+// One block: the budget floor(kDropFrac * total) (the rule's comparison in
 // fp64), then a walk over sizes 1..budget in order, a block-wide scan per
 // chunk of 1024 sizes, to the first size that does not fit whole.
 __global__ __launch_bounds__(1024) void k_drop_find(const int32_t* __restrict__ cnt,
-                                                    const unsigned long long* __restrict__ total, double drop_frac,
-                                                    DropRule* rule) {
+                                                    const unsigned long long* __restrict__ total, DropRule* rule) {
   __shared__ unsigned long long sc[1024];
   __shared__ int done;
   __shared__ unsigned long long base_s;
   const unsigned long long t = *total;
-  const long long bud = (long long)floor(drop_frac * (double)t);
+  const long long bud = (long long)floor(kDropFrac * (double)t);
   if (threadIdx.x == 0) {
     done = 0;
     base_s = 0;
@@ -788,6 +857,7 @@ __global__ __launch_bounds__(1024) void k_drop_find(const int32_t* __restrict__ 
     rule->budget = bud;
     rule->s_star = (int32_t)(bud + 1);   // every size <= budget fits: the first size > budget stops the walk
     rule->m = 0;
+    rule->first = 0;
   }
   __syncthreads();
   for (long long s0 = 1; s0 <= bud; s0 += 1024) {
@@ -816,121 +886,8 @@ __global__ __launch_bounds__(1024) void k_drop_find(const int32_t* __restrict__ 
   }
 }
 
-// ---------------------------------------------------------------------------
-// Device-wide exclusive scan of 0/1 flags in three launches: per-block
-// counts, a scan of the counts in one block, then per-block prefix and
-// scatter. Flag sources:
-//   kind 0 (roots of size s*):  rank[i] = number of such roots before i
-//   kind 1 (list):              out[pos] = i for border columns and kept pixels
-// Fraction control (a benchmark knob, not the paper's): exactly `want`
-// pixels ranked as (1) border columns by raster index, (2) kept pixels by
-// component size descending, then raster index, (3) all other pixels by
-// chessboard distance to (1)+(2) ascending, then h(i) = mix64(i ^ seed), then
-// raster index. The selection is threshold-based: a radix select finds the
-// key of the want-th pixel within the class it falls in, ties at that key go
-// by raster order (a device-wide scan).
-struct RadixSel {
-  unsigned long long prefix;   // key bits found so far (top digits first)
-  long long need;              // rank (1-based) of the wanted key among the candidates
-  long long below;             // candidates with a smaller key (of the digits fixed so far)
-};
-
-struct FracState {
-  long long want, n0, n1;
-  int32_t mode;                // 0: border only, 1: + kept pixels, 2: + other pixels
-  RadixSel s1;                 // kept pixels: key ~size (size descending)
-  RadixSel s2;                 // other pixels: key distance
-  RadixSel s3;                 // other pixels at distance s2.prefix: key h(i)
-};
-
-struct ScanCtx {
-  const int32_t* parent;  // flattened: root of each boundary pixel, -1 elsewhere
-  const int32_t* size;    // size at roots
-  const DropRule* rule;   // paper filter (nullptr: configured filter)
-  int64_t min_cc;
-  int32_t W;
-  int64_t N;
-  int32_t* rank;          // kind 0 output
-  uint32_t* out;          // kind 1 output
-  uint8_t* refined;       // kind 1 optional output: kept map
-  long long* count;       // kind 1: list length
-  const FracState* fc;    // fraction control (nullptr: list = border columns + kept pixels)
-  const int32_t* dist;    // chessboard distance to border + kept pixels
-  int32_t* frank;         // kinds 2, 3 output: rank of a tie in raster order
-  unsigned long long seed;
-  const uint8_t* cls;     // fraction control: 0 border column, 1 kept, 2 other
-  // The flags of a scan, one bit per element (word i >> 6, bit i & 63):
-  // written by the counting pass, read by the applying pass instead of
-  // working the flags out again (nullptr: both passes work them out).
-  unsigned long long* bits;
-};
-
-// Kept: the pixel's component (root r, -1 for no boundary pixel) passes the filter.
-__device__ __forceinline__ bool kept_root(const ScanCtx& c, int32_t r) {
-  if (r < 0) return false;
-  const int32_t s = c.size[r];
-  if (!c.rule) return s >= c.min_cc;
-  if (s < c.rule->s_star) return false;
-  if (s == c.rule->s_star) return c.rank[r] >= c.rule->m;
-  return true;
-}
-__device__ __forceinline__ bool kept(const ScanCtx& c, int64_t i) { return kept_root(c, c.parent[i]); }
-
-// SplitMix64's output function (Steele, Lea and Flood; constants as
-// published by Vigna), on the raster index xor the seed.
-__device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
-  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
-  z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
-  return z ^ (z >> 31);
-}
-
-__device__ __forceinline__ bool border(const ScanCtx& c, int64_t i) {
-  const int x = (int)((uint32_t)i % (uint32_t)c.W);   // W * H < 2^31: 32-bit division suffices
-  return x == 0 || x == c.W - 1;
-}
-
-__device__ __forceinline__ int32_t comp_size(const ScanCtx& c, int64_t i) { return c.size[c.parent[i]]; }
-
-__device__ __forceinline__ bool selected(const ScanCtx& c, int64_t i) {
-  const bool b = border(c, i);
-  if (!c.fc) return b || kept(c, i);
-  const FracState& f = *c.fc;
-  if (f.mode == 0) {
-    if (!b) return false;
-    const int64_t y = (uint32_t)i / (uint32_t)c.W;
-    const int64_t rank0 = c.W == 1 ? y : 2 * y + (((uint32_t)i % (uint32_t)c.W) == (uint32_t)(c.W - 1) ? 1 : 0);
-    return rank0 < f.want;
-  }
-  if (b) return true;
-  const bool k = c.cls[i] == 1;
-  if (f.mode == 1) {
-    if (!k) return false;
-    const uint32_t key = ~(uint32_t)comp_size(c, i);
-    const uint32_t kstar = (uint32_t)f.s1.prefix;
-    return key < kstar || (key == kstar && c.frank[i] < f.s1.need - f.s1.below);
-  }
-  if (k) return true;
-  const uint32_t d = (uint32_t)c.dist[i], dstar = (uint32_t)f.s2.prefix;
-  if (d != dstar) return d < dstar;
-  const unsigned long long h = mix64((unsigned long long)i ^ c.seed);
-  return h < f.s3.prefix || (h == f.s3.prefix && c.frank[i] < f.s3.need - f.s3.below);
-}
-
-template <int KIND>
-__device__ __forceinline__ bool flag(const ScanCtx& c, int64_t i) {
-  if constexpr (KIND == 0) {
-    return c.parent[i] == (int32_t)i && c.size[i] == c.rule->s_star;
-  } else if constexpr (KIND == 1) {
-    return selected(c, i);
-  } else if constexpr (KIND == 2) {   // kept, not border, size at the threshold
-    return c.cls[i] == 1 && ~(uint32_t)comp_size(c, i) == (uint32_t)c.fc->s1.prefix;
-  } else {                            // other pixels at the threshold distance and hash
-    return c.cls[i] == 2 && (uint32_t)c.dist[i] == (uint32_t)c.fc->s2.prefix &&
-           mix64((unsigned long long)i ^ c.seed) == c.fc->s3.prefix;
-  }
-}
-
-// Inclusive scan of one value per lane across the wavefront (shuffles).
+// Exclusive scan of one value per thread across a block of kWaves wavefronts:
+// wavefront scans by shuffles, then the wavefront totals through LDS.
 __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -940,9 +897,6 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t v) {
   }
   return v;
 }
-
-// Exclusive scan of the per-lane values of a block of kWaves wavefronts:
-// wavefront scans, then the wavefront totals through LDS (two barriers).
 template <int kWaves>
 __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wtot, uint32_t& total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -960,469 +914,820 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t* wtot, 
   total = all;
   return before + incl - v;
 }
-
-template <int KIND>
-__global__ __launch_bounds__(kBlock) void k_scan_count(ScanCtx c, uint32_t* bsum) {
-  __shared__ uint32_t s;
-  if (threadIdx.x == 0) s = 0;
-  __syncthreads();
-  const int64_t i0 = (int64_t)blockIdx.x * kScanPer;
-  uint32_t m = 0;
-#pragma unroll
-  for (int j0 = 0; j0 < kScanPer; j0 += kBlock) {
-    const int64_t i = i0 + j0 + threadIdx.x;
-    const bool fl = i < c.N && flag<KIND>(c, i);
-    m += fl;
-    if (c.bits) {
-      // the wavefront's 64 consecutive elements as one word
-      const unsigned long long w = __builtin_amdgcn_ballot_w64(fl);
-      if ((threadIdx.x & 63) == 0) c.bits[(i0 + j0 + threadIdx.x) >> 6] = w;
-    }
-  }
-  m = wave_scan_incl(m);   // lane 63: the wavefront's count
-  if ((threadIdx.x & 63) == 63) atomicAdd(&s, m);
-  __syncthreads();
-  if (threadIdx.x == 0) bsum[blockIdx.x] = s;
+// Sum of the counts of the blocks before this one (at most kSelBlocks of them).
+__device__ __forceinline__ uint32_t counts_before(const uint32_t* bsum, uint32_t* wtot) {
+  uint32_t v = 0;
+  for (int j = threadIdx.x; j < (int)blockIdx.x; j += blockDim.x) v += bsum[j];
+  uint32_t all;
+  block_scan_excl<kBlock / 64>(v, wtot, all);
+  return all;
 }
 
-// exclusive scan of nb block counts in place (one block of 1024 threads):
-// the counts are read into LDS with coalesced loads (up to kTopLds of them;
-// beyond that straight from global memory), each thread sums a contiguous
-// run of them, the runs are scanned across the block, then each thread
-// writes its run's prefixes back to LDS and the block stores them coalesced.
-constexpr int kTopLds = 12288;   // 48 KB: 4096x3072 pixels at 1024 per count
-__global__ __launch_bounds__(1024) void k_scan_top(uint32_t* bsum, int64_t nb, long long* total) {
+// Roots of size s* per block of b.per words (at run starts, as k_drop_count).
+__global__ __launch_bounds__(kBlock) void k_root_count(Bits b, const unsigned long long* __restrict__ B,
+                                                       const int32_t* __restrict__ size, const DropRule* rule,
+                                                       uint32_t* bsum) {
+  __shared__ uint32_t part;
+  if (threadIdx.x == 0) part = 0;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int32_t s_star = rule->s_star;
+  uint32_t mine = 0;
+  if (rule->m > 0) {
+    const int64_t w_end = min((int64_t)(blockIdx.x + 1) * b.per, b.words);
+    for (int64_t w0 = (int64_t)blockIdx.x * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
+      int32_t s[kWaveWords];
+      at_run_starts(wave_words(b, B, w0, w_end), size, 0, s);
+#pragma unroll
+      for (int j = 0; j < kWaveWords; ++j)
+        mine += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(s[j] == s_star));   // s* >= 1
+    }
+  }
+  if (lane == 0 && mine) atomicAdd(&part, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = part;
+}
+
+// One block: the first kept root of size s*, the one with m such roots before
+// it in raster order (there is one: s* does not fit whole).
+__global__ __launch_bounds__(1024) void k_root_find(Bits b, const unsigned long long* __restrict__ B,
+                                                    const int32_t* __restrict__ size, const uint32_t* __restrict__ bsum,
+                                                    int nb, DropRule* rule) {
   __shared__ uint32_t wtot[16];
-  __shared__ uint32_t v[kTopLds];
-  const bool in_lds = nb <= kTopLds;
-  if (in_lds)
-    for (int64_t b = threadIdx.x; b < nb; b += 1024) v[b] = bsum[b];
+  __shared__ int blk_s;
+  __shared__ uint32_t left_s;
+  const uint32_t m = (uint32_t)rule->m;
+  if (m == 0) return;
+  constexpr int kPer = kSelBlocks / 1024;
+  uint32_t v[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int j = threadIdx.x * kPer + k;
+    v[k] = j < nb ? bsum[j] : 0u;
+    sum += v[k];
+  }
+  uint32_t all, before = block_scan_excl<16>(sum, wtot, all);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (before <= m && m < before + v[k]) { blk_s = threadIdx.x * kPer + k; left_s = m - before; }
+    before += v[k];
+  }
   __syncthreads();
-  uint32_t* src = in_lds ? v : bsum;
-  const int64_t per = (nb + 1023) / 1024;
-  const int64_t b0 = (int64_t)threadIdx.x * per, b1 = min(b0 + per, nb);
-  uint32_t run = 0;
-  for (int64_t b = b0; b < b1; ++b) run += src[b];
-  uint32_t all;
-  uint32_t pos = block_scan_excl<16>(run, wtot, all);   // (its barriers order the reads above before the writes below)
-  for (int64_t b = b0; b < b1; ++b) {
-    const uint32_t c = src[b];
-    src[b] = pos;
-    pos += c;
+  if (threadIdx.x >= 64) return;
+  // one wavefront walks the block's words
+  const int lane = threadIdx.x;
+  const int32_t s_star = rule->s_star;
+  uint32_t left = left_s;
+  const int64_t w_end = min((int64_t)(blk_s + 1) * b.per, b.words);
+  for (int64_t w0 = (int64_t)blk_s * b.per; w0 < w_end; w0 += kWaveWords) {
+    const WaveWords w = wave_words(b, B, w0, w_end);
+    int32_t s[kWaveWords];
+    at_run_starts(w, size, 0, s);
+#pragma unroll
+    for (int j = 0; j < kWaveWords; ++j) {
+      const unsigned long long hm = __builtin_amdgcn_ballot_w64(s[j] == s_star);
+      const uint32_t c = (uint32_t)__builtin_popcountll(hm);
+      if (left < c) {
+        if (s[j] == s_star && (uint32_t)__builtin_popcountll(hm & ((1ull << lane) - 1ull)) == left)
+          rule->first = w.first(j) + lane;
+        return;
+      }
+      left -= c;
+    }
   }
-  if (in_lds) {
-    __syncthreads();
-    for (int64_t b = threadIdx.x; b < nb; b += 1024) bsum[b] = v[b];
-  }
-  if (threadIdx.x == 0 && total) *total = (long long)all;
 }
 
-template <int KIND>
-__global__ __launch_bounds__(kBlock) void k_scan_apply(ScanCtx c, const uint32_t* bsum) {
-  // thread t owns elements i0 + per t .. i0 + per t + per - 1 (in order)
-  __shared__ uint32_t sc[kBlock / 64];
-  const int64_t i0 = (int64_t)blockIdx.x * kScanPer;
-  constexpr int per = kScanPer / kBlock;
-  static_assert(64 % per == 0, "a thread's flags lie in one word");
-  bool f[per];
-  uint32_t m = 0;
-  if (c.bits) {
-    const int64_t e = i0 + (int64_t)threadIdx.x * per;   // per divides 64: one word holds the thread's flags
-    const unsigned long long w = c.bits[e >> 6] >> (e & 63);
+// Kept pixels: those of components that pass the filter. A component's root
+// and size are looked up once per horizontal run and word, at the run's first
+// pixel; the runs that pass go out whole by one addition (adding a run's
+// start bit clears the run). kept (optional): kept pixels; base: kept pixels
+// and border columns; refined (optional): the kept map as bytes; bsum
+// (optional): base pixels per block; n1 (optional): kept pixels off the
+// border columns, in kN1Parts counters (adds to one word from every block
+// queue up one after another at the memory side). With n1 every run's first
+// pixel gets its component's size (roots hold it already, and no other
+// pixel's is read here), which the counting passes then read without a look
+// at the root.
+__global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long long* __restrict__ B,
+                                                 const int32_t* __restrict__ parent, int32_t* size, const DropRule* rule,
+                                                 int64_t min_cc, unsigned long long* kept,
+                                                 unsigned long long* base, uint8_t* refined, uint32_t* bsum,
+                                                 unsigned long long* n1) {
+  __shared__ uint32_t nsel, nkept;
+  if (threadIdx.x == 0) nsel = nkept = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int32_t s_star = rule ? rule->s_star : 0, first = rule ? rule->first : 0;
+  uint32_t csel = 0, ckept = 0;
+  const int64_t w_end = min((int64_t)(blockIdx.x + 1) * b.per, b.words);
+  for (int64_t w0 = (int64_t)blockIdx.x * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
+    const WaveWords w = wave_words(b, B, w0, w_end);
+    int32_t r[kWaveWords], s[kWaveWords];
+    at_run_starts(w, parent, -1, r);
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-      f[j] = (w >> j) & 1ull;
-      m += f[j];
+    for (int j = 0; j < kWaveWords; ++j) {
+      s[j] = 0;
+      if (r[j] >= 0) s[j] = size[r[j]];
     }
-  } else {
+    unsigned long long kv = 0ull;   // lane j: word j's kept pixels
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-      const int64_t i = i0 + (int64_t)threadIdx.x * per + j;
-      f[j] = i < c.N && flag<KIND>(c, i);
-      m += f[j];
+    for (int j = 0; j < kWaveWords; ++j) {
+      const unsigned long long m = w.word(j);
+      if (!m) continue;
+      const bool ok = r[j] >= 0 && (rule ? s[j] > s_star || (s[j] == s_star && r[j] >= first) : s[j] >= min_cc);
+      const unsigned long long k = m & ~(m + __builtin_amdgcn_ballot_w64(ok));
+      if (lane == j) kv = k;
+      if (n1) {
+        const int32_t i = w.first(j) + lane;
+        if (r[j] >= 0 && r[j] != i) size[i] = s[j];
+      }
+    }
+    if (lane < kWaveWords && w0 + lane < w_end) {
+      if (kept) kept[w0 + lane] = kv;
+      base[w0 + lane] = kv | w.border;
+      csel += (uint32_t)__builtin_popcountll(kv | w.border);
+      ckept += (uint32_t)__builtin_popcountll(kv & ~w.border);
+    }
+    if (refined) {
+      for (int j = 0; j < kWaveWords && w0 + j < w_end; ++j) {
+        const int x = 64 * (int)((uint32_t)(w0 + j) % (uint32_t)b.wpr) + lane;
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)kv, j), hi = __builtin_amdgcn_readlane((uint32_t)(kv >> 32), j);
+        const int i = w.first(j) + lane;
+        if (x < b.W) refined[i] = (uint8_t)(((lane < 32 ? lo : hi) >> (lane & 31)) & 1u);
+      }
     }
   }
-  uint32_t all;
-  uint32_t pos = bsum[blockIdx.x] + block_scan_excl<kBlock / 64>(m, sc, all);
-#pragma unroll
-  for (int j = 0; j < per; ++j) {
-    const int64_t i = i0 + (int64_t)threadIdx.x * per + j;
-    if (i >= c.N) break;
-    if constexpr (KIND == 0) {
-      if (f[j]) c.rank[i] = (int32_t)pos;
-    } else if constexpr (KIND == 1) {
-      if (f[j]) c.out[pos] = (uint32_t)i;
-      if (c.refined) c.refined[i] = kept(c, i) ? 1 : 0;
-    } else {
-      if (f[j]) c.frank[i] = (int32_t)pos;
-    }
-    pos += f[j];
+  if (lane < kWaveWords) {
+    atomicAdd(&nsel, csel);
+    atomicAdd(&nkept, ckept);
   }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (bsum) bsum[blockIdx.x] = nsel;
+    if (n1 && nkept) atomicAdd(&n1[blockIdx.x % kN1Parts], (unsigned long long)nkept);
+  }
+}
+
+// The list: the raster indices of the map's set pixels, in order, and their
+// number. A block adds up the counts of the blocks before it (there are at
+// most kSelBlocks), then its words' counts; a wavefront writes a word's
+// pixels with one lane each, side by side.
+__global__ __launch_bounds__(kBlock) void k_list(Bits b, const unsigned long long* __restrict__ sel,
+                                                 const uint32_t* __restrict__ bsum, uint32_t* out, long long* count) {
+  __shared__ uint32_t wtot[kBlock / 64];
+  __shared__ uint32_t pre[kSelWords], first[kSelWords];
+  __shared__ unsigned long long word[kSelWords];
+  uint32_t pos = counts_before(bsum, wtot);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t w_end = min((int64_t)(blockIdx.x + 1) * b.per, b.words);
+  for (int64_t w0 = (int64_t)blockIdx.x * b.per; w0 < w_end; w0 += kSelWords) {
+    unsigned long long w = 0ull;
+    if (threadIdx.x < kSelWords && w0 + threadIdx.x < w_end) w = sel[w0 + threadIdx.x];
+    uint32_t all;
+    const uint32_t before = block_scan_excl<kBlock / 64>((uint32_t)__builtin_popcountll(w), wtot, all);
+    if (threadIdx.x < kSelWords) {
+      pre[threadIdx.x] = before;
+      word[threadIdx.x] = w;
+      first[threadIdx.x] = (uint32_t)word_pos(b, w0 + threadIdx.x).i;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int j = wv * kWaveWords; j < (wv + 1) * kWaveWords; ++j) {
+      const unsigned long long mv = word[j];
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)mv), hi = __builtin_amdgcn_readfirstlane((uint32_t)(mv >> 32));
+      if (__builtin_amdgcn_inverse_ballot_w64((unsigned long long)hi << 32 | lo))
+        out[pos + pre[j] + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u))] = first[j] + lane;
+    }
+    pos += all;
+    __syncthreads();   // pre and word are rewritten
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (long long)pos;
 }
 
 // ---------------------------------------------------------------------------
-// Fraction control kernels.
-// Class of every pixel (0 border column, 1 kept, 2 other) and the kept count.
-// Class of every pixel: 0 border column, 1 kept, 2 other; and the count of
-// kept pixels. Four pixels per thread and step: one 16-byte load of their
-// parents, one word of classes written (the workspace keeps both arrays
-// 256-byte aligned), the column of the first one divided out once.
-__global__ __launch_bounds__(kBlock) void k_fc_class(ScanCtx c, uint8_t* cls, unsigned long long* n1) {
-  __shared__ unsigned long long part;
-  if (threadIdx.x == 0) part = 0;
+// Fraction control (a benchmark knob, not the paper's): exactly `want`
+// pixels ranked as (1) border columns by raster index, (2) kept pixels by
+// component size descending, then raster index, (3) all other pixels by
+// chessboard distance to (1)+(2) ascending, then h(i) = mix64(i ^ seed). The
+// selection is threshold-based: counting passes find the key of the want-th
+// pixel within the class it falls in; ties of (2) at that key go by raster
+// order, and h takes every index to a different value, so (3) has none.
+struct FcArgs {
+  long long want, n0;             // pixels wanted; border pixels
+  const unsigned long long* n1;   // kept pixels off the border, in kN1Parts parts
+  unsigned long long seed;
+};
+struct FcPlan {
+  int mode;         // the class the want-th pixel falls in: 0 border columns, 1 kept pixels, 2 other pixels
+  long long need;   // its rank (1-based) in that class
+};
+// Worked out by every wavefront that asks (one load and six adds).
+__device__ __forceinline__ FcPlan fc_plan(const FcArgs& a) {
+  static_assert(kN1Parts == 64, "one part per lane");
+  unsigned long long n = a.n1[threadIdx.x & 63];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+  const long long n1 = (long long)n;
+  if (a.want <= a.n0) return FcPlan{0, a.want};
+  if (a.want <= a.n0 + n1) return FcPlan{1, a.want - a.n0};
+  return FcPlan{2, a.want - a.n0 - n1};
+}
+
+// SplitMix64's output function (Steele, Lea and Flood; constants as
+// published by Vigna), on the raster index xor the seed. Each of its steps
+// is invertible, so different indices have different values.
+__device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
+  return z ^ (z >> 31);
+}
+
+// Counting select, kDigit bits per pass from the top: a pass counts the
+// digits of the keys that match the digits found so far; the next one finds
+// the digit whose count range holds the wanted rank before it counts.
+constexpr int kDigit = 12, kBins = 1 << kDigit;
+struct RadixSel {
+  unsigned long long prefix;   // key bits found so far (top digits first)
+  long long need;              // rank (1-based) of the wanted key
+  long long below;             // keys smaller than those with the prefix
+};
+// The state after the counts of a pass at `shift` (the whole block works it
+// out; block 0 writes it to `out` for later launches).
+__device__ __forceinline__ RadixSel sel_pick(RadixSel r, const uint32_t* hist, int shift, RadixSel* out) {
+  __shared__ uint32_t wtot[kBlock / 64];
+  __shared__ unsigned long long found_d;
+  __shared__ long long found_below;
+  constexpr int kPer = kBins / kBlock;
+  uint32_t v[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) { v[k] = hist[threadIdx.x * kPer + k]; sum += v[k]; }
+  uint32_t all;
+  long long before = r.below + (long long)block_scan_excl<kBlock / 64>(sum, wtot, all);
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (before < r.need && r.need <= before + (long long)v[k]) {
+      found_d = (unsigned long long)(threadIdx.x * kPer + k);
+      found_below = before;
+    }
+    before += v[k];
+  }
   __syncthreads();
-  unsigned long long mine = 0;
-  auto cls_of = [&](int x, int32_t r) -> uint32_t {
-    return (x == 0 || x == c.W - 1) ? 0u : (kept_root(c, r) ? 1u : 2u);
-  };
-  // the filter's fields once; the four component sizes of a quad gathered
-  // together (from index 0 for pixels without a component), so a quad costs
-  // two round trips to memory, not five
-  const bool rule = c.rule != nullptr;
-  const int32_t s_star = rule ? c.rule->s_star : 0, m_star = rule ? c.rule->m : 0;
-  const int64_t nq = c.N >> 2;
-  const int4* pq = (const int4*)c.parent;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += (int64_t)gridDim.x * blockDim.x) {
-    const int4 p = pq[q];
-    int x = (int)((uint32_t)(q << 2) % (uint32_t)c.W);   // W * H < 2^31: 32-bit division suffices
-    const int32_t r[4] = {p.x, p.y, p.z, p.w};
-    int32_t sz[4];
+  r.prefix |= found_d << shift;   // (the wanted rank lies within the counts: need <= keys of the class)
+  r.below = found_below;
+  if (out && blockIdx.x == 0 && threadIdx.x == 0) *out = r;
+  __syncthreads();
+  return r;
+}
+
+// Mode 1, one counting pass over the kept pixels' keys ~size.
+__device__ __forceinline__ void size_pass(const Bits& b, const unsigned long long* kept, const int32_t* size, RadixSel rs, const uint32_t* prev_hist, int prev_shift,
+                                          RadixSel* state, int shift, uint32_t* hist, uint32_t* bins) {
+  if (prev_hist) rs = sel_pick(rs, prev_hist, prev_shift, state);
+  for (int k = threadIdx.x; k < kBins; k += kBlock) bins[k] = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int hi = shift + kDigit;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t w0 = kWaveWords * ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)); w0 < b.words; w0 += kWaveWords * nw) {
+    const WaveWords w = wave_words(b, kept, w0, b.words);   // whole runs of the boundary map
+    int32_t s[kWaveWords];
+    at_run_starts(w, size, 0, s);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) sz[b] = c.size[r[b] < 0 ? 0 : r[b]];
-    uint32_t w = 0u;
+    for (int j = 0; j < kWaveWords; ++j) {
+      const unsigned long long m = w.word(j);
+      if (!m) continue;
+      const uint32_t key = ~(uint32_t)s[j];   // one add per run, of its pixels off the border columns
+      const unsigned long long bd = w.border_of(j);
+      if (s[j] > 0 && (hi >= 32 || (key >> hi) == (uint32_t)(rs.prefix >> hi)))
+        atomicAdd(&bins[(key >> shift) & (kBins - 1)], (uint32_t)__builtin_popcountll(run_from(m, lane) & ~bd));
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kBins; k += kBlock)
+    if (bins[k]) atomicAdd(&hist[k], bins[k]);
+}
+
+// Mode 2: distances up to kLevels by dilation of the base map, 3 x 3 per
+// level, on bits: a wavefront holds 128 rows (two per lane) x 192 columns in
+// registers, rows beyond a lane's own by DPP, and keeps the inner 98 rows x
+// 128 columns, which none of a launch's 15 levels reaches from outside. A
+// pixel's level goes to kLevelBits planes (0 for base pixels and those
+// further away) and the pixels per level are counted, in kLvParts copies. A
+// second launch goes on from the first one's outcome where the want-th pixel
+// lies further away: 15 levels cover the workloads' lists (31 in one launch
+// keep a quarter of what a wavefront holds: 26 us at 4096x2304 against 20). Pixels beyond both
+// take the distance passes below (k_far_*).
+constexpr int kLevelBits = 5, kLvStage = 15, kLevels = 2 * kLvStage + 1, kLvParts = 64;   // levels 1 .. 15 and 16 .. 30
+constexpr int kLvRows = 128 - 2 * kLvStage;   // 98
+constexpr int kLvWords = 6;                   // 32-column words held, the inner four kept
+
+__device__ __forceinline__ uint32_t lane_up(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, false);   // wave_shr:1, zeros in
+}
+__device__ __forceinline__ uint32_t lane_down(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130, 0xf, 0xf, false);   // wave_shl:1, zeros in
+}
+
+struct LevelSel {
+  int level;
+  long long need;
+};
+__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need);
+
+// Planes 0 .. 3 of a map word lie side by side, plane 4 apart after them (it
+// is read for levels above 15 only). STAGE 0: levels 1 .. 15 of `from` (the
+// base map), and the pixels reached to `reach`. STAGE 1: levels 16 .. 30 of
+// `from` (what stage 0 reached) into the planes.
+template <int STAGE>
+__global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, const unsigned long long* __restrict__ from,
+                                                      unsigned long long* __restrict__ planes,
+                                                      unsigned long long* __restrict__ reach, uint32_t* lcount) {
+  __shared__ uint32_t cnt[kLvStage];
+  const FcPlan plan = fc_plan(a);
+  if (plan.mode != 2) return;
+  if constexpr (STAGE == 1)
+    if (level_pick(lcount, plan.need).level != 0) return;
+  if (threadIdx.x < kLvStage) cnt[threadIdx.x] = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int c = 2 * ((int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6));   // the first of the wavefront's two word columns
+  const int y0 = (int)blockIdx.y * kLvRows;
+  if (c < b.wpr) {
+    constexpr int M = kLvWords;
+    const uint32_t* src = (const uint32_t*)from;   // 32-bit halves of the map's words, low half first
+    uint32_t cur[2][M], in[2][M - 2], pl[4][2][M - 2], got[2][M - 2];
+    int y[2];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      bool kp = r[b] >= 0;
-      if (kp) {
-        if (!rule) kp = sz[b] >= c.min_cc;
-        else kp = sz[b] > s_star || (sz[b] == s_star && c.rank[r[b]] >= m_star);
+    for (int r = 0; r < 2; ++r) {
+      y[r] = y0 - kLvStage + 2 * lane + r;
+      const bool row = y[r] >= 0 && y[r] < b.H;
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const int w = 2 * c - 1 + i;
+        cur[r][i] = row && w >= 0 && w < 2 * b.wpr ? src[(int64_t)y[r] * 2 * b.wpr + w] : 0u;
       }
-      const uint32_t k = (x == 0 || x == c.W - 1) ? 0u : (kp ? 1u : 2u);
-      w |= k << (8 * b);
-      mine += k == 1u ? 1ull : 0ull;
-      x = x + 1 == c.W ? 0 : x + 1;
+      // inner pixels inside the image
+      const bool inner = row && y[r] >= y0 && y[r] < y0 + kLvRows;
+#pragma unroll
+      for (int i = 0; i < M - 2; ++i) {
+        const int left = b.W - (64 * c + 32 * i);   // columns of the image from the word's first on
+        in[r][i] = !inner || left <= 0 ? 0u : (left >= 32 ? ~0u : (1u << left) - 1u);
+        got[r][i] = 0u;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) pl[p][r][i] = 0u;
+      }
     }
-    ((uint32_t*)cls)[q] = w;
-  }
-  if (blockIdx.x == 0)
-    for (int64_t i = (nq << 2) + threadIdx.x; i < c.N; i += blockDim.x) {
-      const uint32_t k = cls_of((int)((uint32_t)i % (uint32_t)c.W), c.parent[i]);
-      cls[i] = (uint8_t)k;
-      mine += k == 1u ? 1ull : 0ull;
-    }
-  // one LDS add per wavefront (adds to one word from every lane serialise)
+#pragma unroll 1
+    for (int k = 0; k < kLvStage; ++k) {
+      const int code = STAGE == 0 ? k + 1 : k;   // the low four bits of the level
+      uint32_t h[2][M];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
-  if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&part, mine);
-  __syncthreads();
-  // one of kN1Parts counters per block: adds to a single word from thousands
-  // of blocks queue up one after another at the memory side
-  if (threadIdx.x == 0 && part) atomicAdd(&n1[blockIdx.x % kN1Parts], part);
-}
-
-// Which class the want-th pixel falls in, and the rank wanted inside it.
-__global__ void k_fc_plan(FracState* f, const unsigned long long* n1, long long want, long long n0,
-                          unsigned long long s1_prefix) {
-  f->want = want;
-  f->n0 = n0;
-  long long nk = 0;
-  for (int k = 0; k < kN1Parts; ++k) nk += (long long)n1[k];
-  f->n1 = nk;
-  f->s1 = RadixSel{s1_prefix, 0, 0};
-  f->s2 = RadixSel{0, 0, 0};
-  f->s3 = RadixSel{0, 0, 0};
-  if (f->want <= f->n0) { f->mode = 0; return; }
-  if (f->want <= f->n0 + f->n1) { f->mode = 1; f->s1.need = f->want - f->n0; return; }
-  f->mode = 2;
-  f->s2.need = f->want - f->n0 - f->n1;
-}
-
-// The rank wanted at distance s2.prefix among the other pixels.
-__global__ void k_fc_after_dist(FracState* f) { f->s3 = RadixSel{0, f->s2.need - f->s2.below, 0}; }
-
-// Radix select, one 8-bit digit per pass from the top: per-block digit
-// histograms of the candidates whose higher digits match, then one block
-// picks the digit where the running count reaches `need`.
-template <int SEL>
-__device__ __forceinline__ bool rs_key(const ScanCtx& c, int64_t i, unsigned long long& key) {
-  if constexpr (SEL == 1) {
-    if (c.cls[i] != 1) return false;
-    key = ~(uint32_t)comp_size(c, i);
-  } else {
-    static_assert(SEL == 2, "the hash select runs over compacted candidates (k_rs_hist_cands)");
-    if (c.cls[i] != 2) return false;
-    key = (uint32_t)c.dist[i];
-  }
-  return true;
-}
-
-// One radix-select pass: counts of the candidates' digit at `shift` among
-// keys whose higher digits match the prefix so far, in 16 bank-staggered LDS
-// copies (lane l adds to copy l % 16; see k_hist), then one global add per
-// digit and block.
-// The state of a select after the pick of a finished pass: the digit d at
-// `shift` whose count range holds the wanted rank (counts of smaller digits
-// before it), taken by every block of the next pass from that pass's counts
-// (256 threads, one digit each), so that no launch is needed for the pick.
-// Block 0 writes the state to `out` for the passes after.
-__device__ __forceinline__ RadixSel rs_after_pick(const RadixSel* in, const uint32_t* hist, int shift, RadixSel* out) {
-  __shared__ uint32_t wtot[kBlock / 64];
-  __shared__ int sel_d;
-  __shared__ long long sel_below;
-  const RadixSel r = *in;
-  if (threadIdx.x == 0) sel_d = -1;
-  const int d = threadIdx.x;
-  const uint32_t v = hist[d];
-  uint32_t total = 0u;
-  const long long before = r.below + (long long)block_scan_excl<kBlock / 64>(v, wtot, total);   // (its barriers order sel_d)
-  if (r.need > 0 && before < r.need && r.need <= before + (long long)v) { sel_d = d; sel_below = before; }
-  __syncthreads();
-  RadixSel o = r;
-  if (sel_d >= 0) {
-    o.prefix |= (unsigned long long)sel_d << shift;
-    o.below = sel_below;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *out = o;
-  return o;
-}
-
-// The select's state for a counting pass: `in` itself for the first pass
-// (in_hist null), else `in` after the pick of the previous pass's counts.
-__device__ __forceinline__ RadixSel rs_state(const RadixSel* in, const uint32_t* in_hist, int in_shift,
-                                             RadixSel* out) {
-  return in_hist ? rs_after_pick(in, in_hist, in_shift, out) : *in;
-}
-
-template <int SEL>
-__global__ __launch_bounds__(kBlock) void k_rs_hist(ScanCtx c, const RadixSel* in, const uint32_t* in_hist,
-                                                    int in_shift, RadixSel* out, int shift, uint32_t* hist) {
-  __shared__ uint32_t h[kHistCopies][257];
-  const RadixSel rs = rs_state(in, in_hist, in_shift, out);
-  for (int i = threadIdx.x; i < kHistCopies * 257; i += blockDim.x) (&h[0][0])[i] = 0u;
-  __syncthreads();
-  uint32_t* mine = h[threadIdx.x & (kHistCopies - 1)];
-  const unsigned long long pre = rs.prefix;
-  const int hi = shift + 8;   // digits above this one must match the prefix
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  auto count = [&](int64_t i) {
-    unsigned long long key = 0;
-    bool cand = rs_key<SEL>(c, i, key);
-    if (cand && hi < 64 && (key >> hi) != (pre >> hi)) cand = false;
-    if (cand) atomicAdd(&mine[(uint32_t)((key >> shift) & 0xFF)], 1u);
-  };
-  // four pixels per thread and step, their classes in one word (the grid is
-  // small, so each thread needs several loads in flight), then the tail
-  const int64_t nq = c.N >> 2;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += stride) {
-    const uint32_t k4 = ((const uint32_t*)c.cls)[q];   // 4-byte aligned: in the 256-byte aligned workspace
-    // classes 0, 1, 2: bit 0 marks class 1, bit 1 class 2
-    if (!(k4 & (SEL == 1 ? 0x01010101u : 0x02020202u))) continue;
-    // the quad's keys: (kept) four parents then four sizes, each group
-    // loaded together; (other) four distances in one load
-    uint32_t key[4];
-    if constexpr (SEL == 1) {
-      const int4 p = ((const int4*)c.parent)[q];
-      const int32_t r[4] = {p.x, p.y, p.z, p.w};
+      for (int r = 0; r < 2; ++r)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) key[b] = ~(uint32_t)c.size[r[b] < 0 ? 0 : r[b]];
-    } else {
-      const int4 d = ((const int4*)c.dist)[q];
-      key[0] = (uint32_t)d.x; key[1] = (uint32_t)d.y; key[2] = (uint32_t)d.z; key[3] = (uint32_t)d.w;
-    }
+        for (int i = 0; i < M; ++i)
+          h[r][i] = cur[r][i] | __builtin_amdgcn_alignbit(cur[r][i], i > 0 ? cur[r][i - 1] : 0u, 31) |
+                    __builtin_amdgcn_alignbit(i < M - 1 ? cur[r][i + 1] : 0u, cur[r][i], 1);
+      uint32_t n = 0u, rest = 0u;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      if (((k4 >> (8 * b)) & 0xFFu) != (SEL == 1 ? 1u : 2u)) continue;
-      if (hi < 64 && ((unsigned long long)key[b] >> hi) != (pre >> hi)) continue;
-      atomicAdd(&mine[(key[b] >> shift) & 0xFFu], 1u);
-    }
-  }
-  if (blockIdx.x == 0)
-    for (int64_t i = (nq << 2) + threadIdx.x; i < c.N; i += blockDim.x) count(i);
-  __syncthreads();
-  uint32_t t = 0;
-  for (int k = 0; k < kHistCopies; ++k) t += h[k][threadIdx.x];
-  if (t) atomicAdd(&hist[threadIdx.x], t);
-}
-
-// The pick of a select's last pass: the final state to `out` (may be `in`).
-__global__ __launch_bounds__(256) void k_rs_pick(const RadixSel* in, const uint32_t* hist, int shift, RadixSel* out) {
-  rs_after_pick(in, hist, shift, out);
-}
-
-// The candidates of the hash select (other pixels at the selected distance),
-// compacted once, so that its eight passes read a short list instead of the
-// class and distance of every pixel. Order in the list does not matter: the
-// select only counts keys, and the final list comes from the raster-order
-// scan. Each block takes kCandPer pixels a step, each thread four adjacent
-// ones per load (a word of classes, 16 bytes of distances), and reserves
-// their places with one atomic (a few hundred per image: adds to one word
-// queue up one after another at the memory side).
-constexpr int kCandPer = 16384;
-__global__ __launch_bounds__(kBlock) void k_fc_cands(ScanCtx c, int32_t* cand, unsigned long long* ncand) {
-  constexpr int kQuads = kCandPer / (4 * kBlock);   // quads per thread and step
-  static_assert(kQuads * 4 * kBlock == kCandPer && 4 * kQuads <= 64, "one mask word per thread");
-  __shared__ uint32_t wtot[kBlock / 64];
-  __shared__ unsigned long long base;
-  const FracState* f = c.fc;
-  if (f->mode != 2) return;
-  const int32_t dsel = (int32_t)f->s2.prefix;
-  const int64_t nq = c.N >> 2;
-  const uint32_t* cw = (const uint32_t*)c.cls;   // 256-byte aligned workspace arrays
-  const int4* dq = (const int4*)c.dist;
-  for (int64_t b0 = (int64_t)blockIdx.x * kCandPer; b0 < c.N; b0 += (int64_t)gridDim.x * kCandPer) {
-    uint64_t m = 0u;   // bit 4k + b: pixel 4 (q0 + k kBlock) + b is a candidate
-    const int64_t q0 = (b0 >> 2) + threadIdx.x;
+      for (int i = 0; i < M; ++i) {
+        const uint32_t both = h[0][i] | h[1][i];
+        const uint32_t v[2] = {both | lane_up(h[1][i]), both | lane_down(h[0][i])};
 #pragma unroll
-    for (int k = 0; k < kQuads; ++k) {
-      const int64_t q = q0 + (int64_t)k * kBlock;
-      if (q < nq) {
-        const uint32_t k4 = cw[q];
-        if (k4 & 0x02020202u) {   // some class-2 pixel among the four
-          const int4 d = dq[q];
-          const int32_t dv[4] = {d.x, d.y, d.z, d.w};
+        for (int r = 0; r < 2; ++r) {
+          if (i >= 1 && i < M - 1) {
+            const uint32_t d = v[r] & ~cur[r][i] & in[r][i - 1];
+            n += __builtin_popcount(d);
+            rest |= in[r][i - 1] & ~v[r];
+            got[r][i - 1] |= d;
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
-            if (((k4 >> (8 * b)) & 0xFFu) == 2u && dv[b] == dsel) m |= 1ull << (4 * k + b);
+            for (int p = 0; p < 4; ++p)
+              if (code >> p & 1) pl[p][r][i - 1] |= d;
+          }
+          cur[r][i] = v[r];
         }
-      } else if (q == nq) {   // the last N % 4 pixels
-        for (int64_t i = q << 2; i < c.N; ++i)
-          if (c.cls[i] == 2 && c.dist[i] == dsel) m |= 1ull << (4 * k + (int)(i - (q << 2)));
+      }
+      // sums over rows of 16 lanes, then one LDS add per row of lanes
+      n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x111, 0xf, 0xf, false);
+      n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x112, 0xf, 0xf, false);
+      n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x114, 0xf, 0xf, false);
+      n += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n, 0x118, 0xf, 0xf, false);
+      if ((lane & 15) == 15 && n) atomicAdd(&cnt[k], n);
+      if (!__builtin_amdgcn_ballot_w64(rest != 0u)) break;   // every inner pixel reached
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (y[r] < y0 || y[r] >= y0 + kLvRows || y[r] >= b.H) continue;
+#pragma unroll
+      for (int j = 0; j < (M - 2) / 2; ++j) {
+        if (c + j >= b.wpr) continue;
+        const int64_t at = (int64_t)y[r] * b.wpr + c + j;
+        auto word = [](uint32_t lo, uint32_t hi) { return (unsigned long long)lo | (unsigned long long)hi << 32; };
+        unsigned long long v[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) v[p] = word(pl[p][r][2 * j], pl[p][r][2 * j + 1]);
+        ulonglong2* q = (ulonglong2*)(planes + 4 * at);
+        if constexpr (STAGE == 1) {
+          const ulonglong2 lo = q[0], hi = q[1];
+          v[0] |= lo.x; v[1] |= lo.y; v[2] |= hi.x; v[3] |= hi.y;
+          planes[4 * b.words + at] = word(got[r][2 * j], got[r][2 * j + 1]);
+        } else {
+          reach[at] = word(cur[r][2 * j + 1] & in[r][2 * j], cur[r][2 * j + 2] & in[r][2 * j + 1]);
+        }
+        q[0] = ulonglong2{v[0], v[1]};
+        q[1] = ulonglong2{v[2], v[3]};
       }
     }
-    const uint32_t cnt = (uint32_t)__builtin_popcountll(m);
-    uint32_t total = 0u;
-    const uint32_t before = block_scan_excl<kBlock / 64>(cnt, wtot, total);
-    if (threadIdx.x == 0) base = total ? atomicAdd(ncand, (unsigned long long)total) : 0ull;
+  }
+  __syncthreads();
+  const int part = (int)((blockIdx.y * gridDim.x + blockIdx.x) % kLvParts);
+  if (threadIdx.x < kLvStage && cnt[threadIdx.x])
+    atomicAdd(&lcount[part * (kLevels + 1) + 1 + STAGE * kLvStage + threadIdx.x], cnt[threadIdx.x]);
+}
+
+// Mode 2: the level of the want-th pixel and its rank within it, from the
+// level counts; level 0: it lies further away than those counted.
+__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need) {
+  __shared__ unsigned long long sum[kLevels + 1];
+  if (threadIdx.x <= kLevels) sum[threadIdx.x] = 0ull;
+  __syncthreads();
+  // thread t adds up every 8th part of level t % 32
+  static_assert(kBlock == 8 * (kLevels + 1) && kLvParts % 8 == 0, "threads cover the levels eight times");
+  const int l = threadIdx.x % (kLevels + 1), p0 = threadIdx.x / (kLevels + 1);
+  uint32_t v[kLvParts / 8];
+#pragma unroll
+  for (int k = 0; k < kLvParts / 8; ++k) v[k] = lcount[(p0 + 8 * k) * (kLevels + 1) + l];
+  unsigned long long s = 0ull;
+#pragma unroll
+  for (int k = 0; k < kLvParts / 8; ++k) s += v[k];
+  if (s) atomicAdd(&sum[l], s);
+  __syncthreads();
+  LevelSel r{0, need};
+  for (int k = 1; k <= kLevels; ++k) {
+    const long long n = (long long)sum[k];
+    if (r.need <= n) { r.level = k; break; }
+    r.need -= n;
+  }
+  __syncthreads();
+  return r;
+}
+// ... and once the distance passes have run: they leave levels 1 (nearer than
+// the wanted distance) and 2 (at it) in the planes, and the rank in `far`.
+__device__ __forceinline__ LevelSel level_final(const uint32_t* lcount, const long long* far_need, long long need) {
+  LevelSel r = level_pick(lcount, need);
+  if (r.level == 0) { r.level = 2; r.need = *far_need; }
+  return r;
+}
+struct LevelWords {
+  unsigned long long inner, ring;   // pixels of lower levels (not 0), and of the level
+};
+__device__ __forceinline__ LevelWords level_words(const Bits& b, const unsigned long long* planes, int64_t wi, int level) {
+  const ulonglong2* q = (const ulonglong2*)(planes + 4 * wi);
+  const ulonglong2 lo = q[0], hi = q[1];
+  const unsigned long long p[kLevelBits] = {lo.x, lo.y, hi.x, hi.y, level > kLvStage ? planes[4 * b.words + wi] : 0ull};
+  unsigned long long lt = 0ull, eq = ~0ull, any = 0ull;
+#pragma unroll
+  for (int k = kLevelBits - 1; k >= 0; --k) {
+    any |= p[k];
+    if (level >> k & 1) { lt |= eq & ~p[k]; eq &= p[k]; }
+    else eq &= ~p[k];
+  }
+  return LevelWords{lt & any, eq & any};
+}
+
+// Mode 2, the ring (other pixels at the wanted distance): counts of the top
+// kHashDigit bits of h, gathered in LDS, in kHashParts copies (one add to
+// memory per pixel into 2^14 bins took 26 us at 4096x2304, 14 us so).
+constexpr int kHashDigit = 8, kHashBins = 1 << kHashDigit, kHashParts = 8;
+static_assert(kHashBins == kBlock, "one bin per thread");
+// f(i) for the block's ring pixels i: the words' set bits are queued in LDS
+// first and then taken by all threads alike, since a ring fills some words and
+// leaves most empty.
+constexpr int kRingWords = kBlock;          // words a block queues at a time
+constexpr int kRingGroups = 4;              // of them per block in small images
+template <typename F>
+__device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, F f) {
+  __shared__ uint16_t queue[64 * kRingWords];   // word << 6 | bit
+  __shared__ int first[kRingWords];
+  __shared__ uint32_t wtot[kBlock / 64];
+  for (int64_t w0 = (int64_t)blockIdx.x * kRingWords; w0 < b.words; w0 += (int64_t)gridDim.x * kRingWords) {
+    const int64_t wi = w0 + threadIdx.x;
+    unsigned long long m = wi < b.words ? level_words(b, planes, wi, level).ring : 0ull;
+    uint32_t all;
+    uint32_t at = block_scan_excl<kBlock / 64>((uint32_t)__builtin_popcountll(m), wtot, all);
+    if (m) first[threadIdx.x] = word_pos(b, wi).i;
+    for (; m; m &= m - 1ull) queue[at++] = (uint16_t)(threadIdx.x << 6 | (uint32_t)__builtin_ctzll(m));
     __syncthreads();
-    unsigned long long pos = base + before;
-    for (int k = 0; k < kQuads; ++k)
-      for (int b = 0; b < 4; ++b)
-        if (m >> (4 * k + b) & 1ull) cand[pos++] = (int32_t)(((q0 + (int64_t)k * kBlock) << 2) + b);
-    __syncthreads();   // base is rewritten by the next step
+    for (uint32_t k = threadIdx.x; k < all; k += kBlock) f((uint32_t)(first[queue[k] >> 6] + (queue[k] & 63)));
+    __syncthreads();   // the queue is rewritten
   }
 }
-
-// One hash-select pass over the compacted candidates (as k_rs_hist).
-__global__ __launch_bounds__(kBlock) void k_rs_hist_cands(const int32_t* cand, const unsigned long long* ncand,
-                                                          unsigned long long seed, const RadixSel* in,
-                                                          const uint32_t* in_hist, int in_shift, RadixSel* out,
-                                                          int shift, uint32_t* hist) {
-  __shared__ uint32_t h[kHistCopies][257];
-  const RadixSel rs = rs_state(in, in_hist, in_shift, out);
-  for (int i = threadIdx.x; i < kHistCopies * 257; i += blockDim.x) (&h[0][0])[i] = 0u;
+__global__ __launch_bounds__(kBlock) void k_ring_count(Bits b, FcArgs a, const unsigned long long* __restrict__ planes,
+                                                       const uint32_t* __restrict__ lcount,
+                                                       const long long* __restrict__ far_need, uint32_t* hash_hist) {
+  __shared__ uint32_t bins[kHashBins];
+  const FcPlan pl = fc_plan(a);
+  if (pl.mode != 2) return;
+  for (int k = threadIdx.x; k < kHashBins; k += kBlock) bins[k] = 0u;
+  const LevelSel ls = level_final(lcount, far_need, pl.need);   // (its barriers order the bins)
+  for_ring(b, planes, ls.level, [&](uint32_t i) {
+    atomicAdd(&bins[mix64((unsigned long long)i ^ a.seed) >> (64 - kHashDigit)], 1u);
+  });
   __syncthreads();
-  uint32_t* mine = h[threadIdx.x & (kHistCopies - 1)];
-  const unsigned long long pre = rs.prefix;
-  const int hi = shift + 8;
-  const int64_t n = (int64_t)*ncand;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  auto count = [&](int32_t px) {
-    const unsigned long long key = mix64((unsigned long long)px ^ seed);
-    if (hi < 64 && (key >> hi) != (pre >> hi)) return;
-    atomicAdd(&mine[(uint32_t)((key >> shift) & 0xFF)], 1u);
-  };
-  // four candidates per 16-byte load (the list starts 256-byte aligned in
-  // the workspace), so few threads still keep several loads in flight
-  const int64_t nq = n >> 2;
-  const int4* cq = (const int4*)cand;
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nq; q += stride) {
-    const int4 v = cq[q];
-    count(v.x); count(v.y); count(v.z); count(v.w);
+  uint32_t* out = hash_hist + (blockIdx.x % kHashParts) * kHashBins;
+  for (int k = threadIdx.x; k < kHashBins; k += kBlock)
+    if (bins[k]) atomicAdd(&out[k], bins[k]);
+}
+// The hashes of the ring's pixels in the bin that holds the wanted rank, and
+// the rank within it.
+struct RingBin {
+  long long need;
+  unsigned long long n;   // hashes listed
+};
+__global__ __launch_bounds__(kBlock) void k_ring_bin(Bits b, FcArgs a, const unsigned long long* __restrict__ planes,
+                                                     const uint32_t* __restrict__ lcount,
+                                                     const long long* __restrict__ far_need,
+                                                     const uint32_t* __restrict__ hash_hist, RingBin* rb,
+                                                     unsigned long long* list) {
+  constexpr int kHold = 512;
+  __shared__ uint32_t wtot[kBlock / 64];
+  __shared__ uint32_t bin_s, held;
+  __shared__ long long need_s;
+  __shared__ unsigned long long hold[kHold], at_s;
+  const FcPlan pl = fc_plan(a);
+  if (pl.mode != 2) return;
+  if (threadIdx.x == 0) held = 0u;
+  const LevelSel ls = level_final(lcount, far_need, pl.need);
+  uint32_t v = 0;
+#pragma unroll
+  for (int q = 0; q < kHashParts; ++q) v += hash_hist[q * kHashBins + threadIdx.x];
+  uint32_t all;
+  const long long before = (long long)block_scan_excl<kBlock / 64>(v, wtot, all);
+  if (before < ls.need && ls.need <= before + (long long)v) {
+    bin_s = threadIdx.x;
+    need_s = ls.need - before;
   }
-  if (blockIdx.x == 0)
-    for (int64_t k = (nq << 2) + threadIdx.x; k < n; k += blockDim.x) count(cand[k]);
   __syncthreads();
-  uint32_t t = 0;
-  for (int k = 0; k < kHistCopies; ++k) t += h[k][threadIdx.x];
-  if (t) atomicAdd(&hist[threadIdx.x], t);
+  const unsigned long long bin = bin_s;
+  if (blockIdx.x == 0 && threadIdx.x == 0) rb->need = need_s;
+  // held in LDS first, so that a block takes its places in the list at once
+  for_ring(b, planes, ls.level, [&](uint32_t i) {
+    const unsigned long long h = mix64((unsigned long long)i ^ a.seed);
+    if (h >> (64 - kHashDigit) != bin) return;
+    const uint32_t k = atomicAdd(&held, 1u);
+    if (k < kHold) hold[k] = h;
+    else list[atomicAdd(&rb->n, 1ull)] = h;
+  });
+  __syncthreads();
+  const int n = (int)min(held, (uint32_t)kHold);
+  if (threadIdx.x == 0 && n) at_s = atomicAdd(&rb->n, (unsigned long long)n);
+  __syncthreads();
+  for (int k = threadIdx.x; k < n; k += kBlock) list[at_s + k] = hold[k];
 }
 
-// Chessboard distance to the border columns and kept pixels: per column the
-// vertical distance to the nearest such pixel, then per pixel the minimum
-// over columns x' of max(|x - x'|, that distance), searched outwards until
-// |x - x'| reaches the best found (the border columns bound it).
+// The hash of rank rb->need among the listed ones (they differ): the listed
+// hashes in LDS where they fit, narrowed digit by digit to a few, which are
+// ranked against each other.
+__device__ __forceinline__ unsigned long long ring_threshold(const RingBin* rb, const unsigned long long* list) {
+  constexpr int kKeys = 1536, kFew = 256;
+  __shared__ unsigned long long keys[kKeys], few[kFew], thr;
+  __shared__ uint32_t hist[256], wtot[kBlock / 64], nfew, dig_s, cnt_s;
+  __shared__ long long need_s;
+  const int64_t m = (int64_t)rb->n;
+  const bool in_lds = m <= kKeys;
+  if (in_lds)
+    for (int t = threadIdx.x; t < (int)m; t += kBlock) keys[t] = list[t];
+  const unsigned long long* src = in_lds ? keys : list;
+  long long need = rb->need;
+  int shift = 64 - kHashDigit;
+  unsigned long long prefix = 0ull;
+  bool first = true;   // nothing fixed beyond the bin yet
+  int64_t count = m;
+  while (count > kFew && shift > 0) {
+    const int next = shift > 8 ? shift - 8 : 0;
+    hist[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int64_t t = threadIdx.x; t < m; t += kBlock) {
+      const unsigned long long k = src[t];
+      if (first || k >> shift == prefix) atomicAdd(&hist[(k >> next) & ((1ull << (shift - next)) - 1ull)], 1u);
+    }
+    __syncthreads();
+    const uint32_t v = hist[threadIdx.x];
+    uint32_t all;
+    const long long before = (long long)block_scan_excl<kBlock / 64>(v, wtot, all);
+    if (before < need && need <= before + (long long)v) { dig_s = threadIdx.x; cnt_s = v; need_s = need - before; }
+    if (first && threadIdx.x == 0) thr = src[0] >> shift;   // the bin's own bits
+    __syncthreads();
+    if (first) prefix = thr;
+    prefix = prefix << (shift - next) | dig_s;
+    need = need_s;
+    count = cnt_s;
+    shift = next;
+    first = false;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) nfew = 0u;
+  __syncthreads();
+  for (int64_t t = threadIdx.x; t < m; t += kBlock) {
+    const unsigned long long k = src[t];
+    if (first || k >> shift == prefix) few[atomicAdd(&nfew, 1u)] = k;   // at most kFew (one once every digit is fixed)
+  }
+  __syncthreads();
+  if (threadIdx.x < nfew) {
+    const unsigned long long k = few[threadIdx.x];
+    long long below = 0;
+    for (uint32_t j = 0; j < nfew; ++j) below += few[j] < k ? 1 : 0;
+    if (below == need - 1) thr = k;
+  }
+  __syncthreads();
+  return thr;
+}
+
+// The selected pixels as a map, and their number per block of b.per words.
+__global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const unsigned long long* __restrict__ kept,
+                                                      const unsigned long long* __restrict__ base,
+                                                      const int32_t* __restrict__ size, const RadixSel* s1, const uint32_t* __restrict__ s1_hist,
+                                                      const uint32_t* __restrict__ ties,
+                                                      const unsigned long long* __restrict__ planes,
+                                                      const uint32_t* __restrict__ lcount,
+                                                      const long long* __restrict__ far_need,
+                                                      const RingBin* __restrict__ rb,
+                                                      const unsigned long long* __restrict__ ring,
+                                                      unsigned long long* sel, uint32_t* bsum) {
+  __shared__ uint32_t wtot[kBlock / 64];
+  __shared__ uint32_t nsel;
+  __shared__ unsigned long long tw[kSelWords], ow[kSelWords];
+  if (threadIdx.x == 0) nsel = 0u;
+  const FcPlan pl = fc_plan(a);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t w_begin = (int64_t)blockIdx.x * b.per, w_end = min(w_begin + b.per, b.words);
+  uint32_t c = 0;
+  __syncthreads();
+  if (pl.mode == 2) {
+    const LevelSel ls = level_final(lcount, far_need, pl.need);
+    const unsigned long long thr = ring_threshold(rb, ring);
+    for (int64_t wi = w_begin + threadIdx.x; wi < w_end; wi += kBlock) {
+      const LevelWords lw = level_words(b, planes, wi, ls.level);
+      const WordPos p = word_pos(b, wi);
+      const int64_t i0 = p.i;
+      unsigned long long s = base[wi] | lw.inner;
+      for (unsigned long long r = lw.ring; r; r &= r - 1ull) {
+        const int k = __builtin_ctzll(r);
+        if (mix64((unsigned long long)(i0 + k) ^ a.seed) <= thr) s |= 1ull << k;
+      }
+      sel[wi] = s;
+      c += (uint32_t)__builtin_popcountll(s);
+    }
+  } else if (pl.mode == 0) {
+    // border columns by raster index
+    for (int64_t wi = w_begin + threadIdx.x; wi < w_end; wi += kBlock) {
+      const WordPos p = word_pos(b, wi);
+      const long long left = b.W == 1 ? p.y : 2LL * p.y, right = b.W == 1 ? p.y : 2LL * p.y + 1;   // their ranks
+      unsigned long long s = 0ull;
+      if (p.c == 0 && left < a.want) s |= 1ull;
+      if (p.c == b.wpr - 1 && right < a.want) s |= 1ull << ((b.W - 1) & 63);
+      sel[wi] = s;
+      c += (uint32_t)__builtin_popcountll(s);
+    }
+  } else {
+    // kept pixels of larger components, and the first of those of size s* in
+    // raster order: ties before this block from the blocks' counts
+    const RadixSel rs = sel_pick(*s1, s1_hist, 0, nullptr);
+    const uint32_t s_star = ~(uint32_t)rs.prefix;
+    long long quota = rs.need - rs.below - (long long)counts_before(ties, wtot);
+    for (int64_t w0 = w_begin; w0 < w_end; w0 += kSelWords) {
+      const WaveWords w = wave_words(b, kept, w0 + kWaveWords * wv, w_end);
+      int32_t s[kWaveWords];
+      at_run_starts(w, size, 0, s);
+      unsigned long long tv = 0ull, ov = 0ull;   // lane j: word j's ties, and its pixels of larger components
+#pragma unroll
+      for (int j = 0; j < kWaveWords; ++j) {
+        const unsigned long long m = w.word(j);
+        if (!m) continue;
+        const unsigned long long gt = __builtin_amdgcn_ballot_w64(s[j] > 0 && (uint32_t)s[j] > s_star);
+        const unsigned long long eq = __builtin_amdgcn_ballot_w64(s[j] > 0 && (uint32_t)s[j] == s_star);
+        if (lane == j) { tv = m & ~(m + eq); ov = m & ~(m + gt); }
+      }
+      if (lane < kWaveWords) {
+        tw[kWaveWords * wv + lane] = tv & ~w.border;
+        ow[kWaveWords * wv + lane] = ov | w.border;
+      }
+      __syncthreads();
+      const unsigned long long t = threadIdx.x < kSelWords ? tw[threadIdx.x] : 0ull;
+      uint32_t all;
+      const uint32_t before = block_scan_excl<kBlock / 64>((uint32_t)__builtin_popcountll(t), wtot, all);
+      if (threadIdx.x < kSelWords && w0 + threadIdx.x < w_end) {
+        unsigned long long s = ow[threadIdx.x];
+        long long left = quota - (long long)before;
+        for (unsigned long long m = t; m && left > 0; m &= m - 1ull, --left) s |= m & (~m + 1ull);   // the lowest set bits
+        sel[w0 + threadIdx.x] = s;
+        c += (uint32_t)__builtin_popcountll(s);
+      }
+      quota -= (long long)all;
+      __syncthreads();   // tw and ow are rewritten
+    }
+  }
+  c = wave_scan_incl(c);
+  if (lane == 63 && c) atomicAdd(&nsel, c);
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = nsel;
+}
+
+// Mode 1: pixels of size s* per block of b.per words, for their ranks.
+__device__ __forceinline__ void tie_pass(const Bits& b, const unsigned long long* kept, const int32_t* size,
+                                         uint32_t s_star, int64_t block, uint32_t* ties, uint32_t* part) {
+  if (threadIdx.x == 0) *part = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t mine = 0;
+  const int64_t w_end = min((block + 1) * b.per, b.words);
+  for (int64_t w0 = block * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
+    const WaveWords w = wave_words(b, kept, w0, w_end);
+    int32_t s[kWaveWords];
+    at_run_starts(w, size, 0, s);
+#pragma unroll
+    for (int j = 0; j < kWaveWords; ++j)
+      if (s[j] > 0 && (uint32_t)s[j] == s_star) mine += (uint32_t)__builtin_popcountll(run_from(w.word(j), lane) & ~w.border_of(j));
+  }
+  if (mine) atomicAdd(part, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) ties[block] = *part;
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// Mode 2 with the want-th pixel further than kLevels from the base map:
+// chessboard distances of every pixel. Per column the vertical distance g to
+// the nearest base pixel, then per pixel the minimum over columns x' of
+// max(|x - x'|, g(x')) (the border columns bound it).
 constexpr int32_t kFar = 1 << 30;
 constexpr int kSegRows = 32;   // rows per column segment
 
-__device__ __forceinline__ bool in_set(const ScanCtx& c, int64_t i) { return c.cls[i] != 2; }
-
-// Per (column, 32-row segment): the last and first selected row in it.
-__global__ __launch_bounds__(kBlock) void k_dt_seg(ScanCtx c, int32_t H, int32_t nseg, int32_t* last, int32_t* first) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nseg * c.W) return;
-  const int x = (int)((uint32_t)t % (uint32_t)c.W), sg = (int)((uint32_t)t / (uint32_t)c.W);   // t < N < 2^31
-  int lo = -1, fi = kFar;
-  for (int y = sg * kSegRows; y < min(H, (sg + 1) * kSegRows); ++y)
-    if (in_set(c, (int64_t)y * c.W + x)) { lo = y; if (fi == kFar) fi = y; }
-  last[t] = lo;
-  first[t] = fi;
-}
-
-// Per column: the nearest selected row above each segment and below it. The
-// records are read kCarryBatch at a time before any result is written, so a
-// thread has that many loads in flight instead of one round trip per segment.
-constexpr int kCarryBatch = 16;
-__global__ __launch_bounds__(kBlock) void k_dt_carry(int32_t W, int32_t nseg, const int32_t* __restrict__ last,
-                                                     const int32_t* __restrict__ first, int32_t* __restrict__ up,
-                                                     int32_t* __restrict__ down) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= W) return;
-  int u = -kFar;
-  for (int s0 = 0; s0 < nseg; s0 += kCarryBatch) {
-    int v[kCarryBatch];
+// Per (word column, 32-row segment): the columns with a base pixel in it.
+__device__ __forceinline__ void far_segments(const Bits& b, const unsigned long long* base, int nseg,
+                                             unsigned long long* segor) {
+  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < (int64_t)nseg * b.wpr; t += (int64_t)gridDim.x * kBlock) {
+    const int sg = (int)(t / b.wpr), c = (int)(t % b.wpr);
+    const int y0 = sg * kSegRows, n = min(b.H - y0, kSegRows);
+    unsigned long long v[kSegRows], m = 0ull;
 #pragma unroll
-    for (int k = 0; k < kCarryBatch; ++k) v[k] = s0 + k < nseg ? last[(int64_t)(s0 + k) * W + x] : -1;
+    for (int k = 0; k < kSegRows; ++k) v[k] = k < n ? base[(int64_t)(y0 + k) * b.wpr + c] : 0ull;
 #pragma unroll
-    for (int k = 0; k < kCarryBatch; ++k) {
-      if (s0 + k >= nseg) break;
-      up[(int64_t)(s0 + k) * W + x] = u;
-      if (v[k] >= 0) u = v[k];
-    }
-  }
-  int d = kFar;
-  for (int s1 = nseg - 1; s1 >= 0; s1 -= kCarryBatch) {   // segments s1, s1 - 1, ...
-    int v[kCarryBatch];
-#pragma unroll
-    for (int k = 0; k < kCarryBatch; ++k) v[k] = s1 - k >= 0 ? first[(int64_t)(s1 - k) * W + x] : kFar;
-#pragma unroll
-    for (int k = 0; k < kCarryBatch; ++k) {
-      if (s1 - k < 0) break;
-      down[(int64_t)(s1 - k) * W + x] = d;
-      if (v[k] < kFar) d = v[k];
-    }
+    for (int k = 0; k < kSegRows; ++k) m |= v[k];
+    segor[t] = m;
   }
 }
 
-// g = vertical distance to the nearest selected pixel of the column. The
-// segment's selection bits are read first (all loads in flight at once),
-// then both passes run on registers and the results are written once.
-__global__ __launch_bounds__(kBlock) void k_dt_col(ScanCtx c, int32_t H, int32_t nseg, const int32_t* up,
-                                                   const int32_t* down, int32_t* g) {
-  static_assert(kSegRows <= 32, "one mask word per segment");
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nseg * c.W) return;
-  const int x = (int)((uint32_t)t % (uint32_t)c.W), sg = (int)((uint32_t)t / (uint32_t)c.W);   // t < N < 2^31
-  const int y0 = sg * kSegRows, n = min(H - y0, kSegRows);
-  uint32_t sel = 0u;   // bit k: row y0 + k is selected
+// g for one (word column, segment) per wavefront, lane = column: inside the
+// segment from its 32 words; beyond it, segment by segment away from it until
+// every column has met a base pixel (or the image ends).
+__device__ __forceinline__ void far_columns(const Bits& b, const unsigned long long* base, int nseg,
+                                            const unsigned long long* segor, int32_t* g) {
+  const int lane = threadIdx.x & 63;
+  const int64_t items = (int64_t)nseg * b.wpr, nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); t < items; t += nw) {
+    const int sg = (int)(t / b.wpr), c = (int)(t % b.wpr);
+    const int y0 = sg * kSegRows, n = min(b.H - y0, kSegRows);
+    const int x = 64 * c + lane;
+    uint32_t sel = 0u;   // bit k: row y0 + k holds a base pixel in this column
 #pragma unroll
-  for (int k = 0; k < kSegRows; ++k)
-    if (k < n && in_set(c, (int64_t)(y0 + k) * c.W + x)) sel |= 1u << k;
-  int gv[kSegRows];
-  int u = up[t];
+    for (int k = 0; k < kSegRows; ++k) {
+      const unsigned long long w = k < n ? base[(int64_t)(y0 + k) * b.wpr + c] : 0ull;
+      sel |= (uint32_t)(w >> lane & 1ull) << k;
+    }
+    int up = -kFar, down = kFar;   // nearest base rows above and below the segment
+    unsigned long long need = ~0ull;
+    for (int s = sg - 1; s >= 0 && need; --s) {
+      const unsigned long long hit = segor[(int64_t)s * b.wpr + c] & need;
+      if (!hit) continue;
+      need &= ~hit;
+      for (int y = s * kSegRows; y < (s + 1) * kSegRows; ++y)
+        if ((hit & base[(int64_t)y * b.wpr + c]) >> lane & 1ull) up = y;
+    }
+    need = ~0ull;
+    for (int s = sg + 1; s < nseg && need; ++s) {
+      const unsigned long long hit = segor[(int64_t)s * b.wpr + c] & need;
+      if (!hit) continue;
+      need &= ~hit;
+      for (int y = min(b.H, (s + 1) * kSegRows) - 1; y >= s * kSegRows; --y)
+        if ((hit & base[(int64_t)y * b.wpr + c]) >> lane & 1ull) down = y;
+    }
+    int gv[kSegRows];
 #pragma unroll
-  for (int k = 0; k < kSegRows; ++k) {
-    if (sel >> k & 1u) u = y0 + k;
-    gv[k] = u < 0 ? kFar : y0 + k - u;
+    for (int k = 0; k < kSegRows; ++k) {
+      if (sel >> k & 1u) up = y0 + k;
+      gv[k] = up < 0 ? kFar : y0 + k - up;
+    }
+#pragma unroll
+    for (int k = kSegRows - 1; k >= 0; --k) {
+      if (sel >> k & 1u) down = y0 + k;
+      if (down < kFar) gv[k] = min(gv[k], down - (y0 + k));
+    }
+    if (x < b.W) {
+#pragma unroll
+      for (int k = 0; k < kSegRows; ++k)
+        if (k < n) g[(int64_t)(y0 + k) * b.W + x] = gv[k];
+    }
   }
-  int d = down[t];
-#pragma unroll
-  for (int k = kSegRows - 1; k >= 0; --k) {
-    if (sel >> k & 1u) d = y0 + k;
-    if (d < kFar) gv[k] = min(gv[k], d - (y0 + k));
-  }
-#pragma unroll
-  for (int k = 0; k < kSegRows; ++k)
-    if (k < n) g[(int64_t)(y0 + k) * c.W + x] = gv[k];
 }
 
 // One block per row; rows up to kRowLds pixels wide are searched in LDS,
@@ -1433,10 +1738,11 @@ __global__ __launch_bounds__(kBlock) void k_dt_col(ScanCtx c, int32_t H, int32_t
 // pixel far from the selected set costs about d/16 + 32 steps, not d.
 constexpr int kRowLds = 8192;
 constexpr int kDtBlk = 16;
-__global__ __launch_bounds__(kBlock) void k_dt_row(ScanCtx c, int32_t H, const int32_t* g, int32_t* dist) {
+__global__ __launch_bounds__(kBlock) void k_far_row(Bits b, const int32_t* far, const int32_t* g, int32_t* dist) {
   __shared__ int32_t row[kRowLds];
   __shared__ int32_t bmin[kRowLds / kDtBlk];
-  const int W = c.W;
+  if (!*far) return;
+  const int W = b.W, H = b.H;
   const bool in_lds = W <= kRowLds;
   const int nb = (W + kDtBlk - 1) / kDtBlk;
   for (int y = blockIdx.x; y < H; y += gridDim.x) {
@@ -1491,17 +1797,18 @@ __global__ __launch_bounds__(kBlock) void k_dt_row(ScanCtx c, int32_t H, const i
 // search over k, each next one from its left neighbour, since d changes by
 // at most 1 from a pixel to the next (a minimum of functions of slope at most
 // 1), which leaves at most two tests: k = d - 1, then k = d.
-// The same pass counts the distances of the other pixels (class 2), whose
-// select then needs one pick over the counts (k_fc_dist_pick) instead of
-// radix passes over every pixel: distances are below W (the border columns
-// are selected), so the counts have at most 4096 bins.
+// The same pass counts the distances of the other pixels (those not in the
+// base map): they are below W (the border columns are base pixels), so the
+// counts have at most 4096 bins and no counting pass follows.
 constexpr int kStW = 4096;
 constexpr int kStLevels = 13;   // ranges of 1 .. 4096
 constexpr int kStBlock = 1024;
-__global__ __launch_bounds__(kStBlock) void k_dt_row_st(int32_t W, int32_t H, const int32_t* g, int32_t* dist,
-                                                        const uint8_t* cls, uint32_t* dhist) {
+__global__ __launch_bounds__(kStBlock) void k_far_row_st(Bits bt, const int32_t* far, const int32_t* g, int32_t* dist,
+                                                         const unsigned long long* base, uint32_t* dhist) {
   __shared__ uint16_t st[kStLevels][kStW];
   __shared__ uint32_t hloc[kStW];
+  if (!*far) return;
+  const int W = bt.W, H = bt.H;
   for (int b = threadIdx.x; b < kStW; b += kStBlock) hloc[b] = 0u;
   const int levels = 32 - __builtin_clz((unsigned)W);   // 2^(levels-1) <= W
   const int run = (W + kStBlock - 1) / kStBlock;
@@ -1553,15 +1860,15 @@ __global__ __launch_bounds__(kStBlock) void k_dt_row_st(int32_t W, int32_t H, co
         if (within(x0, mid)) hi = mid;
         else lo = mid + 1;
       }
-      const uint8_t* crow = cls + (int64_t)y * W;
+      auto other = [&](int x) { return !map_bit(base, bt.wpr, x, y); };
       int d = lo;
       drow[x0] = d;
-      if (crow[x0] == 2) atomicAdd(&hloc[d], 1u);
+      if (other(x0)) atomicAdd(&hloc[d], 1u);
       for (int x = x0 + 1; x < x1; ++x) {
         if (d > 0 && within(x, d - 1)) d = d - 1;
         else if (!within(x, d)) d = d + 1;
         drow[x] = d;
-        if (crow[x] == 2) atomicAdd(&hloc[d], 1u);
+        if (other(x)) atomicAdd(&hloc[d], 1u);
       }
     }
     __syncthreads();
@@ -1570,31 +1877,90 @@ __global__ __launch_bounds__(kStBlock) void k_dt_row_st(int32_t W, int32_t H, co
     if (hloc[b]) atomicAdd(&dhist[b], hloc[b]);
 }
 
-// The distance select from the counts of k_dt_row_st: the smallest distance
-// D whose running count reaches s2.need, and the count below it (what the
-// radix passes would leave in s2). One block; each thread sums four bins.
-__global__ __launch_bounds__(kStBlock) void k_fc_dist_pick(FracState* f, const uint32_t* dhist, int32_t W) {
-  static_assert(kStW == 4 * kStBlock, "four bins per thread");
-  __shared__ uint32_t wtot[kStBlock / 64];
-  const long long need = f->s2.need;
-  const int b0 = threadIdx.x * 4;
-  uint32_t v[4], sum = 0u;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    v[k] = b0 + k < W ? dhist[b0 + k] : 0u;
-    sum += v[k];
+// One counting pass over the other pixels' distances (rows wider than the
+// range-minimum search takes).
+__global__ __launch_bounds__(kBlock) void k_dist_pass(Bits b, FcArgs a, const int32_t* far,
+                                                      const unsigned long long* __restrict__ base,
+                                                      const int32_t* __restrict__ dist, const RadixSel* in,
+                                                      const uint32_t* prev_hist, int prev_shift, RadixSel* state,
+                                                      int shift, uint32_t* hist) {
+  __shared__ uint32_t bins[kBins];
+  if (!*far) return;
+  RadixSel rs = in ? *in : RadixSel{0, fc_plan(a).need, 0};
+  if (prev_hist) rs = sel_pick(rs, prev_hist, prev_shift, state);
+  for (int k = threadIdx.x; k < kBins; k += kBlock) bins[k] = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, hi = shift + kDigit;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t wi = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); wi < b.words; wi += nw) {
+    const WordPos p = word_pos(b, wi);
+    if (64 * p.c + lane >= b.W || (base[wi] >> lane & 1ull)) continue;
+    const unsigned long long key = (uint32_t)dist[p.i + lane];
+    if ((key >> hi) == (rs.prefix >> hi)) atomicAdd(&bins[(key >> shift) & (kBins - 1)], 1u);
   }
-  uint32_t total = 0u;
-  long long before = (long long)block_scan_excl<kStBlock / 64>(sum, wtot, total);
-  if (need <= 0 || !(before < need && need <= before + (long long)sum)) return;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (need <= before + (long long)v[k]) {
-      f->s2.prefix = (unsigned long long)(b0 + k);
-      f->s2.below = before;
-      return;
-    }
-    before += v[k];
+  __syncthreads();
+  for (int k = threadIdx.x; k < kBins; k += kBlock)
+    if (bins[k]) atomicAdd(&hist[k], bins[k]);
+}
+
+// The launches of the two rarer classes share their places in the sequence
+// (only one of them does anything): the counting passes of mode 1, and the
+// distance passes of mode 2 beyond kLevels.
+// First: sizes, top digit | columns with base pixels per segment.
+__global__ __launch_bounds__(kBlock) void k_fc_first(Bits b, FcArgs a, const unsigned long long* kept,
+                                                     const unsigned long long* base, const int32_t* size,
+                                                     unsigned long long prefix, int shift,
+                                                     uint32_t* hist, const uint32_t* lcount, int nseg,
+                                                     unsigned long long* segor) {
+  __shared__ uint32_t bins[kBins];
+  const FcPlan pl = fc_plan(a);
+  if (pl.mode == 1) size_pass(b, kept, size, RadixSel{prefix, pl.need, 0}, nullptr, 0, nullptr, shift, hist, bins);
+  else if (pl.mode == 2 && level_pick(lcount, pl.need).level == 0) far_segments(b, base, nseg, segor);
+}
+// Second: sizes, a lower digit | column distances, and the flag that the
+// launches after it go by.
+__global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const unsigned long long* kept,
+                                                      const unsigned long long* base, const int32_t* size, const RadixSel* in, unsigned long long prefix,
+                                                      const uint32_t* prev_hist, int prev_shift, RadixSel* state, int shift,
+                                                      uint32_t* hist, const uint32_t* lcount, int nseg,
+                                                      const unsigned long long* segor, int32_t* g, int32_t* far) {
+  __shared__ uint32_t bins[kBins];
+  const FcPlan pl = fc_plan(a);
+  if (pl.mode == 1) {
+    size_pass(b, kept, size, in ? *in : RadixSel{prefix, pl.need, 0}, prev_hist, prev_shift, state, shift, hist,
+              bins);
+  } else if (g && pl.mode == 2 && level_pick(lcount, pl.need).level == 0) {
+    far_columns(b, base, nseg, segor, g);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *far = 1;
+  }
+}
+// Last: pixels of the wanted size per block | levels 1 and 2 from the distances.
+__global__ __launch_bounds__(kBlock) void k_fc_last(Bits b, FcArgs a, int nb, const unsigned long long* kept,
+                                                    const unsigned long long* base, const int32_t* size, const RadixSel* s1, const uint32_t* s1_hist,
+                                                    uint32_t* ties, const int32_t* far, const int32_t* dist,
+                                                    const RadixSel* sd, const uint32_t* sd_hist,
+                                                    unsigned long long* planes, long long* far_need) {
+  __shared__ uint32_t part;
+  const FcPlan pl = fc_plan(a);
+  if (pl.mode == 1) {
+    const RadixSel rs = sel_pick(*s1, s1_hist, 0, nullptr);
+    for (int64_t block = blockIdx.x; block < nb; block += gridDim.x)
+      tie_pass(b, kept, size, ~(uint32_t)rs.prefix, block, ties, &part);
+    return;
+  }
+  if (!*far) return;
+  const RadixSel rs = sel_pick(sd ? *sd : RadixSel{0, pl.need, 0}, sd_hist, 0, nullptr);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *far_need = rs.need - rs.below;
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  for (int64_t wi = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); wi < b.words; wi += nw) {
+    const WordPos p = word_pos(b, wi);
+    const unsigned long long bw = base[wi];
+    const bool in = 64 * p.c + lane < b.W && !(bw >> lane & 1ull);
+    const unsigned long long d = in ? (unsigned long long)(uint32_t)dist[p.i + lane] : ~0ull;
+    const unsigned long long nearer = __builtin_amdgcn_ballot_w64(in && d < rs.prefix);
+    const unsigned long long at = __builtin_amdgcn_ballot_w64(in && d == rs.prefix);
+    if (lane < 4) planes[4 * wi + lane] = lane == 0 ? nearer : lane == 1 ? at : 0ull;
   }
 }
 
@@ -1610,32 +1976,51 @@ int fail(int st, const char* fmt, ...) {
 size_t a256(size_t v) { return (v + 255) / 256 * 256; }
 
 struct Layout {
-  size_t L8, cls, B, parent, size, cnt, bsum, bits, hist, g, dist, frank, rhist, dhist, lut, misc, end;
+  size_t L8, B, kept, base, sel, planes, parent, size, g, dist, segor, bsum, ties, lut;
+  size_t clear, hist, misc, lcount, shist, dhist, hhist, cnt, clear_front, clear_frac, clear_all;   // cleared at the start
+  size_t end;
+  int64_t ncnt;
 };
+
+Bits map_bits(int32_t W, int32_t H) {
+  Bits b{};
+  b.W = W;
+  b.H = H;
+  b.wpr = (W + 63) / 64;
+  b.words = (int64_t)H * b.wpr;
+  b.per = kSelWords * ((b.words + (int64_t)kSelWords * kSelBlocks - 1) / ((int64_t)kSelWords * kSelBlocks));
+  return b;
+}
 
 Layout layout(int32_t W, int32_t H) {
   const int64_t N = (int64_t)W * H;
-  // `dist` first holds the column pass's four per-segment arrays
-  const int64_t seg_words = 4LL * ((H + kSegRows - 1) / kSegRows) * W;
+  const Bits b = map_bits(W, H);
   Layout o{};
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off += a256(bytes); return at; };
   o.L8 = take(N);
-  o.cls = take(N);
-  o.B = take((size_t)H * ((W + 63) / 64) * 8);
+  for (size_t* m : {&o.B, &o.kept, &o.base, &o.sel}) *m = take((size_t)b.words * 8);
+  o.planes = take((size_t)b.words * 8 * kLevelBits);
   o.parent = take((size_t)N * 4);
   o.size = take((size_t)N * 4);
-  o.cnt = take(((size_t)N + 1) * 4);
-  o.bsum = take(((size_t)(N + kScanPer - 1) / kScanPer + 1) * 4);
-  o.bits = take((size_t)(N + kScanPer - 1) / kScanPer * (kScanPer / 8));
-  o.hist = take(256 * 8);
   o.g = take((size_t)N * 4);
-  o.dist = take((size_t)std::max<int64_t>(N, seg_words) * 4);
-  o.frank = take((size_t)N * 4);
-  o.rhist = take(256 * 4 * kRsPasses * 3);   // one zeroed count array per pass of each of the three selects
-  o.dhist = take(kStW * 4);
+  o.dist = take((size_t)N * 4);
+  o.segor = take((size_t)((H + kSegRows - 1) / kSegRows) * b.wpr * 8);
+  o.bsum = take(kSelBlocks * 4);
+  o.ties = take(kSelBlocks * 4);
   o.lut = take(256);
+  o.clear = off;
+  o.hist = take(256 * 8);
   o.misc = take(kMiscBytes);
+  o.clear_front = off;
+  o.lcount = take((size_t)kLvParts * (kLevels + 1) * 4);
+  o.shist = take((size_t)3 * kBins * 4);   // one count array per pass of a select
+  o.dhist = take((size_t)3 * kBins * 4);
+  o.hhist = take((size_t)kHashParts * kHashBins * 4);
+  o.clear_frac = off;
+  o.ncnt = (int64_t)(kDropFrac * (double)N) + 2;   // sizes that the paper filter's budget can hold
+  o.cnt = take((size_t)o.ncnt * 4);
+  o.clear_all = off;
   o.end = off;
   return o;
 }
@@ -1739,8 +2124,12 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   hipStream_t s = (hipStream_t)stream;
   char* base = (char*)workspace;
   uint8_t* L8 = (uint8_t*)(base + Lo.L8);
+  const Bits bt = map_bits(W, H);
   unsigned long long* B = (unsigned long long*)(base + Lo.B);
-  const int32_t wpr = (W + 63) / 64;   // words per row of the maps held as bits
+  unsigned long long* kept = (unsigned long long*)(base + Lo.kept);
+  unsigned long long* bmap = (unsigned long long*)(base + Lo.base);
+  unsigned long long* sel = (unsigned long long*)(base + Lo.sel);
+  const int32_t wpr = bt.wpr;
   int32_t* parent = (int32_t*)(base + Lo.parent);
   int32_t* size = (int32_t*)(base + Lo.size);
   int32_t* cnt = (int32_t*)(base + Lo.cnt);
@@ -1751,20 +2140,21 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   int32_t* passes = (int32_t*)misc;
   unsigned long long* total = (unsigned long long*)(misc + 128);
   DropRule* rule = (DropRule*)(misc + 192);
-  FracState* fs = (FracState*)(misc + 256);
+  int32_t* far = (int32_t*)(misc + 256);
+  long long* far_need = (long long*)(misc + 264);
+  RingBin* rb = (RingBin*)(misc + 320);
+  RadixSel* s1 = (RadixSel*)(misc + 384);   // the size select's states after its picks
+  RadixSel* sd = (RadixSel*)(misc + 448);   // the distance select's
   unsigned long long* n1 = (unsigned long long*)(misc + 1024);   // kN1Parts partial counts
-  RadixSel* rsv = (RadixSel*)(misc + 704);   // a select's state after each pass's pick (kRsPasses)
-  static_assert(704 + kRsPasses * sizeof(RadixSel) <= 1024, "misc layout");
-  int32_t* gcol = (int32_t*)(base + Lo.g);
-  int32_t* dist = (int32_t*)(base + Lo.dist);
-  int32_t* frank = (int32_t*)(base + Lo.frank);
-  uint32_t* rhist = (uint32_t*)(base + Lo.rhist);
-  static_assert(sizeof(FracState) <= 256, "misc layout");
+  static_assert(sizeof(RingBin) <= 64 && 2 * sizeof(RadixSel) <= 64 && 1024 + kN1Parts * 8 <= kMiscBytes, "misc layout");
   const int g = grid_for(N);
 
-  // Clear the small counters with kernels (no memset nodes if the caller captures the stream).
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(kBlock), 0, s, (uint8_t*)hist, (int64_t)(256 * 8), (uint8_t)0);
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(kBlock), 0, s, (uint8_t*)misc, (int64_t)kMiscBytes, (uint8_t)0);
+  {
+    const size_t to = mode == 1 ? Lo.clear_all : frac >= 0.0 ? Lo.clear_frac : Lo.clear_front;
+    const int64_t bytes = (int64_t)(to - Lo.clear);
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)std::min<int64_t>((bytes / 16 + kBlock - 1) / kBlock, 1024)), dim3(kBlock),
+                       0, s, (uint4*)(base + Lo.clear), bytes);
+  }
   // grey rows without gaps are the lightness image itself (no copy)
   const uint8_t* lum = L8;
   if (C == 1 && pitch == W) lum = img;
@@ -1785,114 +2175,90 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   hipLaunchKernelGGL(k_cc_edges, gt, dim3(128), 0, s, B, wpr, W, H, parent);
   hipLaunchKernelGGL(k_cc_flatten, dim3(g), dim3(kBlock), 0, s, N, parent, size);
 
-  const int64_t nb = (N + kScanPer - 1) / kScanPer;
-  ScanCtx c{};
-  c.parent = parent; c.size = size; c.rule = nullptr; c.min_cc = min_cc; c.W = W; c.N = N;
-  c.rank = cnt;   // the rank array reuses cnt: ranks are written after k_drop_find has read the counts
-  c.out = out_idx; c.refined = out_refined; c.count = (long long*)out_count;
-  c.bits = (unsigned long long*)(base + Lo.bits);
+  const int nb = (int)((bt.words + bt.per - 1) / bt.per);
+  // passes over words, kSelWords per block and step
+  const int gw = (int)std::min<int64_t>((bt.words + kSelWords - 1) / kSelWords, 1024);
   if (mode == 1) {
-    hipLaunchKernelGGL(k_fill, dim3(g), dim3(kBlock), 0, s, (uint8_t*)cnt, (int64_t)(N + 1) * 4, (uint8_t)0);
     // at most 512 blocks: each block's closing adds (its total and its small
     // sizes' counts) go to the same few global words, so fewer blocks wait less
-    hipLaunchKernelGGL(k_drop_count, dim3(std::min(g, 512)), dim3(kBlock), 0, s, size, N, total, cnt);
-    hipLaunchKernelGGL(k_drop_find, dim3(1), dim3(1024), 0, s, cnt, total, 0.04, rule);
-    c.rule = rule;
-    // rank of each root of size s* among those roots, in raster order
-    hipLaunchKernelGGL(k_scan_count<0>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, nb, (long long*)nullptr);
-    hipLaunchKernelGGL(k_scan_apply<0>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
+    hipLaunchKernelGGL(k_drop_count, dim3(std::min(gw, 512)), dim3(kBlock), 0, s, bt, B, size, Lo.ncnt, total, cnt);
+    hipLaunchKernelGGL(k_drop_find, dim3(1), dim3(1024), 0, s, cnt, total, rule);
+    hipLaunchKernelGGL(k_root_count, dim3(nb), dim3(kBlock), 0, s, bt, B, size, rule, bsum);
+    hipLaunchKernelGGL(k_root_find, dim3(1), dim3(1024), 0, s, bt, B, size, bsum, nb, rule);
   }
-  if (frac >= 0.0) {
-    const long long want = std::min<long long>((long long)N, std::llround(frac * (double)N));
-    const long long n0 = W == 1 ? H : 2LL * H;
-    uint8_t* cls = (uint8_t*)(base + Lo.cls);
-    hipLaunchKernelGGL(k_fc_class, dim3(g), dim3(kBlock), 0, s, c, cls, n1);
-    // Component sizes are at most N: with N below 2^24 the top digit of ~size is
-    // 0xFF for every kept pixel, so it is set here and its pass skipped.
+  const DropRule* dr = mode == 1 ? rule : nullptr;
+  if (frac < 0.0) {
+    hipLaunchKernelGGL(k_kept, dim3(nb), dim3(kBlock), 0, s, bt, B, parent, size, dr, (int64_t)min_cc,
+                       (unsigned long long*)nullptr, sel, out_refined, bsum, (unsigned long long*)nullptr);
+  } else {
+    FcArgs fa{};
+    fa.want = std::min<long long>((long long)N, std::llround(frac * (double)N));
+    fa.n0 = W == 1 ? H : 2LL * H;
+    fa.n1 = n1;
+    fa.seed = (unsigned long long)seed;
+    unsigned long long* planes = (unsigned long long*)(base + Lo.planes);
+    uint32_t* lcount = (uint32_t*)(base + Lo.lcount);
+    uint32_t* shist = (uint32_t*)(base + Lo.shist);
+    uint32_t* dhist = (uint32_t*)(base + Lo.dhist);
+    uint32_t* hhist = (uint32_t*)(base + Lo.hhist);
+    uint32_t* ties = (uint32_t*)(base + Lo.ties);
+    int32_t* gcol = (int32_t*)(base + Lo.g);
+    int32_t* dist = (int32_t*)(base + Lo.dist);
+    unsigned long long* segor = (unsigned long long*)(base + Lo.segor);
+    const int nseg = (H + kSegRows - 1) / kSegRows;
+    hipLaunchKernelGGL(k_kept, dim3(nb), dim3(kBlock), 0, s, bt, B, parent, size, dr, (int64_t)min_cc, kept, bmap,
+                       out_refined, (uint32_t*)nullptr, n1);
+    const dim3 gl((wpr + 2 * (kBlock / 64) - 1) / (2 * (kBlock / 64)), (H + kLvRows - 1) / kLvRows);
+    hipLaunchKernelGGL(k_fc_levels<0>, gl, dim3(kBlock), 0, s, bt, fa, bmap, planes, sel, lcount);
+    hipLaunchKernelGGL(k_fc_levels<1>, gl, dim3(kBlock), 0, s, bt, fa, sel, planes, (unsigned long long*)nullptr, lcount);
+    // Component sizes are at most N: with N below 2^24 the keys' top 8 bits
+    // are ones, and two digits remain; else three.
     const bool small = N < (1LL << 24);
-    hipLaunchKernelGGL(k_fc_plan, dim3(1), dim3(1), 0, s, fs, n1, want, n0, small ? 0xFF000000ull : 0ull);
-    c.fc = fs; c.dist = dist; c.frank = frank; c.seed = (unsigned long long)seed; c.cls = cls;
-    // radix-select histograms: at most 512 blocks (each ends with up to 256
-    // global adds). Pass p counts into its own zeroed array and starts from
-    // the state after the pick of pass p - 1's counts (rsv[p - 1], written by
-    // its block 0); one pick launch after the last pass sets the final state.
-    const int gr = std::min(g, 512);
-    hipLaunchKernelGGL(k_fill, dim3(1), dim3(kBlock), 0, s, (uint8_t*)rhist, (int64_t)(256 * 4 * kRsPasses * 3),
-                       (uint8_t)0);
-    int nsel = 0;
-    auto select = [&](RadixSel* st, int first_shift, int last_shift, auto launch_pass) {
-      uint32_t* const hs = rhist + 256 * kRsPasses * nsel++;   // this select's count arrays
-      int p = 0, prev_shift = 0;
-      for (int sh = first_shift; sh >= last_shift; sh -= 8, ++p) {
-        const RadixSel* in = p <= 1 ? st : &rsv[p - 1];
-        const uint32_t* in_hist = p == 0 ? nullptr : hs + 256 * (p - 1);
-        launch_pass(in, in_hist, prev_shift, &rsv[p], sh, hs + 256 * p);
-        prev_shift = sh;
-      }
-      hipLaunchKernelGGL(k_rs_pick, dim3(1), dim3(256), 0, s, p <= 1 ? (const RadixSel*)st : &rsv[p - 1],
-                         hs + 256 * (p - 1), prev_shift, st);
-    };
-    select(&fs->s1, small ? 16 : 24, 0,   // kept pixels: size descending
-           [&](const RadixSel* in, const uint32_t* ih, int ish, RadixSel* out, int sh, uint32_t* h) {
-             hipLaunchKernelGGL(k_rs_hist<1>, dim3(gr), dim3(kBlock), 0, s, c, in, ih, ish, out, sh, h);
-           });
-    hipLaunchKernelGGL(k_scan_count<2>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, nb, (long long*)nullptr);
-    hipLaunchKernelGGL(k_scan_apply<2>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
-    {
-      // segment summaries live in `dist` until the column pass is done
-      const int nseg = (H + kSegRows - 1) / kSegRows;
-      const int64_t ns = (int64_t)nseg * W;
-      int32_t* last = dist;
-      int32_t* first = dist + ns;
-      int32_t* up = dist + 2 * ns;
-      int32_t* down = dist + 3 * ns;
-      const unsigned gs = (unsigned)((ns + kBlock - 1) / kBlock);
-      hipLaunchKernelGGL(k_dt_seg, dim3(gs), dim3(kBlock), 0, s, c, H, nseg, last, first);
-      hipLaunchKernelGGL(k_dt_carry, dim3((W + kBlock - 1) / kBlock), dim3(kBlock), 0, s, W, nseg, last, first, up, down);
-      hipLaunchKernelGGL(k_dt_col, dim3(gs), dim3(kBlock), 0, s, c, H, nseg, up, down, gcol);
+    const unsigned long long prefix = small ? 0xFF000000ull : 0ull;
+    const int gs = std::min(gw, 512);   // (each block ends with up to kBins global adds)
+    int sh = small ? kDigit : 2 * kDigit, np = 0;
+    hipLaunchKernelGGL(k_fc_first, dim3(gs), dim3(kBlock), 0, s, bt, fa, kept, bmap, size, prefix, sh, shist, lcount,
+                       nseg, segor);
+    for (++np; sh > 0; ++np) {
+      const int prev = sh;
+      sh -= kDigit;
+      hipLaunchKernelGGL(k_fc_second, dim3(np == 1 ? gw : gs), dim3(kBlock), 0, s, bt, fa, kept, bmap, size,
+                         np == 1 ? (const RadixSel*)nullptr : s1 + np - 2, prefix, shist + (np - 1) * kBins, prev,
+                         s1 + np - 1, sh, shist + np * kBins, lcount, nseg, segor, np == 1 ? gcol : (int32_t*)nullptr, far);
     }
+    const RadixSel* s1_last = s1 + np - 2;
+    const uint32_t* s1_hist = shist + (np - 1) * kBins;
+    const RadixSel* sd_last = nullptr;
+    const uint32_t* sd_hist = dhist;
     if (W <= kStW && H <= 65535) {
       // one block per CU (the table takes most of the LDS), each over rows in turn
-      uint32_t* dhist = (uint32_t*)(base + Lo.dhist);
-      hipLaunchKernelGGL(k_fill, dim3(1), dim3(kBlock), 0, s, (uint8_t*)dhist, (int64_t)(kStW * 4), (uint8_t)0);
-      hipLaunchKernelGGL(k_dt_row_st, dim3(H < 256 ? H : 256), dim3(kStBlock), 0, s, W, H, gcol, dist, cls, dhist);
-      hipLaunchKernelGGL(k_fc_dist_pick, dim3(1), dim3(kStBlock), 0, s, fs, dhist, W);
+      hipLaunchKernelGGL(k_far_row_st, dim3(H < 256 ? H : 256), dim3(kStBlock), 0, s, bt, far, gcol, dist, bmap, dhist);
     } else {
-      hipLaunchKernelGGL(k_dt_row, dim3(H < 16384 ? H : 16384), dim3(kBlock), 0, s, c, H, gcol, dist);
-      // Distances are below W (the border columns are selected), so digits at
-      // and above a power of two >= W are 0 for every candidate: the pick
-      // would add 0 to the prefix and to the count below, so those passes are skipped.
-      int top = 24;
-      while (top >= 8 && (int64_t)W <= (1LL << top)) top -= 8;
-      select(&fs->s2, top, 0,   // other pixels: distance
-             [&](const RadixSel* in, const uint32_t* ih, int ish, RadixSel* out, int sh, uint32_t* h) {
-               hipLaunchKernelGGL(k_rs_hist<2>, dim3(gr), dim3(kBlock), 0, s, c, in, ih, ish, out, sh, h);
-             });
+      hipLaunchKernelGGL(k_far_row, dim3(H < 16384 ? H : 16384), dim3(kBlock), 0, s, bt, far, gcol, dist);
+      // distances are below W (the border columns are base pixels)
+      int dsh = W <= kBins ? 0 : W <= (1 << 24) ? kDigit : 2 * kDigit;
+      for (int k = 0;; ++k) {
+        hipLaunchKernelGGL(k_dist_pass, dim3(gs), dim3(kBlock), 0, s, bt, fa, far, bmap, dist,
+                           k < 2 ? (const RadixSel*)nullptr : sd + k - 2, k == 0 ? (const uint32_t*)nullptr : sd_hist,
+                           dsh + kDigit, k == 0 ? (RadixSel*)nullptr : sd + k - 1, dsh, dhist + k * kBins);
+        sd_last = k == 0 ? nullptr : sd + k - 1;
+        sd_hist = dhist + k * kBins;
+        if (dsh == 0) break;
+        dsh -= kDigit;
+      }
     }
-    hipLaunchKernelGGL(k_fc_after_dist, dim3(1), dim3(1), 0, s, fs);
-    // other pixels at that distance: hash, over their compacted list (in the
-    // column-distance buffer, free once the row pass has run)
-    int32_t* cand = gcol;
-    unsigned long long* ncand = (unsigned long long*)(misc + 640);
-    hipLaunchKernelGGL(k_fc_cands, dim3((unsigned)std::min<int64_t>((N + kCandPer - 1) / kCandPer, 8192)),
-                       dim3(kBlock), 0, s, c, cand, ncand);
-    select(&fs->s3, 56, 0,   // the hash
-           [&](const RadixSel* in, const uint32_t* ih, int ish, RadixSel* out, int sh, uint32_t* h) {
-             hipLaunchKernelGGL(k_rs_hist_cands, dim3(std::min(gr, 64)), dim3(kBlock), 0, s, cand, ncand,
-                                (unsigned long long)seed, in, ih, ish, out, sh, h);
-           });
-    hipLaunchKernelGGL(k_scan_count<3>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, nb, (long long*)nullptr);
-    hipLaunchKernelGGL(k_scan_apply<3>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
+    hipLaunchKernelGGL(k_fc_last, dim3(std::min(gw, 1024)), dim3(kBlock), 0, s, bt, fa, nb, kept, bmap, size, s1_last,
+                       s1_hist, ties, far, dist, sd_last, sd_hist, planes, far_need);
+    // the hashes of one bin's ring pixels are listed in the place of the column
+    // and pixel distances (8 bytes per pixel between them)
+    unsigned long long* ring = (unsigned long long*)gcol;
+    const int gr = (int)std::min<int64_t>((bt.words + kRingGroups * kRingWords - 1) / (kRingGroups * kRingWords), 1024);
+    hipLaunchKernelGGL(k_ring_count, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist);
+    hipLaunchKernelGGL(k_ring_bin, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist, rb, ring);
+    hipLaunchKernelGGL(k_fc_select, dim3(nb), dim3(kBlock), 0, s, bt, fa, kept, bmap, size, s1_last, s1_hist, ties,
+                       planes, lcount, far_need, rb, ring, sel, bsum);
   }
-  // the kept map, when asked for, is worked out per element in the applying
-  // pass anyway: the flags are then worked out there too
-  if (out_refined) c.bits = nullptr;
-  hipLaunchKernelGGL(k_scan_count<1>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, bsum, nb, (long long*)out_count);
-  hipLaunchKernelGGL(k_scan_apply<1>, dim3((unsigned)nb), dim3(kBlock), 0, s, c, bsum);
+  hipLaunchKernelGGL(k_list, dim3(nb), dim3(kBlock), 0, s, bt, sel, bsum, out_idx, (long long*)out_count);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SBS_ERR_HIP, "boundaries: %s", hipGetErrorString(e));
   return SBS_OK;

@@ -183,3 +183,45 @@ def test_refinement_tiles(torch, sbs, W, H):
         for mode, Ks in ((0, (2, 5, 6, 9)), (1, (2, 4, 16, 17))):
             for K in Ks:
                 check_front(torch, sbs, view, img, K, mode, 5, f"{W}x{H} offset {off} mode {mode} K {K}")
+
+
+def check_fraction(torch, sbs, img, K, mode, min_cc, frac, seed, what):
+    got = sbs.boundaries(dev(torch, img), K=K, mode=mode, min_cc=min_cc, frac=frac, seed=seed).cpu().numpy().view(np.uint32)
+    exp = oracle.boundaries(img, K=K, mode=mode, min_cc=min_cc, frac=frac, seed=seed)
+    assert np.array_equal(got, exp), f"{what}: {got.size} and {exp.size} pixels, {np.setdiff1d(got, exp).size} differ"
+
+
+@pytest.mark.parametrize("W,H", [(300, 260), (128, 98), (129, 99), (700, 40)])
+def test_fraction_control_levels(torch, sbs, W, H):
+    """Fractions that end at every distance a small scene has: the levels of
+    both dilation launches (1 .. 15 and 16 .. 30), their last and first ones,
+    and the distance passes beyond, on maps around the dilation's tiles (128
+    columns, 98 rows)."""
+    img = np.full((H, W), 40, np.uint8)
+    img[H // 3:H // 3 + 14, W // 2:W // 2 + 20] = 210
+    _, kept = oracle.boundaries(img, K=2, mode=0, min_cc=1, frac=-1.0, return_map=True)
+    base = kept.astype(bool)
+    base[:, 0] = base[:, -1] = True
+    from scipy.ndimage import distance_transform_cdt
+    dist = distance_transform_cdt(~base, metric="chessboard")
+    for d in sorted({1, 2, 14, 15, 16, 17, 29, 30, 31, 32, 40, int(dist.max())}):
+        inside, ring = int((dist < d).sum()), int((dist == d).sum())
+        for k in {1, ring // 2, ring}:
+            if ring and k:
+                check_fraction(torch, sbs, img, 2, 0, 1, (inside + k) / (W * H), 77 + d, f"{W}x{H} distance {d} rank {k}")
+
+
+@pytest.mark.parametrize("W,H", [(64, 33), (131, 70), (4200, 4096)])
+def test_fraction_control_component_sizes(torch, sbs, W, H):
+    """Fractions that end among the kept pixels: within a component size that
+    many components share (ties by raster order), at the largest and at the
+    smallest, and on an image of 2^24 pixels and more (a third digit)."""
+    rng = np.random.default_rng(W)
+    img = np.zeros((H, W), np.uint8)
+    for k in range(W * H // 500 if W < 1000 else 400):
+        y, x, r = int(rng.integers(0, H)), int(rng.integers(0, W)), int(rng.integers(3, 8))
+        img[y:y + r, x:x + r] = 200
+    _, kept = oracle.boundaries(img, K=2, mode=0, min_cc=1, frac=-1.0, return_map=True)
+    n1, n0 = int(kept[:, 1:-1].sum()), 2 * H
+    for share in ((0.5,) if W > 1000 else (0.0, 0.1, 0.33, 0.5, 0.77, 1.0)):
+        check_fraction(torch, sbs, img, 2, 0, 1, (n0 + 1 + share * (n1 - 1)) / (W * H), 3, f"{W}x{H} share {share}")
