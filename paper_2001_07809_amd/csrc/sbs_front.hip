@@ -504,221 +504,6 @@ __global__ __launch_bounds__(64) void k_refine(const uint8_t* __restrict__ lum, 
 }
 
 // ---------------------------------------------------------------------------
-// Connected components by union-find. A link always points a larger root at
-// a smaller one, so a component's root ends as its smallest index.
-// Root of a, halving the path on the way (each visited pixel is pointed at
-// its grandparent with an atomic minimum, so a link only ever moves towards
-// smaller indices of the same component).
-__device__ __forceinline__ int32_t uf_find(int32_t* parent, int32_t a) {
-  for (;;) {
-    const int32_t p = __hip_atomic_load(&parent[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (p == a) return a;
-    const int32_t pp = __hip_atomic_load(&parent[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (pp == p) return p;
-    atomicMin(&parent[a], pp);
-    a = pp;
-  }
-}
-
-__device__ __forceinline__ void uf_union(int32_t* parent, int32_t a, int32_t b) {
-  for (;;) {
-    a = uf_find(parent, a);
-    b = uf_find(parent, b);
-    if (a == b) return;
-    if (a < b) { const int32_t t = a; a = b; b = t; }
-    // a > b, a was a root when found: make it point at b unless it moved meanwhile
-    const int32_t old = atomicMin(&parent[a], b);
-    if (old == a) return;
-    a = old;   // a was linked elsewhere concurrently: continue from there
-  }
-}
-
-// Two-level merge. k_cc_tile: one block per tile of kTileW x kTileH pixels
-// runs the same union-find on the tile's pixels in LDS (links from larger to
-// smaller local raster index, which is the global raster order within the
-// tile), then writes for every pixel of the tile the global index of its
-// tile root (-1 off the boundary map) and the tile roots' local sizes (0
-// elsewhere), which initialises the whole forest. k_cc_edges then unions, through the global forest, only the
-// neighbour pairs that cross a tile edge. The forest's roots stay the
-// smallest raster index of their component.
-constexpr int kTileW = 64, kTileH = 32;
-static_assert(kTileW == 64, "k_cc_tile: one wavefront per tile row");
-static_assert(kTileW + 2 * (kTileH - 1) <= 128, "k_cc_edges: one thread per tile edge pixel");
-
-__device__ __forceinline__ int32_t lds_find(int32_t* lp, int32_t a) {
-  for (;;) {
-    const int32_t p = lp[a];
-    if (p == a) return a;
-    const int32_t pp = lp[p];
-    if (pp == p) return p;
-    atomicMin(&lp[a], pp);
-    a = pp;
-  }
-}
-
-__device__ __forceinline__ void lds_union(int32_t* lp, int32_t a, int32_t b) {
-  for (;;) {
-    a = lds_find(lp, a);
-    b = lds_find(lp, b);
-    if (a == b) return;
-    if (a < b) { const int32_t t = a; a = b; b = t; }
-    const int32_t old = atomicMin(&lp[a], b);
-    if (old == a) return;
-    a = old;
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_cc_tile(const unsigned long long* __restrict__ B, int32_t wpr, int32_t W,
-                                                    int32_t H, int32_t* parent, int32_t* size) {
-  __shared__ int32_t lp[kTileW * kTileH];
-  __shared__ int32_t lsz[kTileW * kTileH];
-  const int x0 = blockIdx.x * kTileW, y0 = blockIdx.y * kTileH;
-  const int lx = threadIdx.x & (kTileW - 1);
-  constexpr int kRowsPerPass = kBlock / kTileW;
-  // wavefront w takes the band of rows w kBand .. w kBand + kBand - 1, one
-  // row per pass, so a row's upward unions meet a row its own wavefront
-  // linked one pass before (short paths to the roots)
-  constexpr int kBand = kTileH / kRowsPerPass;
-  bool on[kTileH / kRowsPerPass], first[kTileH / kRowsPerPass];
-#pragma unroll
-  for (int j = 0; j < kTileH / kRowsPerPass; ++j) {
-    const int ly = (int)(threadIdx.x / kTileW) * kBand + j;
-    // a wavefront holds one tile row, one word of the map (kTileW == 64):
-    // each pixel links straight to the first pixel of its horizontal run, so
-    // left neighbours need no union below
-    const uint64_t row = y0 + ly < H ? B[(int64_t)(y0 + ly) * wpr + blockIdx.x] : 0ull;
-    on[j] = (row >> lx) & 1ull;
-    const uint64_t upto = lx == 63 ? ~0ull : ((2ull << lx) - 1ull);   // bits 0 .. lx
-    const uint64_t gaps = ~row & upto;
-    const int start = gaps ? 64 - __builtin_clzll(gaps) : 0;   // just past the last gap at or before lx
-    first[j] = start == lx;
-    lp[ly * kTileW + lx] = on[j] ? ly * kTileW + start : -1;
-    lsz[ly * kTileW + lx] = 0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kTileH / kRowsPerPass; ++j) {
-    if (!on[j]) continue;
-    const int ly = (int)(threadIdx.x / kTileW) * kBand + j;
-    const int l = ly * kTileW + lx;
-    // the tile's neighbours before this pixel in raster order (8-connectivity;
-    // the left one is in its run already). Above: one union per horizontal
-    // run of the row above that touches the pixel and not the pixel before
-    // it in its own run (those are joined through that pixel already), so
-    // a run's first pixel takes the first pixel of each run among its three
-    // upper neighbours, every later pixel only a run starting up-right.
-    if (ly > 0) {
-      const int u = l - kTileW;
-      const bool ul = lx > 0 && lp[u - 1] >= 0, uc = lp[u] >= 0, ur = lx + 1 < kTileW && lp[u + 1] >= 0;
-      if (first[j]) {
-        if (ul) lds_union(lp, l, u - 1);
-        if (uc && !ul) lds_union(lp, l, u);
-      }
-      if (ur && !uc) lds_union(lp, l, u + 1);
-    }
-  }
-  __syncthreads();
-  // every pixel of the tile gets its parent (-1 off the boundary map), so no
-  // separate pass initialises the forest
-#pragma unroll
-  for (int j = 0; j < kTileH / kRowsPerPass; ++j) {
-    const int ly = (int)(threadIdx.x / kTileW) * kBand + j;
-    if (x0 + lx >= W || y0 + ly >= H) continue;
-    int32_t gp = -1;
-    if (on[j]) {
-      const int32_t r = lds_find(lp, ly * kTileW + lx);
-      gp = (y0 + r / kTileW) * W + x0 + (r % kTileW);
-      atomicAdd(&lsz[r], 1);
-    }
-    parent[(int64_t)(y0 + ly) * W + x0 + lx] = gp;
-  }
-  __syncthreads();
-  // each tile root's local component size, at the root (0 everywhere else)
-#pragma unroll
-  for (int j = 0; j < kTileH / kRowsPerPass; ++j) {
-    const int ly = (int)(threadIdx.x / kTileW) * kBand + j;
-    const int l = ly * kTileW + lx;
-    if (x0 + lx < W && y0 + ly < H) size[(int64_t)(y0 + ly) * W + x0 + lx] = on[j] ? lsz[l] : 0;
-  }
-}
-
-// Neighbour pairs across tile edges: thread t of a tile's block takes edge
-// pixel t (its top row, then its left and right columns below the top row).
-// Along the top row the rule of k_cc_tile applies: the row's runs are joined
-// inside the tile already and so are the runs of the row above (inside its
-// tiles, or by the left-column unions of the tile holding their right part),
-// so a run's first pixel takes up-left, and up when up-left is off, and every
-// pixel takes up-right only when up is off.
-__device__ __forceinline__ bool map_bit(const unsigned long long* B, int32_t wpr, int x, int y) {
-  return (B[(int64_t)y * wpr + (x >> 6)] >> (x & 63)) & 1ull;
-}
-
-__global__ __launch_bounds__(128) void k_cc_edges(const unsigned long long* __restrict__ B, int32_t wpr, int32_t W,
-                                                  int32_t H, int32_t* parent) {
-  const int x0 = blockIdx.x * kTileW, y0 = blockIdx.y * kTileH;
-  const int t = threadIdx.x;
-  int lx = 0, ly = 0;
-  if (t < kTileW) { lx = t; ly = 0; }
-  else if (t < kTileW + kTileH - 1) { lx = 0; ly = t - kTileW + 1; }
-  else if (t < kTileW + 2 * (kTileH - 1)) { lx = kTileW - 1; ly = t - kTileW - kTileH + 2; }
-  const int x = x0 + lx, y = y0 + ly;
-  const bool in = t < kTileW + 2 * (kTileH - 1) && x < W && y < H;
-  const int32_t i = y * W + x;
-  const bool on = in && map_bit(B, wpr, x, y);
-  bool first = true;
-  if (t < kTileW) {   // wavefront 0 holds the top row (kTileW == 64)
-    const uint64_t row = __builtin_amdgcn_ballot_w64(on);
-    first = lx == 0 || ((row >> (lx - 1)) & 1ull) == 0;
-  }
-  if (!on) return;
-  // raster-earlier neighbours that lie in another tile
-  if (x > 0 && lx == 0 && map_bit(B, wpr, x - 1, y)) uf_union(parent, i, i - 1);
-  if (y > 0) {
-    const int32_t u = i - W;
-    if (ly == 0) {
-      const bool ul = x > 0 && map_bit(B, wpr, x - 1, y - 1), uc = map_bit(B, wpr, x, y - 1),
-                 ur = x + 1 < W && map_bit(B, wpr, x + 1, y - 1);
-      if (first) {
-        if (ul) uf_union(parent, i, u - 1);
-        if (uc && !ul) uf_union(parent, i, u);
-      }
-      if (ur && !uc) uf_union(parent, i, u + 1);
-    } else {
-      if (lx == 0 && x > 0 && map_bit(B, wpr, x - 1, y - 1)) uf_union(parent, i, u - 1);
-      if (lx == kTileW - 1 && x + 1 < W && map_bit(B, wpr, x + 1, y - 1)) uf_union(parent, i, u + 1);
-    }
-  }
-}
-
-// Roots for every pixel (plain loads: the forest is final), and component
-// sizes at the roots: k_cc_tile left each tile root's local size at the tile
-// root; a tile root that is not its component's root moves its count to the
-// root with one atomic. Roots of components are always tile roots (a
-// component's smallest index is the smallest of its tile part), so no count
-// moves into a tile root that moves its own count away.
-__global__ __launch_bounds__(kBlock) void k_cc_flatten(int64_t N, int32_t* parent, int32_t* size) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += stride) {
-    if (parent[i] < 0) continue;
-    // No link changes after the merge kernels except pixels being pointed at
-    // their root here, so any value read (cached, possibly stale) is an
-    // ancestor of i and the walk ends at i's root.
-    const int32_t t = parent[i];   // its tile root (or, for tile-edge pixels, an ancestor of it)
-    int32_t r = t;
-    for (int32_t q = parent[r]; q != r; q = parent[r]) r = q;
-    parent[i] = r;
-    if (t != r) parent[t] = r;     // shortcut: the tile's other pixels reach r in two steps
-    if (r != (int32_t)i) {
-      const int32_t sz = size[i];
-      if (sz > 0) {
-        size[i] = 0;
-        atomicAdd(&size[r], sz);
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Maps held as bits: word y * wpr + (x >> 6), bit x & 63, the words of a row
 // ending with it. Words in order are pixels in raster order.
 struct Bits {
@@ -774,21 +559,265 @@ __device__ __forceinline__ WaveWords wave_words(const Bits& b, const unsigned lo
   }
   return r;
 }
-// a[i] at the lanes that start a horizontal run of word j, `none` elsewhere.
-__device__ __forceinline__ void at_run_starts(const WaveWords& w, const int32_t* a, int32_t none, int32_t (&v)[kWaveWords]) {
-  const int lane = threadIdx.x & 63;
+// a[node] at the lanes that start a horizontal run of word j (word w0 + j of
+// the map), `none` elsewhere. Node 32 w + k is the k-th run of word w.
+__device__ __forceinline__ int node_of(int64_t wi, unsigned long long starts) {
+  return (int)(32 * wi) + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)starts, 0u));
+}
+__device__ __forceinline__ void at_run_starts(const WaveWords& w, int64_t w0, const int32_t* a, int32_t none,
+                                              int32_t (&v)[kWaveWords]) {
 #pragma unroll
   for (int j = 0; j < kWaveWords; ++j) {
     v[j] = none;
-    const unsigned long long m = w.word(j);
+    const unsigned long long m = w.word(j), st = m & ~(m << 1);
     if (!m) continue;
-    if (__builtin_amdgcn_inverse_ballot_w64(m & ~(m << 1))) v[j] = a[w.first(j) + lane];
+    if (__builtin_amdgcn_inverse_ballot_w64(st)) v[j] = a[node_of(w0 + j, st)];
+  }
+}
+// The same for the runs of `kept`, a map of some of the runs of `w` (whose
+// numbers in their words are those in `w`).
+__device__ __forceinline__ void at_kept_runs(const WaveWords& kept, const WaveWords& w, int64_t w0, const int32_t* a,
+                                             int32_t (&v)[kWaveWords]) {
+#pragma unroll
+  for (int j = 0; j < kWaveWords; ++j) {
+    v[j] = 0;
+    const unsigned long long k = kept.word(j);
+    if (!k) continue;
+    const unsigned long long m = w.word(j);
+    if (__builtin_amdgcn_inverse_ballot_w64(k & ~(k << 1))) v[j] = a[node_of(w0 + j, m & ~(m << 1))];
   }
 }
 // The bits of the horizontal run of w that starts at bit a.
 __device__ __forceinline__ unsigned long long run_from(unsigned long long w, int a) {
   const unsigned long long m = 1ull << a;
   return w & ~(w + m) & ~(m - 1ull);   // adding the start bit clears exactly its run
+}
+
+// Pixel (x, y) of a map.
+__device__ __forceinline__ bool map_bit(const unsigned long long* map, int32_t wpr, int x, int y) {
+  return (map[(int64_t)y * wpr + (x >> 6)] >> (x & 63)) & 1ull;
+}
+
+// ---------------------------------------------------------------------------
+// Connected components by union-find over horizontal runs: a node is a run of
+// one word of the map, node 32 w + k the k-th run of word w (a word holds at
+// most 32), so nodes are in raster order, and parents and sizes lie side by
+// side for a word's few runs. A link always points a larger root at a smaller
+// one, so a component's root ends as its first run. Two levels: k_cc_tile
+// joins the runs of a tile of one word x kTileH rows in LDS and writes each
+// run's tile root and the tile roots' sizes (0 elsewhere), k_cc_edges joins
+// tiles through the global forest, k_cc_flatten points every tile root at its
+// root and moves its size there. Against one node per pixel: 88 -> 56 us at
+// 4096x2304, 46 -> 29 us at 640x480.
+constexpr int kTileH = 32;
+
+// The k-th run's number in a word: the run starts at or below bit a, less one.
+__device__ __forceinline__ int run_at(unsigned long long w, int a) {
+  return __builtin_popcountll((w & ~(w << 1)) & (a == 63 ? ~0ull : (2ull << a) - 1ull)) - 1;
+}
+__device__ __forceinline__ int32_t lds_find(int32_t* lp, int32_t a) {
+  for (;;) {
+    const int32_t p = lp[a];
+    if (p == a) return a;
+    const int32_t pp = lp[p];
+    if (pp == p) return p;
+    atomicMin(&lp[a], pp);   // halve the path: a link only ever moves towards smaller nodes
+    a = pp;
+  }
+}
+__device__ __forceinline__ void lds_union(int32_t* lp, int32_t a, int32_t b) {
+  for (;;) {
+    a = lds_find(lp, a);
+    b = lds_find(lp, b);
+    if (a == b) return;
+    if (a < b) { const int32_t t = a; a = b; b = t; }
+    // a > b, a was a root when found: make it point at b unless it moved meanwhile
+    const int32_t old = atomicMin(&lp[a], b);
+    if (old == a) return;
+    a = old;   // a was linked elsewhere concurrently: continue from there
+  }
+}
+// The same in memory, both sides climbing together (two loads in flight).
+__device__ __forceinline__ void uf_union(int32_t* parent, int32_t a, int32_t b) {
+  auto load = [&](int32_t i) { return __hip_atomic_load(&parent[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  for (;;) {
+    const int32_t pa = load(a), pb = load(b);
+    if (pa == pb) return;
+    const int32_t ga = load(pa), gb = load(pb);
+    if (ga == gb) return;
+    if (ga == pa && gb == pb) {   // two roots
+      const int32_t hi = max(pa, pb), lo = min(pa, pb);
+      const int32_t old = atomicMin(&parent[hi], lo);
+      if (old == hi) return;
+      a = old;   // it was linked elsewhere concurrently: continue from there
+      b = lo;
+      continue;
+    }
+    if (ga != pa) atomicMin(&parent[a], ga);   // halve the paths
+    if (gb != pb) atomicMin(&parent[b], gb);
+    a = ga;
+    b = gb;
+  }
+}
+
+// f(k, n) for every pair of a run of w (its k-th) and a run of the word u of
+// the row above (its n-th) that touch (8-connected, within the word), each at
+// the lane of the run of w's first pixel that touches it, so that the pairs
+// go side by side (a run start that took its run's pairs in turn: tiles 36 us,
+// edges 11 us at 4096x2304, 34 and 10 us so). w and u are the same in every
+// lane.
+template <typename F>
+__device__ __forceinline__ void for_touching(unsigned long long w, unsigned long long u, F f) {
+  const unsigned long long ws = w & ~(w << 1), us = u & ~(u << 1);   // run starts
+  const int kb = node_of(0, ws), nb = node_of(0, us);                // of them below this lane
+  const unsigned long long left = ws & u << 1;                       // run starts with the pixel up-left set ...
+  const unsigned long long up = ws & u & ~(u << 1);                  // ... or not, but the one above
+  const unsigned long long right = w & u >> 1 & ~u;                  // pixels with a run starting up-right
+  if (left | up) {
+    if (__builtin_amdgcn_inverse_ballot_w64(left | up)) f(kb, __builtin_amdgcn_inverse_ballot_w64(left) ? nb - 1 : nb);
+  }
+  if (right) {
+    if (__builtin_amdgcn_inverse_ballot_w64(right)) f(kb + (__builtin_amdgcn_inverse_ballot_w64(ws) ? 0 : -1), nb);
+  }
+}
+
+// One block per tile; wavefront w takes a band of rows, one per step, lane =
+// pixel, acting where runs touch. Bound by the chain of LDS round trips of the
+// unions, one row after another (bands of 8 rows instead of 4: 17 us at
+// 640x480 against 12).
+constexpr int kCcBlock = 512, kBandH = kTileH / (kCcBlock / 64);
+__global__ __launch_bounds__(kCcBlock) void k_cc_tile(Bits b, const unsigned long long* __restrict__ B,
+                                                    int32_t* __restrict__ parent, int32_t* __restrict__ size) {
+  __shared__ int32_t lp[kTileH * 32], lsz[kTileH * 32];
+  __shared__ unsigned long long last[kCcBlock / 64];   // each band's last row
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int c = blockIdx.x, y0 = blockIdx.y * kTileH + wv * kBandH, ly0 = wv * kBandH;
+  const unsigned long long mine = lane < kBandH && y0 + lane < b.H ? B[(int64_t)(y0 + lane) * b.wpr + c] : 0ull;
+  unsigned long long w[kBandH];
+#pragma unroll
+  for (int j = 0; j < kBandH; ++j) {
+    w[j] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, j) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), j) << 32;
+    const unsigned long long st = w[j] & ~(w[j] << 1);
+    if (__builtin_amdgcn_inverse_ballot_w64(st)) {
+      const int n = (ly0 + j) * 32 + node_of(0, st);
+      lp[n] = n;
+      lsz[n] = 0;
+    }
+  }
+  if (lane == 0) last[wv] = w[kBandH - 1];
+  __syncthreads();
+  unsigned long long above = wv > 0 ? last[wv - 1] : 0ull;
+  above = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)above) |
+          (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(above >> 32)) << 32;
+#pragma unroll
+  for (int j = 0; j < kBandH; ++j) {
+    const unsigned long long u = j > 0 ? w[j > 0 ? j - 1 : 0] : above;
+    if (!((w[j] | w[j] << 1 | w[j] >> 1) & u)) continue;
+    const int row = (ly0 + j) * 32;
+    for_touching(w[j], u, [&](int k, int n) { lds_union(lp, row + k, row - 32 + n); });
+  }
+  __syncthreads();
+  int32_t root[kBandH];
+#pragma unroll
+  for (int j = 0; j < kBandH; ++j) {
+    const unsigned long long st = w[j] & ~(w[j] << 1);
+    root[j] = 0;
+    if (!st) continue;
+    if (__builtin_amdgcn_inverse_ballot_w64(st)) {
+      root[j] = lds_find(lp, (ly0 + j) * 32 + node_of(0, st));
+      atomicAdd(&lsz[root[j]], __builtin_popcountll(run_from(w[j], lane)));
+    }
+  }
+  __syncthreads();
+  const int64_t w0 = (int64_t)blockIdx.y * kTileH * b.wpr + c;   // the tile's first word
+#pragma unroll
+  for (int j = 0; j < kBandH; ++j) {
+    const unsigned long long st = w[j] & ~(w[j] << 1);
+    if (!st) continue;
+    if (__builtin_amdgcn_inverse_ballot_w64(st)) {
+      const int k = node_of(0, st), n = (ly0 + j) * 32 + k;
+      const int64_t g = (w0 + (int64_t)(ly0 + j) * b.wpr) * 32 + k;
+      const int r = root[j];
+      parent[g] = (int32_t)((w0 + (int64_t)(r >> 5) * b.wpr) * 32 + (r & 31));
+      size[g] = r == n ? lsz[n] : 0;
+    }
+  }
+}
+
+// Runs that touch across tile edges. The first `vblocks` blocks take the
+// edges between word columns, a thread per row and edge (of the three pairs
+// across it in two rows those that no other pair implies); the others the
+// edges between tile rows, a wavefront per word, lane = pixel.
+__global__ __launch_bounds__(kBlock) void k_cc_edges(Bits b, const unsigned long long* __restrict__ B, int32_t* parent,
+                                                     int vblocks) {
+  if ((int)blockIdx.x < vblocks) {
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int e = b.wpr - 1;   // edges per row
+    if (t >= (int64_t)b.H * e) return;
+    const int y = (int)((uint32_t)t / (uint32_t)e), c = (int)((uint32_t)t % (uint32_t)e);
+    const int64_t wl = (int64_t)y * b.wpr + c, wr = wl + 1;
+    const unsigned long long L = B[wl], R = B[wr];
+    const unsigned long long Lu = y > 0 ? B[wl - b.wpr] : 0ull, Ru = y > 0 ? B[wr - b.wpr] : 0ull;
+    const bool l = L >> 63, r = R & 1ull, lu = Lu >> 63, ru = Ru & 1ull;
+    if (l && r && !(lu && ru)) uf_union(parent, (int32_t)(32 * wl + run_at(L, 63)), (int32_t)(32 * wr));
+    if (l && ru && !lu && !r) uf_union(parent, (int32_t)(32 * wl + run_at(L, 63)), (int32_t)(32 * (wr - b.wpr)));
+    if (lu && r && !l && !ru) uf_union(parent, (int32_t)(32 * (wl - b.wpr) + run_at(Lu, 63)), (int32_t)(32 * wr));
+    return;
+  }
+  const int64_t t = (int64_t)(blockIdx.x - vblocks) * (kBlock / 64) + (threadIdx.x >> 6);
+  const int y = (int)(t / b.wpr + 1) * kTileH, c = (int)(t % b.wpr);
+  if (y >= b.H) return;
+  const int64_t wi = (int64_t)y * b.wpr + c;
+  auto uniform = [](unsigned long long v) {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v) |
+           (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
+  };
+  const unsigned long long w = uniform(B[wi]), u = uniform(B[wi - b.wpr]);
+  for_touching(w, u, [&](int k, int n) { uf_union(parent, (int32_t)(32 * wi + k), (int32_t)(32 * (wi - b.wpr) + n)); });
+}
+
+// Every tile root's root, and the component sizes there: k_cc_tile left each
+// tile root's size at the tile root; one that is not its component's root
+// moves its count with one atomic. Roots of components are tile roots (a
+// component's first run is the first of its tile part), so no count moves
+// into a tile root that moves its own away. A walk writes each ancestor it
+// meets back as its start's parent, so that the walks of a long chain shorten
+// each other (its length halves with every step); no link changes otherwise,
+// so any value read (cached, possibly stale) is an ancestor, and a walk ends
+// at the root. The other runs keep their tile root as parent.
+__global__ __launch_bounds__(kBlock) void k_cc_flatten(Bits b, const unsigned long long* __restrict__ B, int32_t* parent,
+                                                       int32_t* size) {
+  // the block's tile roots are queued first, so that their walks go together
+  __shared__ int2 queue[kSelWords * 32];   // node, size
+  __shared__ uint32_t queued;
+  for (int64_t b0 = (int64_t)blockIdx.x * kSelWords; b0 < b.words; b0 += (int64_t)gridDim.x * kSelWords) {
+    if (threadIdx.x == 0) queued = 0u;
+    __syncthreads();
+    const int64_t w0 = b0 + kWaveWords * (threadIdx.x >> 6);
+    const WaveWords w = wave_words(b, B, w0, b.words);
+    int32_t sz[kWaveWords];
+    at_run_starts(w, w0, size, 0, sz);
+#pragma unroll
+    for (int j = 0; j < kWaveWords; ++j) {
+      if (sz[j] <= 0) continue;
+      const unsigned long long m = w.word(j);
+      queue[atomicAdd(&queued, 1u)] = int2{node_of(w0 + j, m & ~(m << 1)), sz[j]};
+    }
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < queued; k += kBlock) {
+      const int32_t n = queue[k].x, t = parent[n];
+      if (t == n) continue;
+      int32_t r = t;
+      for (int32_t q = parent[r]; q != r; q = parent[r]) {
+        parent[n] = q;
+        r = q;
+      }
+      size[n] = 0;
+      atomicAdd(&size[r], queue[k].y);
+    }
+    __syncthreads();   // the queue is refilled
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -824,7 +853,7 @@ __global__ __launch_bounds__(kBlock) void k_drop_count(Bits b, const unsigned lo
   for (int64_t w0 = kWaveWords * ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)); w0 < b.words; w0 += kWaveWords * nw) {
     const WaveWords w = wave_words(b, B, w0, b.words);
     int32_t s[kWaveWords];
-    at_run_starts(w, size, 0, s);
+    at_run_starts(w, w0, size, 0, s);
     mine += (unsigned long long)__builtin_popcountll(w.v);
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j) {
@@ -937,7 +966,7 @@ __global__ __launch_bounds__(kBlock) void k_root_count(Bits b, const unsigned lo
     const int64_t w_end = min((int64_t)(blockIdx.x + 1) * b.per, b.words);
     for (int64_t w0 = (int64_t)blockIdx.x * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
       int32_t s[kWaveWords];
-      at_run_starts(wave_words(b, B, w0, w_end), size, 0, s);
+      at_run_starts(wave_words(b, B, w0, w_end), w0, size, 0, s);
 #pragma unroll
       for (int j = 0; j < kWaveWords; ++j)
         mine += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(s[j] == s_star));   // s* >= 1
@@ -982,14 +1011,15 @@ __global__ __launch_bounds__(1024) void k_root_find(Bits b, const unsigned long 
   for (int64_t w0 = (int64_t)blk_s * b.per; w0 < w_end; w0 += kWaveWords) {
     const WaveWords w = wave_words(b, B, w0, w_end);
     int32_t s[kWaveWords];
-    at_run_starts(w, size, 0, s);
+    at_run_starts(w, w0, size, 0, s);
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j) {
+      const unsigned long long m = w.word(j), starts = m & ~(m << 1);
       const unsigned long long hm = __builtin_amdgcn_ballot_w64(s[j] == s_star);
       const uint32_t c = (uint32_t)__builtin_popcountll(hm);
       if (left < c) {
         if (s[j] == s_star && (uint32_t)__builtin_popcountll(hm & ((1ull << lane) - 1ull)) == left)
-          rule->first = w.first(j) + lane;
+          rule->first = node_of(w0 + j, starts);
         return;
       }
       left -= c;
@@ -1023,7 +1053,10 @@ __global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long lon
   for (int64_t w0 = (int64_t)blockIdx.x * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
     const WaveWords w = wave_words(b, B, w0, w_end);
     int32_t r[kWaveWords], s[kWaveWords];
-    at_run_starts(w, parent, -1, r);
+    at_run_starts(w, w0, parent, -1, r);
+#pragma unroll
+    for (int j = 0; j < kWaveWords; ++j)
+      if (r[j] >= 0) r[j] = parent[r[j]];   // from the tile root to the root
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j) {
       s[j] = 0;
@@ -1038,8 +1071,8 @@ __global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long lon
       const unsigned long long k = m & ~(m + __builtin_amdgcn_ballot_w64(ok));
       if (lane == j) kv = k;
       if (n1) {
-        const int32_t i = w.first(j) + lane;
-        if (r[j] >= 0 && r[j] != i) size[i] = s[j];
+        const int32_t n = node_of(w0 + j, m & ~(m << 1));
+        if (r[j] >= 0 && r[j] != n) size[n] = s[j];
       }
     }
     if (lane < kWaveWords && w0 + lane < w_end) {
@@ -1180,7 +1213,8 @@ __device__ __forceinline__ RadixSel sel_pick(RadixSel r, const uint32_t* hist, i
 }
 
 // Mode 1, one counting pass over the kept pixels' keys ~size.
-__device__ __forceinline__ void size_pass(const Bits& b, const unsigned long long* kept, const int32_t* size, RadixSel rs, const uint32_t* prev_hist, int prev_shift,
+__device__ __forceinline__ void size_pass(const Bits& b, const unsigned long long* B, const unsigned long long* kept,
+                                          const int32_t* size, RadixSel rs, const uint32_t* prev_hist, int prev_shift,
                                           RadixSel* state, int shift, uint32_t* hist, uint32_t* bins) {
   if (prev_hist) rs = sel_pick(rs, prev_hist, prev_shift, state);
   for (int k = threadIdx.x; k < kBins; k += kBlock) bins[k] = 0u;
@@ -1189,9 +1223,9 @@ __device__ __forceinline__ void size_pass(const Bits& b, const unsigned long lon
   const int hi = shift + kDigit;
   const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
   for (int64_t w0 = kWaveWords * ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)); w0 < b.words; w0 += kWaveWords * nw) {
-    const WaveWords w = wave_words(b, kept, w0, b.words);   // whole runs of the boundary map
+    const WaveWords w = wave_words(b, kept, w0, b.words);
     int32_t s[kWaveWords];
-    at_run_starts(w, size, 0, s);
+    at_kept_runs(w, wave_words(b, B, w0, b.words), w0, size, s);
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j) {
       const unsigned long long m = w.word(j);
@@ -1543,7 +1577,8 @@ __device__ __forceinline__ unsigned long long ring_threshold(const RingBin* rb, 
 }
 
 // The selected pixels as a map, and their number per block of b.per words.
-__global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const unsigned long long* __restrict__ kept,
+__global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const unsigned long long* __restrict__ B,
+                                                      const unsigned long long* __restrict__ kept,
                                                       const unsigned long long* __restrict__ base,
                                                       const int32_t* __restrict__ size, const RadixSel* s1, const uint32_t* __restrict__ s1_hist,
                                                       const uint32_t* __restrict__ ties,
@@ -1595,9 +1630,10 @@ __global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const un
     const uint32_t s_star = ~(uint32_t)rs.prefix;
     long long quota = rs.need - rs.below - (long long)counts_before(ties, wtot);
     for (int64_t w0 = w_begin; w0 < w_end; w0 += kSelWords) {
-      const WaveWords w = wave_words(b, kept, w0 + kWaveWords * wv, w_end);
+      const int64_t wf = w0 + kWaveWords * wv;
+      const WaveWords w = wave_words(b, kept, wf, w_end);
       int32_t s[kWaveWords];
-      at_run_starts(w, size, 0, s);
+      at_kept_runs(w, wave_words(b, B, wf, w_end), wf, size, s);
       unsigned long long tv = 0ull, ov = 0ull;   // lane j: word j's ties, and its pixels of larger components
 #pragma unroll
       for (int j = 0; j < kWaveWords; ++j) {
@@ -1633,7 +1669,7 @@ __global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const un
 }
 
 // Mode 1: pixels of size s* per block of b.per words, for their ranks.
-__device__ __forceinline__ void tie_pass(const Bits& b, const unsigned long long* kept, const int32_t* size,
+__device__ __forceinline__ void tie_pass(const Bits& b, const unsigned long long* B, const unsigned long long* kept, const int32_t* size,
                                          uint32_t s_star, int64_t block, uint32_t* ties, uint32_t* part) {
   if (threadIdx.x == 0) *part = 0u;
   __syncthreads();
@@ -1643,7 +1679,7 @@ __device__ __forceinline__ void tie_pass(const Bits& b, const unsigned long long
   for (int64_t w0 = block * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
     const WaveWords w = wave_words(b, kept, w0, w_end);
     int32_t s[kWaveWords];
-    at_run_starts(w, size, 0, s);
+    at_kept_runs(w, wave_words(b, B, w0, w_end), w0, size, s);
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j)
       if (s[j] > 0 && (uint32_t)s[j] == s_star) mine += (uint32_t)__builtin_popcountll(run_from(w.word(j), lane) & ~w.border_of(j));
@@ -1907,19 +1943,21 @@ __global__ __launch_bounds__(kBlock) void k_dist_pass(Bits b, FcArgs a, const in
 // (only one of them does anything): the counting passes of mode 1, and the
 // distance passes of mode 2 beyond kLevels.
 // First: sizes, top digit | columns with base pixels per segment.
-__global__ __launch_bounds__(kBlock) void k_fc_first(Bits b, FcArgs a, const unsigned long long* kept,
+__global__ __launch_bounds__(kBlock) void k_fc_first(Bits b, FcArgs a, const unsigned long long* B,
+    const unsigned long long* kept,
                                                      const unsigned long long* base, const int32_t* size,
                                                      unsigned long long prefix, int shift,
                                                      uint32_t* hist, const uint32_t* lcount, int nseg,
                                                      unsigned long long* segor) {
   __shared__ uint32_t bins[kBins];
   const FcPlan pl = fc_plan(a);
-  if (pl.mode == 1) size_pass(b, kept, size, RadixSel{prefix, pl.need, 0}, nullptr, 0, nullptr, shift, hist, bins);
+  if (pl.mode == 1) size_pass(b, B, kept, size, RadixSel{prefix, pl.need, 0}, nullptr, 0, nullptr, shift, hist, bins);
   else if (pl.mode == 2 && level_pick(lcount, pl.need).level == 0) far_segments(b, base, nseg, segor);
 }
 // Second: sizes, a lower digit | column distances, and the flag that the
 // launches after it go by.
-__global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const unsigned long long* kept,
+__global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const unsigned long long* B,
+    const unsigned long long* kept,
                                                       const unsigned long long* base, const int32_t* size, const RadixSel* in, unsigned long long prefix,
                                                       const uint32_t* prev_hist, int prev_shift, RadixSel* state, int shift,
                                                       uint32_t* hist, const uint32_t* lcount, int nseg,
@@ -1927,7 +1965,7 @@ __global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const un
   __shared__ uint32_t bins[kBins];
   const FcPlan pl = fc_plan(a);
   if (pl.mode == 1) {
-    size_pass(b, kept, size, in ? *in : RadixSel{prefix, pl.need, 0}, prev_hist, prev_shift, state, shift, hist,
+    size_pass(b, B, kept, size, in ? *in : RadixSel{prefix, pl.need, 0}, prev_hist, prev_shift, state, shift, hist,
               bins);
   } else if (g && pl.mode == 2 && level_pick(lcount, pl.need).level == 0) {
     far_columns(b, base, nseg, segor, g);
@@ -1935,7 +1973,8 @@ __global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const un
   }
 }
 // Last: pixels of the wanted size per block | levels 1 and 2 from the distances.
-__global__ __launch_bounds__(kBlock) void k_fc_last(Bits b, FcArgs a, int nb, const unsigned long long* kept,
+__global__ __launch_bounds__(kBlock) void k_fc_last(Bits b, FcArgs a, int nb, const unsigned long long* B,
+    const unsigned long long* kept,
                                                     const unsigned long long* base, const int32_t* size, const RadixSel* s1, const uint32_t* s1_hist,
                                                     uint32_t* ties, const int32_t* far, const int32_t* dist,
                                                     const RadixSel* sd, const uint32_t* sd_hist,
@@ -1945,7 +1984,7 @@ __global__ __launch_bounds__(kBlock) void k_fc_last(Bits b, FcArgs a, int nb, co
   if (pl.mode == 1) {
     const RadixSel rs = sel_pick(*s1, s1_hist, 0, nullptr);
     for (int64_t block = blockIdx.x; block < nb; block += gridDim.x)
-      tie_pass(b, kept, size, ~(uint32_t)rs.prefix, block, ties, &part);
+      tie_pass(b, B, kept, size, ~(uint32_t)rs.prefix, block, ties, &part);
     return;
   }
   if (!*far) return;
@@ -2001,8 +2040,8 @@ Layout layout(int32_t W, int32_t H) {
   o.L8 = take(N);
   for (size_t* m : {&o.B, &o.kept, &o.base, &o.sel}) *m = take((size_t)b.words * 8);
   o.planes = take((size_t)b.words * 8 * kLevelBits);
-  o.parent = take((size_t)N * 4);
-  o.size = take((size_t)N * 4);
+  o.parent = take((size_t)b.words * 32 * 4);   // one entry per node
+  o.size = take((size_t)b.words * 32 * 4);
   o.g = take((size_t)N * 4);
   o.dist = take((size_t)N * 4);
   o.segor = take((size_t)((H + kSegRows - 1) / kSegRows) * b.wpr * 8);
@@ -2170,14 +2209,16 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     hipLaunchKernelGGL(k_refine<1>, rf_grid(kRfRows<1>), dim3(64), 0, s, lum, W, H, K, lut, B, wpr, (uint8_t*)nullptr, words);
     if (out_labels) hipLaunchKernelGGL(k_label, dim3(g), dim3(kBlock), 0, s, lum, N, lut, out_labels);
   }
-  const dim3 gt((W + kTileW - 1) / kTileW, (H + kTileH - 1) / kTileH);
-  hipLaunchKernelGGL(k_cc_tile, gt, dim3(kBlock), 0, s, B, wpr, W, H, parent, size);
-  hipLaunchKernelGGL(k_cc_edges, gt, dim3(128), 0, s, B, wpr, W, H, parent);
-  hipLaunchKernelGGL(k_cc_flatten, dim3(g), dim3(kBlock), 0, s, N, parent, size);
+  const int nty = (H + kTileH - 1) / kTileH;
+  // passes over words, kSelWords per block and step
+  const int gw = (int)std::min<int64_t>((bt.words + kSelWords - 1) / kSelWords, 2048);
+  hipLaunchKernelGGL(k_cc_tile, dim3(wpr, nty), dim3(kCcBlock), 0, s, bt, B, parent, size);
+  const int64_t vb = ((int64_t)H * (wpr - 1) + kBlock - 1) / kBlock;
+  const int64_t hb = ((int64_t)(nty - 1) * wpr + kBlock / 64 - 1) / (kBlock / 64);
+  if (vb + hb > 0) hipLaunchKernelGGL(k_cc_edges, dim3((unsigned)(vb + hb)), dim3(kBlock), 0, s, bt, B, parent, (int)vb);
+  hipLaunchKernelGGL(k_cc_flatten, dim3(gw), dim3(kBlock), 0, s, bt, B, parent, size);
 
   const int nb = (int)((bt.words + bt.per - 1) / bt.per);
-  // passes over words, kSelWords per block and step
-  const int gw = (int)std::min<int64_t>((bt.words + kSelWords - 1) / kSelWords, 1024);
   if (mode == 1) {
     // at most 512 blocks: each block's closing adds (its total and its small
     // sizes' counts) go to the same few global words, so fewer blocks wait less
@@ -2206,8 +2247,10 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     int32_t* dist = (int32_t*)(base + Lo.dist);
     unsigned long long* segor = (unsigned long long*)(base + Lo.segor);
     const int nseg = (H + kSegRows - 1) / kSegRows;
-    hipLaunchKernelGGL(k_kept, dim3(nb), dim3(kBlock), 0, s, bt, B, parent, size, dr, (int64_t)min_cc, kept, bmap,
-                       out_refined, (uint32_t*)nullptr, n1);
+    Bits bk = bt;   // (no counts per block here: one batch of words each)
+    bk.per = kSelWords;
+    hipLaunchKernelGGL(k_kept, dim3((unsigned)((bt.words + kSelWords - 1) / kSelWords)), dim3(kBlock), 0, s, bk, B, parent,
+                       size, dr, (int64_t)min_cc, kept, bmap, out_refined, (uint32_t*)nullptr, n1);
     const dim3 gl((wpr + 2 * (kBlock / 64) - 1) / (2 * (kBlock / 64)), (H + kLvRows - 1) / kLvRows);
     hipLaunchKernelGGL(k_fc_levels<0>, gl, dim3(kBlock), 0, s, bt, fa, bmap, planes, sel, lcount);
     hipLaunchKernelGGL(k_fc_levels<1>, gl, dim3(kBlock), 0, s, bt, fa, sel, planes, (unsigned long long*)nullptr, lcount);
@@ -2217,12 +2260,12 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     const unsigned long long prefix = small ? 0xFF000000ull : 0ull;
     const int gs = std::min(gw, 512);   // (each block ends with up to kBins global adds)
     int sh = small ? kDigit : 2 * kDigit, np = 0;
-    hipLaunchKernelGGL(k_fc_first, dim3(gs), dim3(kBlock), 0, s, bt, fa, kept, bmap, size, prefix, sh, shist, lcount,
+    hipLaunchKernelGGL(k_fc_first, dim3(gs), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size, prefix, sh, shist, lcount,
                        nseg, segor);
     for (++np; sh > 0; ++np) {
       const int prev = sh;
       sh -= kDigit;
-      hipLaunchKernelGGL(k_fc_second, dim3(np == 1 ? gw : gs), dim3(kBlock), 0, s, bt, fa, kept, bmap, size,
+      hipLaunchKernelGGL(k_fc_second, dim3(np == 1 ? gw : gs), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size,
                          np == 1 ? (const RadixSel*)nullptr : s1 + np - 2, prefix, shist + (np - 1) * kBins, prev,
                          s1 + np - 1, sh, shist + np * kBins, lcount, nseg, segor, np == 1 ? gcol : (int32_t*)nullptr, far);
     }
@@ -2247,7 +2290,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
         dsh -= kDigit;
       }
     }
-    hipLaunchKernelGGL(k_fc_last, dim3(std::min(gw, 1024)), dim3(kBlock), 0, s, bt, fa, nb, kept, bmap, size, s1_last,
+    hipLaunchKernelGGL(k_fc_last, dim3(std::min(gw, 1024)), dim3(kBlock), 0, s, bt, fa, nb, B, kept, bmap, size, s1_last,
                        s1_hist, ties, far, dist, sd_last, sd_hist, planes, far_need);
     // the hashes of one bin's ring pixels are listed in the place of the column
     // and pixel distances (8 bytes per pixel between them)
@@ -2255,7 +2298,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     const int gr = (int)std::min<int64_t>((bt.words + kRingGroups * kRingWords - 1) / (kRingGroups * kRingWords), 1024);
     hipLaunchKernelGGL(k_ring_count, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist);
     hipLaunchKernelGGL(k_ring_bin, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist, rb, ring);
-    hipLaunchKernelGGL(k_fc_select, dim3(nb), dim3(kBlock), 0, s, bt, fa, kept, bmap, size, s1_last, s1_hist, ties,
+    hipLaunchKernelGGL(k_fc_select, dim3(nb), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size, s1_last, s1_hist, ties,
                        planes, lcount, far_need, rb, ring, sel, bsum);
   }
   hipLaunchKernelGGL(k_list, dim3(nb), dim3(kBlock), 0, s, bt, sel, bsum, out_idx, (long long*)out_count);
