@@ -1301,7 +1301,7 @@ struct LevelSel {
   int level;
   long long need;
 };
-__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need);
+__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need, int last = kLevels);
 
 // Planes 0 .. 3 of a map word lie side by side, plane 4 apart after them (it
 // is read for levels above 15 only). STAGE 0: levels 1 .. 15 of `from` (the
@@ -1315,7 +1315,7 @@ __global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, const un
   const FcPlan plan = fc_plan(a);
   if (plan.mode != 2) return;
   if constexpr (STAGE == 1)
-    if (level_pick(lcount, plan.need).level != 0) return;
+    if (level_pick(lcount, plan.need, kLvStage).level != 0) return;   // (other blocks may have added to the levels beyond)
   if (threadIdx.x < kLvStage) cnt[threadIdx.x] = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63;
@@ -1414,8 +1414,8 @@ __global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, const un
 }
 
 // Mode 2: the level of the want-th pixel and its rank within it, from the
-// level counts; level 0: it lies further away than those counted.
-__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need) {
+// counts of levels up to `last`; level 0: it lies further away than those.
+__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need, int last) {
   __shared__ unsigned long long sum[kLevels + 1];
   if (threadIdx.x <= kLevels) sum[threadIdx.x] = 0ull;
   __syncthreads();
@@ -1431,7 +1431,7 @@ __device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long
   if (s) atomicAdd(&sum[l], s);
   __syncthreads();
   LevelSel r{0, need};
-  for (int k = 1; k <= kLevels; ++k) {
+  for (int k = 1; k <= last; ++k) {
     const long long n = (long long)sum[k];
     if (r.need <= n) { r.level = k; break; }
     r.need -= n;

@@ -211,6 +211,15 @@ def test_fraction_control_levels(torch, sbs, W, H):
                 check_fraction(torch, sbs, img, 2, 0, 1, (inside + k) / (W * H), 77 + d, f"{W}x{H} distance {d} rank {k}")
 
 
+def test_fraction_control_levels_many_blocks(torch, sbs):
+    """A list that ends within the first level of the second dilation launch,
+    on an image whose blocks do not all run at once: those that start late
+    have the counts of the others before them."""
+    W, H = 64, 200000
+    img = np.full((H, W), 40, np.uint8)
+    check_fraction(torch, sbs, img, 1, 0, 1, (32 * H + H // 9) / (W * H), 7, f"{W}x{H}")
+
+
 @pytest.mark.parametrize("W,H", [(64, 33), (131, 70), (4200, 4096)])
 def test_fraction_control_component_sizes(torch, sbs, W, H):
     """Fractions that end among the kept pixels: within a component size that
