@@ -54,97 +54,184 @@ __device__ __forceinline__ double srgb_linear(int v) {
 // L8 as a function of Y is a non-decreasing step function, so a pixel's
 // value is the number of steps at or below its Y: t[v] (v = 1 .. 255) is the
 // smallest Y whose L8 is at least v (+inf if none). The table comes from the
-// host (light_steps below); the kernel then needs no cube root per pixel.
+// host (light_steps below).
 struct LightSteps {
   double t[256];
 };
 
-__global__ __launch_bounds__(kBlock) void k_light(const uint8_t* __restrict__ img, int32_t W, int32_t H, int32_t C,
-                                                  int64_t pitch, uint8_t* __restrict__ L8, LightSteps steps) {
-#pragma clang fp contract(off)
-  __shared__ double lin[256];
-  __shared__ double t[256];
-  if (C == 3) {
-    lin[threadIdx.x] = srgb_linear((int)threadIdx.x);
-    t[threadIdx.x] = steps.t[threadIdx.x];
-    __syncthreads();
+// A block's histogram: LDS adds into 16 copies of the bins (lane l uses copy
+// l % 16; copies are 257 words apart, so equal values in different copies
+// fall in different banks), then one global add per bin and block, into one
+// of kHistParts copies in turn: adds to the same 128 bytes are served one
+// after another, some 10 ns each, and would be most of a small image's time.
+constexpr int kHistCopies = 16, kHistParts = 16;
+struct BlockHist {
+  uint32_t h[kHistCopies][257];
+  __device__ __forceinline__ void clear() {
+    for (int i = threadIdx.x; i < kHistCopies * 257; i += kBlock) (&h[0][0])[i] = 0u;
   }
-  const int64_t N = (int64_t)W * H;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-    const int y = (int)((uint32_t)i / (uint32_t)W), x = (int)((uint32_t)i % (uint32_t)W);   // N < 2^31
-    const uint8_t* p = img + (int64_t)y * pitch + (int64_t)x * C;
-    if (C == 1) { L8[i] = p[0]; continue; }
-    const double Y = 0.2126 * lin[p[0]] + 0.7152 * lin[p[1]] + 0.0722 * lin[p[2]];
-    int v = 0;
+  __device__ __forceinline__ void add(uint32_t v) { atomicAdd(&h[threadIdx.x & (kHistCopies - 1)][v], 1u); }
+  __device__ __forceinline__ void store(uint32_t* hist) const {
+    uint32_t t = 0;
 #pragma unroll
-    for (int st = 128; st; st >>= 1)
-      if (Y >= t[v + st]) v += st;
-    L8[i] = (uint8_t)v;
+    for (int c = 0; c < kHistCopies; ++c) t += h[c][threadIdx.x];
+    if (t) atomicAdd(&hist[(blockIdx.x % kHistParts) * 256 + threadIdx.x], t);
   }
-}
+};
 
-// Gray images: L8 is the image itself (rows gathered from the pitch).
-__global__ __launch_bounds__(kBlock) void k_gray(const uint8_t* __restrict__ img, int32_t W, int32_t H, int64_t pitch,
-                                                 uint8_t* __restrict__ L8) {
-  const int64_t N = (int64_t)W * H;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-    const int y = (int)((uint32_t)i / (uint32_t)W), x = (int)((uint32_t)i % (uint32_t)W);   // N < 2^31
-    L8[i] = img[(int64_t)y * pitch + x];
-  }
-}
-
-// RGB rows whose width is a multiple of 4 at word-aligned addresses: four
-// pixels per thread from three aligned words, one word written.
-// Four pixels per thread from three aligned words. The step search starts
-// from a table over Y in 1/4096 buckets: coarse[b] is the last step at or
-// below b/4096, and since consecutive steps lie more than 1/4096 apart (the
-// host checks it before it takes this kernel) a bucket holds at most one
-// step, so one comparison finishes the search (instead of eight dependent
-// LDS reads). Built per block from the steps, for a grid of a few blocks per CU.
-constexpr int kLightBuckets = 4096;
-__global__ __launch_bounds__(kBlock) void k_light4(const uint8_t* __restrict__ img, int32_t W, int32_t H,
-                                                   int64_t pitch, uint8_t* __restrict__ L8, LightSteps steps) {
+// RGB: four pixels per thread from 12 bytes of a row (at any alignment), two
+// such groups in flight; rows end in a group of fewer, read by bytes. HIST:
+// the values are counted on the way.
+// The value comes from Y in fp32 and the hardware's log2 and exp2. That is
+// within 2e-4 of 255/100 L* (3 roundings of 2^-24 on Y, a third of them left
+// by the cube root; log2 within 2^-21 of values up to 7, a third of that
+// left; exp2 within 2^-23: 296 times 2.6e-7, and 2^-16 of the last sums), so
+// a value nearer than kLightEps to where it changes is decided on Y in fp64
+// and the steps, as any other would be: one pixel in 500, with one branch for
+// a thread's four (a branch per pixel kept their LDS reads one after another:
+// 19 us at 4096x2304, 17 us so). Y in fp64 and the steps' search for every
+// pixel were bound by LDS reads of 8 bytes: 17 us and the histogram's own pass
+// 15 us; 1390x1110, rows not word-aligned: 17 -> 5.9 us; 640x480: 5.7 + 3.8 ->
+// 5.3 us.
+constexpr float kLightEps = 0x1p-10f;
+template <bool HIST>
+__global__ __launch_bounds__(kBlock) void k_light(const uint8_t* __restrict__ img, int32_t W, int32_t H, int64_t pitch,
+                                                  uint8_t* __restrict__ L8, LightSteps steps, uint32_t* hist) {
 #pragma clang fp contract(off)
-  __shared__ double lin[256];
-  __shared__ double t[256];
-  __shared__ uint8_t coarse[kLightBuckets + 1];
-  lin[threadIdx.x] = srgb_linear((int)threadIdx.x);
-  t[threadIdx.x] = steps.t[threadIdx.x];
-  __syncthreads();
+  __shared__ double lin[256], t[257];
+  __shared__ float linf[256];
+  __shared__ BlockHist bh[1];
   {
-    // step k covers buckets ceil(t[k] 4096) .. ceil(t[k + 1] 4096) - 1 (step 0 from bucket 0)
-    const int k = threadIdx.x;
-    auto first_bucket = [&](int j) -> int {
-      return j > 255 ? kLightBuckets + 1 : (int)fmin(ceil(t[j] * (double)kLightBuckets), (double)(kLightBuckets + 1));
-    };
-    const int b0 = k == 0 ? 0 : first_bucket(k), b1 = first_bucket(k + 1);
-    for (int b = b0; b < b1; ++b) coarse[b] = (uint8_t)k;
+    const double l = srgb_linear((int)threadIdx.x);
+    lin[threadIdx.x] = l;
+    linf[threadIdx.x] = (float)l;
+    t[threadIdx.x] = steps.t[threadIdx.x];
+    if (threadIdx.x == 0) t[256] = HUGE_VAL;
   }
+  if constexpr (HIST) bh[0].clear();
   __syncthreads();
-  const int64_t Q = (int64_t)W * H / 4;   // groups of four pixels (W % 4 == 0)
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < Q; g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = 4 * g;
-    const int y = (int)((uint32_t)i / (uint32_t)W), x = (int)((uint32_t)i % (uint32_t)W);   // N < 2^31
-    const uint32_t* p = (const uint32_t*)(img + (int64_t)y * pitch + (int64_t)x * 3);
-    const uint32_t w0 = p[0], w1 = p[1], w2 = p[2];
-    const uint32_t px[4][3] = {{w0 & 0xFFu, (w0 >> 8) & 0xFFu, (w0 >> 16) & 0xFFu},
-                               {w0 >> 24, w1 & 0xFFu, (w1 >> 8) & 0xFFu},
-                               {(w1 >> 16) & 0xFFu, w1 >> 24, w2 & 0xFFu},
-                               {(w2 >> 8) & 0xFFu, (w2 >> 16) & 0xFFu, w2 >> 24}};
-    uint32_t out = 0;
+  constexpr double e = 6.0 / 29.0;
+  constexpr float kE3 = (float)(e * e * e), kLinear = (float)(295.8 / (3 * e * e));
+  const uint32_t gpr = ((uint32_t)W + 3u) / 4u;   // groups per row (gpr H < 2^31)
+  const uint32_t groups = gpr * (uint32_t)H, stride = gridDim.x * kBlock;
+  struct Group {
+    int64_t at;   // of its first pixel in L8
+    int n;        // its pixels
+    uint32_t w[3];
+  };
+  auto fetch = [&](uint32_t g) {
+    const uint32_t y = H == 1 ? 0u : g / gpr, x = 4u * (g - y * gpr);
+    Group q;
+    q.at = (int64_t)y * W + x;
+    q.n = min((int)(W - x), 4);
+    const uint8_t* p = img + (int64_t)y * pitch + 3 * (int64_t)x;
+    if (q.n == 4) {
+      __builtin_memcpy(q.w, p, 12);
+    } else {
+      uint8_t c[12];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) c[k] = k < 3 * q.n ? p[k] : (uint8_t)0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        q.w[k] = c[4 * k] | (uint32_t)c[4 * k + 1] << 8 | (uint32_t)c[4 * k + 2] << 16 | (uint32_t)c[4 * k + 3] << 24;
+    }
+    return q;
+  };
+  auto take = [&](const Group& q) {
+    const uint32_t px[4][3] = {{q.w[0] & 0xFFu, (q.w[0] >> 8) & 0xFFu, (q.w[0] >> 16) & 0xFFu},
+                               {q.w[0] >> 24, q.w[1] & 0xFFu, (q.w[1] >> 8) & 0xFFu},
+                               {(q.w[1] >> 16) & 0xFFu, q.w[1] >> 24, q.w[2] & 0xFFu},
+                               {(q.w[2] >> 8) & 0xFFu, (q.w[2] >> 16) & 0xFFu, q.w[2] >> 24}};
+    int v[4];
+    bool near[4], any = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const double Y = 0.2126 * lin[px[k][0]] + 0.7152 * lin[px[k][1]] + 0.0722 * lin[px[k][2]];
-      int v = coarse[min((int)(Y * (double)kLightBuckets), kLightBuckets)];   // Y >= 0
-      if (v < 255 && Y >= t[v + 1]) ++v;
-      out |= (uint32_t)v << (8 * k);
+      const float Y = __builtin_fmaf(0.0722f, linf[px[k][2]], __builtin_fmaf(0.7152f, linf[px[k][1]], 0.2126f * linf[px[k][0]]));
+      const float root = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(Y) * (1.0f / 3.0f));
+      const float s = Y > kE3 ? __builtin_fmaf(295.8f, root, -40.3f) : __builtin_fmaf(kLinear, Y, 0.5f);
+      v[k] = (int)s;
+      near[k] = fabsf(s - (float)v[k] - 0.5f) > 0.5f - kLightEps;
+      any |= near[k];
     }
-    *(uint32_t*)(L8 + i) = out;
+    // one branch for the four of them: theirs are worked out side by side
+    if (any) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (!near[k]) continue;
+        const double Y = 0.2126 * lin[px[k][0]] + 0.7152 * lin[px[k][1]] + 0.0722 * lin[px[k][2]];
+        const int up = Y >= t[v[k] + 1] ? 1 : 0, down = Y < t[v[k]] ? 1 : 0;
+        v[k] += up - down;
+      }
+    }
+    if (q.n == 4) {
+      const uint32_t o = (uint32_t)(v[0] | v[1] << 8 | v[2] << 16 | v[3] << 24);
+      __builtin_memcpy(L8 + q.at, &o, 4);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k >= q.n) break;
+      if (q.n != 4) L8[q.at + k] = (uint8_t)v[k];
+      if constexpr (HIST) bh[0].add((uint32_t)v[k]);
+    }
+  };
+  for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < groups; g += 2u * stride) {
+    const bool two = g + stride < groups;
+    const Group q0 = fetch(g);
+    Group q1 = q0;
+    if (two) q1 = fetch(g + stride);
+    take(q0);
+    if (two) take(q1);
+  }
+  if constexpr (HIST) {
+    __syncthreads();
+    bh[0].store(hist);
   }
 }
 
-// Lightness of an image on `s`: the four-pixel kernel where its layout allows.
-void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t pitch, uint8_t* L8, int grid,
+// Gray images, 16 pixels of a row per thread (at any alignment), the rest of
+// a row by bytes: L8 is the image itself (COPY: its rows gathered from the
+// pitch). HIST: the values are counted.
+template <bool COPY, bool HIST>
+__global__ __launch_bounds__(kBlock) void k_gray(const uint8_t* __restrict__ img, int32_t W, int32_t H, int64_t pitch,
+                                                 uint8_t* __restrict__ L8, uint32_t* hist) {
+  __shared__ BlockHist bh[1];
+  if constexpr (HIST) {
+    bh[0].clear();
+    __syncthreads();
+  }
+  const uint32_t gpr = ((uint32_t)W + 15u) / 16u;
+  const uint32_t groups = gpr * (uint32_t)H, stride = gridDim.x * kBlock;   // (groups < 2^31, stride at most 2^21)
+  for (uint32_t g = blockIdx.x * kBlock + threadIdx.x; g < groups; g += stride) {
+    const uint32_t y = g / gpr, x = 16u * (g - y * gpr);
+    const uint8_t* p = img + (int64_t)y * pitch + x;
+    uint8_t* o = L8 + (int64_t)y * W + x;
+    if (x + 16u <= (uint32_t)W) {
+      uint32_t w[4];
+      __builtin_memcpy(w, p, 16);
+      if constexpr (COPY) __builtin_memcpy(o, w, 16);
+      if constexpr (HIST) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) bh[0].add((w[j] >> (8 * b)) & 0xFFu);
+      }
+    } else {
+      for (uint32_t k = 0; x + k < (uint32_t)W; ++k) {
+        const uint8_t v = p[k];
+        if constexpr (COPY) o[k] = v;
+        if constexpr (HIST) bh[0].add(v);
+      }
+    }
+  }
+  if constexpr (HIST) {
+    __syncthreads();
+    bh[0].store(hist);
+  }
+}
+
+// Lightness of an image on `s` (L8 null: a gray image without gaps, only
+// counted); hist null: not counted.
+void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t pitch, uint8_t* L8, uint32_t* hist,
                   hipStream_t s);
 
 // n bytes of zeros (16-byte aligned, a multiple of 16), by a kernel: no
@@ -152,38 +239,6 @@ void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t p
 __global__ __launch_bounds__(kBlock) void k_clear(uint4* p, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n / 16; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = uint4{0u, 0u, 0u, 0u};
-}
-
-// Histogram: 16-byte loads (16 pixels per thread and step where the buffer
-// is 16-byte aligned), LDS atomic adds into 16 copies of the bins (lane l
-// uses copy l % 16; copies are 257 words apart, so equal values in different
-// copies fall in different banks), then one global add per bin and block.
-constexpr int kHistCopies = 16;
-__global__ __launch_bounds__(kBlock) void k_hist(const uint8_t* __restrict__ L8, int64_t N,
-                                                 unsigned long long* __restrict__ hist) {
-  __shared__ uint32_t h[kHistCopies][257];
-  for (int i = threadIdx.x; i < kHistCopies * 257; i += blockDim.x) (&h[0][0])[i] = 0u;
-  __syncthreads();
-  uint32_t* mine = h[threadIdx.x & (kHistCopies - 1)];
-  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-  int64_t head = 0;
-  if (((uintptr_t)L8 & 15u) == 0) {
-    const int64_t nv = N >> 4;
-    for (int64_t v = tid; v < nv; v += stride) {
-      const uint4 q = *(const uint4*)(L8 + 16 * v);
-      const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) atomicAdd(&mine[(w[j] >> (8 * b)) & 0xFFu], 1u);
-    }
-    head = nv << 4;
-  }
-  for (int64_t i = head + tid; i < N; i += stride) atomicAdd(&mine[L8[i]], 1u);
-  __syncthreads();
-  uint32_t t = 0;
-  for (int c = 0; c < kHistCopies; ++c) t += h[c][threadIdx.x];
-  if (t) atomicAdd(&hist[threadIdx.x], (unsigned long long)t);
 }
 
 // K-means on the occupied bins, one block, thread b owns bin b. Centres are
@@ -198,7 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_hist(const uint8_t* __restrict__ L8,
 // every bin to a few words queued up lane by lane. A pass is a chain of three
 // barriers (K = 10 at 1390x1110: 44 us with the adds, 31 us so; K = 4 at
 // 4096x2304: 13 and 8.6 us; at 640x480: 11 and 6.9 us).
-__global__ __launch_bounds__(256) void k_kmeans(const unsigned long long* __restrict__ hist, int32_t K,
+__global__ __launch_bounds__(256) void k_kmeans(const uint32_t* __restrict__ hist, int32_t K,
                                                 uint8_t* __restrict__ lut, int32_t* __restrict__ passes_out) {
   __shared__ long long S[kMaxK], Nn[kMaxK];
   __shared__ double M[kMaxK + 4];   // S / N rounded to double, then far away values
@@ -208,7 +263,14 @@ __global__ __launch_bounds__(256) void k_kmeans(const unsigned long long* __rest
   __shared__ int lo_s, hi_s, changed;
   __shared__ int rank[kMaxK];
   const int b = threadIdx.x, lane = b & 63;
-  const long long hb = (long long)hist[b];
+  long long hb = 0;
+  {
+    uint32_t v[kHistParts];
+#pragma unroll
+    for (int q = 0; q < kHistParts; ++q) v[q] = hist[q * 256 + b];
+#pragma unroll
+    for (int q = 0; q < kHistParts; ++q) hb += v[q];
+  }
   if (b == 0) { lo_s = 256; hi_s = -1; }
   long long cn = hb, cw = b * hb;
 #pragma unroll
@@ -2084,7 +2146,7 @@ Layout layout(int32_t W, int32_t H) {
   o.ties = take(kSelBlocks * 4);
   o.lut = take(256);
   o.clear = off;
-  o.hist = take(256 * 8);
+  o.hist = take(kHistParts * 256 * 4);
   o.misc = take(kMiscBytes);
   o.clear_front = off;
   o.lcount = take((size_t)kLvParts * (kLevels + 1) * 4);
@@ -2135,22 +2197,28 @@ const LightSteps& light_steps() {
   return steps;
 }
 
-void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t pitch, uint8_t* L8, int grid,
+void launch_light(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t pitch, uint8_t* L8, uint32_t* hist,
                   hipStream_t s) {
-  // the bucket table of k_light4 needs consecutive steps more than a bucket apart
-  static const bool coarse_ok = [] {
-    const LightSteps& st = light_steps();
-    for (int k = 1; k < 255; ++k)
-      if (std::isfinite(st.t[k + 1]) && !(st.t[k + 1] - st.t[k] > 1.0 / kLightBuckets)) return false;
-    return true;
-  }();
-  if (C == 1)
-    hipLaunchKernelGGL(k_gray, dim3(grid), dim3(kBlock), 0, s, img, W, H, pitch, L8);
-  else if (coarse_ok && (W & 3) == 0 && (pitch & 3) == 0 && ((uintptr_t)img & 3) == 0 && ((uintptr_t)L8 & 3) == 0)
-    hipLaunchKernelGGL(k_light4, dim3(std::min(grid, 1024)), dim3(kBlock), 0, s, img, W, H, pitch, L8,
-                       light_steps());
-  else
-    hipLaunchKernelGGL(k_light, dim3(grid), dim3(kBlock), 0, s, img, W, H, C, pitch, L8, light_steps());
+  if (pitch == (int64_t)W * C) {   // rows without gaps are one row
+    W *= H;
+    H = 1;
+    pitch = (int64_t)W * C;
+  }
+  // at most 4 blocks per CU of RGB (their tables and closing adds) and 2 of gray
+  const int per = C == 3 ? 4 : 16;
+  const int64_t groups = ((int64_t)W + per - 1) / per * H;
+  const dim3 grid((unsigned)std::min<int64_t>((groups + kBlock - 1) / kBlock, C == 3 ? 1024 : L8 && !hist ? 8192 : 512));
+  const dim3 block(kBlock);
+  if (C == 3) {
+    if (hist) hipLaunchKernelGGL(k_light<true>, grid, block, 0, s, img, W, H, pitch, L8, light_steps(), hist);
+    else hipLaunchKernelGGL(k_light<false>, grid, block, 0, s, img, W, H, pitch, L8, light_steps(), hist);
+  } else if (!hist) {
+    hipLaunchKernelGGL((k_gray<true, false>), grid, block, 0, s, img, W, H, pitch, L8, hist);
+  } else if (L8) {
+    hipLaunchKernelGGL((k_gray<true, true>), grid, block, 0, s, img, W, H, pitch, L8, hist);
+  } else {
+    hipLaunchKernelGGL((k_gray<false, true>), grid, block, 0, s, img, W, H, pitch, L8, hist);
+  }
 }
 
 int grid_for(int64_t n) {
@@ -2169,7 +2237,7 @@ int sbs_lightness(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t p
     return fail(SBS_ERR_INVALID_ARG, "bad image geometry");
   if (!img || !out_l8) return fail(SBS_ERR_INVALID_ARG, "NULL pointer");
   hipStream_t s = (hipStream_t)stream;
-  launch_light(img, W, H, C, pitch, out_l8, grid_for((int64_t)W * H), s);
+  launch_light(img, W, H, C, pitch, out_l8, nullptr, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SBS_ERR_HIP, "lightness: %s", hipGetErrorString(e));
   return SBS_OK;
@@ -2208,7 +2276,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   int32_t* size = (int32_t*)(base + Lo.size);
   int32_t* cnt = (int32_t*)(base + Lo.cnt);
   uint32_t* bsum = (uint32_t*)(base + Lo.bsum);
-  unsigned long long* hist = (unsigned long long*)(base + Lo.hist);
+  uint32_t* hist = (uint32_t*)(base + Lo.hist);
   uint8_t* lut = (uint8_t*)(base + Lo.lut);
   char* misc = base + Lo.misc;
   int32_t* passes = (int32_t*)misc;
@@ -2230,11 +2298,9 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
                        0, s, (uint4*)(base + Lo.clear), bytes);
   }
   // grey rows without gaps are the lightness image itself (no copy)
-  const uint8_t* lum = L8;
-  if (C == 1 && pitch == W) lum = img;
-  else launch_light(img, W, H, C, pitch, L8, g, s);
-  // at most 512 blocks: each ends with up to 256 global adds
-  hipLaunchKernelGGL(k_hist, dim3(std::min(grid_for((N + 15) / 16), 512)), dim3(kBlock), 0, s, lum, N, hist);
+  const bool same = C == 1 && pitch == W;
+  const uint8_t* lum = same ? img : L8;
+  launch_light(img, W, H, C, pitch, same ? nullptr : L8, hist, s);
   hipLaunchKernelGGL(k_kmeans, dim3(1), dim3(256), 0, s, hist, K, lut, passes);
   const int32_t words = (W & 3) == 0 && ((uintptr_t)lum & 3) == 0 ? 1 : 0;
   auto rf_grid = [&](int rows) { return dim3((W + kRfCols - 1) / kRfCols, (H + rows - 1) / rows); };

@@ -234,3 +234,21 @@ def test_fraction_control_component_sizes(torch, sbs, W, H):
     n1, n0 = int(kept[:, 1:-1].sum()), 2 * H
     for share in ((0.5,) if W > 1000 else (0.0, 0.1, 0.33, 0.5, 0.77, 1.0)):
         check_fraction(torch, sbs, img, 2, 0, 1, (n0 + 1 + share * (n1 - 1)) / (W * H), 3, f"{W}x{H} share {share}")
+
+
+@pytest.mark.parametrize("C", [1, 3])
+def test_lightness_rows(torch, sbs, C):
+    """Rows of every remainder of the groups that a thread takes (4 RGB pixels,
+    16 grey ones), with and without gaps, at odd addresses; the histogram taken
+    on the way gives the same labels."""
+    rng = np.random.default_rng(C)
+    for W in (1, 2, 3, 4, 5, 15, 16, 17, 31, 33, 65):
+        for H, pad, off in ((1, 0, 0), (7, 0, 1), (7, 1, 0), (9, 4, 2), (40, 13, 3)):
+            pitch = W * C + pad
+            buf = rng.integers(0, 256, off + H * pitch, dtype=np.uint8)
+            img = np.ascontiguousarray(buf[off:].reshape(H, pitch)[:, :W * C].reshape((H, W, C) if C == 3 else (H, W)))
+            d = dev(torch, buf)
+            view = torch.as_strided(d, (H, W, C) if C == 3 else (H, W), (pitch, C, 1) if C == 3 else (pitch, 1), off)
+            what = f"{W}x{H}x{C} pitch {pitch} offset {off}"
+            assert np.array_equal(sbs.lightness(view).cpu().numpy(), oracle.lightness(img)), what
+            check_front(torch, sbs, view, img, 4, 0, 2, what)
