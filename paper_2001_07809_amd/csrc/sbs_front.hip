@@ -1312,13 +1312,13 @@ __device__ __forceinline__ RadixSel sel_pick(RadixSel r, const uint32_t* hist, i
 // Mode 1, one counting pass over the kept pixels' keys ~size.
 __device__ __forceinline__ void size_pass(const Bits& b, const unsigned long long* B, const unsigned long long* kept,
                                           const int32_t* size, RadixSel rs, const uint32_t* prev_hist, int prev_shift,
-                                          RadixSel* state, int shift, uint32_t* hist, uint32_t* bins) {
+                                          RadixSel* state, int shift, uint32_t* hist, uint32_t* bins, int blocks) {
   if (prev_hist) rs = sel_pick(rs, prev_hist, prev_shift, state);
   for (int k = threadIdx.x; k < kBins; k += kBlock) bins[k] = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int hi = shift + kDigit;
-  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
+  const int64_t nw = (int64_t)blocks * (kBlock / 64);
   for (int64_t w0 = kWaveWords * ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)); w0 < b.words; w0 += kWaveWords * nw) {
     const WaveWords w = wave_words(b, kept, w0, b.words);
     int32_t s[kWaveWords];
@@ -1336,6 +1336,46 @@ __device__ __forceinline__ void size_pass(const Bits& b, const unsigned long lon
   __syncthreads();
   for (int k = threadIdx.x; k < kBins; k += kBlock)
     if (bins[k]) atomicAdd(&hist[k], bins[k]);
+}
+
+// The counting passes of mode 1, from the keys' top digit at `top` down: the
+// state after pass p's pick is state[p], its counts are hist[p * kBins ..].
+struct SizeSel {
+  const unsigned long long *B, *kept;
+  const int32_t* size;
+  unsigned long long prefix;   // digits known beforehand
+  int top;                     // shift of the first pass: (passes - 1) kDigit
+  RadixSel* state;
+  uint32_t* hist;
+  int blocks;                  // that count: each ends with up to kBins adds to memory
+};
+__device__ __forceinline__ void size_digit(const Bits& b, const SizeSel& z, int pass, long long need, uint32_t* bins) {
+  if ((int)blockIdx.x >= z.blocks) return;
+  const int shift = z.top - pass * kDigit;
+  const RadixSel in = pass < 2 ? RadixSel{z.prefix, need, 0} : z.state[pass - 2];
+  size_pass(b, z.B, z.kept, z.size, in, pass ? z.hist + (pass - 1) * kBins : nullptr, shift + kDigit,
+            pass ? z.state + pass - 1 : nullptr, shift, z.hist + pass * kBins, bins, z.blocks);
+}
+// The size of mode 1's want-th pixel, after the last pass.
+__device__ __forceinline__ RadixSel size_found(const SizeSel& z, long long need) {
+  const int last = z.top / kDigit;
+  return sel_pick(last ? z.state[last - 1] : RadixSel{z.prefix, need, 0}, z.hist + last * kBins, 0, nullptr);
+}
+
+constexpr int kSegRows = 32;   // rows per column segment of the distance passes
+// Per (word column, 32-row segment): the columns with a base pixel in it.
+__device__ __forceinline__ void far_segments(const Bits& b, const unsigned long long* base, int nseg,
+                                             unsigned long long* segor) {
+  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < (int64_t)nseg * b.wpr; t += (int64_t)gridDim.x * kBlock) {
+    const int sg = (int)(t / b.wpr), c = (int)(t % b.wpr);
+    const int y0 = sg * kSegRows, n = min(b.H - y0, kSegRows);
+    unsigned long long v[kSegRows], m = 0ull;
+#pragma unroll
+    for (int k = 0; k < kSegRows; ++k) v[k] = k < n ? base[(int64_t)(y0 + k) * b.wpr + c] : 0ull;
+#pragma unroll
+    for (int k = 0; k < kSegRows; ++k) m |= v[k];
+    segor[t] = m;
+  }
 }
 
 // Mode 2: distances up to kLevels by dilation of the base map, 3 x 3 per
@@ -1368,21 +1408,35 @@ __device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long
 // Planes 0 .. 3 of a map word lie side by side, plane 4 apart after them (it
 // is read for levels above 15 only). STAGE 0: levels 1 .. 15 of `from` (the
 // base map), and the pixels reached to `reach`. STAGE 1: levels 16 .. 30 of
-// `from` (what stage 0 reached) into the planes.
+// `from` (what stage 0 reached) into the planes, and what the distance passes
+// need of the base map's columns in case that they follow.
+// The first two counting passes of mode 1 take these launches' places (one of
+// the two modes has nothing to do in them, and an idle launch costs 5 us of
+// the device and 8 us of the caller's thread): gx x gy blocks for the levels,
+// in a row, further ones for the counting.
 template <int STAGE>
-__global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, const unsigned long long* __restrict__ from,
+__global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, SizeSel z, int gx, int gy,
+                                                      const unsigned long long* __restrict__ from,
                                                       unsigned long long* __restrict__ planes,
-                                                      unsigned long long* __restrict__ reach, uint32_t* lcount) {
-  __shared__ uint32_t cnt[kLvStage];
+                                                      unsigned long long* __restrict__ reach, uint32_t* lcount,
+                                                      const unsigned long long* __restrict__ base, int nseg,
+                                                      unsigned long long* __restrict__ segor) {
+  __shared__ uint32_t bins[kBins];
+  uint32_t* cnt = bins;   // the levels' counts
   const FcPlan plan = fc_plan(a);
+  if (plan.mode == 1) size_digit(b, z, STAGE, plan.need, bins);
   if (plan.mode != 2) return;
-  if constexpr (STAGE == 1)
+  if constexpr (STAGE == 1) {
     if (level_pick(lcount, plan.need, kLvStage).level != 0) return;   // (other blocks may have added to the levels beyond)
+    far_segments(b, base, nseg, segor);
+  }
+  if ((int)blockIdx.x >= gx * gy) return;
+  const int bx = (int)blockIdx.x % gx, by = (int)blockIdx.x / gx;
   if (threadIdx.x < kLvStage) cnt[threadIdx.x] = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int c = 2 * ((int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6));   // the first of the wavefront's two word columns
-  const int y0 = (int)blockIdx.y * kLvRows;
+  const int c = 2 * (bx * (kBlock / 64) + (int)(threadIdx.x >> 6));   // the first of the wavefront's two word columns
+  const int y0 = by * kLvRows;
   if (c < b.wpr) {
     constexpr int M = kLvWords;
     const uint32_t* src = (const uint32_t*)from;   // 32-bit halves of the map's words, low half first
@@ -1470,7 +1524,7 @@ __global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, const un
     }
   }
   __syncthreads();
-  const int part = (int)((blockIdx.y * gridDim.x + blockIdx.x) % kLvParts);
+  const int part = (int)(blockIdx.x % kLvParts);
   if (threadIdx.x < kLvStage && cnt[threadIdx.x])
     atomicAdd(&lcount[part * (kLevels + 1) + 1 + STAGE * kLvStage + threadIdx.x], cnt[threadIdx.x]);
 }
@@ -1532,17 +1586,20 @@ constexpr int kHashDigit = 8, kHashBins = 1 << kHashDigit, kHashParts = 8;
 static_assert(kHashBins == kBlock, "one bin per thread");
 // f(i) for the block's ring pixels i: the words' set bits are queued in LDS
 // first and then taken by all threads alike, since a ring fills some words and
-// leaves most empty.
+// leaves most empty. `blocks` blocks take `chunk` words (at most kRingWords) in
+// turn, each after prepare(their first word).
 constexpr int kRingWords = kBlock;          // words a block queues at a time
 constexpr int kRingGroups = 4;              // of them per block in small images
-template <typename F>
-__device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, F f) {
+template <typename P, typename F>
+__device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, int blocks,
+                                         int chunk, P prepare, F f) {
   __shared__ uint16_t queue[64 * kRingWords];   // word << 6 | bit
   __shared__ int first[kRingWords];
   __shared__ uint32_t wtot[kBlock / 64];
-  for (int64_t w0 = (int64_t)blockIdx.x * kRingWords; w0 < b.words; w0 += (int64_t)gridDim.x * kRingWords) {
+  for (int64_t w0 = (int64_t)blockIdx.x * chunk; w0 < b.words; w0 += (int64_t)blocks * chunk) {
+    prepare(w0);
     const int64_t wi = w0 + threadIdx.x;
-    unsigned long long m = wi < b.words ? level_words(b, planes, wi, level).ring : 0ull;
+    unsigned long long m = (int)threadIdx.x < chunk && wi < b.words ? level_words(b, planes, wi, level).ring : 0ull;
     uint32_t all;
     uint32_t at = block_scan_excl<kBlock / 64>((uint32_t)__builtin_popcountll(m), wtot, all);
     if (m) first[threadIdx.x] = word_pos(b, wi).i;
@@ -1551,22 +1608,6 @@ __device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long
     for (uint32_t k = threadIdx.x; k < all; k += kBlock) f((uint32_t)(first[queue[k] >> 6] + (queue[k] & 63)));
     __syncthreads();   // the queue is rewritten
   }
-}
-__global__ __launch_bounds__(kBlock) void k_ring_count(Bits b, FcArgs a, const unsigned long long* __restrict__ planes,
-                                                       const uint32_t* __restrict__ lcount,
-                                                       const long long* __restrict__ far_need, uint32_t* hash_hist) {
-  __shared__ uint32_t bins[kHashBins];
-  const FcPlan pl = fc_plan(a);
-  if (pl.mode != 2) return;
-  for (int k = threadIdx.x; k < kHashBins; k += kBlock) bins[k] = 0u;
-  const LevelSel ls = level_final(lcount, far_need, pl.need);   // (its barriers order the bins)
-  for_ring(b, planes, ls.level, [&](uint32_t i) {
-    atomicAdd(&bins[mix64((unsigned long long)i ^ a.seed) >> (64 - kHashDigit)], 1u);
-  });
-  __syncthreads();
-  uint32_t* out = hash_hist + (blockIdx.x % kHashParts) * kHashBins;
-  for (int k = threadIdx.x; k < kHashBins; k += kBlock)
-    if (bins[k]) atomicAdd(&out[k], bins[k]);
 }
 // The hashes of the ring's pixels in the bin that holds the wanted rank, and
 // the rank within it.
@@ -1601,7 +1642,7 @@ __global__ __launch_bounds__(kBlock) void k_ring_bin(Bits b, FcArgs a, const uns
   const unsigned long long bin = bin_s;
   if (blockIdx.x == 0 && threadIdx.x == 0) rb->need = need_s;
   // held in LDS first, so that a block takes its places in the list at once
-  for_ring(b, planes, ls.level, [&](uint32_t i) {
+  for_ring(b, planes, ls.level, (int)gridDim.x, kRingWords, [](int64_t) {}, [&](uint32_t i) {
     const unsigned long long h = mix64((unsigned long long)i ^ a.seed);
     if (h >> (64 - kHashDigit) != bin) return;
     const uint32_t k = atomicAdd(&held, 1u);
@@ -1674,11 +1715,8 @@ __device__ __forceinline__ unsigned long long ring_threshold(const RingBin* rb, 
 }
 
 // The selected pixels as a map, and their number per block of b.per words.
-__global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const unsigned long long* __restrict__ B,
-                                                      const unsigned long long* __restrict__ kept,
-                                                      const unsigned long long* __restrict__ base,
-                                                      const int32_t* __restrict__ size, const RadixSel* s1, const uint32_t* __restrict__ s1_hist,
-                                                      const uint32_t* __restrict__ ties,
+__global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const unsigned long long* __restrict__ base,
+                                                      SizeSel z, const uint32_t* __restrict__ ties,
                                                       const unsigned long long* __restrict__ planes,
                                                       const uint32_t* __restrict__ lcount,
                                                       const long long* __restrict__ far_need,
@@ -1723,14 +1761,14 @@ __global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const un
   } else {
     // kept pixels of larger components, and the first of those of size s* in
     // raster order: ties before this block from the blocks' counts
-    const RadixSel rs = sel_pick(*s1, s1_hist, 0, nullptr);
+    const RadixSel rs = size_found(z, pl.need);
     const uint32_t s_star = ~(uint32_t)rs.prefix;
     long long quota = rs.need - rs.below - (long long)counts_before(ties, wtot);
     for (int64_t w0 = w_begin; w0 < w_end; w0 += kSelWords) {
       const int64_t wf = w0 + kWaveWords * wv;
-      const WaveWords w = wave_words(b, kept, wf, w_end);
+      const WaveWords w = wave_words(b, z.kept, wf, w_end);
       int32_t s[kWaveWords];
-      at_kept_runs(w, wave_words(b, B, wf, w_end), wf, size, s);
+      at_kept_runs(w, wave_words(b, z.B, wf, w_end), wf, z.size, s);
       unsigned long long tv = 0ull, ov = 0ull;   // lane j: word j's ties, and its pixels of larger components
 #pragma unroll
       for (int j = 0; j < kWaveWords; ++j) {
@@ -1793,23 +1831,6 @@ __device__ __forceinline__ void tie_pass(const Bits& b, const unsigned long long
 // the nearest base pixel, then per pixel the minimum over columns x' of
 // max(|x - x'|, g(x')) (the border columns bound it).
 constexpr int32_t kFar = 1 << 30;
-constexpr int kSegRows = 32;   // rows per column segment
-
-// Per (word column, 32-row segment): the columns with a base pixel in it.
-__device__ __forceinline__ void far_segments(const Bits& b, const unsigned long long* base, int nseg,
-                                             unsigned long long* segor) {
-  for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < (int64_t)nseg * b.wpr; t += (int64_t)gridDim.x * kBlock) {
-    const int sg = (int)(t / b.wpr), c = (int)(t % b.wpr);
-    const int y0 = sg * kSegRows, n = min(b.H - y0, kSegRows);
-    unsigned long long v[kSegRows], m = 0ull;
-#pragma unroll
-    for (int k = 0; k < kSegRows; ++k) v[k] = k < n ? base[(int64_t)(y0 + k) * b.wpr + c] : 0ull;
-#pragma unroll
-    for (int k = 0; k < kSegRows; ++k) m |= v[k];
-    segor[t] = m;
-  }
-}
-
 // g for one (word column, segment) per wavefront, lane = column: inside the
 // segment from its 32 words; beyond it, segment by segment away from it until
 // every column has met a base pixel (or the image ends).
@@ -2036,68 +2057,75 @@ __global__ __launch_bounds__(kBlock) void k_dist_pass(Bits b, FcArgs a, const in
     if (bins[k]) atomicAdd(&hist[k], bins[k]);
 }
 
-// The launches of the two rarer classes share their places in the sequence
-// (only one of them does anything): the counting passes of mode 1, and the
-// distance passes of mode 2 beyond kLevels.
-// First: sizes, top digit | columns with base pixels per segment.
-__global__ __launch_bounds__(kBlock) void k_fc_first(Bits b, FcArgs a, const unsigned long long* B,
-    const unsigned long long* kept,
-                                                     const unsigned long long* base, const int32_t* size,
-                                                     unsigned long long prefix, int shift,
-                                                     uint32_t* hist, const uint32_t* lcount, int nseg,
-                                                     unsigned long long* segor) {
-  __shared__ uint32_t bins[kBins];
-  const FcPlan pl = fc_plan(a);
-  if (pl.mode == 1) size_pass(b, B, kept, size, RadixSel{prefix, pl.need, 0}, nullptr, 0, nullptr, shift, hist, bins);
-  else if (pl.mode == 2 && level_pick(lcount, pl.need).level == 0) far_segments(b, base, nseg, segor);
-}
-// Second: sizes, a lower digit | column distances, and the flag that the
-// launches after it go by.
-__global__ __launch_bounds__(kBlock) void k_fc_second(Bits b, FcArgs a, const unsigned long long* B,
-    const unsigned long long* kept,
-                                                      const unsigned long long* base, const int32_t* size, const RadixSel* in, unsigned long long prefix,
-                                                      const uint32_t* prev_hist, int prev_shift, RadixSel* state, int shift,
-                                                      uint32_t* hist, const uint32_t* lcount, int nseg,
-                                                      const unsigned long long* segor, int32_t* g, int32_t* far) {
+// Between the levels and the distance passes: column distances, and the flag
+// that the launches after it go by | mode 1's third digit (images of 2^24
+// pixels and more).
+__global__ __launch_bounds__(kBlock) void k_fc_columns(Bits b, FcArgs a, SizeSel z, const unsigned long long* base,
+                                                       const uint32_t* lcount, int nseg,
+                                                       const unsigned long long* segor, int32_t* g, int32_t* far) {
   __shared__ uint32_t bins[kBins];
   const FcPlan pl = fc_plan(a);
   if (pl.mode == 1) {
-    size_pass(b, B, kept, size, in ? *in : RadixSel{prefix, pl.need, 0}, prev_hist, prev_shift, state, shift, hist,
-              bins);
-  } else if (g && pl.mode == 2 && level_pick(lcount, pl.need).level == 0) {
+    if (z.top >= 2 * kDigit) size_digit(b, z, 2, pl.need, bins);
+  } else if (pl.mode == 2 && level_pick(lcount, pl.need).level == 0) {
     far_columns(b, base, nseg, segor, g);
     if (blockIdx.x == 0 && threadIdx.x == 0) *far = 1;
   }
 }
-// Last: pixels of the wanted size per block | levels 1 and 2 from the distances.
-__global__ __launch_bounds__(kBlock) void k_fc_last(Bits b, FcArgs a, int nb, const unsigned long long* B,
-    const unsigned long long* kept,
-                                                    const unsigned long long* base, const int32_t* size, const RadixSel* s1, const uint32_t* s1_hist,
-                                                    uint32_t* ties, const int32_t* far, const int32_t* dist,
-                                                    const RadixSel* sd, const uint32_t* sd_hist,
-                                                    unsigned long long* planes, long long* far_need) {
-  __shared__ uint32_t part;
+// Counts: mode 1's pixels of the wanted size per block of b.per words | the
+// ring's hashes by their top digit, after the distance passes from the planes
+// that their outcome gives (levels 1: nearer than the wanted distance, 2: at
+// it), made here. `gr` blocks count where the planes are there: each closes
+// with adds to the same 1 KB, and more of them only wait for each other.
+constexpr int kFarWords = 64;   // words a block makes at a time, 16 per wavefront
+__global__ __launch_bounds__(kBlock) void k_fc_count(Bits b, FcArgs a, SizeSel z, int nb, int gr,
+                                                     const unsigned long long* base, uint32_t* ties, const int32_t* dist,
+                                                     const RadixSel* sd, const uint32_t* sd_hist,
+                                                     const uint32_t* lcount, unsigned long long* planes,
+                                                     long long* far_need, uint32_t* hash_hist) {
+  __shared__ uint32_t part, bins[kHashBins];
   const FcPlan pl = fc_plan(a);
   if (pl.mode == 1) {
-    const RadixSel rs = sel_pick(*s1, s1_hist, 0, nullptr);
+    const RadixSel rs = size_found(z, pl.need);
     for (int64_t block = blockIdx.x; block < nb; block += gridDim.x)
-      tie_pass(b, B, kept, size, ~(uint32_t)rs.prefix, block, ties, &part);
+      tie_pass(b, z.B, z.kept, z.size, ~(uint32_t)rs.prefix, block, ties, &part);
     return;
   }
-  if (!*far) return;
-  const RadixSel rs = sel_pick(sd ? *sd : RadixSel{0, pl.need, 0}, sd_hist, 0, nullptr);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *far_need = rs.need - rs.below;
-  const int lane = threadIdx.x & 63;
-  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
-  for (int64_t wi = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); wi < b.words; wi += nw) {
-    const WordPos p = word_pos(b, wi);
-    const unsigned long long bw = base[wi];
-    const bool in = 64 * p.c + lane < b.W && !(bw >> lane & 1ull);
-    const unsigned long long d = in ? (unsigned long long)(uint32_t)dist[p.i + lane] : ~0ull;
-    const unsigned long long nearer = __builtin_amdgcn_ballot_w64(in && d < rs.prefix);
-    const unsigned long long at = __builtin_amdgcn_ballot_w64(in && d == rs.prefix);
-    if (lane < 4) planes[4 * wi + lane] = lane == 0 ? nearer : lane == 1 ? at : 0ull;
+  if (pl.mode != 2) return;
+  bins[threadIdx.x] = 0u;
+  const LevelSel ls = level_pick(lcount, pl.need);   // (its barriers order the bins)
+  auto count = [&](uint32_t i) {
+    atomicAdd(&bins[mix64((unsigned long long)i ^ a.seed) >> (64 - kHashDigit)], 1u);
+  };
+  if (ls.level != 0) {
+    if ((int)blockIdx.x >= gr) return;
+    for_ring(b, planes, ls.level, gr, kRingWords, [](int64_t) {}, count);
+  } else {
+    const RadixSel rs = sel_pick(sd ? *sd : RadixSel{0, pl.need, 0}, sd_hist, 0, nullptr);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *far_need = rs.need - rs.below;
+    const int lane = threadIdx.x & 63;
+    auto make = [&](int64_t w0) {
+      constexpr int kPer = kFarWords / (kBlock / 64);
+      const int64_t first = w0 + kPer * (threadIdx.x >> 6);
+#pragma unroll 4
+      for (int k = 0; k < kPer; ++k) {
+        const int64_t wi = first + k;
+        if (wi >= b.words) break;
+        const WordPos p = word_pos(b, wi);
+        const unsigned long long bw = base[wi];
+        const bool in = 64 * p.c + lane < b.W && !(bw >> lane & 1ull);
+        const unsigned long long d = in ? (unsigned long long)(uint32_t)dist[p.i + lane] : ~0ull;
+        const unsigned long long nearer = __builtin_amdgcn_ballot_w64(in && d < rs.prefix);
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(in && d == rs.prefix);
+        if (lane < 4) planes[4 * wi + lane] = lane == 0 ? nearer : lane == 1 ? at : 0ull;
+      }
+      __syncthreads();   // the block reads its words' planes back
+    };
+    for_ring(b, planes, 2, (int)gridDim.x, kFarWords, make, count);
   }
+  __syncthreads();
+  uint32_t* out = hash_hist + (blockIdx.x % kHashParts) * kHashBins;
+  if (bins[threadIdx.x]) atomicAdd(&out[threadIdx.x], bins[threadIdx.x]);
 }
 
 int fail(int st, const char* fmt, ...) {
@@ -2352,26 +2380,17 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     bk.per = kSelWords;
     hipLaunchKernelGGL(k_kept, dim3((unsigned)((bt.words + kSelWords - 1) / kSelWords)), dim3(kBlock), 0, s, bk, B, parent,
                        size, dr, (int64_t)min_cc, kept, bmap, out_refined, (uint32_t*)nullptr, n1);
-    const dim3 gl((wpr + 2 * (kBlock / 64) - 1) / (2 * (kBlock / 64)), (H + kLvRows - 1) / kLvRows);
-    hipLaunchKernelGGL(k_fc_levels<0>, gl, dim3(kBlock), 0, s, bt, fa, bmap, planes, sel, lcount);
-    hipLaunchKernelGGL(k_fc_levels<1>, gl, dim3(kBlock), 0, s, bt, fa, sel, planes, (unsigned long long*)nullptr, lcount);
     // Component sizes are at most N: with N below 2^24 the keys' top 8 bits
     // are ones, and two digits remain; else three.
     const bool small = N < (1LL << 24);
-    const unsigned long long prefix = small ? 0xFF000000ull : 0ull;
-    const int gs = std::min(gw, 512);   // (each block ends with up to kBins global adds)
-    int sh = small ? kDigit : 2 * kDigit, np = 0;
-    hipLaunchKernelGGL(k_fc_first, dim3(gs), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size, prefix, sh, shist, lcount,
-                       nseg, segor);
-    for (++np; sh > 0; ++np) {
-      const int prev = sh;
-      sh -= kDigit;
-      hipLaunchKernelGGL(k_fc_second, dim3(np == 1 ? gw : gs), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size,
-                         np == 1 ? (const RadixSel*)nullptr : s1 + np - 2, prefix, shist + (np - 1) * kBins, prev,
-                         s1 + np - 1, sh, shist + np * kBins, lcount, nseg, segor, np == 1 ? gcol : (int32_t*)nullptr, far);
-    }
-    const RadixSel* s1_last = s1 + np - 2;
-    const uint32_t* s1_hist = shist + (np - 1) * kBins;
+    const int gs = std::min(gw, 512);
+    const SizeSel z{B, kept, size, small ? 0xFF000000ull : 0ull, small ? kDigit : 2 * kDigit, s1, shist, gs};
+    const int gx = (wpr + 2 * (kBlock / 64) - 1) / (2 * (kBlock / 64)), gy = (H + kLvRows - 1) / kLvRows;
+    const dim3 gl((unsigned)std::max(gx * gy, gs));
+    hipLaunchKernelGGL(k_fc_levels<0>, gl, dim3(kBlock), 0, s, bt, fa, z, gx, gy, bmap, planes, sel, lcount, bmap, nseg, segor);
+    hipLaunchKernelGGL(k_fc_levels<1>, gl, dim3(kBlock), 0, s, bt, fa, z, gx, gy, sel, planes, (unsigned long long*)nullptr,
+                       lcount, bmap, nseg, segor);
+    hipLaunchKernelGGL(k_fc_columns, dim3(gw), dim3(kBlock), 0, s, bt, fa, z, bmap, lcount, nseg, segor, gcol, far);
     const RadixSel* sd_last = nullptr;
     const uint32_t* sd_hist = dhist;
     if (W <= kStW && H <= 65535) {
@@ -2391,16 +2410,14 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
         dsh -= kDigit;
       }
     }
-    hipLaunchKernelGGL(k_fc_last, dim3(std::min(gw, 1024)), dim3(kBlock), 0, s, bt, fa, nb, B, kept, bmap, size, s1_last,
-                       s1_hist, ties, far, dist, sd_last, sd_hist, planes, far_need);
     // the hashes of one bin's ring pixels are listed in the place of the column
     // and pixel distances (8 bytes per pixel between them)
     unsigned long long* ring = (unsigned long long*)gcol;
     const int gr = (int)std::min<int64_t>((bt.words + kRingGroups * kRingWords - 1) / (kRingGroups * kRingWords), 1024);
-    hipLaunchKernelGGL(k_ring_count, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist);
+    hipLaunchKernelGGL(k_fc_count, dim3(std::min(std::max(gw, gr), 1024)), dim3(kBlock), 0, s, bt, fa, z, nb, gr, bmap, ties, dist,
+                       sd_last, sd_hist, lcount, planes, far_need, hhist);
     hipLaunchKernelGGL(k_ring_bin, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist, rb, ring);
-    hipLaunchKernelGGL(k_fc_select, dim3(nb), dim3(kBlock), 0, s, bt, fa, B, kept, bmap, size, s1_last, s1_hist, ties,
-                       planes, lcount, far_need, rb, ring, sel, bsum);
+    hipLaunchKernelGGL(k_fc_select, dim3(nb), dim3(kBlock), 0, s, bt, fa, bmap, z, ties, planes, lcount, far_need, rb, ring, sel, bsum);
   }
   hipLaunchKernelGGL(k_list, dim3(nb), dim3(kBlock), 0, s, bt, sel, bsum, out_idx, (long long*)out_count);
   const hipError_t e = hipGetLastError();
