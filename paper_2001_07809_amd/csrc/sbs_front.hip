@@ -297,6 +297,56 @@ __global__ __launch_bounds__(256) void k_kmeans(const uint32_t* __restrict__ his
     if (b == 0) *passes_out = 0;
     return;
   }
+  if (hi - lo + 1 >= K) {
+    // The first centres ascend strictly, and then they always do: a bin lies
+    // at or below its centre's midpoint with the next one and above that with
+    // the one before, so means keep their order, and so does a centre without
+    // bins (its neighbours' means stay on their side of it). A pass is then
+    // the K - 1 midpoints, the last bin at or below each, and the prefix sums
+    // there; no bin changes where the pixels below the midpoints are the same.
+    // One wavefront, lane = centre, no barriers.
+    if (b < 64) {
+      const bool mine = b < K;
+      long long s = lo + ((long long)(2 * b + 1) * (hi - lo + 1)) / (2 * K), n = 1;
+      long long below = -1;   // pixels at or below the midpoint above this centre
+      int t = 255;            // the last bin of this centre
+      int pass = 0;
+      for (; pass < kMaxPasses; ++pass) {
+        const double m = (double)s / (double)n;   // s < 2^40 and n < 2^32: both exact, the quotient rounded once
+        const double next = __shfl_down(m, 1);
+        t = 255;
+        if (b < K - 1) {
+          // |error| < 2^-44: where an integer lies closer, whether that bin is
+          // at or below the midpoint is decided exactly
+          const double mid = 0.5 * (m + next), r = rint(mid);
+          t = (int)floor(mid);
+          if (fabs(mid - r) < 0x1p-40) t = -1 - (int)r;
+        }
+        if (__builtin_amdgcn_ballot_w64(t < 0)) {
+          const long long s1 = __shfl_down(s, 1), n1 = __shfl_down(n, 1);
+          if (t < 0) {
+            const int r = -1 - t;
+            t = (__int128)(2LL * r * n) * n1 <= (__int128)s * n1 + (__int128)s1 * n ? r : r - 1;
+          }
+        }
+        const long long up = pn[t + 1], uw = pw[t + 1];
+        const bool moved = mine && up != below;
+        below = up;
+        if (!__builtin_amdgcn_ballot_w64(moved) && pass > 0) break;
+        long long dn = __shfl_up(up, 1), dw = __shfl_up(uw, 1);
+        if (b == 0) dn = dw = 0;
+        if (mine && up - dn > 0) { s = uw - dw; n = up - dn; }
+      }
+      if (mine) to[b] = t;
+      if (b == 0) *passes_out = pass + 1;
+    }
+    __syncthreads();
+    int k = 0;
+    for (int j = 0; j < K - 1; ++j) k += b > to[j] ? 1 : 0;
+    lut[b] = hb > 0 ? (uint8_t)k : 0;
+    return;
+  }
+  // fewer grey levels than clusters: equal centres, each bin by itself
   if (b < K) { S[b] = lo + ((long long)(2 * b + 1) * (hi - lo + 1)) / (2 * K); Nn[b] = 1; }
   int assign = -1;
   int pass = 0;

@@ -252,3 +252,18 @@ def test_lightness_rows(torch, sbs, C):
             what = f"{W}x{H}x{C} pitch {pitch} offset {off}"
             assert np.array_equal(sbs.lightness(view).cpu().numpy(), oracle.lightness(img)), what
             check_front(torch, sbs, view, img, 4, 0, 2, what)
+
+
+@pytest.mark.parametrize("K", [1, 2, 9, 10, 33, 64])
+def test_kmeans_level_ranges(torch, sbs, K):
+    """Ranges of grey levels just below, at and above the number of clusters
+    (equal first centres below it), few and many occupied levels, clusters that
+    stay empty, and midpoints that fall on a level."""
+    rng = np.random.default_rng(K)
+    for span in sorted({1, max(K - 1, 1), K, K + 1, 2 * K, 200, 256}):
+        for levels in {1, 2, 5, span}:
+            lo = int(rng.integers(0, 256 - span + 1))
+            used = np.unique(np.concatenate([[0, span - 1], rng.integers(0, span, min(levels, span))])) + lo
+            img = used[rng.integers(0, used.size, (40, 70))].astype(np.uint8)
+            img[0, :2] = lo, lo + span - 1
+            check_front(torch, sbs, dev(torch, img), img, K, 0, 5, f"K {K}, {used.size} levels of {span} from {lo}")
