@@ -189,13 +189,18 @@ Tiles tiles_of(const sbs_frame& f, int chunk, int ty, int cpl, bool tail) {
 // 1 us (8 disparities) or 1.9 us (16) per row, so a launch that cannot fill
 // the slots is as long as its longest item. Below an eighth of the slots the
 // smallest items win (384x288 grey 50 -> 27 us against 8 x 32 items, 640x480
-// 54 -> 28 us); then 16 disparities at rows that double as the launch grows
-// fourfold: 16 rows (1390x1110, block 21, dmax 63: 76 -> 63 us against 8 x
-// 32; 2560x1440: 167 -> 137 us; 8 frames of 640x480: 96 -> 86 us), 32 rows
-// (4096x2304: 357 -> 325 us; a serving mix of ten frames: 690 -> 629 us
-// against 8 x 64), 64 rows (8192x4608: 16 rows 1094, 64 rows 941 us; 6 frames
-// of 4096x2304 1.55 -> 1.42 ms against 128 rows), 96 rows (24 such frames:
-// 64 rows 5.39, 96 rows 5.36, 128 rows 5.44 ms), 128 rows beyond.
+// 54 -> 28 us); then 16 disparities at rows that grow with the launch: 16 rows
+// (1390x1110, block 21, dmax 63: 76 -> 63 us against 8 x 32; 8 frames of
+// 640x480: 96 -> 86 us), from three times the slots 32 rows (2976x2008, dmax
+// 125: 256 -> 240 us against 16 rows; 4096x2304: 357 -> 325 us; a serving mix
+// of ten frames: 690 -> 629 us against 8 x 64), 64 rows (8192x4608: 16 rows
+// 1094, 64 rows 941 us; 6 frames of 4096x2304 1.55 -> 1.42 ms against 128
+// rows), 96 rows (24 such frames: 64 rows 5.39, 96 rows 5.36, 128 rows 5.44
+// ms), 128 rows beyond. Between two and three times the slots, items of 16
+// disparities come out at little more than one round of either height, and
+// 8 x 32, as many as of 16 x 16 with half their window starts, share out
+// better (2552x1600, dmax 116: 16 x 16 197, 8 x 32 174, 16 x 32 194 us;
+// 3057x1762, dmax 102: 218, 206, 219; 3072x2304, dmax 74: 200, 206, 195).
 Plan default_plan(const sbs_frame* frames, int nframes) {
   int64_t n16 = 0;
   for (int i = 0; i < nframes; ++i)
@@ -203,8 +208,8 @@ Plan default_plan(const sbs_frame* frames, int nframes) {
   constexpr int64_t kSlots = 256 * 16;
   Plan p;
   p.wpc = 16;
-  p.chunk = n16 < kSlots / 8 ? 8 : 16;
-  p.ty = n16 < kSlots / 8 ? 8 : n16 < 4 * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
+  p.chunk = n16 < kSlots / 8 || (n16 >= 2 * kSlots && n16 < 3 * kSlots) ? 8 : 16;
+  p.ty = n16 < kSlots / 8 ? 8 : n16 < 2 * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
   return p;
 }
 
