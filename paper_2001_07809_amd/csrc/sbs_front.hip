@@ -1453,7 +1453,24 @@ struct LevelSel {
   int level;
   long long need;
 };
-__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need, int last = kLevels);
+// This thread's part of the level counts: loaded before anything is decided,
+// with the plan's own load (one after the other, and the hash counts after
+// them, were three round trips to memory at the start of each of five
+// launches); kept() holds the loads there.
+struct LevelCounts {
+  uint32_t v[kLvParts / 8];
+  __device__ __forceinline__ explicit LevelCounts(const uint32_t* lcount) {
+    // thread t adds up every 8th part of level t % 32
+    static_assert(kBlock == 8 * (kLevels + 1) && kLvParts % 8 == 0, "threads cover the levels eight times");
+#pragma unroll
+    for (int k = 0; k < kLvParts / 8; ++k) v[k] = lcount[threadIdx.x + 8 * (kLevels + 1) * k];
+  }
+  __device__ __forceinline__ void kept() const {
+#pragma unroll
+    for (int k = 0; k < kLvParts / 8; ++k) asm volatile("" ::"v"(v[k]));
+  }
+};
+__device__ __forceinline__ LevelSel level_pick(const LevelCounts& lc, long long need, int last = kLevels);
 
 // Planes 0 .. 3 of a map word lie side by side, plane 4 apart after them (it
 // is read for levels above 15 only). STAGE 0: levels 1 .. 15 of `from` (the
@@ -1473,11 +1490,13 @@ __global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, SizeSel 
                                                       unsigned long long* __restrict__ segor) {
   __shared__ uint32_t bins[kBins];
   uint32_t* cnt = bins;   // the levels' counts
+  const LevelCounts lc(lcount);
   const FcPlan plan = fc_plan(a);
+  if constexpr (STAGE == 1) lc.kept();
   if (plan.mode == 1) size_digit(b, z, STAGE, plan.need, bins);
   if (plan.mode != 2) return;
   if constexpr (STAGE == 1) {
-    if (level_pick(lcount, plan.need, kLvStage).level != 0) return;   // (other blocks may have added to the levels beyond)
+    if (level_pick(lc, plan.need, kLvStage).level != 0) return;   // (other blocks may have added to the levels beyond)
     far_segments(b, base, nseg, segor);
   }
   if ((int)blockIdx.x >= gx * gy) return;
@@ -1581,20 +1600,14 @@ __global__ __launch_bounds__(kBlock) void k_fc_levels(Bits b, FcArgs a, SizeSel 
 
 // Mode 2: the level of the want-th pixel and its rank within it, from the
 // counts of levels up to `last`; level 0: it lies further away than those.
-__device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long need, int last) {
+__device__ __forceinline__ LevelSel level_pick(const LevelCounts& lc, long long need, int last) {
   __shared__ unsigned long long sum[kLevels + 1];
   if (threadIdx.x <= kLevels) sum[threadIdx.x] = 0ull;
   __syncthreads();
-  // thread t adds up every 8th part of level t % 32
-  static_assert(kBlock == 8 * (kLevels + 1) && kLvParts % 8 == 0, "threads cover the levels eight times");
-  const int l = threadIdx.x % (kLevels + 1), p0 = threadIdx.x / (kLevels + 1);
-  uint32_t v[kLvParts / 8];
-#pragma unroll
-  for (int k = 0; k < kLvParts / 8; ++k) v[k] = lcount[(p0 + 8 * k) * (kLevels + 1) + l];
   unsigned long long s = 0ull;
 #pragma unroll
-  for (int k = 0; k < kLvParts / 8; ++k) s += v[k];
-  if (s) atomicAdd(&sum[l], s);
+  for (int k = 0; k < kLvParts / 8; ++k) s += lc.v[k];
+  if (s) atomicAdd(&sum[threadIdx.x % (kLevels + 1)], s);
   __syncthreads();
   LevelSel r{0, need};
   for (int k = 1; k <= last; ++k) {
@@ -1607,8 +1620,8 @@ __device__ __forceinline__ LevelSel level_pick(const uint32_t* lcount, long long
 }
 // ... and once the distance passes have run: they leave levels 1 (nearer than
 // the wanted distance) and 2 (at it) in the planes, and the rank in `far`.
-__device__ __forceinline__ LevelSel level_final(const uint32_t* lcount, const long long* far_need, long long need) {
-  LevelSel r = level_pick(lcount, need);
+__device__ __forceinline__ LevelSel level_final(const LevelCounts& lc, const long long* far_need, long long need) {
+  LevelSel r = level_pick(lc, need);
   if (r.level == 0) { r.level = 2; r.need = *far_need; }
   return r;
 }
@@ -1631,15 +1644,17 @@ __device__ __forceinline__ LevelWords level_words(const Bits& b, const unsigned 
 
 // Mode 2, the ring (other pixels at the wanted distance): counts of the top
 // kHashDigit bits of h, gathered in LDS, in kHashParts copies (one add to
-// memory per pixel into 2^14 bins took 26 us at 4096x2304, 14 us so).
-constexpr int kHashDigit = 8, kHashBins = 1 << kHashDigit, kHashParts = 8;
-static_assert(kHashBins == kBlock, "one bin per thread");
+// memory per pixel into 2^14 bins took 26 us at 4096x2304, 2^8 bins in LDS 16
+// us and left lists that do not fit the LDS of those that rank them; 2^10 bins
+// 11 us).
+constexpr int kHashDigit = 10, kHashBins = 1 << kHashDigit, kHashParts = 4;
+static_assert(kHashBins == 4 * kBlock, "four bins per thread");
 // f(i) for the block's ring pixels i: the words' set bits are queued in LDS
 // first and then taken by all threads alike, since a ring fills some words and
 // leaves most empty. `blocks` blocks take `chunk` words (at most kRingWords) in
 // turn, each after prepare(their first word).
 constexpr int kRingWords = kBlock;          // words a block queues at a time
-constexpr int kRingGroups = 4;              // of them per block in small images
+constexpr int kRingGroups = 2;              // of them per block in small images (4 leave half the CUs without a block at 4096x2304)
 template <typename P, typename F>
 __device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, int blocks,
                                          int chunk, P prepare, F f) {
@@ -1675,18 +1690,29 @@ __global__ __launch_bounds__(kBlock) void k_ring_bin(Bits b, FcArgs a, const uns
   __shared__ uint32_t bin_s, held;
   __shared__ long long need_s;
   __shared__ unsigned long long hold[kHold], at_s;
+  const LevelCounts lc(lcount);
+  uint32_t v[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int q = 0; q < kHashParts; ++q) {
+    const uint4 h = ((const uint4*)(hash_hist + q * kHashBins))[threadIdx.x];
+    v[0] += h.x; v[1] += h.y; v[2] += h.z; v[3] += h.w;
+  }
   const FcPlan pl = fc_plan(a);
+  lc.kept();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) asm volatile("" ::"v"(v[j]));
   if (pl.mode != 2) return;
   if (threadIdx.x == 0) held = 0u;
-  const LevelSel ls = level_final(lcount, far_need, pl.need);
-  uint32_t v = 0;
-#pragma unroll
-  for (int q = 0; q < kHashParts; ++q) v += hash_hist[q * kHashBins + threadIdx.x];
+  const LevelSel ls = level_final(lc, far_need, pl.need);
   uint32_t all;
-  const long long before = (long long)block_scan_excl<kBlock / 64>(v, wtot, all);
-  if (before < ls.need && ls.need <= before + (long long)v) {
-    bin_s = threadIdx.x;
-    need_s = ls.need - before;
+  long long before = (long long)block_scan_excl<kBlock / 64>(v[0] + v[1] + v[2] + v[3], wtot, all);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (before < ls.need && ls.need <= before + (long long)v[j]) {
+      bin_s = 4u * threadIdx.x + (uint32_t)j;
+      need_s = ls.need - before;
+    }
+    before += v[j];
   }
   __syncthreads();
   const unsigned long long bin = bin_s;
@@ -1777,13 +1803,15 @@ __global__ __launch_bounds__(kBlock) void k_fc_select(Bits b, FcArgs a, const un
   __shared__ uint32_t nsel;
   __shared__ unsigned long long tw[kSelWords], ow[kSelWords];
   if (threadIdx.x == 0) nsel = 0u;
+  const LevelCounts lc(lcount);
   const FcPlan pl = fc_plan(a);
+  lc.kept();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t w_begin = (int64_t)blockIdx.x * b.per, w_end = min(w_begin + b.per, b.words);
   uint32_t c = 0;
   __syncthreads();
   if (pl.mode == 2) {
-    const LevelSel ls = level_final(lcount, far_need, pl.need);
+    const LevelSel ls = level_final(lc, far_need, pl.need);
     const unsigned long long thr = ring_threshold(rb, ring);
     for (int64_t wi = w_begin + threadIdx.x; wi < w_end; wi += kBlock) {
       const LevelWords lw = level_words(b, planes, wi, ls.level);
@@ -2114,10 +2142,12 @@ __global__ __launch_bounds__(kBlock) void k_fc_columns(Bits b, FcArgs a, SizeSel
                                                        const uint32_t* lcount, int nseg,
                                                        const unsigned long long* segor, int32_t* g, int32_t* far) {
   __shared__ uint32_t bins[kBins];
+  const LevelCounts lc(lcount);
   const FcPlan pl = fc_plan(a);
+  lc.kept();
   if (pl.mode == 1) {
     if (z.top >= 2 * kDigit) size_digit(b, z, 2, pl.need, bins);
-  } else if (pl.mode == 2 && level_pick(lcount, pl.need).level == 0) {
+  } else if (pl.mode == 2 && level_pick(lc, pl.need).level == 0) {
     far_columns(b, base, nseg, segor, g);
     if (blockIdx.x == 0 && threadIdx.x == 0) *far = 1;
   }
@@ -2134,7 +2164,9 @@ __global__ __launch_bounds__(kBlock) void k_fc_count(Bits b, FcArgs a, SizeSel z
                                                      const uint32_t* lcount, unsigned long long* planes,
                                                      long long* far_need, uint32_t* hash_hist) {
   __shared__ uint32_t part, bins[kHashBins];
+  const LevelCounts lc(lcount);
   const FcPlan pl = fc_plan(a);
+  lc.kept();
   if (pl.mode == 1) {
     const RadixSel rs = size_found(z, pl.need);
     for (int64_t block = blockIdx.x; block < nb; block += gridDim.x)
@@ -2142,8 +2174,8 @@ __global__ __launch_bounds__(kBlock) void k_fc_count(Bits b, FcArgs a, SizeSel z
     return;
   }
   if (pl.mode != 2) return;
-  bins[threadIdx.x] = 0u;
-  const LevelSel ls = level_pick(lcount, pl.need);   // (its barriers order the bins)
+  for (int k = threadIdx.x; k < kHashBins; k += kBlock) bins[k] = 0u;
+  const LevelSel ls = level_pick(lc, pl.need);   // (its barriers order the bins)
   auto count = [&](uint32_t i) {
     atomicAdd(&bins[mix64((unsigned long long)i ^ a.seed) >> (64 - kHashDigit)], 1u);
   };
@@ -2175,7 +2207,8 @@ __global__ __launch_bounds__(kBlock) void k_fc_count(Bits b, FcArgs a, SizeSel z
   }
   __syncthreads();
   uint32_t* out = hash_hist + (blockIdx.x % kHashParts) * kHashBins;
-  if (bins[threadIdx.x]) atomicAdd(&out[threadIdx.x], bins[threadIdx.x]);
+  for (int k = threadIdx.x; k < kHashBins; k += kBlock)
+    if (bins[k]) atomicAdd(&out[k], bins[k]);
 }
 
 int fail(int st, const char* fmt, ...) {
