@@ -250,9 +250,9 @@ __global__ __launch_bounds__(kBlock) void k_clear(uint4* p, int64_t n) {
 // On a line a centre's bins are an interval (two centres part at their
 // midpoint, and equal ones leave all to the lower k), so a cluster's sums are
 // differences of the histogram's prefix sums at its ends; 64-bit LDS adds of
-// every bin to a few words queued up lane by lane. A pass is a chain of three
-// barriers (K = 10 at 1390x1110: 44 us with the adds, 31 us so; K = 4 at
-// 4096x2304: 13 and 8.6 us; at 640x480: 11 and 6.9 us).
+// every bin to a few words queued up lane by lane, five barriers a pass (K = 10
+// at 1390x1110: 44 us; K = 4 at 4096x2304: 13 us), three so (31 and 9 us), and
+// none where one wavefront can do it (8.5 and 4.5 us).
 __global__ __launch_bounds__(256) void k_kmeans(const uint32_t* __restrict__ hist, int32_t K,
                                                 uint8_t* __restrict__ lut, int32_t* __restrict__ passes_out) {
   __shared__ long long S[kMaxK], Nn[kMaxK];
@@ -807,11 +807,10 @@ __device__ __forceinline__ void uf_union(int32_t* parent, int32_t a, int32_t b) 
   }
 }
 
-// f(k, n) for every pair of a run of w (its k-th) and a run of the word u of
-// the row above (its n-th) that touch (8-connected, within the word), each at
-// the lane of the run of w's first pixel that touches it, so that the pairs
-// go side by side (a run start that took its run's pairs in turn: tiles 36 us,
-// edges 11 us at 4096x2304, 34 and 10 us so). w and u are the same in every
+// Every pair of a run of w (its k-th) and a run of the word u of the row above
+// (its n-th) that touch (8-connected, within the word), each at the lane of the
+// run of w's first pixel that touches it: f(lanes, k, n) is called by all lanes
+// with the lanes that have a pair, twice at most. w and u are the same in every
 // lane.
 template <typename F>
 __device__ __forceinline__ void for_touching(unsigned long long w, unsigned long long u, F f) {
@@ -820,37 +819,44 @@ __device__ __forceinline__ void for_touching(unsigned long long w, unsigned long
   const unsigned long long left = ws & u << 1;                       // run starts with the pixel up-left set ...
   const unsigned long long up = ws & u & ~(u << 1);                  // ... or not, but the one above
   const unsigned long long right = w & u >> 1 & ~u;                  // pixels with a run starting up-right
-  if (left | up) {
-    if (__builtin_amdgcn_inverse_ballot_w64(left | up)) f(kb, __builtin_amdgcn_inverse_ballot_w64(left) ? nb - 1 : nb);
-  }
-  if (right) {
-    if (__builtin_amdgcn_inverse_ballot_w64(right)) f(kb + (__builtin_amdgcn_inverse_ballot_w64(ws) ? 0 : -1), nb);
-  }
+  if (left | up) f(left | up, kb, __builtin_amdgcn_inverse_ballot_w64(left) ? nb - 1 : nb);
+  if (right) f(right, kb + (__builtin_amdgcn_inverse_ballot_w64(ws) ? 0 : -1), nb);
 }
 
-// One block per tile; wavefront w takes a band of rows, one per step, lane =
-// pixel, acting where runs touch. Bound by the chain of LDS round trips of the
-// unions, one row after another (bands of 8 rows instead of 4: 17 us at
-// 640x480 against 12).
+// One block per tile; wavefront w takes a band of rows. Its rows' runs and the
+// pairs that touch are queued in LDS first, a row at a time with lane = pixel,
+// and then taken 64 at a time: the unions and walks are chains of LDS round
+// trips, and row by row a band went through twelve of them, most lanes idle
+// (4096x2304: 35 -> 24 us, 640x480: 10 -> 7.5 us).
 constexpr int kCcBlock = 512, kBandH = kTileH / (kCcBlock / 64);
 __global__ __launch_bounds__(kCcBlock) void k_cc_tile(Bits b, const unsigned long long* __restrict__ B,
                                                     int32_t* __restrict__ parent, int32_t* __restrict__ size) {
+  constexpr int kPairs = kBandH * 64, kNodes = kBandH * 32;   // at most, per band
+  static_assert(kNodes % 64 == 0, "whole rounds of nodes");
   __shared__ int32_t lp[kTileH * 32], lsz[kTileH * 32];
   __shared__ unsigned long long last[kCcBlock / 64];   // each band's last row
+  __shared__ uint32_t pairs[kCcBlock / 64][kPairs];    // node | node above << 16
+  __shared__ uint32_t nodes[kCcBlock / 64][kNodes];    // node | pixels of the run << 16
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int c = blockIdx.x, y0 = blockIdx.y * kTileH + wv * kBandH, ly0 = wv * kBandH;
   const unsigned long long mine = lane < kBandH && y0 + lane < b.H ? B[(int64_t)(y0 + lane) * b.wpr + c] : 0ull;
+  auto below = [](unsigned long long m) {   // set bits below this lane
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  };
   unsigned long long w[kBandH];
+  int nn = 0, np = 0;
 #pragma unroll
   for (int j = 0; j < kBandH; ++j) {
     w[j] = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, j) |
            (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), j) << 32;
     const unsigned long long st = w[j] & ~(w[j] << 1);
     if (__builtin_amdgcn_inverse_ballot_w64(st)) {
-      const int n = (ly0 + j) * 32 + node_of(0, st);
+      const int k = below(st), n = (ly0 + j) * 32 + k;
       lp[n] = n;
       lsz[n] = 0;
+      nodes[wv][nn + k] = (uint32_t)n | (uint32_t)__builtin_popcountll(run_from(w[j], lane)) << 16;
     }
+    nn += __builtin_popcountll(st);
   }
   if (lane == 0) last[wv] = w[kBandH - 1];
   __syncthreads();
@@ -862,33 +868,35 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_tile(Bits b, const unsigned lon
     const unsigned long long u = j > 0 ? w[j > 0 ? j - 1 : 0] : above;
     if (!((w[j] | w[j] << 1 | w[j] >> 1) & u)) continue;
     const int row = (ly0 + j) * 32;
-    for_touching(w[j], u, [&](int k, int n) { lds_union(lp, row + k, row - 32 + n); });
+    for_touching(w[j], u, [&](unsigned long long lanes, int k, int n) {
+      if (__builtin_amdgcn_inverse_ballot_w64(lanes)) pairs[wv][np + below(lanes)] = (uint32_t)(row + k) | (uint32_t)(row - 32 + n) << 16;
+      np += __builtin_popcountll(lanes);
+    });
+  }
+  asm volatile("" ::: "memory");   // (a wavefront's LDS operations are done in the order it issues them)
+  for (int i = lane; i < np; i += 64) {
+    const uint32_t q = pairs[wv][i];
+    lds_union(lp, (int32_t)(q & 0xFFFFu), (int32_t)(q >> 16));
   }
   __syncthreads();
-  int32_t root[kBandH];
+  uint32_t node[kNodes / 64];
+  int32_t root[kNodes / 64];
 #pragma unroll
-  for (int j = 0; j < kBandH; ++j) {
-    const unsigned long long st = w[j] & ~(w[j] << 1);
-    root[j] = 0;
-    if (!st) continue;
-    if (__builtin_amdgcn_inverse_ballot_w64(st)) {
-      root[j] = lds_find(lp, (ly0 + j) * 32 + node_of(0, st));
-      atomicAdd(&lsz[root[j]], __builtin_popcountll(run_from(w[j], lane)));
-    }
+  for (int i = 0; i < kNodes / 64; ++i) {
+    if (64 * i + lane >= nn) continue;
+    node[i] = nodes[wv][64 * i + lane];
+    root[i] = lds_find(lp, (int32_t)(node[i] & 0xFFFFu));
+    atomicAdd(&lsz[root[i]], (int32_t)(node[i] >> 16));
   }
   __syncthreads();
   const int64_t w0 = (int64_t)blockIdx.y * kTileH * b.wpr + c;   // the tile's first word
 #pragma unroll
-  for (int j = 0; j < kBandH; ++j) {
-    const unsigned long long st = w[j] & ~(w[j] << 1);
-    if (!st) continue;
-    if (__builtin_amdgcn_inverse_ballot_w64(st)) {
-      const int k = node_of(0, st), n = (ly0 + j) * 32 + k;
-      const int64_t g = (w0 + (int64_t)(ly0 + j) * b.wpr) * 32 + k;
-      const int r = root[j];
-      parent[g] = (int32_t)((w0 + (int64_t)(r >> 5) * b.wpr) * 32 + (r & 31));
-      size[g] = r == n ? lsz[n] : 0;
-    }
+  for (int i = 0; i < kNodes / 64; ++i) {
+    if (64 * i + lane >= nn) continue;
+    const int n = (int)(node[i] & 0xFFFFu), r = root[i];
+    const int64_t g = (w0 + (int64_t)(n >> 5) * b.wpr) * 32 + (n & 31);
+    parent[g] = (int32_t)((w0 + (int64_t)(r >> 5) * b.wpr) * 32 + (r & 31));
+    size[g] = r == n ? lsz[n] : 0;
   }
 }
 
@@ -921,7 +929,10 @@ __global__ __launch_bounds__(kBlock) void k_cc_edges(Bits b, const unsigned long
            (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32;
   };
   const unsigned long long w = uniform(B[wi]), u = uniform(B[wi - b.wpr]);
-  for_touching(w, u, [&](int k, int n) { uf_union(parent, (int32_t)(32 * wi + k), (int32_t)(32 * (wi - b.wpr) + n)); });
+  for_touching(w, u, [&](unsigned long long lanes, int k, int n) {
+    if (__builtin_amdgcn_inverse_ballot_w64(lanes))
+      uf_union(parent, (int32_t)(32 * wi + k), (int32_t)(32 * (wi - b.wpr) + n));
+  });
 }
 
 // Every tile root's root, and the component sizes there: k_cc_tile left each
@@ -1176,8 +1187,8 @@ __global__ __launch_bounds__(1024) void k_root_find(Bits b, const unsigned long 
 
 // Kept pixels: those of components that pass the filter. A component's root
 // and size are looked up once per horizontal run and word, at the run's first
-// pixel; the runs that pass go out whole by one addition (adding a run's
-// start bit clears the run). kept (optional): kept pixels; base: kept pixels
+// pixel, 64 runs at a time from a queue in LDS (word by word, most
+// lanes idle: 22 us at 4096x2304, 15 us so); the runs that pass go out whole by one addition (adding a run's start bit clears the run). kept (optional): kept pixels; base: kept pixels
 // and border columns; refined (optional): the kept map as bytes; bsum
 // (optional): base pixels per block; n1 (optional): kept pixels off the
 // border columns, in kN1Parts counters (adds to one word from every block
@@ -1191,6 +1202,8 @@ __global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long lon
                                                  unsigned long long* base, uint8_t* refined, uint32_t* bsum,
                                                  unsigned long long* n1) {
   __shared__ uint32_t nsel, nkept;
+  __shared__ uint16_t runs[kBlock / 64][kWaveWords * 32];     // word << 11 | first bit << 5 | number in the word
+  __shared__ uint32_t pass[kBlock / 64][2 * kWaveWords];      // the first bits of the runs that pass
   if (threadIdx.x == 0) nsel = nkept = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -1199,29 +1212,31 @@ __global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long lon
   const int64_t w_end = min((int64_t)(blockIdx.x + 1) * b.per, b.words);
   for (int64_t w0 = (int64_t)blockIdx.x * b.per + kWaveWords * wv; w0 < w_end; w0 += kSelWords) {
     const WaveWords w = wave_words(b, B, w0, w_end);
-    int32_t r[kWaveWords], s[kWaveWords];
-    at_run_starts(w, w0, parent, -1, r);
-#pragma unroll
-    for (int j = 0; j < kWaveWords; ++j)
-      if (r[j] >= 0) r[j] = parent[r[j]];   // from the tile root to the root
+    if (lane < 2 * kWaveWords) pass[wv][lane] = 0u;
+    int nn = 0;
 #pragma unroll
     for (int j = 0; j < kWaveWords; ++j) {
-      s[j] = 0;
-      if (r[j] >= 0) s[j] = size[r[j]];
-    }
-    unsigned long long kv = 0ull;   // lane j: word j's kept pixels
-#pragma unroll
-    for (int j = 0; j < kWaveWords; ++j) {
-      const unsigned long long m = w.word(j);
+      const unsigned long long m = w.word(j), st = m & ~(m << 1);
       if (!m) continue;
-      const bool ok = r[j] >= 0 && (rule ? s[j] > s_star || (s[j] == s_star && r[j] >= first) : s[j] >= min_cc);
-      const unsigned long long k = m & ~(m + __builtin_amdgcn_ballot_w64(ok));
-      if (lane == j) kv = k;
-      if (n1) {
-        const int32_t n = node_of(w0 + j, m & ~(m << 1));
-        if (r[j] >= 0 && r[j] != n) size[n] = s[j];
+      if (__builtin_amdgcn_inverse_ballot_w64(st)) {
+        const int k = node_of(0, st);
+        runs[wv][nn + k] = (uint16_t)(j << 11 | lane << 5 | k);
       }
+      nn += __builtin_popcountll(st);
     }
+    asm volatile("" ::: "memory");   // (a wavefront's LDS operations are done in the order it issues them)
+    for (int i = lane; i < nn; i += 64) {
+      const uint32_t q = runs[wv][i], j = q >> 11, bit = q >> 5 & 63u;
+      const int32_t n = (int32_t)(32 * (w0 + j)) + (int32_t)(q & 31u);
+      const int32_t r = parent[parent[n]];   // from the tile root to the root
+      const int32_t s = size[r];
+      if (rule ? s > s_star || (s == s_star && r >= first) : s >= min_cc) atomicOr(&pass[wv][2 * j + (bit >> 5)], 1u << (bit & 31u));
+      if (n1 && r != n) size[n] = s;
+    }
+    asm volatile("" ::: "memory");
+    unsigned long long kv = 0ull;   // lane j: word j's kept pixels
+    if (lane < kWaveWords) kv = w.v & ~(w.v + ((unsigned long long)pass[wv][2 * lane + 1] << 32 | pass[wv][2 * lane]));
+    asm volatile("" ::: "memory");
     if (lane < kWaveWords && w0 + lane < w_end) {
       if (kept) kept[w0 + lane] = kv;
       base[w0 + lane] = kv | w.border;
