@@ -22,8 +22,71 @@ namespace sbs_post {
 
 constexpr int kRowThreads = 256;
 
+// A list in raster order (repeats side by side allowed), as the front end
+// writes it, is filled row by row from the list itself (k_rc_fill): each row's
+// entries are a piece of it, and no slot per pixel is cleared, scattered to
+// and read back (4096x2304: 49 -> 35 us,
+// three launches with nothing to do among them; other lists pay the check, 3
+// us, and the blocks' look at its flags). k_rc_check finds out: ok[block] for its piece of
+// `per` entries, and row_start[y], the first entry of row y or later (indexes
+// past the image count as row H). A block stops at its first descent, before
+// the rows of those entries are written: between entries in no order they
+// would be far apart.
+constexpr int kRcBlocks = 1024;   // at most: four flags per thread of the blocks that ask
+__global__ __launch_bounds__(256) void k_rc_check(const uint32_t* idx, int64_t n, int32_t W, int32_t H, int64_t per,
+                                                  int32_t* row_start, uint8_t* ok) {
+  const uint32_t N = (uint32_t)W * (uint32_t)H;
+  auto row = [&](uint32_t p) -> int { return p < N ? (int)(p / (uint32_t)W) : H; };
+  const int64_t k1 = min((blockIdx.x + 1) * per, n);
+  for (int64_t k0 = blockIdx.x * per; k0 < k1; k0 += 4 * 256) {
+    const int64_t k = k0 + 4 * (int)threadIdx.x;
+    const int m = (int)max(min(k1 - k, (int64_t)4), (int64_t)0);
+    uint32_t p[4] = {0u, 0u, 0u, 0u};
+    if (m == 4) {
+      __builtin_memcpy(p, idx + k, 16);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < m) p[j] = idx[k + j];
+    }
+    const uint32_t before = m > 0 && k > 0 ? idx[k - 1] : 0u;
+    bool down = m > 0 && p[0] < before;
+#pragma unroll
+    for (int j = 1; j < 4; ++j) down |= j < m && p[j] < p[j - 1];
+    if (__syncthreads_or(down)) {
+      if (threadIdx.x == 0) ok[blockIdx.x] = 0;
+      return;
+    }
+    int r = k > 0 ? row(before) : -1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j >= m) break;
+      const int to = row(p[j]);
+      while (r < to) row_start[++r] = (int32_t)(k + j);
+    }
+    if (m > 0 && k + m == n)
+      while (r < H) row_start[++r] = (int32_t)n;
+  }
+  if (threadIdx.x == 0) ok[blockIdx.x] = 1;
+}
+struct RcOrder {
+  const uint8_t* ok;   // null: not checked
+  int n;               // its flags
+  __device__ __forceinline__ bool ordered() const {   // (asked by whole blocks of 256 threads)
+    if (!ok) return false;
+    uint8_t v[kRcBlocks / 256];   // (past the last flag: that one again, so that the loads go together)
+#pragma unroll
+    for (int j = 0; j < kRcBlocks / 256; ++j) v[j] = ok[min((int)threadIdx.x + 256 * j, n - 1)];
+    bool all = true;
+#pragma unroll
+    for (int j = 0; j < kRcBlocks / 256; ++j) all &= v[j] != 0;
+    return __syncthreads_and(all);
+  }
+};
+
 // slot[p] = largest list position k with idx[k] == p (so a repeated index keeps its last value).
-__global__ __launch_bounds__(256) void k_rc_clear(int32_t* slot, int64_t N) {
+__global__ __launch_bounds__(256) void k_rc_clear(int32_t* slot, int64_t N, RcOrder o) {
+  if (o.ordered()) return;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x)
     slot[i] = -1;
 }
@@ -33,23 +96,155 @@ __global__ __launch_bounds__(256) void k_rc_clear(int32_t* slot, int64_t N) {
 // one), so a pixel holds one of its positions; then every entry whose
 // position is above what its pixel holds raises it with an atomic maximum,
 // which leaves the largest (only repeats that are not adjacent need one).
-__global__ __launch_bounds__(256) void k_rc_scatter(const uint32_t* idx, int64_t n, int64_t N, int32_t* slot) {
+__global__ __launch_bounds__(256) void k_rc_scatter(const uint32_t* idx, int64_t n, int64_t N, int32_t* slot,
+                                                    RcOrder o) {
+  if (o.ordered()) return;
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t p = idx[k];
     if ((int64_t)p < N && (k + 1 == n || idx[k + 1] != p)) slot[p] = (int32_t)k;
   }
 }
-__global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int64_t n, int64_t N, int32_t* slot) {
+__global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int64_t n, int64_t N, int32_t* slot,
+                                                        RcOrder o) {
+  if (o.ordered()) return;
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t p = idx[k];
     if ((int64_t)p < N && slot[p] < (int32_t)k) atomicMax(&slot[p], (int32_t)k);
   }
 }
 
-// Algorithm 1, one block of four wavefronts per row: a pixel strictly
-// between two consecutive listed pixels of the row that carry the same
-// disparity takes it. Each wavefront owns a quarter of the row's 64-pixel
-// chunks and walks them one pixel per lane (coalesced): a ballot marks a
+// Algorithm 1: a pixel strictly between two consecutive listed pixels of the
+// row that carry the same disparity takes it. Output: f[p] = disparity or -1
+// (undetermined).
+// Rows up to kFillW pixels, one wavefront per row: lane l holds the l-th 64
+// pixels' listed ones as a word and the number of listed pixels before it, and
+// the row's listed disparities lie side by side in LDS. A pixel's place among
+// them (bits up to its own) gives its neighbours' values with two LDS reads,
+// the same for every pixel, and nothing waits for another wavefront: a row is
+// a chain of four round trips to memory and some 64 steps of 64 pixels. A
+// block of four wavefronts per row, meeting at barriers, took as long whether
+// it worked this way or carried the nearest listed value from chunk to chunk
+// with lane shuffles, in both directions: 29 us at 4096x2304 against 22, 12.5 at 1390x1110 against 7.6.
+constexpr int kFillW = 4096;
+__global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, const uint32_t* idx, const uint8_t* disp,
+                                                         int32_t W, int32_t H, int16_t* f, RcOrder o,
+                                                         const int32_t* row_start) {
+  constexpr int kWaves = kRowThreads / 64;
+  __shared__ __attribute__((aligned(8))) uint32_t maps[kWaves][kFillW / 32];   // listed pixels (ordered lists)
+  __shared__ int pres[kWaves][kFillW / 64];
+  __shared__ int16_t vals[kWaves][kFillW + 2];   // -1, the row's listed disparities from left to right, -2
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t* map = maps[wv];
+  int* pre_s = pres[wv];
+  int16_t* val = vals[wv];
+  const int nch = (W + 63) >> 6;
+  // (a wavefront's LDS operations are done in the order it issues them)
+  auto in_order = [] { asm volatile("" ::: "memory"); };
+  const bool ordered = o.ordered();
+  for (int y = blockIdx.x * kWaves + wv; y < H; y += gridDim.x * kWaves) {
+    uint32_t lo = 0u, hi = 0u;   // this lane's word
+    int pre = 0, total = 0;      // listed pixels before it, and in the row
+    if (ordered) {
+      const uint32_t first = (uint32_t)y * (uint32_t)W;
+      const uint32_t k0 = __builtin_amdgcn_readfirstlane(row_start[y]), k1 = __builtin_amdgcn_readfirstlane(row_start[y + 1]);
+      *(uint2*)(map + 2 * lane) = uint2{0u, 0u};
+      in_order();
+      // (an entry's place is its number in the row if none repeats)
+      constexpr int kBatch = 12;   // (a list of 18% has 737 entries in a row of 4096 pixels)
+      for (uint32_t kb = k0 + lane; kb < k1; kb += 64 * kBatch) {
+        uint32_t x[kBatch];
+        int d[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const uint32_t k = min(kb + 64 * j, k1 - 1);   // past the last entry: that one again, so that the loads go together
+          x[j] = idx[k];
+          d[j] = disp[k];
+        }
+        in_order();
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const uint32_t k = kb + 64 * j, xx = x[j] - first;
+          if (k >= k1 || xx >= (uint32_t)W) continue;
+          atomicOr(&map[xx >> 5], 1u << (xx & 31));
+          if (k - k0 < (uint32_t)kFillW) val[1 + (k - k0)] = (int16_t)d[j];
+        }
+      }
+      in_order();
+      lo = map[2 * lane];
+      hi = map[2 * lane + 1];
+      const int c = __builtin_popcount(lo) + __builtin_popcount(hi);
+      int upto = c;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(upto, off);
+        if (lane >= off) upto += v;
+      }
+      pre = upto - c;
+      total = __builtin_amdgcn_readlane(upto, 63);
+      if ((uint32_t)total != k1 - k0) {
+        // repeats: the last of each run, at its pixel's place
+        pre_s[lane] = pre;
+        in_order();
+        for (uint32_t k = k0 + lane; k < k1; k += 64) {
+          const uint32_t p = idx[k], xx = p - first;
+          if (xx >= (uint32_t)W || (k + 1 < k1 && idx[k + 1] == p)) continue;
+          const uint32_t w = xx >> 5;
+          const int at = pre_s[xx >> 6] + ((w & 1) ? __builtin_popcount(map[w - 1]) : 0) +
+                         __builtin_popcount(map[w] & ((1u << (xx & 31)) - 1u));
+          val[1 + at] = (int16_t)disp[k];
+        }
+      }
+    } else {
+      const int32_t* srow = slot + (int64_t)y * W;
+      constexpr int kBatch = 16;   // 64-pixel words in flight
+      for (int g = 0; g < nch; g += kBatch) {
+        int v[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const int x = ((g + j) << 6) + lane;
+          v[j] = x < W ? srow[x] : -1;   // slot here, disparity below
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) v[j] = v[j] >= 0 ? (int)disp[v[j]] : -1;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const uint64_t m = __builtin_amdgcn_ballot_w64(v[j] >= 0);
+          const uint32_t ml = (uint32_t)m, mh = (uint32_t)(m >> 32);
+          if (v[j] >= 0) val[1 + total + __builtin_amdgcn_mbcnt_hi(mh, __builtin_amdgcn_mbcnt_lo(ml, 0u))] = (int16_t)v[j];
+          if (lane == g + j) { lo = ml; hi = mh; pre = total; }
+          total += __builtin_popcountll(m);
+        }
+      }
+    }
+    if (lane == 0) { val[0] = -1; val[total + 1] = -2; }
+    in_order();
+    int16_t* frow = f + (int64_t)y * W;
+    // (kStep words side by side: one at a time, their LDS reads were a chain)
+    constexpr int kStep = 8;
+    for (int c = 0; c < nch; c += kStep) {
+      int left[kStep], right[kStep];
+      uint64_t m[kStep];
+#pragma unroll
+      for (int j = 0; j < kStep; ++j) {
+        const uint32_t ml = __builtin_amdgcn_readlane(lo, c + j), mh = __builtin_amdgcn_readlane(hi, c + j);
+        const int before = __builtin_amdgcn_readlane(pre, c + j) + (int)__builtin_amdgcn_mbcnt_hi(mh, __builtin_amdgcn_mbcnt_lo(ml, 0u));
+        m[j] = (uint64_t)mh << 32 | ml;
+        left[j] = val[before];
+        right[j] = val[before + 1];   // its own value if it is listed
+      }
+#pragma unroll
+      for (int j = 0; j < kStep; ++j) {
+        const int x = ((c + j) << 6) + lane;
+        const int v = __builtin_amdgcn_inverse_ballot_w64(m[j]) || left[j] == right[j] ? right[j] : -1;
+        if (x < W) frow[x] = (int16_t)v;
+      }
+    }
+    in_order();   // the next row rewrites the tables
+  }
+}
+
+// Wider rows, one block of four wavefronts per row: each owns a quarter of the
+// row's 64-pixel chunks and walks them one pixel per lane: a ballot marks a
 // chunk's listed pixels, the nearest one at or left of each lane comes from
 // the mask's bits up to the lane (its value by a lane shuffle), and the last
 // listed value of the chunks before is carried as a wave-uniform value. A
@@ -58,10 +253,9 @@ __global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int
 // quarter's first and last listed values; after an exchange through LDS a
 // right-to-left pass finds the nearest listed pixel on the right the same
 // way, takes the one on the left from the quarters before where it was
-// missing, and decides. Output: f[p] = disparity or -1 (undetermined).
-constexpr int kFillChunks = 16;   // 64-pixel chunks per quarter held in registers (rows up to 4096 pixels)
-__global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, const uint8_t* disp, int32_t W,
-                                                           int32_t H, int16_t* f) {
+// missing, and decides.
+__global__ __launch_bounds__(kRowThreads) void k_rc_fill_wide(const int32_t* slot, const uint8_t* disp, int32_t W,
+                                                              int32_t H, int16_t* f) {
   constexpr int kWaves = kRowThreads / 64;
   __shared__ int q_first[kWaves], q_last[kWaves];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -69,57 +263,6 @@ __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, co
   const int c0 = min(wv * per, nch), c1 = min(c0 + per, nch);
   const uint64_t upto = (2ull << lane) - 1ull;    // bits 0 .. lane
   const uint64_t from = ~((1ull << lane) - 1ull); // bits lane .. 63
-  if (per <= kFillChunks) {
-    // a quarter of at most kFillChunks chunks: its slots are loaded at once,
-    // then its disparities, and both passes run on registers (one round trip
-    // to memory for each, and the row is written once)
-    for (int y = blockIdx.x; y < H; y += gridDim.x) {
-      const int32_t* srow = slot + (int64_t)y * W;
-      int16_t* frow = f + (int64_t)y * W;
-      int v[kFillChunks];
-#pragma unroll
-      for (int i = 0; i < kFillChunks; ++i) {
-        const int x = ((c0 + i) << 6) + lane;
-        v[i] = (c0 + i < c1 && x < W) ? srow[x] : -1;   // slot here, disparity below
-      }
-#pragma unroll
-      for (int i = 0; i < kFillChunks; ++i) v[i] = v[i] >= 0 ? (int)disp[v[i]] : -1;
-      int lft[kFillChunks];   // nearest listed value at or left of the pixel within the quarter, -2: none
-      int carry = -2, first = -1;
-#pragma unroll
-      for (int i = 0; i < kFillChunks; ++i) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(v[i] >= 0);
-        const uint64_t b = m & upto;
-        const int left = __shfl(v[i], b ? 63 - __builtin_clzll(b) : 0);
-        lft[i] = b ? left : carry;
-        if (m) {
-          if (first < 0) first = __shfl(v[i], __builtin_ctzll(m));
-          carry = __shfl(v[i], 63 - __builtin_clzll(m));
-        }
-      }
-      if (lane == 0) { q_first[wv] = first; q_last[wv] = carry < 0 ? -1 : carry; }
-      __syncthreads();
-      int cl = -1, cr = -1;   // nearest listed value in the quarters to the left / right
-      for (int j = wv - 1; j >= 0 && cl < 0; --j) cl = q_last[j];
-      for (int j = wv + 1; j < kWaves && cr < 0; ++j) cr = q_first[j];
-      __syncthreads();   // the next row rewrites q_first / q_last
-      carry = cr;
-#pragma unroll
-      for (int i = kFillChunks - 1; i >= 0; --i) {
-        const int x = ((c0 + i) << 6) + lane;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(v[i] >= 0);
-        const uint64_t b = m & from;
-        const int right = b ? __shfl(v[i], __builtin_ctzll(b)) : carry;
-        if (c0 + i < c1 && x < W) {
-          int left = lft[i];
-          if (left == -2) left = cl;
-          frow[x] = (int16_t)(v[i] >= 0 ? v[i] : ((left >= 0 && left == right) ? left : -1));
-        }
-        if (m) carry = __shfl(v[i], __builtin_ctzll(m));
-      }
-    }
-    return;
-  }
   for (int y = blockIdx.x; y < H; y += gridDim.x) {
     const int32_t* srow = slot + (int64_t)y * W;
     int16_t* frow = f + (int64_t)y * W;
@@ -171,10 +314,10 @@ __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, co
 // short walks fill the chip better than fewer long ones; more for images
 // over 1M rows so the segments fit the grid), one thread per
 // (column, segment): k_rc_colseg records each segment's topmost and
-// bottommost determined value, k_rc_chunks / k_rc_colscan / k_rc_segscan
-// turn those records into the nearest determined value above and below each
-// segment (scans down and up each column over chunk summaries, so a column
-// with few determined pixels costs O(nseg), not O(nseg^2)), and k_rc_peek
+// bottommost determined value, k_rc_carry turns those records into the
+// nearest determined value above and below each segment (scans down and up
+// each column, so a column with few determined pixels costs O(nseg), not
+// O(nseg^2)), and k_rc_peek
 // resolves the segment's rows in two passes
 // (threads of a block cover adjacent columns, so every row access is
 // coalesced).
@@ -213,99 +356,78 @@ __global__ __launch_bounds__(256) void k_rc_colseg(const int16_t* f, int32_t W, 
 
 // In place: seg_last[sg] becomes the nearest determined value above segment
 // sg (the last one of the segments before it), seg_first[sg] the nearest
-// below it (the first one of the segments after it); -1 where none. Three
-// launches over chunks of kScanBatch segments: k_rc_chunks sums up each
-// chunk (its last and first determined value; one thread per column and
-// chunk), k_rc_colscan turns the summaries into the same nearest values per
-// chunk (one thread per column, a pass down and one up, kScanBatch records
-// in flight), and k_rc_segscan rewrites each chunk's records from its
-// chunk's carries (one thread per column and chunk). A column's sequential
-// work is its chunk count, a sixteenth of its segment count.
-constexpr int kScanBatch = 16;
-__global__ __launch_bounds__(256) void k_rc_chunks(int32_t W, int32_t nseg, const int16_t* seg_first,
-                                                   const int16_t* seg_last, int16_t* ch_first, int16_t* ch_last) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int c = blockIdx.y;
-  if (x >= W) return;
-  const int s0 = c * kScanBatch;
+// below it (the first one of the segments after it); -1 where none. A block
+// takes 64 columns, lane = column, and its 16 wavefronts a sixteenth of the
+// segments each: every wavefront sums its part up (last and first determined
+// value), takes what the others' summaries leave above and below it, and
+// rewrites its part, kept in registers where it is at most kScanBatch
+// segments, else read again kScanBatch at a time. (Three launches over chunks
+// of 16 segments took 12 us at 4096x2304, 6.5 us so.)
+constexpr int kScanBatch = 16, kScanWaves = 16;
+__global__ __launch_bounds__(64 * kScanWaves) void k_rc_carry(int32_t W, int32_t nseg, int16_t* seg_first,
+                                                              int16_t* seg_last) {
+  __shared__ int16_t sum_first[kScanWaves][64], sum_last[kScanWaves][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int x = min((int)blockIdx.x * 64 + lane, W - 1);
+  const bool mine = (int)blockIdx.x * 64 + lane < W;
+  const int per = (nseg + kScanWaves - 1) / kScanWaves;
+  const int s0 = min(wv * per, nseg), s1 = min(s0 + per, nseg);
   int16_t vl[kScanBatch], vf[kScanBatch];
-#pragma unroll
-  for (int k = 0; k < kScanBatch; ++k) {
-    const bool in = s0 + k < nseg;
-    vl[k] = in ? seg_last[(int64_t)(s0 + k) * W + x] : (int16_t)-1;
-    vf[k] = in ? seg_first[(int64_t)(s0 + k) * W + x] : (int16_t)-1;
-  }
   int16_t last = -1, first = -1;
-#pragma unroll
-  for (int k = 0; k < kScanBatch; ++k) {
-    if (vl[k] >= 0) last = vl[k];
-    if (first < 0 && vf[k] >= 0) first = vf[k];
-  }
-  ch_last[(int64_t)c * W + x] = last;
-  ch_first[(int64_t)c * W + x] = first;
-}
-
-// In place over n records of each column: last[i] becomes the last
-// non-negative value of records 0 .. i - 1, first[i] the first of records
-// i + 1 .. n - 1 (-1 where none). Records are read kScanBatch at a time
-// before any of them is written.
-__global__ __launch_bounds__(256) void k_rc_colscan(int32_t W, int32_t n, int16_t* first, int16_t* last) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= W) return;
-  int16_t carry = -1;
-  for (int s0 = 0; s0 < n; s0 += kScanBatch) {
-    int16_t v[kScanBatch];
-#pragma unroll
-    for (int k = 0; k < kScanBatch; ++k) v[k] = s0 + k < n ? last[(int64_t)(s0 + k) * W + x] : (int16_t)-1;
+  for (int s = s0; s < s1; s += kScanBatch) {
 #pragma unroll
     for (int k = 0; k < kScanBatch; ++k) {
-      if (s0 + k >= n) break;
-      last[(int64_t)(s0 + k) * W + x] = carry;
-      if (v[k] >= 0) carry = v[k];
+      const bool in = s + k < s1;
+      vl[k] = in ? seg_last[(int64_t)(s + k) * W + x] : (int16_t)-1;
+      vf[k] = in ? seg_first[(int64_t)(s + k) * W + x] : (int16_t)-1;
     }
-  }
-  carry = -1;
-  for (int s1 = n - 1; s1 >= 0; s1 -= kScanBatch) {   // records s1, s1 - 1, ...
-    int16_t v[kScanBatch];
-#pragma unroll
-    for (int k = 0; k < kScanBatch; ++k) v[k] = s1 - k >= 0 ? first[(int64_t)(s1 - k) * W + x] : (int16_t)-1;
 #pragma unroll
     for (int k = 0; k < kScanBatch; ++k) {
-      if (s1 - k < 0) break;
-      first[(int64_t)(s1 - k) * W + x] = carry;
-      if (v[k] >= 0) carry = v[k];
+      if (vl[k] >= 0) last = vl[k];
+      if (first < 0 && vf[k] >= 0) first = vf[k];
     }
   }
-}
-
-__global__ __launch_bounds__(256) void k_rc_segscan(int32_t W, int32_t nseg, int16_t* seg_first, int16_t* seg_last,
-                                                    const int16_t* ch_first, const int16_t* ch_last) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int c = blockIdx.y;
-  if (x >= W) return;
-  const int s0 = c * kScanBatch;
-  int16_t vl[kScanBatch], vf[kScanBatch];
+  sum_first[wv][lane] = first;
+  sum_last[wv][lane] = last;
+  __syncthreads();
+  int16_t above = -1, below = -1;
 #pragma unroll
-  for (int k = 0; k < kScanBatch; ++k) {
-    const bool in = s0 + k < nseg;
-    vl[k] = in ? seg_last[(int64_t)(s0 + k) * W + x] : (int16_t)-1;
-    vf[k] = in ? seg_first[(int64_t)(s0 + k) * W + x] : (int16_t)-1;
+  for (int j = 0; j < kScanWaves; ++j) {
+    const int16_t l = sum_last[j][lane], d = sum_first[kScanWaves - 1 - j][lane];
+    if (j < wv && l >= 0) above = l;
+    if (kScanWaves - 1 - j > wv && d >= 0) below = d;
   }
-  // the last determined value of the chunks before this one, the first of
-  // those after it (one chunk: none)
-  int16_t above = gridDim.y > 1 ? ch_last[(int64_t)c * W + x] : (int16_t)-1;
-  int16_t below = gridDim.y > 1 ? ch_first[(int64_t)c * W + x] : (int16_t)-1;
+  const bool held = per <= kScanBatch;
+  for (int s = s0; s < s1; s += kScanBatch) {
+    if (!held) {
 #pragma unroll
-  for (int k = 0; k < kScanBatch; ++k) {
-    if (s0 + k >= nseg) break;
-    seg_last[(int64_t)(s0 + k) * W + x] = above;
-    if (vl[k] >= 0) above = vl[k];
+      for (int k = 0; k < kScanBatch; ++k) vl[k] = s + k < s1 ? seg_last[(int64_t)(s + k) * W + x] : (int16_t)-1;
+    }
+#pragma unroll
+    for (int k = 0; k < kScanBatch; ++k) {
+      if (s + k >= s1) break;
+      if (mine) seg_last[(int64_t)(s + k) * W + x] = above;
+      if (vl[k] >= 0) above = vl[k];
+    }
   }
+  for (int s = s1 - 1; s >= s0; s -= kScanBatch) {   // held: vf[k] is segment s0 + k; else vf[k] is s - k
+    if (held) {
 #pragma unroll
-  for (int k = kScanBatch - 1; k >= 0; --k) {
-    if (s0 + k >= nseg) continue;
-    seg_first[(int64_t)(s0 + k) * W + x] = below;
-    if (vf[k] >= 0) below = vf[k];
+      for (int k = kScanBatch - 1; k >= 0; --k) {
+        if (s0 + k >= s1) continue;
+        if (mine) seg_first[(int64_t)(s0 + k) * W + x] = below;
+        if (vf[k] >= 0) below = vf[k];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kScanBatch; ++k) vf[k] = s - k >= s0 ? seg_first[(int64_t)(s - k) * W + x] : (int16_t)-1;
+#pragma unroll
+      for (int k = 0; k < kScanBatch; ++k) {
+        if (s - k < s0) break;
+        if (mine) seg_first[(int64_t)(s - k) * W + x] = below;
+        if (vf[k] >= 0) below = vf[k];
+      }
+    }
   }
 }
 
@@ -316,7 +438,7 @@ __global__ __launch_bounds__(256) void k_rc_peek(const int16_t* f, int32_t W, in
   const int sg = blockIdx.y;
   if (x >= W) return;
   const int y0 = sg * seglen, y1 = min(y0 + seglen, H);
-  // nearest determined value above the segment, and below it (k_rc_segscan)
+  // nearest determined value above the segment, and below it (k_rc_carry)
   int16_t last = above_seg[(int64_t)sg * W + x];
   int16_t below = below_seg[(int64_t)sg * W + x];
   auto resolve = [&](int a, int b) -> uint8_t {
@@ -1045,7 +1167,7 @@ extern "C" {
 size_t sbs_reconstruct_workspace_bytes(int32_t W, int32_t H) {
   if (W < 1 || H < 1) return 0;
   const size_t N = (size_t)W * H;
-  return align256(N * 4) + align256(N * 2) + align256(N * 2);
+  return align256(N * 4) + align256(N * 2) + align256(N * 2) + align256(((size_t)H + 1) * 4) + kRcBlocks;
 }
 
 int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t W, int32_t H, int32_t threshold,
@@ -1061,34 +1183,35 @@ int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t
   int32_t* slot = (int32_t*)base;
   int16_t* f = (int16_t*)(base + align256(N * 4));
   int16_t* up = (int16_t*)(base + align256(N * 4) + align256(N * 2));
-  hipLaunchKernelGGL(k_rc_clear, dim3(1024), dim3(256), 0, s, slot, N);
+  int32_t* row_start = (int32_t*)(base + align256(N * 4) + 2 * align256(N * 2));
+  RcOrder o{nullptr, 0};
+  // (wider rows are filled from slots)
+  if (n > 0 && W <= kFillW) {
+    const int64_t per = ((n + kRcBlocks - 1) / kRcBlocks + 1023) / 1024 * 1024;
+    uint8_t* ok = (uint8_t*)row_start + align256(((size_t)H + 1) * 4);
+    o = RcOrder{ok, (int)((n + per - 1) / per)};
+    hipLaunchKernelGGL(k_rc_check, dim3(o.n), dim3(256), 0, s, idx, n, W, H, per, row_start, ok);
+  }
+  hipLaunchKernelGGL(k_rc_clear, dim3(1024), dim3(256), 0, s, slot, N, o);
   if (n > 0) {
     const unsigned sg = (unsigned)std::min<int64_t>((n + 1023) / 1024, 2048);
-    hipLaunchKernelGGL(k_rc_scatter, dim3(sg), dim3(256), 0, s, idx, n, N, slot);
-    hipLaunchKernelGGL(k_rc_scatter_max, dim3(sg), dim3(256), 0, s, idx, n, N, slot);
+    hipLaunchKernelGGL(k_rc_scatter, dim3(sg), dim3(256), 0, s, idx, n, N, slot, o);
+    hipLaunchKernelGGL(k_rc_scatter_max, dim3(sg), dim3(256), 0, s, idx, n, N, slot, o);
   }
-  hipLaunchKernelGGL(k_rc_fill, dim3(H < 65536 ? H : 65536), dim3(kRowThreads), 0, s, slot, disp, W, H, f);
-  // The column pass's segment records and their chunk summaries reuse the
-  // slot array (no longer read after k_rc_fill): 2 x (nseg + nch) x W int16,
-  // within its 4 x W x H bytes (summaries only when nch > 1, i.e. H > 256:
-  // then nseg + nch <= H / 16 + H / 256 + 2 < H).
+  const dim3 rows(H < 65536 ? H : 65536);
+  if (W <= kFillW)
+    hipLaunchKernelGGL(k_rc_fill, dim3((rows.x + 3) / 4), dim3(kRowThreads), 0, s, slot, idx, disp, W, H, f, o, row_start);
+  else
+    hipLaunchKernelGGL(k_rc_fill_wide, rows, dim3(kRowThreads), 0, s, slot, disp, W, H, f);
+  // The column pass's segment records reuse the slot array (no longer read
+  // after k_rc_fill): 2 x nseg x W int16, within its 4 x W x H bytes.
   const int seglen = std::max(kColSeg, (H + 65534) / 65535);
   const int nseg = (H + seglen - 1) / seglen;
   int16_t* seg_first = (int16_t*)slot;
   int16_t* seg_last = seg_first + (int64_t)nseg * W;
   const dim3 cg((W + 255) / 256, nseg);
   hipLaunchKernelGGL(k_rc_colseg, cg, dim3(256), 0, s, f, W, H, seglen, seg_first, seg_last);
-  // chunk summaries after the segment records, still inside the slot array
-  const int nch = (nseg + kScanBatch - 1) / kScanBatch;
-  int16_t* ch_first = seg_last + (int64_t)nseg * W;
-  int16_t* ch_last = ch_first + (int64_t)nch * W;
-  const dim3 chg((W + 255) / 256, nch);
-  // (one chunk: no carries to take, and no room needed for summaries)
-  if (nch > 1) {
-    hipLaunchKernelGGL(k_rc_chunks, chg, dim3(256), 0, s, W, nseg, seg_first, seg_last, ch_first, ch_last);
-    hipLaunchKernelGGL(k_rc_colscan, dim3((W + 255) / 256), dim3(256), 0, s, W, nch, ch_first, ch_last);
-  }
-  hipLaunchKernelGGL(k_rc_segscan, chg, dim3(256), 0, s, W, nseg, seg_first, seg_last, ch_first, ch_last);
+  hipLaunchKernelGGL(k_rc_carry, dim3((unsigned)(((int64_t)W + 63) / 64)), dim3(64 * kScanWaves), 0, s, W, nseg, seg_first, seg_last);
   hipLaunchKernelGGL(k_rc_peek, cg, dim3(256), 0, s, f, W, H, threshold, seglen, seg_last, seg_first, up, out_map);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SBS_ERR_HIP, "reconstruct: %s", hipGetErrorString(e));

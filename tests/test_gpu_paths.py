@@ -267,3 +267,21 @@ def test_kmeans_level_ranges(torch, sbs, K):
             img = used[rng.integers(0, used.size, (40, 70))].astype(np.uint8)
             img[0, :2] = lo, lo + span - 1
             check_front(torch, sbs, dev(torch, img), img, K, 0, 5, f"K {K}, {used.size} levels of {span} from {lo}")
+
+
+@pytest.mark.parametrize("W,H,n", [(1, 9, 5), (64, 5, 40), (65, 7, 1024), (4095, 6, 5000), (4096, 300, 1100000)])
+def test_reconstruct_lists_in_order_and_not(torch, sbs, W, H, n):
+    """Lists in raster order, with repeats and entries past the image, and the
+    same ones with a single descent: at the start, at the end, at the edges of
+    the 1024 entries a block checks at a time and where blocks meet."""
+    rng = np.random.default_rng(n)
+    idx = np.sort(rng.integers(0, W * H + 3, n)).astype(np.uint32)
+    disp = rng.integers(0, 3, n).astype(np.uint8)
+    at = [None] + [k for k in (1, 1023, 1024, 2048, n - 1) if 0 < k < n]
+    for k in at:
+        p = idx.copy()
+        if k is not None:
+            p[k - 1], p[k] = max(int(p[k - 1]), 1), 0
+        exp = oracle.reconstruct(p, disp, W, H, 1)
+        got = sbs.reconstruct(dev(torch, p.view(np.int32)), dev(torch, disp), W, H, 1).cpu().numpy()
+        assert np.array_equal(got, exp), f"{W}x{H}, {n} entries, descent at {k}: {(got != exp).sum()} pixels differ"
