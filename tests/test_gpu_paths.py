@@ -285,3 +285,22 @@ def test_reconstruct_lists_in_order_and_not(torch, sbs, W, H, n):
         exp = oracle.reconstruct(p, disp, W, H, 1)
         got = sbs.reconstruct(dev(torch, p.view(np.int32)), dev(torch, disp), W, H, 1).cpu().numpy()
         assert np.array_equal(got, exp), f"{W}x{H}, {n} entries, descent at {k}: {(got != exp).sum()} pixels differ"
+
+
+@pytest.mark.parametrize("C", [1, 3])
+def test_blur_edge_tiles(torch, sbs, C):
+    """Images narrower than a group of four pixels, than a tile, and around the
+    widths where a tile becomes an interior one, at odd addresses and pitches:
+    every column of the edge tiles' clamped groups."""
+    rng = np.random.default_rng(C)
+    for W in (1, 2, 3, 4, 5, 9, 63, 66, 72, 73, 76, 77, 135, 140):
+        for H, pad, off in ((1, 0, 0), (35, 1, 1), (40, 4, 3)):
+            pitch = W * C + pad
+            buf = rng.integers(0, 256, off + H * pitch, dtype=np.uint8)
+            rows = buf[off:].reshape(H, pitch)[:, :W * C].reshape((H, W, C) if C == 3 else (H, W))
+            depth = rng.integers(0, 4, (H, W)).astype(np.uint8)
+            d = dev(torch, buf)
+            view = torch.as_strided(d, (H, W, C) if C == 3 else (H, W), (pitch, C, 1) if C == 3 else (pitch, 1), off)
+            got = sbs.selective_blur(view, dev(torch, depth), [(1, 1)], 2.0).cpu().numpy()
+            exp = oracle.blur(np.ascontiguousarray(rows), depth, [(1, 1)], 2.0)
+            assert np.abs(got - exp).max() <= 1e-3, f"{W}x{H}x{C} pitch {pitch} offset {off}"
