@@ -20,8 +20,8 @@
 
 namespace sbs {
 hipError_t launch_put_desc(FrameDev* table, const FrameDev* host, int nframes, hipStream_t s);
-hipError_t launch_prologue(const FrameDev* table, int f0, int nf, int max_rows, int64_t max_n, WsHeader* hdr,
-                           hipStream_t s);
+hipError_t launch_prologue(const FrameDev* table, int nf, int max_rows, int64_t max_n, WsHeader* hdr, hipStream_t s);
+hipError_t launch_prologue_one(const FrameDev& f, FrameDev* entry, WsHeader* hdr, hipStream_t s);
 hipError_t launch_finalize(const FrameDev* table, int f0, int nf, hipStream_t s);
 hipError_t launch_tile_grid(const FrameDev* table, int fi, int64_t nitems, int chunk, bool wide, hipStream_t s);
 hipError_t launch_tile_persistent(const FrameDev* table, int nframes, const QueueTotals& totals, int chunk, bool wide,
@@ -454,12 +454,11 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     max_rows = std::max(max_rows, L.ph);
     max_n = std::max(max_n, f.n);
   }
-  hipError_t e = launch_put_desc(table, host.data(), nframes, s);
-  if (e != hipSuccess) return hip_fail(e, "descriptor upload");
+  hipError_t e = hipSuccess;
   if (mode == kPerFrame || mode == kSingle) {
     for (int i = 0; i < nframes; ++i) {
       if (frames[i].n == 0) continue;
-      e = launch_prologue(table, i, 1, host[(size_t)i].ph, frames[i].n, hdr, s);
+      e = launch_prologue_one(host[(size_t)i], table + i, hdr, s);
       if (e != hipSuccess) return hip_fail(e, "prologue");
       hipEvent_t ev = nullptr;
       if (timed) timing_begin(s, &ev);
@@ -470,7 +469,9 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
       if (e != hipSuccess) return hip_fail(e, "finalize");
     }
   } else {
-    e = launch_prologue(table, 0, nframes, max_rows, max_n, hdr, s);
+    e = launch_put_desc(table, host.data(), nframes, s);
+    if (e != hipSuccess) return hip_fail(e, "descriptor upload");
+    e = launch_prologue(table, nframes, max_rows, max_n, hdr, s);
     if (e != hipSuccess) return hip_fail(e, "prologue");
     const bool wide = std::find(cpl.begin(), cpl.end(), 8) != cpl.end();
     // wide launches hold at most 12 wavefronts per CU (3 per SIMD)

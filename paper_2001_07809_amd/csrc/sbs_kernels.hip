@@ -7,19 +7,20 @@
 // the same rows, with replicate padding and ties to the smaller d.
 //
 // Tiled path (per frame; every kernel also runs over a whole batch of frames):
-//   k_check     clears the result keys, answers indices >= W*H, finds out
-//               whether the list is in strictly increasing raster order
-//               (a repeated index sends it down the pixel-map path), and for
-//               each row and tile column the first list slot at or after the
-//               tile's first pixel (read by the tile kernel on ordered lists).
-//   k_prep      replicate-padded RGBx copy of the right image (one u32 per
+//   k_prep      two parts side by side. The list's: clears the result keys,
+//               answers indices >= W*H, finds out whether the list is in
+//               strictly increasing raster order (a repeated index sends it
+//               down the pixel-map path), and for each row and tile column the
+//               first list slot at or after the tile's first pixel (read by
+//               the tile kernel on ordered lists). The images': a
+//               replicate-padded RGBx copy of the right image (one u32 per
 //               pixel, so one v_sad_u8 covers all channels of a pixel), and of
 //               the left image: whole, or only the edge bands that tiles
 //               reaching past an image edge read (RGB images in 4-byte-aligned
-//               rows, which the other tiles read in place). For an unordered
-//               list it also clears the pixel->slot map and row bits.
-//   k_scatter   unordered lists: map[p] = a slot k with idx[k] == p, and
-//               per row one bit per 64-column group that holds a listed pixel.
+//               rows, which the other tiles read in place).
+//   k_clear_map, k_scatter  unordered lists: map[p] = a slot k with
+//               idx[k] == p, and per row one bit per 64-column group that
+//               holds a listed pixel.
 //   k_tile_*    the column-sum kernel. One wavefront owns a tile of output
 //               columns x rows and a chunk of disparities. Each lane owns four
 //               adjacent window columns. Walking down the tile's rows it keeps,
@@ -63,9 +64,10 @@ typedef __attribute__((address_space(1))) uint32_t g_uint32_rw;
 typedef __attribute__((address_space(1))) u32x4 g_uint4_rw;
 
 // ---------------------------------------------------------------------------
-// Descriptor upload: the descriptors travel inside the kernel argument, so a
-// captured graph replays them without touching host memory. Each frame's
-// state words are reset here, before any kernel reads them.
+// Descriptor upload (launches over many frames): the descriptors travel
+// inside the kernel argument, so a captured graph replays them without
+// touching host memory. Each frame's state words are reset here, before any
+// kernel reads them. A launch of one frame hands its descriptor to k_prep.
 __global__ void k_put_desc(FrameDev* table, DescBatch b) {
   int i = threadIdx.x;
   if (i < b.count) {
@@ -94,8 +96,19 @@ __global__ void k_reset_head(WsHeader* h, int grid) {
 // caller's arrays allow them (idx 16-byte aligned; keys live in the
 // workspace), entry by entry otherwise.
 constexpr int64_t kShortRange = 8;   // list-range cells one thread writes alone
-__global__ __launch_bounds__(256) void k_check(const FrameDev* __restrict__ table, int f0, WsHeader* hdr) {
-  const FrameDev& f = table[f0 + blockIdx.y];
+// One frame per launch (kOne): a block leaves its outcome in its words of the
+// copies' spare rows (find_state puts them together), since there is no
+// launch before this one to reset the state words that the blocks of many
+// frames' lists add to.
+__device__ __forceinline__ uint32_t* spare_left(const FrameDev& f) { return f.lp + (int64_t)f.ph * f.lpw; }
+__device__ __forceinline__ uint32_t* spare_right(const FrameDev& f) { return f.rp + (int64_t)f.ph * f.rpw; }
+template <bool kOne>
+__device__ __forceinline__ void check_list(const FrameDev& f, int blocks, WsHeader* hdr) {
+  __shared__ uint32_t bad_s;
+  if constexpr (kOne) {
+    if (threadIdx.x == 0) bad_s = ~0u;
+    __syncthreads();
+  }
   const int64_t N = (int64_t)f.W * f.H, n = f.n;
   const uint32_t* idx = f.idx;
   uint32_t* keys = f.keys;
@@ -119,7 +132,7 @@ __global__ __launch_bounds__(256) void k_check(const FrameDev* __restrict__ tabl
   };
   if (n == 0 && blockIdx.x == 0)
     for (int64_t j = threadIdx.x; j < cells; j += blockDim.x) f.tptr[j] = 0;
-  for (int64_t k = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); k < n; k += 4 * (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t k = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); k < n; k += 4 * (int64_t)blocks * blockDim.x) {
     uint32_t p[4] = {0u, 0u, 0u, 0u};
     if (vec && k + 3 < n) {
       const u32x4 v = *(g_uint4*)(idx + k);
@@ -142,7 +155,7 @@ __global__ __launch_bounds__(256) void k_check(const FrameDev* __restrict__ tabl
     // A wavefront that has seen a descent writes none: the list is unordered
     // then and its cells are not read, while a shuffled list's ascending
     // neighbours would each span half the image (a shuffled list of 55,296
-    // entries at 640x480: k_check 41 -> 5 us).
+    // entries at 640x480: 41 -> 5 us).
     int64_t rlo[5], rhi[5];
     int32_t rv[5];
     if (!__builtin_amdgcn_ballot_w64(unsorted)) {
@@ -191,15 +204,47 @@ __global__ __launch_bounds__(256) void k_check(const FrameDev* __restrict__ tabl
         f.out_disp[k + j] = 255;
         if (f.out_cost) f.out_cost[k + j] = 0xFFFFFFFFu;
         atomicOr(&hdr->error, 1u);
-        atomicMin((unsigned long long*)(f.state + 2), (unsigned long long)(k + j));
+        if constexpr (kOne) atomicMin(&bad_s, (uint32_t)(k + j));   // (n < 2^31)
+        else atomicMin((unsigned long long*)(f.state + 2), (unsigned long long)(k + j));
       }
     }
   }
-  if (__builtin_amdgcn_ballot_w64(unsorted) && (threadIdx.x & 63) == 0) atomicOr(f.state, kUnsorted);
+  if constexpr (kOne) {
+    const bool any = __syncthreads_or(unsorted);
+    if (threadIdx.x == 0) {
+      spare_left(f)[blockIdx.x] = any ? kUnsorted : 0u;
+      spare_right(f)[blockIdx.x] = bad_s;
+    }
+  } else {
+    if (__builtin_amdgcn_ballot_w64(unsorted) && (threadIdx.x & 63) == 0) atomicOr(f.state, kUnsorted);
+  }
 }
 
-// Padded copies (and, for unordered lists, map and row-bit clearing). One
-// block per padded row (grid-stride); each thread writes groups of four
+// Whether the list is unordered. checks > 0 (one frame per launch): from the
+// outcomes of its list's blocks, and block 0 writes the state words for the
+// kernels after this one.
+__device__ __forceinline__ bool find_state(const FrameDev& f, int checks) {
+  if (checks == 0) return (*f.state & kUnsorted) != 0;
+  __shared__ uint32_t bad_s;
+  if (threadIdx.x == 0) bad_s = ~0u;
+  uint32_t any = 0u, bad = ~0u;
+  for (int t = threadIdx.x; t < checks; t += blockDim.x) {
+    any |= spare_left(f)[t];
+    if (blockIdx.x == 0) bad = min(bad, spare_right(f)[t]);
+  }
+  const bool unsorted = __syncthreads_or(any != 0u);
+  if (blockIdx.x == 0) {
+    if (bad != ~0u) atomicMin(&bad_s, bad);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      *f.state = unsorted ? kUnsorted : 0u;
+      *(uint64_t*)(f.state + 2) = bad_s == ~0u ? (uint64_t)f.n : (uint64_t)bad_s;
+    }
+  }
+  return unsorted;
+}
+
+// Padded copies. One block per padded row (in turn); each thread writes groups of four
 // padded pixels with one 16-byte store. Groups that lie inside the image with
 // a 4-byte-aligned source row read 12 (RGB) or 4 (gray) bytes with aligned
 // dword loads; border groups and unaligned rows read pixel by pixel with
@@ -228,10 +273,8 @@ __device__ __forceinline__ u32x4 pack_group(const uint8_t* row, int ic0, int W, 
 }
 
 constexpr int kPrepBatch = 5;   // right-copy groups per thread in flight (a 4096-pixel row: 1128 groups)
-__global__ __launch_bounds__(256) void k_prep(const FrameDev* __restrict__ table, int f0) {
-  const FrameDev& f = table[f0 + blockIdx.y];
+__device__ __forceinline__ void prep_rows(const FrameDev& f, int block, int blocks, bool clear) {
   const int W = f.W, H = f.H, C = f.C, r = f.r;
-  const bool unsorted = (*f.state & kUnsorted) != 0;
   // Left copy groups written: all of them, or, where the tile kernel reads
   // the left image in place inside it, only the groups that windows reaching
   // past an image edge read (padded words below lpad + span, and from
@@ -240,7 +283,7 @@ __global__ __launch_bounds__(256) void k_prep(const FrameDev* __restrict__ table
   const int band0 = f.linpl ? min((f.lpad + span) >> 2, lg) : lg;
   const int band1 = f.linpl ? min(max(band0, (W + f.lpad - span - 2) >> 2), lg) : lg;
   const int nl = band0 + (lg - band1);
-  for (int v = blockIdx.x; v < f.ph; v += gridDim.x) {
+  for (int v = block; v < f.ph; v += blocks) {
     const int y = clampi(v - r, 0, H - 1);
     const uint8_t* lrow = f.left + (int64_t)y * f.pitch;
     const uint8_t* rrow = f.right + (int64_t)y * f.pitch;
@@ -282,13 +325,43 @@ __global__ __launch_bounds__(256) void k_prep(const FrameDev* __restrict__ table
     } else {
       for (int g = threadIdx.x; g < ng; g += blockDim.x) ro[g] = pack_group(rrow, 4 * g - f.rpad, W, C, ra);
     }
-    if (unsorted && v >= r && v < r + H) {
+    if (clear && v >= r && v < r + H) {
       int32_t* mrow = f.map + (int64_t)(v - r) * W;
       for (int u = threadIdx.x; u < W; u += blockDim.x) mrow[u] = -1;
       uint64_t* brow = f.rowbits + (int64_t)(v - r) * f.rbw;
       for (int u = threadIdx.x; u < f.rbw; u += blockDim.x) brow[u] = 0ull;
     }
   }
+}
+
+// The list's check and the padded copies need nothing of each other: the
+// first `checks` blocks of a frame take its list, the others its rows. A
+// launch of one frame brings its descriptor with it. For small frames the
+// calling thread's launches bound the call (about 5 us each), so theirs also
+// clear the pixel map, needed or not. Calls against descriptor, check and
+// copies in a launch each: 384x288 grey 28.5 -> 22.7 us, 640x480 with a
+// shuffled list 43.7 -> 37.3 us, 1390x1110 RGB 73.6 -> 68 us.
+__global__ __launch_bounds__(256) void k_prep(const FrameDev* __restrict__ table, int checks, WsHeader* hdr) {
+  const FrameDev& f = table[blockIdx.y];
+  if ((int)blockIdx.x < checks) check_list<false>(f, checks, hdr);
+  else prep_rows(f, (int)blockIdx.x - checks, (int)gridDim.x - checks, false);
+}
+__global__ __launch_bounds__(256) void k_prep_one(FrameDev f, FrameDev* entry, int checks, int clear, WsHeader* hdr) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *entry = f;
+  if ((int)blockIdx.x < checks) check_list<true>(f, checks, hdr);
+  else prep_rows(f, (int)blockIdx.x - checks, (int)gridDim.x - checks, clear != 0);
+}
+
+// Unordered lists: the pixel map and the row bits cleared.
+__global__ __launch_bounds__(256) void k_clear_map(const FrameDev* __restrict__ table, int checks) {
+  const FrameDev& f = table[blockIdx.y];
+  if (!find_state(f, checks)) return;
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  const int64_t N = (int64_t)f.W * f.H;
+  for (int64_t q = t0; q < N / 4; q += step)   // (the map is 256-byte aligned)
+    *(g_uint4_rw*)(f.map + 4 * q) = u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+  if (t0 < N % 4) f.map[N - 1 - t0] = -1;
+  for (int64_t u = t0; u < (int64_t)f.H * f.rbw; u += step) f.rowbits[u] = 0ull;
 }
 
 // Unordered lists: map[p] = a slot k with idx[k] == p (of a repeated index,
@@ -305,10 +378,10 @@ __global__ __launch_bounds__(256) void k_prep(const FrameDev* __restrict__ table
 // 7 us so.
 constexpr int kScatterLds = 4096;
 constexpr int kScatterPer = 8;   // entries per thread of the smallest grids
-__global__ __launch_bounds__(256) void k_scatter(const FrameDev* __restrict__ table, int f0) {
+__global__ __launch_bounds__(256) void k_scatter(const FrameDev* __restrict__ table, int checks) {
   __shared__ unsigned long long lbits[kScatterLds];
-  const FrameDev& f = table[f0 + blockIdx.y];
-  if (!(*f.state & kUnsorted)) return;
+  const FrameDev& f = table[blockIdx.y];
+  if (!find_state(f, checks)) return;
   const int64_t N = (int64_t)f.W * f.H, n = f.n;
   const int64_t words = (int64_t)f.H * f.rbw;
   const bool in_lds = words <= kScatterLds;
@@ -1169,7 +1242,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWide ? 3 : 
 
 // Keys split into (disparity, cost), four entries per thread and step. An
 // ordered list holds its indices >= W*H in a tail from the first such slot on
-// (k_check recorded it and answered those entries): the entries before it
+// (check_list recorded it and answered those entries): the entries before it
 // take key k, and the list itself is not read again. An unordered list
 // reads each index for its representative slot. One 4-byte store of
 // disparities and one 16-byte store of costs where the caller's arrays allow
@@ -1198,7 +1271,7 @@ __global__ __launch_bounds__(256) void k_finalize(const FrameDev* __restrict__ t
         const uint32_t p[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          out[j] = (int64_t)p[j] >= N;   // (255, ~0) as k_check wrote them
+          out[j] = (int64_t)p[j] >= N;   // (255, ~0) as check_list wrote them
           key[j] = out[j] ? 0u : keys[f.map[p[j]]];
         }
       }
@@ -1289,14 +1362,38 @@ hipError_t launch_put_desc(FrameDev* table, const FrameDev* host, int nframes, h
 // more each, so that a single frame's list is not walked by 64 blocks alone.
 int list_blocks(int nf) { return nf >= 32 ? 64 : 2048 / nf; }
 
-hipError_t launch_prologue(const FrameDev* table, int f0, int nf, int max_rows, int64_t max_n, WsHeader* hdr,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_check, dim3(list_blocks(nf), nf), dim3(256), 0, s, table, f0, hdr);
-  int gx = max_rows < 2048 ? max_rows : 2048;
-  if (gx < 1) gx = 1;
-  hipLaunchKernelGGL(k_prep, dim3(gx, nf), dim3(256), 0, s, table, f0);
+// Blocks of the list check: those of list_blocks that have entries (more
+// would only delay the rows').
+static int check_blocks(int nf, int64_t max_n) {
+  const int64_t need = (max_n + 4 * 256 - 1) / (4 * 256);
+  return (int)(need < 1 ? 1 : need < list_blocks(nf) ? need : list_blocks(nf));
+}
+static int scatter_blocks(int64_t max_n) {
   const int64_t sx = (max_n + 256 * kScatterPer - 1) / (256 * kScatterPer);
-  hipLaunchKernelGGL(k_scatter, dim3((unsigned)(sx < 256 ? sx : 256), nf), dim3(256), 0, s, table, f0);
+  return (int)(sx < 256 ? sx : 256);
+}
+static int prep_blocks(int max_rows) { return max_rows < 1 ? 1 : max_rows < 2048 ? max_rows : 2048; }
+
+hipError_t launch_prologue(const FrameDev* table, int nf, int max_rows, int64_t max_n, WsHeader* hdr, hipStream_t s) {
+  const int checks = check_blocks(nf, max_n);
+  hipLaunchKernelGGL(k_prep, dim3(checks + prep_blocks(max_rows), nf), dim3(256), 0, s, table, checks, hdr);
+  hipLaunchKernelGGL(k_clear_map, dim3(nf >= 32 ? 16 : 512 / nf, nf), dim3(256), 0, s, table, 0);
+  hipLaunchKernelGGL(k_scatter, dim3(scatter_blocks(max_n), nf), dim3(256), 0, s, table, 0);
+  return hipGetLastError();
+}
+
+// One frame: its descriptor goes to `entry`. The map of up to kClearAlways
+// pixels is cleared with the copies (8 MB: 1.6 us of the bandwidth, against
+// a launch of its own, 2 to 3 us of the device and 5 us of the thread); a
+// larger one only once the list has turned out unordered.
+constexpr int64_t kClearAlways = 1 << 21;
+hipError_t launch_prologue_one(const FrameDev& f, FrameDev* entry, WsHeader* hdr, hipStream_t s) {
+  int checks = check_blocks(1, f.n);
+  if (checks > f.lpw) checks = f.lpw;   // (a word each in the spare rows; rpw >= lpw)
+  const bool clear = (int64_t)f.W * f.H <= kClearAlways;
+  hipLaunchKernelGGL(k_prep_one, dim3(checks + prep_blocks(f.ph)), dim3(256), 0, s, f, entry, checks, clear ? 1 : 0, hdr);
+  if (!clear) hipLaunchKernelGGL(k_clear_map, dim3(256), dim3(256), 0, s, entry, checks);
+  hipLaunchKernelGGL(k_scatter, dim3(scatter_blocks(f.n)), dim3(256), 0, s, entry, clear ? checks : 0);
   return hipGetLastError();
 }
 

@@ -304,3 +304,31 @@ def test_blur_edge_tiles(torch, sbs, C):
             got = sbs.selective_blur(view, dev(torch, depth), [(1, 1)], 2.0).cpu().numpy()
             exp = oracle.blur(np.ascontiguousarray(rows), depth, [(1, 1)], 2.0)
             assert np.abs(got - exp).max() <= 1e-3, f"{W}x{H}x{C} pitch {pitch} offset {off}"
+
+
+@pytest.mark.parametrize("W,H", [(24, 40000), (1024, 2048), (1031, 2035)])
+def test_single_frame_preparation(torch, sbs, W, H):
+    """Single frames at and past the size up to which the pixel map is cleared
+    with the copies (2^21 pixels), and one whose list check has fewer words for
+    its blocks than entries to fill them: ordered lists, one descent, lists in
+    no order, and entries past the image, the first of them anywhere."""
+    rng = np.random.default_rng(W)
+    L, R = pair(rng, W, H, 1)
+    N = W * H
+    base = np.sort(rng.choice(N, min(N // 2, 400000), replace=False))
+    n = base.size
+    lists = {"ordered": base, "in no order": rng.permutation(base)[:30000]}
+    for k in (1, n // 2, n - 1):
+        one = base.copy()
+        one[k - 1], one[k] = one[k], one[k - 1]
+        lists[f"descent at {k}"] = one
+    past = base.copy()
+    past[-3:] = N + 5, N + 6, N + 9
+    lists["ordered, ends past the image"] = past
+    mixed = rng.permutation(base)[:30000]
+    mixed[[7, 12345]] = N
+    lists["in no order, past the image"] = mixed
+    sbs.check_indices()   # (reads and clears the error word)
+    for what, idx in lists.items():
+        check_search(torch, sbs, L, R, idx, 3, 9, f"{W}x{H} {what}")
+        assert sbs.check_indices() == (5 if idx.max() >= N else 0), what
