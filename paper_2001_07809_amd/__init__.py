@@ -324,7 +324,7 @@ def boundaries(img, K: int = 4, mode: int = 0, min_cc: int = 50, frac: float = -
     W, H, C, pitch = _image_args(img)
     dev = img.device
     out = torch.empty(W * H, dtype=torch.int32, device=dev)
-    count = torch.zeros(1, dtype=torch.int64, device=dev)
+    count = torch.empty(1, dtype=torch.int64, device=dev)   # (every call writes it)
     refined = torch.empty((H, W), dtype=torch.uint8, device=dev) if with_maps else None
     labels = torch.empty((H, W), dtype=torch.uint8, device=dev) if with_maps else None
     nb = int(lib().sbs_boundaries_workspace_bytes(W, H))
