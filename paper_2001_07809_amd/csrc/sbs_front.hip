@@ -1185,17 +1185,17 @@ __global__ __launch_bounds__(1024) void k_root_find(Bits b, const unsigned long 
   }
 }
 
-// Kept pixels: those of components that pass the filter. A component's root
-// and size are looked up once per horizontal run and word, at the run's first
-// pixel, 64 runs at a time from a queue in LDS (word by word, most
-// lanes idle: 22 us at 4096x2304, 15 us so); the runs that pass go out whole by one addition (adding a run's start bit clears the run). kept (optional): kept pixels; base: kept pixels
-// and border columns; refined (optional): the kept map as bytes; bsum
-// (optional): base pixels per block; n1 (optional): kept pixels off the
-// border columns, in kN1Parts counters (adds to one word from every block
-// queue up one after another at the memory side). With n1 every run's first
-// pixel gets its component's size (roots hold it already, and no other
-// pixel's is read here), which the counting passes then read without a look
-// at the root.
+// Kept pixels: those of components that pass the filter. A component's root and size
+// are looked up once per horizontal run and word, at the run's first pixel, 64 runs at
+// a time from a queue in LDS (word by word, most lanes idle: 22 us at 4096x2304, 15 us
+// so); the runs that pass go out whole by one addition (adding a run's start bit
+// clears the run). kept (optional): kept pixels; base: kept pixels and border columns;
+// refined (optional): the kept map as bytes; bsum (optional): base pixels per block;
+// n1 (optional): kept pixels off the border columns, in kN1Parts counters (adds to one
+// word from every block queue up one after another at the memory side). With n1 every
+// run's first pixel gets its component's size (roots hold it already, and no other
+// pixel's is read here), which the counting passes then read without a look at the
+// root.
 __global__ __launch_bounds__(kBlock) void k_kept(Bits b, const unsigned long long* __restrict__ B,
                                                  const int32_t* __restrict__ parent, int32_t* size, const DropRule* rule,
                                                  int64_t min_cc, unsigned long long* kept,
@@ -1443,16 +1443,15 @@ __device__ __forceinline__ void far_segments(const Bits& b, const unsigned long 
   }
 }
 
-// Mode 2: distances up to kLevels by dilation of the base map, 3 x 3 per
-// level, on bits: a wavefront holds 128 rows (two per lane) x 192 columns in
-// registers, rows beyond a lane's own by DPP, and keeps the inner 98 rows x
-// 128 columns, which none of a launch's 15 levels reaches from outside. A
-// pixel's level goes to kLevelBits planes (0 for base pixels and those
-// further away) and the pixels per level are counted, in kLvParts copies. A
-// second launch goes on from the first one's outcome where the want-th pixel
-// lies further away: 15 levels cover the workloads' lists (31 in one launch
-// keep a quarter of what a wavefront holds: 26 us at 4096x2304 against 20). Pixels beyond both
-// take the distance passes below (k_far_*).
+// Mode 2: distances up to kLevels by dilation of the base map, 3 x 3 per level, on
+// bits: a wavefront holds 128 rows (two per lane) x 192 columns in registers, rows
+// beyond a lane's own by DPP, and keeps the inner 98 rows x 128 columns, which none of
+// a launch's 15 levels reaches from outside. A pixel's level goes to kLevelBits planes
+// (0 for base pixels and those further away) and the pixels per level are counted, in
+// kLvParts copies. A second launch goes on from the first one's outcome where the
+// want-th pixel lies further away: 15 levels cover the workloads' lists (31 in one
+// launch keep a quarter of what a wavefront holds: 26 us at 4096x2304 against 20).
+// Pixels beyond both take the distance passes below (k_far_*).
 constexpr int kLevelBits = 5, kLvStage = 15, kLevels = 2 * kLvStage + 1, kLvParts = 64;   // levels 1 .. 15 and 16 .. 30
 constexpr int kLvRows = 128 - 2 * kLvStage;   // 98
 constexpr int kLvWords = 6;                   // 32-column words held, the inner four kept
@@ -1669,7 +1668,9 @@ static_assert(kHashBins == 4 * kBlock, "four bins per thread");
 // leaves most empty. `blocks` blocks take `chunk` words (at most kRingWords) in
 // turn, each after prepare(their first word).
 constexpr int kRingWords = kBlock;          // words a block queues at a time
-constexpr int kRingGroups = 2;              // of them per block in small images (4 leave half the CUs without a block at 4096x2304)
+// ... and how often in small images (4 leave half the CUs without a block at
+// 4096x2304)
+constexpr int kRingGroups = 2;
 template <typename P, typename F>
 __device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, int blocks,
                                          int chunk, P prepare, F f) {

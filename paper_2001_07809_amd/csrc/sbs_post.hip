@@ -22,16 +22,15 @@ namespace sbs_post {
 
 constexpr int kRowThreads = 256;
 
-// A list in raster order (repeats side by side allowed), as the front end
-// writes it, is filled row by row from the list itself (k_rc_fill): each row's
-// entries are a piece of it, and no slot per pixel is cleared, scattered to
-// and read back (4096x2304: 49 -> 35 us,
-// three launches with nothing to do among them; other lists pay the check, 3
-// us, and the blocks' look at its flags). k_rc_check finds out: ok[block] for its piece of
-// `per` entries, and row_start[y], the first entry of row y or later (indexes
-// past the image count as row H). A block stops at its first descent, before
-// the rows of those entries are written: between entries in no order they
-// would be far apart.
+// A list in raster order (repeats side by side allowed), as the front end writes it,
+// is filled row by row from the list itself (k_rc_fill): each row's entries are a
+// piece of it, and no slot per pixel is cleared, scattered to and read back
+// (4096x2304: 49 -> 35 us, three launches with nothing to do among them; other lists
+// pay the check, 3 us, and the blocks' look at its flags). k_rc_check finds out:
+// ok[block] for its piece of `per` entries, and row_start[y], the first entry of row y
+// or later (indexes past the image count as row H). A block stops at its first
+// descent, before the rows of those entries are written: between entries in no order
+// they would be far apart.
 constexpr int kRcBlocks = 1024;   // at most: four flags per thread of the blocks that ask
 __global__ __launch_bounds__(256) void k_rc_check(const uint32_t* idx, int64_t n, int32_t W, int32_t H, int64_t per,
                                                   int32_t* row_start, uint8_t* ok) {
@@ -113,18 +112,17 @@ __global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int
   }
 }
 
-// Algorithm 1: a pixel strictly between two consecutive listed pixels of the
-// row that carry the same disparity takes it. Output: f[p] = disparity or -1
-// (undetermined).
-// Rows up to kFillW pixels, one wavefront per row: lane l holds the l-th 64
-// pixels' listed ones as a word and the number of listed pixels before it, and
-// the row's listed disparities lie side by side in LDS. A pixel's place among
-// them (bits up to its own) gives its neighbours' values with two LDS reads,
-// the same for every pixel, and nothing waits for another wavefront: a row is
-// a chain of four round trips to memory and some 64 steps of 64 pixels. A
-// block of four wavefronts per row, meeting at barriers, took as long whether
-// it worked this way or carried the nearest listed value from chunk to chunk
-// with lane shuffles, in both directions: 29 us at 4096x2304 against 22, 12.5 at 1390x1110 against 7.6.
+// Algorithm 1: a pixel strictly between two consecutive listed pixels of the row that
+// carry the same disparity takes it. Output: f[p] = disparity or -1 (undetermined).
+// Rows up to kFillW pixels, one wavefront per row: lane l holds the l-th 64 pixels'
+// listed ones as a word and the number of listed pixels before it, and the row's
+// listed disparities lie side by side in LDS. A pixel's place among them (bits up to
+// its own) gives its neighbours' values with two LDS reads, the same for every pixel,
+// and nothing waits for another wavefront: a row is a chain of four round trips to
+// memory and some 64 steps of 64 pixels. A block of four wavefronts per row, meeting
+// at barriers, took as long whether it worked this way or carried the nearest listed
+// value from chunk to chunk with lane shuffles, in both directions: 29 us at 4096x2304
+// against 22, 12.5 at 1390x1110 against 7.6.
 constexpr int kFillW = 4096;
 __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, const uint32_t* idx, const uint8_t* disp,
                                                          int32_t W, int32_t H, int16_t* f, RcOrder o,
