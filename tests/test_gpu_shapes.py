@@ -1,0 +1,77 @@
+"""Calls at the ends of the size ranges: results against the oracle, and times
+against a call of about as much work and an ordinary shape, where an algorithm
+that is serial along one axis of the image shows as a large factor."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+@pytest.fixture(scope="module")
+def sbs():
+    import paper_2001_07809_amd as m
+    m.lib()
+    return m
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def call_us(torch, fn, reps=10, rounds=5):
+    """Microseconds per call, the best of some rounds of calls in a row."""
+    for _ in range(2):
+        fn()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(reps):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
+def component_images():
+    """Images whose boundary maps hold components as long as the image."""
+    rng = np.random.default_rng(5)
+    noise = lambda W, H: rng.integers(0, 256, (H, W), dtype=np.uint8)
+    checks = lambda W, H: ((((np.arange(W) // 5)[None, :] ^ (np.arange(H) // 5)[:, None]) & 1) * 150).astype(np.uint8)
+    ramp = lambda W, H: np.repeat((np.arange(W) * 255 // max(W - 1, 1)).astype(np.uint8)[None, :], H, 0)
+    return [("noise 100000x20", noise(100000, 20), 10, 1),   # paper mode leaves the frame: two lines that meet at the ends
+            ("ramp 3x20000", ramp(3, 20000), 10, 1),         # a ring of one column on either side
+            ("checks 40x60000", checks(40, 60000), 4, 0),    # a grid all along the image
+            ("checks 60000x40", checks(60000, 40), 4, 0),
+            ("noise 65x20011", noise(65, 20011), 4, 0)]
+
+
+@pytest.mark.parametrize("i", range(5))
+def test_components_along_the_image(torch, sbs, i):
+    what, img, K, mode = component_images()[i]
+    got, kept, _ = sbs.boundaries(dev(torch, img), K=K, mode=mode, min_cc=20, with_maps=True)
+    exp, exp_map = oracle.boundaries(img, K=K, mode=mode, min_cc=20, frac=-1.0, return_map=True)
+    assert np.array_equal(kept.cpu().numpy(), exp_map), what
+    assert np.array_equal(got.cpu().numpy().view(np.uint32), exp), what
+
+
+def test_components_along_the_image_take_no_walk_of_it(torch, sbs):
+    """Two lines of 1,563 tiles that meet at both ends, against noise of as many
+    pixels in a square: 7.4 times the call when one thread walked a line, 1.2
+    times when its tiles shorten the way together."""
+    rng = np.random.default_rng(6)
+    wide = dev(torch, rng.integers(0, 256, (20, 100000), dtype=np.uint8))
+    square = dev(torch, rng.integers(0, 256, (1414, 1414), dtype=np.uint8))
+    t = [call_us(torch, lambda: sbs.boundaries(img, K=10, mode=1)) for img in (wide, square)]
+    assert t[0] < 3 * t[1], t
