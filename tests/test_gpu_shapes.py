@@ -75,3 +75,39 @@ def test_components_along_the_image_take_no_walk_of_it(torch, sbs):
     square = dev(torch, rng.integers(0, 256, (1414, 1414), dtype=np.uint8))
     t = [call_us(torch, lambda: sbs.boundaries(img, K=10, mode=1)) for img in (wide, square)]
     assert t[0] < 3 * t[1], t
+
+
+def check_reconstruct(torch, sbs, idx, disp, W, H, what):
+    exp = oracle.reconstruct(idx, disp, W, H, 1)
+    got = sbs.reconstruct(dev(torch, idx.view(np.int32)), dev(torch, disp), W, H, 1).cpu().numpy()
+    assert np.array_equal(got, exp), f"{what}: {(got != exp).sum()} pixels differ"
+
+
+@pytest.mark.parametrize("W,H", [(5, 40), (7, 2049), (40, 2500), (4096, 300)])
+def test_reconstruct_rows_without_entries(torch, sbs, W, H):
+    """Ordered lists with runs of empty rows around the length that one thread
+    writes (32 rows), before the first entry, after the last one, and several
+    long ones in one thread's and in one block's entries."""
+    rng = np.random.default_rng(H)
+    N = W * H
+    lists = {"first": [0], "last": [N - 1], "ends": [0, N - 1], "past the image": [N // 2, N + 3, N + 4]}
+    for step in (2, 31, 32, 33, 34, 300):
+        lists[f"every {step} rows"] = np.arange(0, H, step) * W + W // 2
+    lists["few"] = np.sort(rng.choice(N, 6, replace=False))
+    lists["clusters"] = np.concatenate([np.arange(40) + at for at in (0, N // 3, N // 2, N - 40)])
+    for what, lst in lists.items():
+        idx = np.asarray(lst, dtype=np.uint32)
+        check_reconstruct(torch, sbs, idx, rng.integers(0, 4, idx.size).astype(np.uint8), W, H, f"{W}x{H} {what}")
+
+
+def test_reconstruct_rows_without_entries_are_written_by_many(torch, sbs):
+    """One entry in 200,000 rows against an 18% list of the same image: 13 times
+    the call when one thread wrote all rows' starts, less than it otherwise."""
+    W, H = 64, 200000
+    rng = np.random.default_rng(1)
+    lists = [np.array([W * H - 1]), np.sort(rng.choice(W * H, W * H * 18 // 100, replace=False))]
+    t = []
+    for lst in lists:
+        idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
+        t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1)))
+    assert t[0] < 2 * t[1], t
