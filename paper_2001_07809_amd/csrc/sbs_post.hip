@@ -33,20 +33,23 @@ constexpr int kRowThreads = 256;
 // they would be far apart. Rows without entries between two of them are written by
 // a wavefront where they are many (a call with one entry, 1390x1110: 55.5 -> 27.5 us,
 // 3x20000: 567 -> 66 us; from 8 rows on and by the whole block, 3x20000 with an entry
-// in every hundred pixels took 117 us, 81 by one thread each; 128 rows by a thread:
-// ten entries at 640x480 32.9 us, 28.3 so).
+// in every hundred pixels took 117 us, 81 by one thread each; up to 128 rows by a
+// thread: ten entries at 640x480 32.9 us, 28.5 so).
+// A row's entries are one wavefront's in k_rc_fill, so a list that has more of them in a
+// row than the row has pixels (repeats; 256 at least, and up to 256 more, since one
+// lane of a wavefront looks) counts as one in no order: 1390x1110, a tenth as many
+// entries on one pixel as there are pixels, beside a 1% list: 726 us a call in order,
+// 38 so.
 constexpr int kRcBlocks = 1024;   // at most: four flags per thread of the blocks that ask
-constexpr int kRcGap = 32;       // rows that one thread writes alone
+constexpr int kRcGap = 32;        // rows that one thread writes alone
+constexpr int kFillW = 4096;      // longest rows that k_rc_fill takes
 __global__ __launch_bounds__(256) void k_rc_check(const uint32_t* idx, int64_t n, int32_t W, int32_t H, int64_t per,
                                                   int32_t* row_start, uint8_t* ok) {
-  __shared__ int gap_lo[5 * 256], gap_hi[5 * 256], gap_k[5 * 256];   // rows gap_lo + 1 .. gap_hi start at entry gap_k
-  __shared__ uint32_t gaps[2];   // in turn: one is cleared while the other counts
   const uint32_t N = (uint32_t)W * (uint32_t)H;
   auto row = [&](uint32_t p) -> int { return p < N ? (int)(p / (uint32_t)W) : H; };
-  if (threadIdx.x < 2) gaps[threadIdx.x] = 0u;
   const int64_t k1 = min((blockIdx.x + 1) * per, n);
-  uint32_t step = 0u;
-  for (int64_t k0 = blockIdx.x * per; k0 < k1; k0 += 4 * 256, step ^= 1u) {
+  const int most = max(W, 256);
+  for (int64_t k0 = blockIdx.x * per; k0 < k1; k0 += 4 * 256) {
     const int64_t k = k0 + 4 * (int)threadIdx.x;
     const int m = (int)max(min(k1 - k, (int64_t)4), (int64_t)0);
     uint32_t p[4] = {0u, 0u, 0u, 0u};
@@ -58,32 +61,34 @@ __global__ __launch_bounds__(256) void k_rc_check(const uint32_t* idx, int64_t n
         if (j < m) p[j] = idx[k + j];
     }
     const uint32_t before = m > 0 && k > 0 ? idx[k - 1] : 0u;
+    const bool look = (threadIdx.x & 63) == 0 && m > 0 && k >= most;
+    const uint32_t far = look ? idx[k - most] : N;
     bool down = m > 0 && p[0] < before;
 #pragma unroll
     for (int j = 1; j < 4; ++j) down |= j < m && p[j] < p[j - 1];
+    down |= look && far < N && row(far) == row(p[0]);
     if (__syncthreads_or(down)) {
       if (threadIdx.x == 0) ok[blockIdx.x] = 0;
       return;
     }
-    if (threadIdx.x == 0) gaps[step ^ 1u] = 0u;
+    // rows r + 1 .. to start at entry `at`: entry by entry, and after the last one
     int r = k > 0 ? row(before) : -1;
-    bool any = false;
-    auto rows_upto = [&](int to, int64_t at) {
-      if ((uint32_t)to - (uint32_t)r > (uint32_t)kRcGap) {
-        const uint32_t q = atomicAdd(&gaps[step], 1u);
-        gap_lo[q] = r; gap_hi[q] = to; gap_k[q] = (int)at;
-        any = true;
-        r = to;
-      }
-      while (r < to) row_start[++r] = (int32_t)at;
-    };
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (j < m) rows_upto(row(p[j]), k + j);
-    if (m > 0 && k + m == n) rows_upto(H, n);
-    if (__syncthreads_or(any))
-      for (uint32_t q = threadIdx.x >> 6; q < gaps[step]; q += 4)
-        for (int y = gap_lo[q] + 1 + (int)(threadIdx.x & 63); y <= gap_hi[q]; y += 64) row_start[y] = gap_k[q];
+    for (int j = 0; j < 5; ++j) {
+      const bool end = m > 0 && k + m == n;
+      const int to = j < 4 ? (j < m ? row(p[j]) : r) : (end ? H : r);
+      const int at = (int)(j < 4 ? k + j : n);
+      uint64_t many = __builtin_amdgcn_ballot_w64((uint32_t)to - (uint32_t)r > (uint32_t)kRcGap);
+      if (!__builtin_amdgcn_inverse_ballot_w64(many))
+        for (int y = r + 1; y <= to; ++y) row_start[y] = at;
+      for (; many; many &= many - 1ull) {
+        const int l = __builtin_ctzll(many);
+        const int lo = __builtin_amdgcn_readlane(r, l), hi = __builtin_amdgcn_readlane(to, l);
+        const int v = __builtin_amdgcn_readlane(at, l);
+        for (int y = lo + 1 + (int)(threadIdx.x & 63); y <= hi; y += 64) row_start[y] = v;
+      }
+      r = to;
+    }
   }
   if (threadIdx.x == 0) ok[blockIdx.x] = 1;
 }
@@ -142,7 +147,6 @@ __global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int
 // at barriers, took as long whether it worked this way or carried the nearest listed
 // value from chunk to chunk with lane shuffles, in both directions: 29 us at 4096x2304
 // against 22, 12.5 at 1390x1110 against 7.6.
-constexpr int kFillW = 4096;
 __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, const uint32_t* idx, const uint8_t* disp,
                                                          int32_t W, int32_t H, int16_t* f, RcOrder o,
                                                          const int32_t* row_start) {
@@ -199,16 +203,31 @@ __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, co
       pre = upto - c;
       total = __builtin_amdgcn_readlane(upto, 63);
       if ((uint32_t)total != k1 - k0) {
-        // repeats: the last of each run, at its pixel's place
+        // repeats: the last of each run, at its pixel's place (entries and their
+        // disparities together, kRep at a time: one at a time, each step was two
+        // round trips to memory)
+        constexpr int kRep = 8;
         pre_s[lane] = pre;
         in_order();
-        for (uint32_t k = k0 + lane; k < k1; k += 64) {
-          const uint32_t p = idx[k], xx = p - first;
-          if (xx >= (uint32_t)W || (k + 1 < k1 && idx[k + 1] == p)) continue;
-          const uint32_t w = xx >> 5;
-          const int at = pre_s[xx >> 6] + ((w & 1) ? __builtin_popcount(map[w - 1]) : 0) +
-                         __builtin_popcount(map[w] & ((1u << (xx & 31)) - 1u));
-          val[1 + at] = (int16_t)disp[k];
+        for (uint32_t kb = k0 + lane; kb < k1; kb += 64 * kRep) {
+          uint32_t x[kRep], nx[kRep];
+          int d[kRep];
+#pragma unroll
+          for (int j = 0; j < kRep; ++j) {
+            const uint32_t k = min(kb + 64 * j, k1 - 1);
+            x[j] = idx[k];
+            nx[j] = idx[min(k + 1, k1 - 1)];
+            d[j] = disp[k];
+          }
+#pragma unroll
+          for (int j = 0; j < kRep; ++j) {
+            const uint32_t k = kb + 64 * j, xx = x[j] - first;
+            if (k >= k1 || xx >= (uint32_t)W || (k + 1 < k1 && nx[j] == x[j])) continue;
+            const uint32_t w = xx >> 5;
+            const int at = pre_s[xx >> 6] + ((w & 1) ? __builtin_popcount(map[w - 1]) : 0) +
+                           __builtin_popcount(map[w] & ((1u << (xx & 31)) - 1u));
+            val[1 + at] = (int16_t)d[j];
+          }
         }
       }
     } else {

@@ -111,3 +111,38 @@ def test_reconstruct_rows_without_entries_are_written_by_many(torch, sbs):
         idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
         t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1)))
     assert t[0] < 2 * t[1], t
+
+
+@pytest.mark.parametrize("W,H", [(3, 700), (64, 40), (255, 60), (256, 61), (1000, 33), (4096, 9)])
+def test_reconstruct_rows_of_many_repeats(torch, sbs, W, H):
+    """Ordered lists with one pixel repeated around the number of entries from
+    which a row's list counts as one in no order (the row's width, at least 256,
+    and 256 more), in the first, a middle and the last row; pixels repeated a
+    few times all over a row; and entries past the image in such numbers."""
+    rng = np.random.default_rng(W)
+    N = W * H
+    base = np.sort(rng.choice(N, max(N // 7, 3), replace=False))
+    most = max(W, 256)
+    for at in (0, N // 2, N - 1):
+        for times in (2, 63, 64, 65, 511, 512, 513, most - 1, most + 1, most + 255, most + 256, most + 257, most + 1400):
+            idx = np.sort(np.concatenate([base, np.full(times, at)])).astype(np.uint32)
+            check_reconstruct(torch, sbs, idx, rng.integers(0, 3, idx.size).astype(np.uint8), W, H, f"{W}x{H} {at} {times} times")
+    for times in (2, 3, 9):
+        idx = np.repeat(np.arange(N // 2, min(N // 2 + W, N)), times).astype(np.uint32)
+        check_reconstruct(torch, sbs, idx, rng.integers(0, 3, idx.size).astype(np.uint8), W, H, f"{W}x{H} a row {times} times")
+    idx = np.concatenate([base, np.full(3000, N), np.full(3000, N + 5)]).astype(np.uint32)
+    check_reconstruct(torch, sbs, idx, rng.integers(0, 3, idx.size).astype(np.uint8), W, H, f"{W}x{H} past the image")
+
+
+def test_reconstruct_repeats_are_taken_by_many(torch, sbs):
+    """A tenth as many entries on one pixel as the image has pixels, beside a 1%
+    list, against that list: 25 times the call when one wavefront took them all."""
+    W, H = 1390, 1110
+    rng = np.random.default_rng(2)
+    few = np.sort(rng.choice(W * H, W * H // 100, replace=False))
+    lists = [np.sort(np.concatenate([few, np.full(W * H // 10, W * H // 2)])), few]
+    t = []
+    for lst in lists:
+        idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
+        t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1)))
+    assert t[0] < 4 * t[1], t
