@@ -1271,7 +1271,7 @@ extern "C" {
 size_t sbs_reconstruct_workspace_bytes(int32_t W, int32_t H) {
   if (W < 1 || H < 1) return 0;
   const size_t N = (size_t)W * H;
-  return align256(N * 4) + align256(N * 2) + align256(N * 2) + align256(((size_t)H + 1) * 4) + kRcBlocks;
+  return align256(N * 4) + align256(N * 2) + align256(N * 2);
 }
 
 int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t W, int32_t H, int32_t threshold,
@@ -1287,12 +1287,15 @@ int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t
   int32_t* slot = (int32_t*)base;
   int16_t* f = (int16_t*)(base + align256(N * 4));
   int16_t* up = (int16_t*)(base + align256(N * 4) + align256(N * 2));
-  int32_t* row_start = (int32_t*)(base + align256(N * 4) + 2 * align256(N * 2));
+  // The check's outcome lies where k_rc_peek works later. Wider rows, and images
+  // too small or narrow for its place (under 3 columns, or some 1200 pixels), are
+  // filled from slots.
+  int32_t* row_start = (int32_t*)up;
+  const size_t row_bytes = align256(((size_t)H + 1) * 4);
   RcOrder o{nullptr, 0};
-  // (wider rows are filled from slots)
-  if (n > 0 && W <= kFillW) {
+  if (n > 0 && W <= kFillW && row_bytes + kRcBlocks <= align256(N * 2)) {
     const int64_t per = ((n + kRcBlocks - 1) / kRcBlocks + 1023) / 1024 * 1024;
-    uint8_t* ok = (uint8_t*)row_start + align256(((size_t)H + 1) * 4);
+    uint8_t* ok = (uint8_t*)row_start + row_bytes;
     o = RcOrder{ok, (int)((n + per - 1) / per)};
     hipLaunchKernelGGL(k_rc_check, dim3(o.n), dim3(256), 0, s, idx, n, W, H, per, row_start, ok);
   }
