@@ -43,6 +43,8 @@ constexpr int kRowThreads = 256;
 constexpr int kRcBlocks = 1024;   // at most: four flags per thread of the blocks that ask
 constexpr int kRcGap = 32;        // rows that one thread writes alone
 constexpr int kFillW = 4096;      // longest rows that k_rc_fill takes
+constexpr int kCheckPixels = 400000, kCheckRows = 256;   // smallest images whose lists are checked
+constexpr int kFewRows = 1024;    // (a block for each CU's four places)
 __global__ __launch_bounds__(256) void k_rc_check(const uint32_t* idx, int64_t n, int32_t W, int32_t H, int64_t per,
                                                   int32_t* row_start, uint8_t* ok) {
   const uint32_t N = (uint32_t)W * (uint32_t)H;
@@ -136,6 +138,76 @@ __global__ __launch_bounds__(256) void k_rc_scatter_max(const uint32_t* idx, int
   }
 }
 
+// Rows of up to kFillW pixels from slots by four wavefronts, for images of few rows,
+// which a wavefront each would leave waiting for a row's chain of round trips (calls
+// with lists in no order, 4096x500: 55.7 -> 50.4 us, 4000x250: 46.5 -> 35.5; from about
+// kFewRows rows on a wavefront each is as fast or faster, 1390x1110: 47.1 us by either,
+// 4096x2304: 113 against 118):
+// a quarter of a row's 64-pixel chunks each, one pixel per lane; a quarter's slots are
+// loaded at once, then its disparities, and both passes run on registers. Left to
+// right: a ballot marks a chunk's listed pixels, the nearest one at or left of each
+// lane comes from the mask's bits up to the lane (its value by a lane shuffle), the
+// last listed value of the chunks before is carried along, and a pixel with no listed
+// one to its left within the quarter is left open. After an exchange of the quarters'
+// first and last listed values through LDS, right to left finds the nearest listed
+// pixel on the right the same way, takes the one on the left from the quarters before
+// where it was missing, and decides.
+__device__ __forceinline__ void fill_rows_by_four(const int32_t* slot, const uint8_t* disp, int32_t W, int32_t H,
+                                                  int16_t* f) {
+  constexpr int kWaves = kRowThreads / 64, kFillChunks = kFillW / 64 / kWaves;
+  __shared__ int q_first[kWaves], q_last[kWaves];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int nch = (W + 63) >> 6, per = (nch + kWaves - 1) / kWaves;   // (at most kFillChunks)
+  const int c0 = min(wv * per, nch), c1 = min(c0 + per, nch);
+  const uint64_t upto = (2ull << lane) - 1ull;    // bits 0 .. lane
+  const uint64_t from = ~((1ull << lane) - 1ull); // bits lane .. 63
+  for (int y = blockIdx.x; y < H; y += gridDim.x) {
+    const int32_t* srow = slot + (int64_t)y * W;
+    int16_t* frow = f + (int64_t)y * W;
+    int v[kFillChunks];
+#pragma unroll
+    for (int i = 0; i < kFillChunks; ++i) {
+      const int x = ((c0 + i) << 6) + lane;
+      v[i] = (c0 + i < c1 && x < W) ? srow[x] : -1;   // slot here, disparity below
+    }
+#pragma unroll
+    for (int i = 0; i < kFillChunks; ++i) v[i] = v[i] >= 0 ? (int)disp[v[i]] : -1;
+    int lft[kFillChunks];   // nearest listed value at or left of the pixel within the quarter, -2: none
+    int carry = -2, first = -1;
+#pragma unroll
+    for (int i = 0; i < kFillChunks; ++i) {
+      const uint64_t m = __builtin_amdgcn_ballot_w64(v[i] >= 0);
+      const uint64_t b = m & upto;
+      const int left = __shfl(v[i], b ? 63 - __builtin_clzll(b) : 0);
+      lft[i] = b ? left : carry;
+      if (m) {
+        if (first < 0) first = __shfl(v[i], __builtin_ctzll(m));
+        carry = __shfl(v[i], 63 - __builtin_clzll(m));
+      }
+    }
+    if (lane == 0) { q_first[wv] = first; q_last[wv] = carry < 0 ? -1 : carry; }
+    __syncthreads();
+    int cl = -1, cr = -1;   // nearest listed value in the quarters to the left / right
+    for (int j = wv - 1; j >= 0 && cl < 0; --j) cl = q_last[j];
+    for (int j = wv + 1; j < kWaves && cr < 0; ++j) cr = q_first[j];
+    __syncthreads();   // the next row rewrites q_first / q_last
+    carry = cr;
+#pragma unroll
+    for (int i = kFillChunks - 1; i >= 0; --i) {
+      const int x = ((c0 + i) << 6) + lane;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(v[i] >= 0);
+      const uint64_t b = m & from;
+      const int right = b ? __shfl(v[i], __builtin_ctzll(b)) : carry;
+      if (c0 + i < c1 && x < W) {
+        int left = lft[i];
+        if (left == -2) left = cl;
+        frow[x] = (int16_t)(v[i] >= 0 ? v[i] : ((left >= 0 && left == right) ? left : -1));
+      }
+      if (m) carry = __shfl(v[i], __builtin_ctzll(m));
+    }
+  }
+}
+
 // Algorithm 1: a pixel strictly between two consecutive listed pixels of the row that
 // carry the same disparity takes it. Output: f[p] = disparity or -1 (undetermined).
 // Rows up to kFillW pixels, one wavefront per row: lane l holds the l-th 64 pixels'
@@ -162,6 +234,10 @@ __global__ __launch_bounds__(kRowThreads) void k_rc_fill(const int32_t* slot, co
   // (a wavefront's LDS operations are done in the order it issues them)
   auto in_order = [] { asm volatile("" ::: "memory"); };
   const bool ordered = o.ordered();
+  if (!ordered && H < kFewRows) {
+    fill_rows_by_four(slot, disp, W, H, f);
+    return;
+  }
   for (int y = blockIdx.x * kWaves + wv; y < H; y += gridDim.x * kWaves) {
     uint32_t lo = 0u, hi = 0u;   // this lane's word
     int pre = 0, total = 0;      // listed pixels before it, and in the row
@@ -398,8 +474,10 @@ __global__ __launch_bounds__(256) void k_rc_colseg(const int16_t* f, int32_t W, 
 // value), takes what the others' summaries leave above and below it, and
 // rewrites its part, kept in registers where it is at most kScanBatch
 // segments, else read again kScanBatch at a time. (Three launches over chunks
-// of 16 segments took 12 us at 4096x2304, 6.5 us so.)
-constexpr int kScanBatch = 16, kScanWaves = 16;
+// of 16 segments took 12 us at 4096x2304, 6.5 us so.) Up to kScanBatch segments
+// one wavefront holds them all.
+constexpr int kScanBatch = 16;
+template <int kScanWaves>
 __global__ __launch_bounds__(64 * kScanWaves) void k_rc_carry(int32_t W, int32_t nseg, int16_t* seg_first,
                                                               int16_t* seg_last) {
   __shared__ int16_t sum_first[kScanWaves][64], sum_last[kScanWaves][64];
@@ -1287,13 +1365,17 @@ int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t
   int32_t* slot = (int32_t*)base;
   int16_t* f = (int16_t*)(base + align256(N * 4));
   int16_t* up = (int16_t*)(base + align256(N * 4) + align256(N * 2));
-  // The check's outcome lies where k_rc_peek works later. Wider rows, and images
-  // too small or narrow for its place (under 3 columns, or some 1200 pixels), are
-  // filled from slots.
+  // The check's outcome lies where k_rc_peek works later. From slots without it:
+  // wider rows; images narrower than its place (under 3 columns); where the launch
+  // that it is costs more than it saves, small images or few rows (ordered 18% lists,
+  // with it and without: 640x480 27.0 and 26.6 us, 800x600 26.6 and 28.2, 1390x1110
+  // 29.2 and 38.8; 4000x250 29.7 and 31.3, but 46.5 and 35.6 for one in no order); and
+  // lists of more than half of the pixels, whose rows are long for a wavefront each
+  // (all pixels of 4096x500: 46.3 and 36.1, of 4096x2304 94.7 and 90.7).
   int32_t* row_start = (int32_t*)up;
   const size_t row_bytes = align256(((size_t)H + 1) * 4);
   RcOrder o{nullptr, 0};
-  if (n > 0 && W <= kFillW && row_bytes + kRcBlocks <= align256(N * 2)) {
+  if (W <= kFillW && N >= kCheckPixels && H > kCheckRows && n > 0 && n <= N / 2 && row_bytes + kRcBlocks <= align256(N * 2)) {
     const int64_t per = ((n + kRcBlocks - 1) / kRcBlocks + 1023) / 1024 * 1024;
     uint8_t* ok = (uint8_t*)row_start + row_bytes;
     o = RcOrder{ok, (int)((n + per - 1) / per)};
@@ -1307,7 +1389,7 @@ int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t
   }
   const dim3 rows(H < 65536 ? H : 65536);
   if (W <= kFillW)
-    hipLaunchKernelGGL(k_rc_fill, dim3((rows.x + 3) / 4), dim3(kRowThreads), 0, s, slot, idx, disp, W, H, f, o, row_start);
+    hipLaunchKernelGGL(k_rc_fill, H < kFewRows ? rows : dim3((rows.x + 3) / 4), dim3(kRowThreads), 0, s, slot, idx, disp, W, H, f, o, row_start);
   else
     hipLaunchKernelGGL(k_rc_fill_wide, rows, dim3(kRowThreads), 0, s, slot, disp, W, H, f);
   // The column pass's segment records reuse the slot array (no longer read
@@ -1318,7 +1400,9 @@ int sbs_reconstruct(const uint32_t* idx, const uint8_t* disp, int64_t n, int32_t
   int16_t* seg_last = seg_first + (int64_t)nseg * W;
   const dim3 cg((W + 255) / 256, nseg);
   hipLaunchKernelGGL(k_rc_colseg, cg, dim3(256), 0, s, f, W, H, seglen, seg_first, seg_last);
-  hipLaunchKernelGGL(k_rc_carry, dim3((unsigned)(((int64_t)W + 63) / 64)), dim3(64 * kScanWaves), 0, s, W, nseg, seg_first, seg_last);
+  const dim3 carry((unsigned)(((int64_t)W + 63) / 64));
+  if (nseg <= kScanBatch) hipLaunchKernelGGL(k_rc_carry<1>, carry, dim3(64), 0, s, W, nseg, seg_first, seg_last);
+  else hipLaunchKernelGGL(k_rc_carry<16>, carry, dim3(64 * 16), 0, s, W, nseg, seg_first, seg_last);
   hipLaunchKernelGGL(k_rc_peek, cg, dim3(256), 0, s, f, W, H, threshold, seglen, seg_last, seg_first, up, out_map);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(SBS_ERR_HIP, "reconstruct: %s", hipGetErrorString(e));

@@ -146,3 +146,35 @@ def test_reconstruct_repeats_are_taken_by_many(torch, sbs):
         idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
         t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1)))
     assert t[0] < 4 * t[1], t
+
+
+@pytest.mark.parametrize("W,H", [(1560, 256), (1560, 257), (1555, 257), (400, 999), (392, 1023), (391, 1024), (391, 1023),
+                                 (4096, 98), (2, 1500), (64, 17), (200, 16)])
+def test_reconstruct_paths(torch, sbs, W, H):
+    """Images around the sizes from which a list is checked (400,000 pixels, 257
+    rows), a row goes to one wavefront whatever the list (1,024 rows) and a
+    column's segments to several (17 of 16 rows), with lists in order and not, of
+    at most half of the pixels and of more."""
+    rng = np.random.default_rng(W * H)
+    N = W * H
+    for n in (N * 18 // 100, N // 2, N // 2 + 1, N):
+        idx = np.sort(rng.choice(N, n, replace=False)).astype(np.uint32)
+        lists = {"in order": idx, "in no order": rng.permutation(idx)}
+        one = idx.copy()
+        one[[n // 3, n // 3 + 1]] = one[[n // 3 + 1, n // 3]]
+        lists["one descent"] = one
+        for what, lst in lists.items():
+            check_reconstruct(torch, sbs, lst, rng.integers(0, 4, n).astype(np.uint8), W, H, f"{W}x{H}, {n} entries {what}")
+
+
+def test_reconstruct_few_long_rows_take_no_longer_than_an_image(torch, sbs):
+    """All pixels of 4000x100, and a shuffled 18% of them, against an ordered 18%
+    of 640x480: 1.5 times the call when a wavefront took a row of either."""
+    rng = np.random.default_rng(3)
+    t = []
+    for W, H, share, shuffle in ((640, 480, 0.18, False), (4000, 100, 1.0, False), (4000, 100, 0.18, True)):
+        lst = rng.choice(W * H, int(W * H * share), replace=False)
+        lst = lst if shuffle else np.sort(lst)
+        idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
+        t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1), reps=30))
+    assert max(t[1:]) < 1.3 * t[0], t
