@@ -182,6 +182,30 @@ Tiles tiles_of(const sbs_frame& f, int chunk, int ty, int cpl, bool tail) {
   return t;
 }
 
+// A launch's time under a plan, in steps of one output row and 8 disparities:
+// the row steps of all items at what the chip's 1024 SIMDs get done (2.5
+// wavefronts' chains each), and the last item's own. A row of the window's
+// first sum, which has no horizontal stage, counts 0.4 steps, 16 disparities
+// 1.4 times 8 (twice where two columns' sums do not pack: such frames run them
+// as two passes), an item's start 2. Fitted to 610 calls and batches of
+// 384x288 to 4096x2304 with blocks of 5 to 127, 18 plans each: the plan of
+// least estimate takes 1.04 times the best one's time on average with blocks
+// above 31 (at most 1.26 times).
+double launch_steps(const sbs_frame* frames, int nframes, int chunk, int ty) {
+  double all = 0, last = 0;
+  for (int i = 0; i < nframes; ++i) {
+    const sbs_frame& f = frames[i];
+    if (f.n <= 0) continue;
+    const Tiles t = tiles_of(f, chunk, ty, 4, nframes == 1);
+    const double start = 0.4 * (f.block - 1), wide = chunk == 8 ? 1.0 : packs(f) ? 1.4 : 2.0;
+    const double main = 2 + wide * (start + t.ty), tail = 2 + wide * (start + t.ty2);
+    const double nmain = (double)t.ntx * t.nty * t.nch, ntail = (double)t.items() - nmain;
+    all += nmain * main + ntail * tail;
+    last = std::max(last, ntail > 0 ? tail : main);
+  }
+  return all / (1024 * 2.5) + last;
+}
+
 // Default plan for the frames one launch covers, by the launch's size as
 // its number of 16-disparity, 16-row items against the chip's 4096 wavefront
 // slots. Larger items amortise the window's first sum (2r + 1 rows) and the
@@ -201,7 +225,26 @@ Tiles tiles_of(const sbs_frame& f, int chunk, int ty, int cpl, bool tail) {
 // 8 x 32, as many as of 16 x 16 with half their window starts, share out
 // better (2552x1600, dmax 116: 16 x 16 197, 8 x 32 174, 16 x 32 194 us;
 // 3057x1762, dmax 102: 218, 206, 219; 3072x2304, dmax 74: 200, 206, 195).
+// These lines hold for blocks up to 31 whose sums pack. A larger window's
+// first sum is worth many rows, and 16 disparities are no gain without packed
+// sums, so launches with such frames take the plan of least estimated time
+// (1390x1110, dmax 63: RGB, block 101: 376 us by the lines above, 124 so; grey
+// 182 and 120; RGB, block 61: 270 and 101; 4096x2304 RGB, dmax 127, block 61:
+// 905 and 388). For smaller windows the estimate is the worse rule (4096x2304,
+// block 21, dmax 127: 328 us, 285 by the lines).
 Plan default_plan(const sbs_frame* frames, int nframes) {
+  for (int i = 0; i < nframes; ++i) {
+    if (frames[i].n <= 0 || (frames[i].block <= 31 && packs(frames[i]))) continue;
+    Plan p;
+    p.wpc = 16;
+    double best = 1e300;
+    for (int chunk : {8, 16})
+      for (int ty : {8, 16, 32, 64, 96}) {
+        const double t = launch_steps(frames, nframes, chunk, ty);
+        if (t < best) { best = t; p.chunk = chunk; p.ty = ty; }
+      }
+    return p;
+  }
   int64_t n16 = 0;
   for (int i = 0; i < nframes; ++i)
     if (frames[i].n > 0) n16 += tiles_of(frames[i], 16, 16, 4, false).items();

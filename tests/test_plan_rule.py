@@ -1,0 +1,52 @@
+"""The plan that a call takes by default (CPU only: plans are chosen on the host)."""
+import pytest
+
+import paper_2001_07809_amd as sbs
+
+SLOTS = 256 * 16   # wavefronts that the chip holds
+
+
+def frame(W, H, C, block, dmax, n=None):
+    return sbs.Frame(1, 1, W, H, C, W * C, 1, n or W * H // 5, block, dmax, 1, None)
+
+
+def items(W, H, block, dmax, chunk, rows, tail=True):
+    """(items, row steps) of a single frame: each item slides 2r rows and takes
+    its own; the last 2048 items' worth of tiles has half the rows."""
+    r = (block - 1) // 2
+    lpad = (r + 4) & ~3
+    cols = (256 - lpad - r) & ~3
+    per = -(-W // cols) * ((dmax + chunk) // chunk)
+    tiles = -(-H // rows)
+    main = max(0, tiles - (-(-2048 // per))) if tail else tiles
+    low = max(1, rows // 2)
+    ntail = -(-max(H - main * rows, 0) // low)
+    return per * (main + ntail), per * (main * (2 * r + rows) + ntail * (2 * r + low)) * chunk // 8
+
+
+@pytest.mark.parametrize("W,H,dmax", [(640, 480, 127), (1390, 1110, 63), (1390, 1110, 255), (1920, 1080, 63), (4096, 2304, 127)])
+@pytest.mark.parametrize("C", [1, 3])
+@pytest.mark.parametrize("block", [33, 41, 47, 61, 81, 101, 127])
+def test_window_starts_do_not_outweigh_the_rows(W, H, dmax, C, block):
+    """Where 8-disparity items of 32 rows fill half of the chip, the plan of a
+    large window slides over no more than 1.6 times their rows (grey, block 101,
+    1390x1110: 2.9 times when the window's size did not count)."""
+    p = sbs.get_plan(frame(W, H, C, block, dmax))
+    ref, steps = items(W, H, block, dmax, 8, 32, tail=False)
+    if ref >= SLOTS // 2:
+        assert items(W, H, block, dmax, p["chunk"], p["tile_rows"])[1] <= 1.6 * steps, p
+
+
+@pytest.mark.parametrize("W,H,dmax", [(384, 288, 15), (640, 480, 31), (1390, 1110, 63), (4096, 2304, 127), (4096, 2304, 15)])
+def test_sums_that_do_not_pack_take_8_disparities(W, H, dmax):
+    """RGB windows above 42 columns run 16 disparities as two passes of 8."""
+    for block in (43, 63, 127):
+        assert sbs.get_plan(frame(W, H, 3, block, dmax))["chunk"] == 8
+
+
+def test_small_windows_by_launch_size():
+    """Blocks up to 31: the smallest items for a launch that cannot fill the
+    chip, taller ones as it grows."""
+    rows = [sbs.get_plan(frame(W, H, C, b, d))["tile_rows"]
+            for W, H, C, b, d in ((384, 288, 1, 15, 15), (1390, 1110, 3, 21, 63), (4096, 2304, 3, 31, 127), (8192, 4608, 3, 31, 127))]
+    assert rows == [8, 16, 32, 64]
