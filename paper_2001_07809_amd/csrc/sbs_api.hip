@@ -418,14 +418,19 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
   int st = device_check(&cus);
   if (st != SBS_OK) return st;
 
-  // One plan per call (from the first frame with work): the persistent kernel is one instance.
+  // One plan per launch (keyed by its first frame with work): one launch covers
+  // all frames in the batched kernel, which is one instance, and one frame
+  // otherwise. (Launches of one frame each on the first frame's plan: a
+  // 4096x2304 frame behind one of 384x288 ran in 8 x 8 items, 481 us for the
+  // two, 342 so.)
   int lead = 0;
   while (lead < nframes && frames[lead].n == 0) ++lead;
-  // One launch covers all frames in the batched kernel, one frame otherwise.
-  const Plan plan = mode == kBatched ? choose_plan(frames, nframes, frames[lead])
-                                     : choose_plan(frames + lead, 1, frames[lead]);
+  std::vector<Plan> plans((size_t)nframes);
   std::vector<int> cpl((size_t)nframes), span((size_t)nframes);
   for (int i = 0; i < nframes; ++i) {
+    Plan& plan = plans[(size_t)i];
+    if (mode != kBatched) plan = choose_plan(frames + i, 1, frames[i]);
+    else plan = i == 0 ? choose_plan(frames, nframes, frames[lead]) : plans[0];
     cpl[(size_t)i] = cpl_of(frames[i], plan.cpl, plan.chunk, plan.ty);
     span[(size_t)i] = kWave * cpl[(size_t)i];
   }
@@ -477,6 +482,7 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     d.dmax = f.dmax;
     d.lpw = L.lpw; d.rpw = L.rpw; d.ph = L.ph; d.lpad = L.lpad; d.rpad = L.rpad; d.rbw = L.rbw;
     d.txo = L.txo;
+    const Plan& plan = plans[(size_t)i];
     const Tiles t = tiles_of(f, plan.chunk, plan.ty, plan.cpl, mode != kBatched);
     d.ty = t.ty;
     d.ty2 = t.ty2;
@@ -505,7 +511,7 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
       if (e != hipSuccess) return hip_fail(e, "prologue");
       hipEvent_t ev = nullptr;
       if (timed) timing_begin(s, &ev);
-      e = launch_tile_grid(table, i, host[(size_t)i].nitems, plan.chunk, cpl[(size_t)i] == 8, s);
+      e = launch_tile_grid(table, i, host[(size_t)i].nitems, plans[(size_t)i].chunk, cpl[(size_t)i] == 8, s);
       timing_end(s, ev);
       if (e != hipSuccess) return hip_fail(e, "tile kernel");
       e = launch_finalize(table, i, 1, s);
@@ -516,6 +522,7 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     if (e != hipSuccess) return hip_fail(e, "descriptor upload");
     e = launch_prologue(table, nframes, max_rows, max_n, hdr, s);
     if (e != hipSuccess) return hip_fail(e, "prologue");
+    const Plan& plan = plans[0];
     const bool wide = std::find(cpl.begin(), cpl.end(), 8) != cpl.end();
     // wide launches hold at most 12 wavefronts per CU (3 per SIMD)
     int64_t grid = (int64_t)cus * (wide ? std::min(plan.wpc, 12) : plan.wpc);

@@ -178,3 +178,29 @@ def test_reconstruct_few_long_rows_take_no_longer_than_an_image(torch, sbs):
         idx, disp = dev(torch, lst.astype(np.int32)), dev(torch, (lst % 60).astype(np.uint8))
         t.append(call_us(torch, lambda: sbs.reconstruct(idx, disp, W, H, 1), reps=30))
     assert max(t[1:]) < 1.3 * t[0], t
+
+
+def search_inputs(torch, W, H, seed):
+    rng = np.random.default_rng(seed)
+    left = rng.integers(0, 256, (H, W, 3), dtype=np.uint8)
+    idx = np.sort(rng.choice(W * H, W * H * 18 // 100, replace=False)).astype(np.uint32)
+    return left, np.roll(left, -4, axis=1), idx
+
+
+def test_per_frame_launches_take_each_frame_s_plan(torch, sbs):
+    """Frames of one, two and three sizes launched one by one: the results are
+    the single calls', and the time does not depend on which frame comes first
+    (1.25 times when the first frame's plan was all frames')."""
+    big, small, mid = search_inputs(torch, 4096, 2304, 1), search_inputs(torch, 200, 150, 2), search_inputs(torch, 640, 480, 3)
+    params = {id(big): (21, 127), id(small): (15, 15), id(mid): (61, 31)}
+    t = []
+    for frames in ([big, small], [small, big], [small, mid, big, mid]):
+        args = [(dev(torch, L), dev(torch, R), dev(torch, i.view(np.int32)), *params[id(f)]) for f in frames for L, R, i in [f]]
+        runner = sbs.BatchRunner(args)
+        runner.run_per_frame()
+        torch.cuda.synchronize()
+        for k, a in enumerate(args):
+            d, c = sbs.sad_disparity(*a)
+            assert torch.equal(runner.disp[k], d) and torch.equal(runner.cost[k], c), k
+        t.append(call_us(torch, runner.run_per_frame))
+    assert t[1] < 1.15 * t[0], t
