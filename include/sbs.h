@@ -146,8 +146,8 @@ int sbs_check_indices(const sbs_frame* frames, int32_t nframes, void* workspace,
 
 /*
  * Autotuner: times each tile plan (columns per lane, disparities per chunk,
- * rows per tile, persistent grid size) on these frames, keeps the fastest, and
- * stores it under the key (arch, W, H, C, block, dmax, density bucket,
+ * rows per tile, persistent grid size) on these frames, the plan that calls
+ * take by default among them, keeps the fastest, and stores it under the key (arch, W, H, C, block, dmax, density bucket,
  * frames per call rounded up to a power of two; taken from the first frame
  * with a non-empty list) in a JSON cache at cache_path (created or updated;
  * NULL: in memory only). Later calls with a matching key use the stored plan.

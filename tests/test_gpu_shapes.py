@@ -204,3 +204,22 @@ def test_per_frame_launches_take_each_frame_s_plan(torch, sbs):
             assert torch.equal(runner.disp[k], d) and torch.equal(runner.cost[k], c), k
         t.append(call_us(torch, runner.run_per_frame))
     assert t[1] < 1.15 * t[0], t
+
+
+def test_tuned_plan_is_no_slower_than_the_default(torch, sbs, tmp_path):
+    """A small frame, whose default plan has lower items than 32 rows, tuned: the
+    tuner has such items among its plans and the default plan itself, so a call
+    on the stored plan takes no longer than one before."""
+    left, right, idx = search_inputs(torch, 392, 296, 4)
+    args = [dev(torch, left[:, :, 0].copy()), dev(torch, right[:, :, 0].copy()), dev(torch, idx.view(np.int32)), 15, 15]
+    d, c = (x.clone() for x in sbs.sad_disparity(*args))
+    before = call_us(torch, lambda: sbs.sad_disparity(*args), reps=40)
+    out = torch.empty_like(d)
+    frame = sbs.make_frame(*args, out, None)
+    assert sbs.get_plan(frame)["tile_rows"] == 8
+    sbs.tune([frame], str(tmp_path / "tuning.json"))
+    assert sbs.get_plan(frame)["tile_rows"] < 32
+    after = call_us(torch, lambda: sbs.sad_disparity(*args), reps=40)
+    d1, c1 = sbs.sad_disparity(*args)
+    assert torch.equal(d, d1) and torch.equal(c, c1) and torch.equal(out, d)
+    assert after < 1.15 * before, (before, after)
