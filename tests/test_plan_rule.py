@@ -50,3 +50,23 @@ def test_small_windows_by_launch_size():
     rows = [sbs.get_plan(frame(W, H, C, b, d))["tile_rows"]
             for W, H, C, b, d in ((384, 288, 1, 15, 15), (1390, 1110, 3, 21, 63), (4096, 2304, 3, 31, 127), (8192, 4608, 3, 31, 127))]
     assert rows == [8, 16, 32, 64]
+
+
+def test_plans_between_two_and_three_times_the_slots():
+    """One frame: 16 disparities and 16 rows, but 8 x 32 for windows above 21
+    whose last 16 disparities are half empty; several: 16 x 32."""
+    def plan(*a):
+        p = sbs.get_plan(frame(*a))
+        return p["chunk"], p["tile_rows"]
+    for C in (1, 3):
+        assert plan(3072, 2304, C, 15, 74) == (16, 16)
+        assert plan(3072, 2304, C, 15, 70) == (16, 16)
+        assert plan(3072, 2304, C, 31, 74) == (16, 16)
+        assert plan(2552, 1600, C, 31, 116) == (8, 32)
+        assert plan(2552, 1600, C, 21, 116) == (16, 16)
+        f = [frame(1390, 1110, C, 31, 63)] * 5
+        p = sbs.Plan()
+        arr = (sbs.Frame * len(f))(*f)
+        import ctypes
+        assert sbs.lib().sbs_get_plan_batched(arr, len(f), ctypes.byref(p)) == 0
+        assert (p.chunk, p.tile_rows) == (16, 32)
