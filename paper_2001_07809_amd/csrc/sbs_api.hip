@@ -489,8 +489,6 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     const Plan& plan = plans[(size_t)i];
     const Tiles t = tiles_of(f, plan.chunk, plan.ty, plan.cpl, mode != kBatched);
     d.ty = t.ty;
-    d.ty2 = t.ty2;
-    d.ysplit = t.ysplit;
     d.ntx = t.ntx;
     d.nty = t.nty;
     d.chunk = plan.chunk;

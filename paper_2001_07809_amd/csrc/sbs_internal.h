@@ -40,13 +40,13 @@ struct FrameDev {
   int32_t lpad, rpad;    // copy column of image column c: c + lpad (left), c + rpad (right); multiples of 4
   int32_t rbw;           // u64 words per row in rowbits
   int32_t txo, ty;       // tile: output columns and rows
-  int32_t ntx, nty;      // tiles per row / column (the main tiles: ty rows each, from the top)
-  int32_t ysplit, ty2;   // rows from ysplit on lie in tiles of ty2 rows (the tail tiles, after the main ones)
+  int32_t ntx, nty;      // tiles per row / column (the main tiles: ty rows each, from the top); the rows
+                         // after nty * ty lie in tiles of ty / 2 rows (the tail tiles, after the main ones)
   int32_t nch, chunk;    // disparity chunks and their size
   int32_t tpw;           // entries per row of tptr (ntx + 1)
   int32_t pack;          // 1: the sum of two window columns (<= 2 * block * 255 * C) fits in 16 bits;
                          // 2: so does a whole window's sum (<= block^2 * 255 * C)
-  int32_t cpl;           // window columns per lane: 4, or 8 (ordered lists, 8-disparity chunks, pack == 1)
+  int32_t cpl;           // window columns per lane: 4, or 8 (ordered lists, 8-disparity chunks, pack > 0)
   int32_t linpl;         // 1: tiles whose window lies inside the image read the left image in place
                          // (C == 3, 4-byte-aligned rows); the left copy then holds only the edge bands
 };
@@ -72,6 +72,7 @@ struct WsHeader {
   __device__ __forceinline__ unsigned long long* head(int q) { return &heads[16 * q]; }
 };
 constexpr size_t kHeaderBytes = 1024;
+static_assert(sizeof(FrameDev) == 280, "sbs_workspace_bytes holds one per frame: callers' buffers are that large");
 static_assert(sizeof(WsHeader) <= kHeaderBytes && 16 * (kQueues - 1) < 16 * kQueues - 8, "header");
 
 // Records `msg` as the calling thread's last error (sbs_last_error) and returns status.

@@ -719,10 +719,10 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   const int f_tpw = f.tpw, f_rbw = f.rbw;
   const int tx = tile % f.ntx, tyi = tile / f.ntx;
   const bool tail = tyi >= f.nty;   // main tiles first, then the lower tail tiles
-  const int f_ty = tail ? f.ty2 : f.ty;
+  const int f_ty = tail ? max(f.ty / 2, 1) : f.ty;
   const int W = f.W, H = f.H, r = f.r;
-  const int x0 = xs, y0 = tail ? f.ysplit + (tyi - f.nty) * f_ty : tyi * f_ty;
-  const int x1 = xe, y1 = min(y0 + f_ty, tail ? H : f.ysplit);
+  const int x0 = xs, y0 = tail ? f.nty * f.ty + (tyi - f.nty) * f_ty : tyi * f_ty;
+  const int x1 = xe, y1 = min(y0 + f_ty, H);
   const int d0 = chunk * DC;
   const int dcount = min(DC, f.dmax + 1 - d0);
   const int lpad = f.lpad;
