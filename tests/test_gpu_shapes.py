@@ -223,3 +223,17 @@ def test_tuned_plan_is_no_slower_than_the_default(torch, sbs, tmp_path):
     d1, c1 = sbs.sad_disparity(*args)
     assert torch.equal(d, d1) and torch.equal(c, c1) and torch.equal(out, d)
     assert after < 1.15 * before, (before, after)
+
+
+@pytest.mark.parametrize("W,H", [(8192, 5), (8193, 5), (9001, 7), (20011, 3)])
+def test_fraction_control_of_wide_rows(torch, sbs, W, H):
+    """Fractions that end far from every boundary pixel, on rows that are
+    searched in LDS (up to 8,192 pixels) and in memory, flat and with a region."""
+    img = np.full((H, W), 40, np.uint8)
+    region = img.copy()
+    region[:, W // 3: W // 3 + 50] = 210
+    for what, im in (("flat", img), ("region", region)):
+        for frac in (0.01, 0.3, 0.77, 0.999):
+            got = sbs.boundaries(dev(torch, im), K=2, mode=0, min_cc=1, frac=frac, seed=5).cpu().numpy().view(np.uint32)
+            exp = oracle.boundaries(im, K=2, mode=0, min_cc=1, frac=frac, seed=5)
+            assert np.array_equal(got, exp), f"{W}x{H} {what} {frac}"
