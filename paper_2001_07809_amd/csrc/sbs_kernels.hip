@@ -687,10 +687,11 @@ __device__ __forceinline__ void slide_row(RowRegs<DC, COLS>& en, RowRegs<DC, COL
 // frame's ntx x nty tiles) for disparity chunk `chunk` (disparities
 // chunk*DC .. +DC-1), COLS window columns per lane. Ordered lists take the
 // whole tile in one pass; unordered lists may take a tile in several
-// narrower passes. The window columns of the pass start lpad > r columns
-// left of xs.
+// narrower passes, and `stack` of them in one (this tile and the ones below).
+// The window columns of the pass start lpad > r columns left of xs.
 template <int DC, bool kSorted, bool kPack, int COLS, bool kNarrow = false>
-__device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int chunk, int xs, int xe, TileLds& smu) {
+__device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int chunk, int xs, int xe, TileLds& smu,
+                                               int stack = 1) {
   static_assert(COLS == 4 || (kSorted && kPack), "8 columns per lane: ordered lists, packed accumulators");
   constexpr int kSpanC = Geom<COLS>::kSpanC;
   static_assert(!kNarrow || (kPack && COLS == 4), "narrow windows: packed accumulators, 4 columns per lane");
@@ -719,9 +720,10 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
   const int f_tpw = f.tpw, f_rbw = f.rbw;
   const int tx = tile % f.ntx, tyi = tile / f.ntx;
   const bool tail = tyi >= f.nty;   // main tiles first, then the lower tail tiles
-  const int f_ty = tail ? max(f.ty / 2, 1) : f.ty;
+  const int tile_ty = tail ? max(f.ty / 2, 1) : f.ty;
+  const int f_ty = kSorted ? tile_ty : stack * tile_ty;
   const int W = f.W, H = f.H, r = f.r;
-  const int x0 = xs, y0 = tail ? f.nty * f.ty + (tyi - f.nty) * f_ty : tyi * f_ty;
+  const int x0 = xs, y0 = tail ? f.nty * f.ty + (tyi - f.nty) * tile_ty : tyi * tile_ty;
   const int x1 = xe, y1 = min(y0 + f_ty, H);
   const int d0 = chunk * DC;
   const int dcount = min(DC, f.dmax + 1 - d0);
@@ -1109,18 +1111,9 @@ __device__ __forceinline__ void tile_item_impl(const FrameDev& f, int tile, int 
 // 8-disparity chunks for frames whose window sums need 32 bits).
 template <bool kPack>
 __device__ __forceinline__ void tile_item8(const FrameDev& f, int tile, int chunk8, bool unsorted, int xs, int xe,
-                                           TileLds& sm) {
-  if (unsorted) tile_item_impl<8, false, kPack, 4>(f, tile, chunk8, xs, xe, sm);
+                                           TileLds& sm, int stack = 1) {
+  if (unsorted) tile_item_impl<8, false, kPack, 4>(f, tile, chunk8, xs, xe, sm, stack);
   else tile_item_impl<8, true, kPack, 4>(f, tile, chunk8, xs, xe, sm);
-}
-
-// The same as an out-of-line call: inside the 16-disparity kernels its
-// registers then do not add to those of the 16-disparity instance (it serves
-// the less common frames there).
-template <bool kPack>
-__device__ __noinline__ void tile_item8_call(const FrameDev& f, int tile, int chunk8, bool unsorted, int xs, int xe,
-                                             TileLds& sm) {
-  tile_item8<kPack>(f, tile, chunk8, unsorted, xs, xe, sm);
 }
 
 // Items of a launch that has frames laid out with 8 columns per lane, other
@@ -1145,8 +1138,12 @@ __device__ __noinline__ void tile_item_wide_rest(const FrameDev& f, int tile, in
 // wide instance, everything else tile_item_wide_rest. Other launches (every
 // frame with 4 columns per lane): a 16-disparity item of an ordered list with
 // packed accumulators runs as one pass; any other frame runs its 16
-// disparities as two 8-disparity passes (same work decomposition, fewer
-// registers).
+// disparities as two 8-disparity passes. Of an unordered list, the items of two
+// tiles one above the other share the two passes: each takes one of them over
+// both tiles, which makes a pass of as many rows and half the window starts, and
+// an item of one pass, not two one after another (20 frames of 352x75 RGB, block
+// 15, dmax 255, reversed lists: 218 -> 205 us; with the passes in this kernel
+// and not behind a call, whose saved registers went through memory, 171).
 template <int DC, bool kWide>
 __device__ __forceinline__ void tile_item(const FrameDev& f, int tile, int chunk, TileLds& sm) {
   const bool unsorted = *(g_uint32*)f.state & kUnsorted;
@@ -1166,17 +1163,25 @@ __device__ __forceinline__ void tile_item(const FrameDev& f, int tile, int chunk
     return;
   }
   constexpr int kParts = DC / 8;
+  int h0 = 0, h1 = kParts, stack = 1;
+  if constexpr (DC == 16) {
+    const int tyi = tile / f.ntx;
+    const bool tail = tyi >= f.nty;
+    const int ty = tail ? max(f.ty / 2, 1) : f.ty;
+    const int j = tail ? tyi - f.nty : tyi, count = tail ? (f.H - f.nty * f.ty + ty - 1) / ty : f.nty;
+    if (unsorted && 16 * chunk + 8 <= f.dmax && 2 * ty <= kMaxTileRows && (j ^ 1) < count) {
+      h0 = j & 1;
+      h1 = h0 + 1;
+      tile -= h0 * f.ntx;
+      stack = 2;
+    }
+  }
 #pragma unroll 1
-  for (int h = 0; h < kParts; ++h) {
+  for (int h = h0; h < h1; ++h) {
     const int c8 = kParts * chunk + h;
     if (c8 * 8 > f.dmax) break;
-    if constexpr (DC == 8) {
-      if (f.pack) tile_item8<true>(f, tile, c8, unsorted, x0, x1, sm);
-      else tile_item8<false>(f, tile, c8, unsorted, x0, x1, sm);
-    } else {
-      if (f.pack) tile_item8_call<true>(f, tile, c8, unsorted, x0, x1, sm);
-      else tile_item8_call<false>(f, tile, c8, unsorted, x0, x1, sm);
-    }
+    if (f.pack) tile_item8<true>(f, tile, c8, unsorted, x0, x1, sm, stack);
+    else tile_item8<false>(f, tile, c8, unsorted, x0, x1, sm, stack);
   }
 }
 

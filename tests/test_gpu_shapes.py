@@ -237,3 +237,60 @@ def test_fraction_control_of_wide_rows(torch, sbs, W, H):
             got = sbs.boundaries(dev(torch, im), K=2, mode=0, min_cc=1, frac=frac, seed=5).cpu().numpy().view(np.uint32)
             exp = oracle.boundaries(im, K=2, mode=0, min_cc=1, frac=frac, seed=5)
             assert np.array_equal(got, exp), f"{W}x{H} {what} {frac}"
+
+
+@pytest.mark.parametrize("H", [1, 7, 8, 9, 16, 17, 33, 130])
+@pytest.mark.parametrize("rows", [8, 16, 128, 256])
+def test_lists_in_no_order_in_stacked_tiles(torch, sbs, H, rows):
+    """Reversed and shuffled lists in items of 16 disparities, which take two
+    tiles one above the other by 8 disparities each: odd and even numbers of
+    tile rows, main and tail tiles, an odd number of 8-disparity chunks, sums
+    that pack and not, a frame on its own and in a batch."""
+    rng = np.random.default_rng(H * rows)
+    for W, C, block, dmax in ((37, 3, 5, 15), (260, 1, 9, 23), (50, 3, 45, 18)):
+        left = rng.integers(0, 256, (H, W, 3) if C == 3 else (H, W), dtype=np.uint8)
+        right = np.roll(left, -3, axis=1)
+        idx = np.sort(rng.choice(W * H, max(W * H // 4, 1), replace=False)).astype(np.uint32)
+        lists = [idx[::-1].copy(), rng.permutation(idx), np.concatenate([idx, idx[:idx.size // 2]])]
+        sbs.set_plan(cols_per_lane=4, chunk=16, tile_rows=rows)
+        try:
+            args = [(dev(torch, left), dev(torch, right), dev(torch, i.view(np.int32)), block, dmax) for i in lists]
+            runner = sbs.BatchRunner(args)
+            runner.run()
+            for k, i in enumerate(lists):
+                ed, ec, _ = oracle.sad(left, right, i, block, dmax)
+                for d, c in (sbs.sad_disparity(*args[k]), (runner.disp[k], runner.cost[k])):
+                    assert np.array_equal(d.cpu().numpy(), ed) and np.array_equal(c.cpu().numpy().view(np.uint32), ec), (W, C, k)
+        finally:
+            sbs.set_plan()
+
+
+def test_main_and_tail_tiles_of_lists_in_no_order(torch, sbs):
+    """Enough items for main tiles above the tail ones, odd numbers of both."""
+    W = 24
+    for H in (9000, 9009, 9020):
+        rng = np.random.default_rng(H)
+        left = rng.integers(0, 256, (H, W), dtype=np.uint8)
+        idx = rng.permutation(W * H)[:W * H // 6].astype(np.uint32)
+        sbs.set_plan(chunk=16, tile_rows=8)
+        try:
+            d, c = sbs.sad_disparity(dev(torch, left), dev(torch, np.roll(left, -2, 1)), dev(torch, idx.view(np.int32)), 5, 31)
+        finally:
+            sbs.set_plan()
+        ed, ec, _ = oracle.sad(left, np.roll(left, -2, 1), idx, 5, 31)
+        assert np.array_equal(d.cpu().numpy(), ed) and np.array_equal(c.cpu().numpy().view(np.uint32), ec), H
+
+
+def test_lists_in_no_order_run_as_in_8_disparity_items(torch, sbs):
+    """A reversed list on the default plan against items of 8 disparities and 32
+    rows, in which it runs in one pass: 1.4 times the call when an item of 16
+    disparities was two passes one after another."""
+    left, right, idx = search_inputs(torch, 1000, 800, 6)
+    args = (dev(torch, left), dev(torch, right), dev(torch, idx[::-1].copy().view(np.int32)), 31, 47)
+    t = [call_us(torch, lambda: sbs.sad_disparity(*args))]
+    sbs.set_plan(cols_per_lane=4, chunk=8, tile_rows=32)
+    try:
+        t.append(call_us(torch, lambda: sbs.sad_disparity(*args)))
+    finally:
+        sbs.set_plan()
+    assert t[0] < 1.2 * t[1], t
