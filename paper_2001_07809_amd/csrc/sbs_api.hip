@@ -499,7 +499,8 @@ int run(const sbs_frame* frames, int nframes, void* workspace, size_t ws_bytes, 
     const int64_t ntiles = f.n > 0 ? (int64_t)t.ntx * t.nrows : 0;
     for (int q = 0; q < kQueues; ++q) {
       d.xbase[q] = qt.t[q];
-      const int64_t tq = ntiles > q ? (ntiles - q + kQueues - 1) / kQueues : 0;
+      const int first = (q - i) & (kQueues - 1);   // this queue's first tile
+      const int64_t tq = ntiles > first ? (ntiles - first + kQueues - 1) / kQueues : 0;
       qt.t[q] += tq * d.nch;
     }
     max_rows = std::max(max_rows, L.ph);

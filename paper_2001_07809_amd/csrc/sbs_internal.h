@@ -12,7 +12,7 @@ constexpr int kMaxChunk = 16;         // largest disparity chunk a kernel instan
 constexpr int kMaxTileRows = 256;     // largest tile height (four 64-bit row masks)
 constexpr int kDescPerLaunch = 8;          // descriptors carried by one upload kernel
 constexpr uint32_t kUnsorted = 1u;         // FrameDev::state bit
-constexpr int kQueues = 8;                 // one work queue per XCD; tile t's items go to queue t % 8
+constexpr int kQueues = 8;                 // one work queue per XCD; tile t's items of frame i go to queue (t + i) % 8
 
 // Per-frame descriptor as the kernels see it (lives in the workspace).
 struct FrameDev {

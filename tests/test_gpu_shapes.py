@@ -294,3 +294,40 @@ def test_lists_in_no_order_run_as_in_8_disparity_items(torch, sbs):
     finally:
         sbs.set_plan()
     assert t[0] < 1.2 * t[1], t
+
+
+def test_batches_of_few_tiles(torch, sbs):
+    """Frames of one to nine tiles, some with empty lists, more and fewer of them
+    than queues: the results are the oracle's."""
+    rng = np.random.default_rng(9)
+    host, args = [], []
+    for t, (W, H, n) in enumerate([(4, 13, 9), (300, 3, 50), (30, 70, 0), (500, 40, 900), (1, 1, 1), (9, 9, 0), (9, 9, 20),
+                                   (260, 20, 300), (2, 90, 40), (700, 9, 100), (20, 5, 30)] * 2):
+        left = rng.integers(0, 256, (H, W, 3), dtype=np.uint8)
+        idx = np.sort(rng.choice(W * H, min(n, W * H), replace=False)).astype(np.uint32)
+        host.append((left, np.roll(left, -1, 1), idx))
+        args.append((*(dev(torch, a) for a in host[-1][:2]), dev(torch, idx.view(np.int32)), 5, (255, 31)[t % 2]))
+    for some in (slice(0, 22), slice(0, 3), slice(2, 6), slice(5, 14)):
+        runner = sbs.BatchRunner(args[some])
+        for _ in range(2):
+            runner.run()
+        for k, (L, R, idx) in enumerate(host[some]):
+            if not idx.size:
+                continue
+            ed, ec, _ = oracle.sad(L, R, idx, 5, args[some][k][4])
+            assert np.array_equal(runner.disp[k].cpu().numpy(), ed), (some, k)
+            assert np.array_equal(runner.cost[k].cpu().numpy().view(np.uint32), ec), (some, k)
+
+
+def test_batches_of_few_tiles_fill_all_queues(torch, sbs):
+    """20 frames of one or two tiles with 256 disparities against the same with
+    8: 2.3 times the call when all their items were in the first two queues, 1.6
+    times over all of them."""
+    rng = np.random.default_rng(10)
+    left = dev(torch, rng.integers(0, 256, (13, 4), dtype=np.uint8))
+    idx = dev(torch, np.arange(0, 52, 2).astype(np.int32))
+    t = []
+    for dmax in (255, 7):
+        runner = sbs.BatchRunner([(left, left, idx, 9, dmax)] * 20)
+        t.append(call_us(torch, runner.run, reps=40))
+    assert t[0] < 2 * t[1], t
