@@ -331,3 +331,36 @@ def test_batches_of_few_tiles_fill_all_queues(torch, sbs):
         runner = sbs.BatchRunner([(left, left, idx, 9, dmax)] * 20)
         t.append(call_us(torch, runner.run, reps=40))
     assert t[0] < 2 * t[1], t
+
+
+@pytest.mark.parametrize("W,H", [(37, 4500), (4200, 2100), (9000, 1500)])
+def test_row_bits_of_large_arrays(torch, sbs, W, H):
+    """Lists in no order on images whose row bits are set in memory (more than
+    4,096 words): ordered but for one descent, reversed, shuffled, sparse,
+    entries past the image among them."""
+    rng = np.random.default_rng(W)
+    left = rng.integers(0, 256, (H, W), dtype=np.uint8)
+    right = np.roll(left, -2, 1)
+    dl, dr = dev(torch, left), dev(torch, right)
+    idx = np.sort(rng.choice(W * H, W * H // 40, replace=False)).astype(np.uint32)
+    for what, lst in {"one descent": np.concatenate([idx, idx[:100]]), "reversed": idx[::-1].copy(), "shuffled": rng.permutation(idx),
+                      "sparse": rng.permutation(idx)[:300], "past": np.concatenate([idx[::-1], [W * H, 2 ** 32 - 1, 5]]).astype(np.uint32)}.items():
+        d, c = sbs.sad_disparity(dl, dr, dev(torch, lst.view(np.int32)), 3, 7)
+        ed, ec, _ = oracle.sad(left, right, np.minimum(lst, W * H - 1), 3, 7)
+        out = lst >= W * H
+        ed[out], ec[out] = 255, 0xFFFFFFFF
+        assert np.array_equal(d.cpu().numpy(), ed) and np.array_equal(c.cpu().numpy().view(np.uint32), ec), what
+
+
+def test_row_bits_of_dense_lists_take_no_atomic_each(torch, sbs):
+    """A dense list with one descent on an image whose row bits do not fit the
+    LDS, against one of as many pixels whose do: 2.2 times the call when every
+    entry set its bit by itself."""
+    t = []
+    for W, H in ((365, 4750), (444, 3905)):
+        rng = np.random.default_rng(H)
+        left = rng.integers(0, 256, (H, W), dtype=np.uint8)
+        idx = np.sort(rng.choice(W * H, W * H * 5 // 6, replace=False))
+        args = (dev(torch, left), dev(torch, left), dev(torch, np.concatenate([idx, idx[:idx.size // 2]]).astype(np.int32)), 5, 31)
+        t.append(call_us(torch, lambda: sbs.sad_disparity(*args)))
+    assert t[0] < 1.4 * t[1], t
