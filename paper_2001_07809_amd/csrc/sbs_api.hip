@@ -227,18 +227,27 @@ double launch_steps(const sbs_frame* frames, int nframes, int chunk, int ty) {
 // window above 21 takes 8 x 32 where 16 disparities would leave half of the
 // last chunk empty (2552x1600, block 31, dmax 116: 16 x 16 177, 8 x 32 163 us;
 // 3072x2304 grey, block 15, dmax 74, chunks full: 149 and 202 us).
-// These lines hold for blocks up to 31 whose sums pack. A larger window's
-// first sum is worth many rows, and 16 disparities are no gain without packed
-// sums, so launches with such frames take the plan of least estimated time
+// These lines hold for blocks up to 31 whose sums pack and 8 disparities and
+// more. A larger window's first sum is worth many rows, and 16 disparities are
+// no gain without packed sums, or where 8 are not searched, so launches with
+// such frames take the plan of least estimated time
 // (1390x1110, dmax 63: RGB, block 101: 376 us by the lines above, 124 so; grey
 // 182 and 120; RGB, block 61: 270 and 101; 4096x2304 RGB, dmax 127, block 61:
-// 905 and 388). For smaller windows the estimate is the worse rule (4096x2304,
-// block 21, dmax 127: 328 us, 285 by the lines).
+// 905 and 388; block 31, dmax 7: 106 and 88). For the others the estimate is
+// the worse rule (4096x2304, block 21, dmax 127: 328 us, 285 by the lines).
 Plan default_plan(const sbs_frame* frames, int nframes) {
+  int64_t n16 = 0;
+  bool lines = true;   // (a frame on its own that cannot fill the chip takes the first line in any case)
   for (int i = 0; i < nframes; ++i) {
-    if (frames[i].n <= 0 || (frames[i].block <= 31 && packs(frames[i]))) continue;
-    Plan p;
-    p.wpc = 16;
+    const sbs_frame& f = frames[i];
+    if (f.n <= 0) continue;
+    n16 += tiles_of(f, 16, 16, 4, false).items();
+    lines &= f.block <= 31 && packs(f) && f.dmax >= 8;
+  }
+  constexpr int64_t kSlots = 256 * 16;
+  Plan p;
+  p.wpc = 16;
+  if (!lines && !(nframes == 1 && n16 < kSlots / 8)) {
     double best = 1e300;
     for (int chunk : {8, 16})
       for (int ty : {8, 16, 32, 64, 96}) {
@@ -247,12 +256,6 @@ Plan default_plan(const sbs_frame* frames, int nframes) {
       }
     return p;
   }
-  int64_t n16 = 0;
-  for (int i = 0; i < nframes; ++i)
-    if (frames[i].n > 0) n16 += tiles_of(frames[i], 16, 16, 4, false).items();
-  constexpr int64_t kSlots = 256 * 16;
-  Plan p;
-  p.wpc = 16;
   p.chunk = n16 < kSlots / 8 ? 8 : 16;
   p.ty = n16 < kSlots / 8 ? 8 : n16 < (nframes == 1 ? 3 : 2) * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
   const bool half = (frames[0].dmax & 15) < 8;   // the last 16 disparities: at most 8 of them searched

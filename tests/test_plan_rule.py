@@ -70,3 +70,14 @@ def test_plans_between_two_and_three_times_the_slots():
         import ctypes
         assert sbs.lib().sbs_get_plan_batched(arr, len(f), ctypes.byref(p)) == 0
         assert (p.chunk, p.tile_rows) == (16, 32)
+
+
+@pytest.mark.parametrize("C", [1, 3])
+def test_fewer_than_8_disparities_take_8(C):
+    """Items of 16 disparities would be half empty."""
+    for W, H in ((1390, 1110), (1920, 1080), (4096, 2304)):
+        for block in (9, 31):
+            for dmax in (0, 7):
+                assert sbs.get_plan(frame(W, H, C, block, dmax))["chunk"] == 8
+    assert sbs.get_plan(frame(4096, 2304, C, 31, 8))["chunk"] == 16
+    assert sbs.get_plan(frame(384, 288, C, 127, 15))["tile_rows"] == 8
