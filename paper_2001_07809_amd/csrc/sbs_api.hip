@@ -215,18 +215,22 @@ double launch_steps(const sbs_frame* frames, int nframes, int chunk, int ty) {
 // smallest items win (384x288 grey 50 -> 27 us against 8 x 32 items, 640x480
 // 54 -> 28 us); then 16 disparities at rows that grow with the launch: 16 rows
 // (1390x1110, block 21, dmax 63: 76 -> 63 us against 8 x 32; 8 frames of
-// 640x480: 96 -> 86 us), 32 rows (2976x2008, dmax 125: 256 -> 240 us against 16
-// rows; 4096x2304: 357 -> 325 us; a serving mix of ten frames: 690 -> 629 us
+// 640x480: 96 -> 86 us), 32 rows (a serving mix of ten frames: 690 -> 629 us
 // against 8 x 64), 64 rows (8192x4608: 16 rows 1094, 64 rows 941 us; 6 frames
 // of 4096x2304 1.55 -> 1.42 ms against 128 rows), 96 rows (24 such frames: 64
-// rows 5.39, 96 rows 5.36, 128 rows 5.44 ms), 128 rows beyond. 32 rows begin at
-// three times the slots for one frame, whose last items are lower ones anyway,
-// and at twice them for several (between the two, geometric means over the best
-// of five plans: one frame, 82 of 1390x1110 to 4096x2304 with blocks up to 31: 16
-// x 16 1.02, 16 x 32 1.04; 48 batches: 1.07 and 1.00). There one frame with a
-// window above 21 takes 8 x 32 where 16 disparities would leave half of the
-// last chunk empty (2552x1600, block 31, dmax 116: 16 x 16 177, 8 x 32 163 us;
-// 3072x2304 grey, block 15, dmax 74, chunks full: 149 and 202 us).
+// rows 5.39, 96 rows 5.36, 128 rows 5.44 ms), 128 rows beyond. For several
+// frames 32 rows begin at twice the slots (48 batches up to three times them:
+// 16 x 16 1.07 times the best of five plans, 16 x 32 1.00). For one frame,
+// whose last items are lower ones anyway, they begin at six times: below that
+// 16 rows are as good for lists spread over the image (4096x2304 RGB, dmax 127:
+// block 15 258 us, 278 in 32 rows; block 21 276 and 291; block 31 303 and 308,
+// 296 in 24 rows), and a list that lies in one region of it has few items of 32
+// rows or more to share out (all pixels of a tenth of the columns, 2902x1473,
+// block 31, dmax 255: 177 us in 32 rows, 119 in 16). Between two and three
+// times the slots one frame with a window above 21 takes 8 x 32 where 16
+// disparities would leave half of the last chunk empty (2552x1600, block 31,
+// dmax 116: 16 x 16 177, 8 x 32 163 us; 3072x2304 grey, block 15, dmax 74,
+// chunks full: 149 and 202 us).
 // These lines hold for blocks up to 31 whose sums pack and 8 disparities and
 // more. A larger window's first sum is worth many rows, and 16 disparities are
 // no gain without packed sums, or where 8 are not searched, so launches with
@@ -248,18 +252,24 @@ Plan default_plan(const sbs_frame* frames, int nframes) {
   Plan p;
   p.wpc = 16;
   if (!lines && !(nframes == 1 && n16 < kSlots / 8)) {
+    // (one frame: no higher than it takes, for lists that lie in one region)
+    const int most = nframes > 1 ? 96 : !packs(frames[0]) || frames[0].block > 47 ? 64 : frames[0].block > 41 || n16 < 2 * kSlots ? 32 : 24;
     double best = 1e300;
     for (int chunk : {8, 16})
-      for (int ty : {8, 16, 32, 64, 96}) {
+      for (int ty : {8, 16, 24, 32, 64, 96}) {
+        if (ty > most) break;
         const double t = launch_steps(frames, nframes, chunk, ty);
         if (t < best) { best = t; p.chunk = chunk; p.ty = ty; }
       }
     return p;
   }
   p.chunk = n16 < kSlots / 8 ? 8 : 16;
-  p.ty = n16 < kSlots / 8 ? 8 : n16 < (nframes == 1 ? 3 : 2) * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
+  p.ty = n16 < kSlots / 8 ? 8 : n16 < (nframes == 1 ? 6 : 2) * kSlots ? 16 : n16 < 16 * kSlots ? 32 : n16 < 64 * kSlots ? 64 : n16 < 256 * kSlots ? 96 : 128;
   const bool half = (frames[0].dmax & 15) < 8;   // the last 16 disparities: at most 8 of them searched
-  if (nframes == 1 && n16 >= 2 * kSlots && n16 < 3 * kSlots && frames[0].block > 21 && half) { p.chunk = 8; p.ty = 32; }
+  if (nframes == 1 && frames[0].block > 21 && n16 >= 2 * kSlots && n16 < 6 * kSlots) {
+    if (n16 >= 3 * kSlots) p.ty = 24;
+    else if (half) { p.chunk = 8; p.ty = 32; }
+  }
   return p;
 }
 

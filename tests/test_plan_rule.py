@@ -48,7 +48,7 @@ def test_small_windows_by_launch_size():
     """Blocks up to 31: the smallest items for a launch that cannot fill the
     chip, taller ones as it grows."""
     rows = [sbs.get_plan(frame(W, H, C, b, d))["tile_rows"]
-            for W, H, C, b, d in ((384, 288, 1, 15, 15), (1390, 1110, 3, 21, 63), (4096, 2304, 3, 31, 127), (8192, 4608, 3, 31, 127))]
+            for W, H, C, b, d in ((384, 288, 1, 15, 15), (1390, 1110, 3, 21, 63), (5000, 3000, 3, 31, 200), (8192, 4608, 3, 31, 127))]
     assert rows == [8, 16, 32, 64]
 
 
@@ -81,3 +81,14 @@ def test_fewer_than_8_disparities_take_8(C):
                 assert sbs.get_plan(frame(W, H, C, block, dmax))["chunk"] == 8
     assert sbs.get_plan(frame(4096, 2304, C, 31, 8))["chunk"] == 16
     assert sbs.get_plan(frame(384, 288, C, 127, 15))["tile_rows"] == 8
+
+
+@pytest.mark.parametrize("C", [1, 3])
+@pytest.mark.parametrize("block", [9, 21, 31, 33, 41])
+def test_one_frame_s_tiles_are_low_enough_for_a_region(C, block):
+    """The pixels of one region of the image lie in few tiles of 32 rows and more:
+    frames of up to six times the slots take 24 rows at most, or 32 by 8
+    disparities, as they did before plans went by size; large windows 32."""
+    for W, H, dmax in ((1390, 1110, 255), (2902, 1473, 255), (4096, 2304, 127)):
+        p = sbs.get_plan(frame(W, H, C, block, dmax))
+        assert p["tile_rows"] <= (32 if p["chunk"] == 8 or block > 31 else 24), p
