@@ -364,3 +364,24 @@ def test_row_bits_of_dense_lists_take_no_atomic_each(torch, sbs):
         args = (dev(torch, left), dev(torch, left), dev(torch, np.concatenate([idx, idx[:idx.size // 2]]).astype(np.int32)), 5, 31)
         t.append(call_us(torch, lambda: sbs.sad_disparity(*args)))
     assert t[0] < 1.4 * t[1], t
+
+
+@pytest.mark.parametrize("K", [1, 2, 4, 5, 6, 17, 33, 63, 64])
+def test_label_images_of_many_clusters(torch, sbs, K):
+    """The label image after open and close at numbers of clusters around groups
+    of four planes and the largest, widths of every remainder of four pixels."""
+    rng = np.random.default_rng(K)
+    for W, H in ((61, 60), (64, 56), (130, 107), (67, 9), (3, 70)):
+        img = np.kron(rng.integers(0, 256, (H // 4 + 1, W // 5 + 1)), np.ones((4, 5)))[:H, :W].astype(np.uint8)
+        _, _, labels = sbs.boundaries(dev(torch, img), K=K, mode=0, min_cc=5, with_maps=True)
+        lab = oracle.label_open_close(oracle.label_pixels(img, oracle.kmeans_bins(oracle.histogram(img), K)[0]))
+        assert np.array_equal(labels.cpu().numpy(), lab), (W, H)
+
+
+def test_label_image_of_many_clusters_is_written_once(torch, sbs):
+    """64 clusters with the label image asked for and without: 3 times the
+    call when a label was read back and written for every four clusters."""
+    rng = np.random.default_rng(8)
+    img = dev(torch, np.kron(rng.integers(0, 256, (60, 80)), np.ones((8, 8))).astype(np.uint8))
+    t = [call_us(torch, lambda: sbs.boundaries(img, K=64, with_maps=maps)) for maps in (True, False)]
+    assert t[0] < 2 * t[1], t
