@@ -1718,9 +1718,6 @@ static_assert(kHashBins == 4 * kBlock, "four bins per thread");
 // leaves most empty. `blocks` blocks take `chunk` words (at most kRingWords) in
 // turn, each after prepare(their first word).
 constexpr int kRingWords = kBlock;          // words a block queues at a time
-// ... and how often in small images (4 leave half the CUs without a block at
-// 4096x2304)
-constexpr int kRingGroups = 2;
 template <typename P, typename F>
 __device__ __forceinline__ void for_ring(const Bits& b, const unsigned long long* planes, int level, int blocks,
                                          int chunk, P prepare, F f) {
@@ -2228,8 +2225,10 @@ __global__ __launch_bounds__(kBlock) void k_fc_columns(Bits b, FcArgs a, SizeSel
 // Counts: mode 1's pixels of the wanted size per block of b.per words | the
 // ring's hashes by their top digit, after the distance passes from the planes
 // that their outcome gives (levels 1: nearer than the wanted distance, 2: at
-// it), made here. `gr` blocks count where the planes are there: each closes
-// with adds to the same 1 KB, and more of them only wait for each other.
+// it), made here. `gr` blocks count where the planes are there, one to a step
+// of the ring, though each closes with adds of its bins to one of kHashParts
+// arrays of 4 KB (half and a quarter as many blocks: 640x480 118, 125 and 130 us
+// a call, 4096x2304 201, 200 and 212).
 constexpr int kFarWords = 64;   // words a block makes at a time, 16 per wavefront
 __global__ __launch_bounds__(kBlock) void k_fc_count(Bits b, FcArgs a, SizeSel z, int nb, int gr,
                                                      const unsigned long long* base, uint32_t* ties, const int32_t* dist,
@@ -2569,7 +2568,7 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
     // the hashes of one bin's ring pixels are listed in the place of the column
     // and pixel distances (8 bytes per pixel between them)
     unsigned long long* ring = (unsigned long long*)gcol;
-    const int gr = (int)std::min<int64_t>((bt.words + kRingGroups * kRingWords - 1) / (kRingGroups * kRingWords), 1024);
+    const int gr = (int)std::min<int64_t>((bt.words + kRingWords - 1) / kRingWords, 1024);
     hipLaunchKernelGGL(k_fc_count, dim3(std::min(std::max(gw, gr), 1024)), dim3(kBlock), 0, s, bt, fa, z, nb, gr, bmap, ties, dist,
                        sd_last, sd_hist, lcount, planes, far_need, hhist);
     hipLaunchKernelGGL(k_ring_bin, dim3(gr), dim3(kBlock), 0, s, bt, fa, planes, lcount, far_need, hhist, rb, ring);
