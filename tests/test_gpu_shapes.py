@@ -385,3 +385,33 @@ def test_label_image_of_many_clusters_is_written_once(torch, sbs):
     img = dev(torch, np.kron(rng.integers(0, 256, (60, 80)), np.ones((8, 8))).astype(np.uint8))
     t = [call_us(torch, lambda: sbs.boundaries(img, K=64, with_maps=maps)) for maps in (True, False)]
     assert t[0] < 2 * t[1], t
+
+
+def test_fraction_control_of_a_large_ring(torch, sbs):
+    """A list that ends among 2.4 million pixels at one distance: over 1,536 of
+    their hashes fall in one bin, more than are ranked in LDS."""
+    W, H = 4096, 2304
+    img = np.repeat((((np.arange(W) // 8) & 1) * 150).astype(np.uint8)[None, :], H, 0)
+    for frac in (0.26, 0.4):
+        got = sbs.boundaries(dev(torch, img), K=2, mode=0, min_cc=1, frac=frac, seed=11).cpu().numpy().view(np.uint32)
+        exp = oracle.boundaries(img, K=2, mode=0, min_cc=1, frac=frac, seed=11)
+        assert np.array_equal(got, exp), frac
+
+
+@pytest.mark.parametrize("nframes,rows", [(2, 64), (7, 96)])
+def test_default_plans_of_tall_tiles(torch, sbs, nframes, rows):
+    """Batches that take 64 and 96 rows without a plan set."""
+    W, H = 4096, 2304
+    rng = np.random.default_rng(rows)
+    left = rng.integers(0, 256, (H, W), dtype=np.uint8)
+    right = np.roll(left, -9, 1)
+    dl, dr = dev(torch, left), dev(torch, right)
+    lists = [np.sort(rng.choice(W * H, 4000, replace=False)).astype(np.uint32) for _ in range(nframes)]
+    lists[0] = (np.arange(4000) + 1000 * W - 77).astype(np.uint32)
+    runner = sbs.BatchRunner([(dl, dr, dev(torch, i.view(np.int32)), 9, 255) for i in lists])
+    assert runner.plan()["tile_rows"] == rows and runner.plan()["chunk"] == 16
+    runner.run()
+    for k, i in enumerate(lists):
+        ed, ec, _ = oracle.sad(left, right, i, 9, 255)
+        assert np.array_equal(runner.disp[k].cpu().numpy(), ed), k
+        assert np.array_equal(runner.cost[k].cpu().numpy().view(np.uint32), ec), k
