@@ -200,7 +200,9 @@ int sbs_sad_disparity_per_frame(const sbs_frame* frames, int32_t nframes, void* 
  * other frames of the same call run with 4. A frame whose
  * min(n, (tile_rows - 1) * W) reaches 2^24 (2^23 at 8 columns per lane) runs
  * with tile_rows halved until it does not. A launch of one frame runs its
- * last work items with half of tile_rows.
+ * last work items with half of tile_rows. Of a list in no order, items of 16
+ * disparities run as items of 8 over two tiles one above the other, and frames
+ * whose window sums do not pack as two passes of 8.
  */
 typedef struct {
   int32_t cols_per_lane;
@@ -324,7 +326,10 @@ int sbs_lightness(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t p
  *                is taken from (after open/close in mode 0)
  *   workspace    device, >= sbs_boundaries_workspace_bytes(W, H) bytes,
  *                256-byte aligned (as hipMalloc returns); the library keeps
- *                nothing in it between calls
+ *                nothing in it between calls. The size is the loaded library's
+ *                own: ask it, and fix none in a program (it has become half of
+ *                what it was for ordinary images, and more than it was for
+ *                those of some 9,000 pixels or fewer, or narrower than 30)
  * W*H <= 2^31 - 1 and H <= 262140 (else SBS_ERR_UNSUPPORTED). Asynchronous
  * on `stream`; SBS_ERR_INVALID_ARG for bad arguments (nothing is launched then).
  */

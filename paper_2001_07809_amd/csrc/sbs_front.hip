@@ -2440,6 +2440,8 @@ int sbs_boundaries(const uint8_t* img, int32_t W, int32_t H, int32_t C, int64_t 
   if (K < 1 || K > kMaxK) return fail(SBS_ERR_INVALID_ARG, "K must be in [1, %d]", kMaxK);
   if (mode != 0 && mode != 1) return fail(SBS_ERR_INVALID_ARG, "mode must be 0 (configured) or 1 (paper)");
   if (mode == 0 && min_cc < 0) return fail(SBS_ERR_INVALID_ARG, "min_cc < 0");
+  // (Within it the runs' numbers fit 32 bits: a row ends with a word of up to 32
+  // runs, so there are at most W H / 2 + 32 H of them, and W H < 2^31.)
   if (H > 4 * 65535) return fail(SBS_ERR_UNSUPPORTED, "H > %d", 4 * 65535);
   if (!(frac < 0.0) && !(frac <= 1.0)) return fail(SBS_ERR_INVALID_ARG, "frac must be < 0 (off) or in [0, 1]");
   const int64_t N = (int64_t)W * H;

@@ -65,9 +65,10 @@ struct QueueTotals {
 struct WsHeader {
   uint32_t error;        // bit 0: an index >= W*H was seen
   uint32_t pad0[15];
-  // The next item of queue q, each on a 128-byte L2 line of its own: adds to
-  // one line queue up one after another at the memory side, and so do reads
-  // of anything beside it.
+  // The next item of queue q, no two on one 128-byte L2 line: adds to one line
+  // queue up one after another at the memory side, and so do reads of anything
+  // beside it. (Queue 0's shares its line with the error word, which only
+  // lists with an index past the image write.)
   unsigned long long heads[16 * kQueues - 8];
   __device__ __forceinline__ unsigned long long* head(int q) { return &heads[16 * q]; }
 };
